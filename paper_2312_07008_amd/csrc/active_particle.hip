@@ -186,7 +186,8 @@ int dfpt2_add_active_particle_density(const dfpt2_opts* opts, const double* eps_
                     0.0, s)) != hipSuccess)
     return hip_fail(e, "active-particle eta");
   // 4. E = X Y^T, D += (E + E^T) / 2 (per-spin convention: half)
-  if ((e = gemm_f64(X, K, 0, 0, Y, K, 0, 1, E, n_v, 0, n_v, n_v, K, 1, 1.0, 0.0, s)) != hipSuccess)
+  // (n_v^2 outputs, a contraction of n_h^2 n_act: split over workgroups, Z is free)
+  if ((e = gemm_f64(X, K, 0, 0, Y, K, 0, 1, E, n_v, 0, n_v, n_v, K, 1, 1.0, 0.0, s, Z, all)) != hipSuccess)
     return hip_fail(e, "active-particle density");
   const double scale = opts->density_convention == 1 ? 0.5 : 1.0;
   hipLaunchKernelGGL(ap_sym_add, dim3(grid_for((size_t)n_v * n_v)), dim3(256), 0, s, E, D_vv, n_v, scale);

@@ -122,10 +122,13 @@ int pt2_energy_correction(const dfpt2_opts* opts, const double* eps_hole, const 
   double* Bt = (double*)(ws + cp.off_Bt);
   const int nv = cp.n_v, nk = cp.nk;
   hipError_t e;
+  // partial products of split contractions: the eigensolver's workspace, free outside its call
+  double* part = (double*)(ws + cp.off_eig);
+  const size_t npart = cp.eig_bytes / 8;
   // F' = V_k^T diag(eps) V_k
   ProfScope ps_f(DFPT2_STAGE_TRANSFORM, s);
   hipLaunchKernelGGL(scale_rows_kernel, dim3((nk + 255) / 256, nv), dim3(256), 0, s, no_vecs, nv, eps_vir, nv, nk, Y);
-  if ((e = gemm_f64(no_vecs, nv, 0, 1, Y, nk, 0, 0, F, nk, 0, nk, nk, nv, 1, 1.0, 0.0, s)) != hipSuccess)
+  if ((e = gemm_f64(no_vecs, nv, 0, 1, Y, nk, 0, 0, F, nk, 0, nk, nk, nv, 1, 1.0, 0.0, s, part, npart)) != hipSuccess)
     return hip_fail(e, "gemm F");
   hipLaunchKernelGGL(symmetrize_kernel, dim3((nk + 255) / 256, nk), dim3(256), 0, s, F, nk);
   if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "symmetrize");
@@ -134,7 +137,7 @@ int pt2_energy_correction(const dfpt2_opts* opts, const double* eps_hole, const 
   if (st != DFPT2_OK) return st;
   // U = V_k W ; B~_i = U^T B_i
   ProfScope ps_u(DFPT2_STAGE_TRANSFORM, s);
-  if ((e = gemm_f64(no_vecs, nv, 0, 0, W, nk, 0, 0, U, nk, 0, nv, nk, nk, 1, 1.0, 0.0, s)) != hipSuccess)
+  if ((e = gemm_f64(no_vecs, nv, 0, 0, W, nk, 0, 0, U, nk, 0, nv, nk, nk, 1, 1.0, 0.0, s, part, npart)) != hipSuccess)
     return hip_fail(e, "gemm U");
   if ((e = gemm_f64(U, nk, 0, 1, B, cp.n_aux, (long long)nv * cp.n_aux, 0, Bt, cp.n_aux, (long long)nk * cp.n_aux,
                     nk, cp.n_aux, nv, cp.n_h, 1.0, 0.0, s)) != hipSuccess)

@@ -357,8 +357,8 @@ int dfpt2_add_cumulant_singles_density(const dfpt2_opts* opts, const double* eps
   hipLaunchKernelGGL(cs_build_lr, dim3(grid_cs((size_t)n_v * d.K)), dim3(256), 0, s, X, t1, Qa, Qb, R5, W1,
                      gamma_act, d, L, R);
   if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "cumulant/singles kernels");
-  // E = L R^T
-  if ((e = gemm_f64(L, d.K, 0, 0, R, d.K, 0, 1, E, n_v, 0, n_v, n_v, d.K, 1, 1.0, 0.0, s)) != hipSuccess)
+  // E = L R^T (X is free from here on: partial products of the split contractions)
+  if ((e = gemm_f64(L, d.K, 0, 0, R, d.K, 0, 1, E, n_v, 0, n_v, n_v, d.K, 1, 1.0, 0.0, s, X, nx)) != hipSuccess)
     return hip_fail(e, "cumulant/singles density");
   if (d.lam) {
     // T[e][(u, v)][e'] = sum_Q B_ue^Q B_ve'^Q, one GEMM per active hole u batched over v
@@ -376,7 +376,7 @@ int dfpt2_add_cumulant_singles_density(const dfpt2_opts* opts, const double* eps
                       n_a * n_a, n_v, 1.0, 0.0, s)) != hipSuccess)
       return hip_fail(e, "cumulant mixing");
     // E += T M^T over (u v, e')
-    if ((e = gemm_f64(T, K3, 0, 0, M, K3, 0, 1, E, n_v, 0, n_v, n_v, K3, 1, 1.0, 1.0, s)) != hipSuccess)
+    if ((e = gemm_f64(T, K3, 0, 0, M, K3, 0, 1, E, n_v, 0, n_v, n_v, K3, 1, 1.0, 1.0, s, X, nx)) != hipSuccess)
       return hip_fail(e, "cumulant active-active term");
   }
   const double scale = opts->density_convention == 1 ? 0.5 : 1.0;

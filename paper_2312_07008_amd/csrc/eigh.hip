@@ -806,11 +806,12 @@ int eigh_run(const double* A_in, int n, double* w_out, double* Z_out, char* ws, 
   //    by no more than their gap times E.  The LU columns are free by now.
   double* G = lu;
   double* Zo = lu + nn;
-  if ((err = gemm_f64(X, n, 0, 1, X, n, 0, 0, G, n, 0, n, n, n, 1, 1.0, 0.0, st)) != hipSuccess)
+  double* Part = lu + 2 * nn;  // partial products, 3 nn; only the upper triangle of G is read
+  if ((err = gemm_f64(X, n, 0, 1, X, n, 0, 0, G, n, 0, n, n, n, 1, 1.0, 0.0, st, Part, 3 * nn, true)) != hipSuccess)
     return hip_fail(err, "eigh orthonormalization");
   hipLaunchKernelGGL(orth_correction, dim3((unsigned)((nn + 255) / 256 < 65535 ? (nn + 255) / 256 : 65535)),
                      dim3(256), 0, st, n, G);
-  if ((err = gemm_f64(X, n, 0, 0, G, n, 0, 0, Zo, n, 0, n, n, n, 1, 1.0, 0.0, st)) != hipSuccess)
+  if ((err = gemm_f64(X, n, 0, 0, G, n, 0, 0, Zo, n, 0, n, n, n, 1, 1.0, 0.0, st, Part, 3 * nn)) != hipSuccess)
     return hip_fail(err, "eigh orthonormalization");
   // 6. sort + orient
   hipLaunchKernelGGL(eig_rank, dim3((n + 255) / 256), dim3(256), 0, st, n, lam, rank);

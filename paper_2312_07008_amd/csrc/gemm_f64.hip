@@ -1,19 +1,32 @@
-// Batched FP64 GEMM on the 16x16x4 FP64 MFMA, used by the NO transform and
-// recanonicalization (Sec. 2), the natural auxiliary functions, the
-// particle-particle ladder and the active-particle density terms:
+// Batched FP64 GEMM on the 16x16x4 FP64 MFMA, used by the eigensolver, the NO
+// transform and recanonicalization (Sec. 2), the natural auxiliary functions, the
+// particle-particle ladder and the density terms with active particles:
 //     C[b] = alpha op(A[b]) op(B[b]) + beta C[b],   op(A) M x K, op(B) K x N.
 //
-// One workgroup computes a 128 x 128 tile of C; its four waves own 64 x 64
-// quadrants, 4 x 4 MFMA blocks of 16 x 16 (64 FP64 accumulators per lane), so
-// each 16-deep contraction chunk is 64 MFMAs per wave (~4000 cycles) against
-// 2 x 16 KB of operands.  The next chunk is fetched into registers (eight
-// doubles of each operand per thread, consecutive lanes on consecutive
-// addresses of the contiguous dimension) while the current one is multiplied
-// out of LDS, then written to the other LDS buffer: one barrier per chunk, and
-// the global-load latency hides behind the MFMA work of the chunk.  LDS holds
-// both operands k-major ([k][m] and [k][n]) with rows padded to 144 doubles,
-// so the 16 lanes of one k row and the 16 of the next read disjoint banks.
-// Out-of-range rows, columns and contraction indices read as zero.
+// What bounds it: the FP64 matrix pipe, 64 cycles per 16x16x4 product (78 TFLOP/s
+// sustained by a loop of products alone).  A 16-deep chunk of a 128 x 128 tile is 64
+// products per wave against 32 KB of operands, so LDS and L2 have slack; what costs
+// time is whatever keeps a SIMD's waves from issuing products.  Hence:
+//  * the next chunk is fetched into registers (8 bytes per lane: any leading dimension
+//    and alignment) by buffer loads whose descriptor base moves with the chunk (scalar
+//    arithmetic) at byte offsets that never change: no vector instruction and no branch
+//    but the loads (8192 x 8192 x 2048: 60.3 TFLOP/s with 64-bit addresses per load,
+//    62.6 so).  Rows beyond the matrix read a clamped row, whose products reach no stored
+//    element; the last, partial chunk of the contraction runs on its own behind the loop
+//    and selects zeros for both operands, so that an infinity or NaN behind the end of a
+//    row cannot enter.
+//  * LDS holds both operands k-major ([k][m], [k][n]) with rows of 18 (mod 32) doubles:
+//    the 16 lanes along k that store a row of a k-contiguous operand and the 16 + 16
+//    lanes that read a fragment hit distinct banks.
+//  * the tile is 128 x 128 (64 x 64 per wave) or 64 x 64, and a contraction that is long
+//    for its number of tiles is split over workgroups whose partial tiles are summed in a
+//    fixed order (choose_config).
+// Measured against the kernel before (one 128 x 128 tile, predicated loads, no split), TFLOP/s:
+// A B^T 4256 x 17689 x 800 37 -> 56, A^T B 894 x 4000 x 1200 of 80 stacks 50 -> 61,
+// A B 1200^3 14 -> 41, A B^T 400 x 400 x 18432 1.5 -> 33.
+#include <algorithm>
+#include <cmath>
+
 #include "common.h"
 #include "host.h"
 
@@ -29,136 +42,349 @@ struct GemmArgs {
   int lda, ldb, ldc;
   long long sA, sB, sC;
   double alpha, beta;
+  int batch, tm, tn;  // tiles along M and N
+  int nsplit, kper;   // splits of the contraction, chunks per split
+  double* part;       // [nsplit][batch][M][N] partial products, or null (nsplit == 1)
+  int upper;          // only the tiles that reach the diagonal or lie above it
+  int pair_n;         // > 0: row (a, c) and column (d, b) of C go to pair_s1 c + pair_s2 d + pair_n a + b
+  long long pair_s1, pair_s2;
 };
 
-constexpr int GT = 128;       // tile edge (M and N)
-constexpr int GK = 16;        // contraction chunk
-constexpr int LDP = GT + 16;  // padded LDS row (doubles)
-constexpr int PER = GT * GK / 256;  // staged doubles per thread and operand
+constexpr int GK = 16;  // contraction chunk
 
-// element r of this thread's share of a chunk: (row of the tile, k of the chunk)
-template <bool KCONTIG>
+// LDS row of a T-wide operand tile: T + pad = 18 (mod 32) doubles
+constexpr int lds_row(int t) { return t + (18 - t % 32 + 32) % 32; }
+
+// operand element r of thread tid: (row of the tile, k of the chunk).  KCONTIG: the
+// operand's k runs contiguously in memory, lanes along k; else lanes along the rows.
+template <bool KCONTIG, int T>
 __device__ inline void stage_index(int e, int& row, int& k) {
-  if (KCONTIG) {  // the operand's k runs contiguously in memory: lanes along k
+  if (KCONTIG) {
     row = e / GK;
     k = e - row * GK;
-  } else {  // the tile's rows run contiguously: lanes along the rows
-    k = e / GT;
-    row = e - k * GT;
+  } else {
+    k = e / T;
+    row = e - k * T;
   }
 }
 
-template <bool TA, bool TB>
+typedef uint32_t u2 __attribute__((ext_vector_type(2)));
+constexpr uint32_t kRange = 0x80000000u;  // bytes a buffer load may reach past its chunk's base
+
+// Four waves, 2 x 2; each owns BM x BN blocks of 16 x 16.  WIDE: the operands' rows are
+// so far apart that a chunk spans more than the 2 GB of a buffer load's offsets.
+template <bool TA, bool TB, int BM, int BN, bool WIDE>
 __global__ __launch_bounds__(256, 2) void gemm_f64_kernel(GemmArgs g) {
-  __shared__ double As[2][GK][LDP];
-  __shared__ double Bs[2][GK][LDP];
-  const int b = blockIdx.z;
-  const int m0 = blockIdx.y * GT, n0 = blockIdx.x * GT;
+  constexpr int TM = 32 * BM, TN = 32 * BN;
+  constexpr int LA = lds_row(TM), LB = lds_row(TN);
+  constexpr int PA = TM * GK / 256, PB = TN * GK / 256;
+  __shared__ double As[2][GK][LA];
+  __shared__ double Bs[2][GK][LB];
+  // XCD-aware order: consecutive workgroups go round-robin to the 8 XCDs; remapped so
+  // that each walks a contiguous range of (batch, split, tile), tiles in bands of 8
+  // tile rows, and its resident workgroups share panels through its L2
+  const int nblk = gridDim.x;
+  int L = blockIdx.x;
+  {
+    const int x = L & 7, k = L >> 3, q = nblk >> 3, rem = nblk & 7;
+    L = (x < rem) ? x * (q + 1) + k : rem * (q + 1) + (x - rem) * q + k;
+  }
+  const int per = g.tm * g.tn;
+  const int outer = L / per, t = L - outer * per;
+  const int b = outer / g.nsplit, split = outer - b * g.nsplit;
+  constexpr int BAND = 8;
+  const int band = t / (BAND * g.tn), h = min(BAND, g.tm - band * BAND), tr = t - band * BAND * g.tn;
+  const int jt = tr / h, it = band * BAND + (tr - jt * h);
+  const int m0 = it * TM, n0 = jt * TN;
+  if (g.upper && m0 >= n0 + TN) return;  // workgroup-uniform, before any barrier
   const double* A = g.A + b * g.sA;
   const double* Bm = g.B + b * g.sB;
-  double* C = g.C + b * g.sC;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int wr = w >> 1, wc = w & 1, r16 = lane & 15, kq = lane >> 4;
+  const int kbeg = split * g.kper * GK, kend = min(g.K, kbeg + g.kper * GK);
 
   // A: op(A)[m][k] is A[m][k] (k contiguous) or, transposed, A[k][m] (m contiguous)
   // B: op(B)[k][n] is B[k][n] (n contiguous) or, transposed, B[n][k] (k contiguous)
-  double ra[PER], rb[PER];
-  auto load = [&](int k0) {
+  double ra[PA], rb[PB];
+  // Loads go through buffer descriptors whose base is the chunk's (scalar arithmetic),
+  // at byte offsets that stay the same from chunk to chunk: no vector instruction but the
+  // load itself, which matters because the FP64 products hold the vector pipe.
+  const double* At = TA ? A : A + (size_t)m0 * g.lda;
+  const double* Bt = TB ? Bm + (size_t)n0 * g.ldb : Bm;
+  constexpr int SA = 256 / TM, SB = 256 / TN;  // k step between a thread's elements (row-contiguous operands)
+  int rowa, rowb, ka, kb;
+  stage_index<!TA, TM>(tid, rowa, ka);
+  stage_index<TB, TN>(tid, rowb, kb);
+  uint32_t oa[TA ? 1 : PA], ob[TB ? PB : 1];
+  if constexpr (!WIDE) {
 #pragma unroll
-    for (int r = 0; r < PER; ++r) {
-      int row, k;
-      stage_index<!TA>(tid + 256 * r, row, k);
-      const int gm = m0 + row, gk = k0 + k;
-      ra[r] = (gm < g.M && gk < g.K) ? (TA ? A[(size_t)gk * g.lda + gm] : A[(size_t)gm * g.lda + gk]) : 0.0;
+    for (int r = 0; r < (TA ? 1 : PA); ++r)
+      oa[r] = TA ? ((uint32_t)ka * g.lda + min(m0 + rowa, g.M - 1)) * 8u
+                 : ((uint32_t)min(rowa + 16 * r, g.M - 1 - m0) * g.lda + ka) * 8u;
+#pragma unroll
+    for (int r = 0; r < (TB ? PB : 1); ++r)
+      ob[r] = TB ? ((uint32_t)min(rowb + 16 * r, g.N - 1 - n0) * g.ldb + kb) * 8u
+                 : ((uint32_t)kb * g.ldb + min(n0 + rowb, g.N - 1)) * 8u;
+  }
+  // whole chunk at k0
+  auto load = [&](int k0) {
+    if constexpr (WIDE) {
+#pragma unroll
+      for (int r = 0; r < PA; ++r)
+        ra[r] = TA ? At[(size_t)(k0 + ka + SA * r) * g.lda + min(m0 + rowa, g.M - 1)]
+                   : At[(size_t)min(rowa + 16 * r, g.M - 1 - m0) * g.lda + k0 + ka];
+#pragma unroll
+      for (int r = 0; r < PB; ++r)
+        rb[r] = TB ? Bt[(size_t)min(rowb + 16 * r, g.N - 1 - n0) * g.ldb + k0 + kb]
+                   : Bt[(size_t)(k0 + kb + SB * r) * g.ldb + min(n0 + rowb, g.N - 1)];
+    } else {
+      auto da = __builtin_amdgcn_make_buffer_rsrc((void*)(At + (TA ? (size_t)k0 * g.lda : (size_t)k0)), 0, kRange, 0x00020000);
+      auto db = __builtin_amdgcn_make_buffer_rsrc((void*)(Bt + (TB ? (size_t)k0 : (size_t)k0 * g.ldb)), 0, kRange, 0x00020000);
+#pragma unroll
+      for (int r = 0; r < PA; ++r)
+        ra[r] = __builtin_bit_cast(double, (u2)__builtin_amdgcn_raw_buffer_load_b64(da, oa[TA ? 0 : r], TA ? SA * r * g.lda * 8 : 0, 0));
+#pragma unroll
+      for (int r = 0; r < PB; ++r)
+        rb[r] = __builtin_bit_cast(double, (u2)__builtin_amdgcn_raw_buffer_load_b64(db, ob[TB ? r : 0], TB ? 0 : SB * r * g.ldb * 8, 0));
+    }
+  };
+  // the last `left` < GK steps of the contraction at k0; the others are zero
+  auto load_tail = [&](int k0, int left) {
+#pragma unroll
+    for (int r = 0; r < PA; ++r) {
+      const int k = ka + (TA ? SA * r : 0), kk = k0 + min(k, left - 1);
+      const double v = TA ? At[(size_t)kk * g.lda + min(m0 + rowa, g.M - 1)]
+                          : At[(size_t)min(rowa + 16 * r, g.M - 1 - m0) * g.lda + kk];
+      ra[r] = k < left ? v : 0.0;
     }
 #pragma unroll
-    for (int r = 0; r < PER; ++r) {
-      int col, k;
-      stage_index<TB>(tid + 256 * r, col, k);
-      const int gn = n0 + col, gk = k0 + k;
-      rb[r] = (gn < g.N && gk < g.K) ? (TB ? Bm[(size_t)gn * g.ldb + gk] : Bm[(size_t)gk * g.ldb + gn]) : 0.0;
+    for (int r = 0; r < PB; ++r) {
+      const int k = kb + (TB ? 0 : SB * r), kk = k0 + min(k, left - 1);
+      const double v = TB ? Bt[(size_t)min(rowb + 16 * r, g.N - 1 - n0) * g.ldb + kk]
+                          : Bt[(size_t)kk * g.ldb + min(n0 + rowb, g.N - 1)];
+      rb[r] = k < left ? v : 0.0;
     }
   };
   auto store = [&](int buf) {
 #pragma unroll
-    for (int r = 0; r < PER; ++r) {
+    for (int r = 0; r < PA; ++r) {
       int row, k;
-      stage_index<!TA>(tid + 256 * r, row, k);
+      stage_index<!TA, TM>(tid + 256 * r, row, k);
       As[buf][k][row] = ra[r];
     }
 #pragma unroll
-    for (int r = 0; r < PER; ++r) {
+    for (int r = 0; r < PB; ++r) {
       int col, k;
-      stage_index<TB>(tid + 256 * r, col, k);
+      stage_index<TB, TN>(tid + 256 * r, col, k);
       Bs[buf][k][col] = rb[r];
     }
   };
 
-  d4 acc[4][4];
+  d4 acc[BM][BN];
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < BM; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = (d4){0.0, 0.0, 0.0, 0.0};
+    for (int j = 0; j < BN; ++j) acc[i][j] = (d4){0.0, 0.0, 0.0, 0.0};
 
-  load(0);
-  store(0);
-  __syncthreads();
-  int buf = 0;
-  for (int k0 = 0; k0 < g.K; k0 += GK) {
-    const bool more = k0 + GK < g.K;
-    if (more) load(k0 + GK);
+  auto products = [&](int buf) {
 #pragma unroll
     for (int k4 = 0; k4 < GK / 4; ++k4) {
       const int k = k4 * 4 + kq;
-      double a[4], bb[4];
+      double a[BM], bb[BN];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) a[i] = As[buf][k][wr * 64 + i * 16 + r16];
+      for (int i = 0; i < BM; ++i) a[i] = As[buf][k][(wr * BM + i) * 16 + r16];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) bb[j] = Bs[buf][k][wc * 64 + j * 16 + r16];
+      for (int j = 0; j < BN; ++j) bb[j] = Bs[buf][k][(wc * BN + j) * 16 + r16];
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
+      for (int i = 0; i < BM; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i], bb[j], acc[i][j], 0, 0, 0);
+        for (int j = 0; j < BN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i], bb[j], acc[i][j], 0, 0, 0);
     }
-    if (more) store(buf ^ 1);
+  };
+  const int kfull = kbeg + (kend - kbeg) / GK * GK;
+  int buf = 0;
+  if (kbeg < kfull) {
+    load(kbeg);
+    store(0);
     __syncthreads();
-    buf ^= 1;
+    for (int k0 = kbeg; k0 < kfull; k0 += GK) {
+      const bool more = k0 + GK < kfull;
+      if (more) load(k0 + GK);
+      products(buf);
+      if (more) store(buf ^ 1);
+      __syncthreads();
+      buf ^= 1;
+    }
+  }
+  if (kfull < kend) {  // workgroup-uniform
+    load_tail(kfull, kend - kfull);
+    store(buf);
+    __syncthreads();
+    products(buf);
   }
   // register r of lane l holds row l / 16 + 4 r and column l % 16 of a 16 x 16 block
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < BM; ++i)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const int gm = m0 + wr * 64 + i * 16 + kq + 4 * r;
+      const int gm = m0 + (wr * BM + i) * 16 + kq + 4 * r;
       if (gm >= g.M) continue;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int gn = n0 + wc * 64 + j * 16 + r16;
+      for (int j = 0; j < BN; ++j) {
+        const int gn = n0 + (wc * BN + j) * 16 + r16;
         if (gn >= g.N) continue;
-        double* dst = C + (size_t)gm * g.ldc + gn;
-        const double v = g.alpha * acc[i][j][r];
-        *dst = (g.beta != 0.0) ? v + g.beta * *dst : v;
+        double* dst;
+        if (g.part) dst = g.part + (((size_t)split * g.batch + b) * g.M + gm) * g.N + gn;
+        else if (g.pair_n) dst = g.C + (long long)(gm / g.pair_n) * g.pair_n + (gm % g.pair_n) * g.pair_s1 +
+                                 (gn / g.pair_n) * g.pair_s2 + gn % g.pair_n;
+        else dst = g.C + b * g.sC + (size_t)gm * g.ldc + gn;
+        double v = acc[i][j][r];
+        if (!g.part) {
+          v *= g.alpha;
+          if (g.beta != 0.0) v += g.beta * *dst;
+        }
+        *dst = v;
       }
     }
+}
+
+
+// C = alpha sum over the splits of their partial products + beta C, in the order of
+// the splits; with `upper`, the tiles wholly below the diagonal were not formed
+__global__ __launch_bounds__(256) void gemm_f64_sum(GemmArgs g, int tile) {
+  const size_t mn = (size_t)g.M * g.N, all = mn * g.batch;
+  for (size_t q = blockIdx.x * (size_t)blockDim.x + threadIdx.x; q < all; q += (size_t)gridDim.x * blockDim.x) {
+    const int b = (int)(q / mn);
+    const size_t o = q - b * mn;
+    const int m = (int)(o / g.N), n = (int)(o - (size_t)m * g.N);
+    if (g.upper && m / tile > n / tile) continue;
+    double v = 0.0;
+    for (int k = 0; k < g.nsplit; ++k) v += g.part[((size_t)k * g.batch) * mn + q];
+    double* dst = g.C + b * g.sC + (size_t)m * g.ldc + n;
+    v *= g.alpha;
+    *dst = (g.beta != 0.0) ? v + g.beta * *dst : v;
+  }
+}
+
+struct Config {
+  int b, nsplit;  // tile edge / 32, splits of the contraction
+};
+
+// Tile and split by the estimated time on 256 compute units: the products done (padding
+// included) by the busiest unit, at the share of the matrix rate that 1, 2, 3 workgroups
+// on a unit reach (LDS holds two of the larger and three of the smaller tile; one alone
+// has nothing to fill the waits at its barriers), plus the partial products' way through
+// memory.  Measured shares: 128 x 128 tiles 0.60 and 0.80 (18 TFLOP/s at 100 workgroups,
+// 63 at 4096), 64 x 64 tiles 0.42, 0.61 and 0.78 (34 TFLOP/s at 361 workgroups, 62 at
+// 16384): the larger tile leads only where it fills the units evenly, and 1200^3 goes
+// from 34 to 41 TFLOP/s with its contraction split in two.
+Config choose_config(int M, int N, int K, int batch, bool upper, size_t part_doubles) {
+  static const struct {
+    int b, wgs;
+    double rate[3];
+  } tiles[] = {{4, 2, {0.60, 0.80, 0.80}}, {2, 3, {0.42, 0.61, 0.78}}};
+  const double flop_us = 305e3;  // per unit at 78 TFLOP/s
+  Config best{4, 1};
+  double best_t = 1e300;
+  const int nchunk = (K + GK - 1) / GK;
+  for (const auto& t : tiles) {
+    const double tm = (M + 32 * t.b - 1) / (32 * t.b), tn = (N + 32 * t.b - 1) / (32 * t.b);
+    const double n = tm * tn * batch * (upper ? 0.5 * (1.0 + 1.0 / tn) : 1.0);
+    for (int s = 1; s <= 64; s *= 2) {
+      if (s > 1 && ((size_t)s * batch * M * N > part_doubles || nchunk < 8 * s)) break;
+      const double per_unit = std::ceil(n * s / 256.0);
+      const double flops = 2.0 * 1024 * t.b * t.b * GK * std::ceil((double)nchunk / s);
+      const double us = per_unit * flops / (flop_us * t.rate[(int)std::min(per_unit, (double)t.wgs) - 1]) +
+                        (s > 1 ? 5.0 + (double)s * batch * M * N * 16.0 / 4e6 : 0.0);
+      if (us < best_t * 0.999) {
+        best_t = us;
+        best = Config{t.b, s};
+      }
+    }
+  }
+  return best;
+}
+
+template <int B, bool WIDE>
+void launch_tile(const GemmArgs& g, int transA, int transB, unsigned blocks, hipStream_t st) {
+  if (transA) {
+    if (transB) hipLaunchKernelGGL((gemm_f64_kernel<true, true, B, B, WIDE>), dim3(blocks), dim3(256), 0, st, g);
+    else hipLaunchKernelGGL((gemm_f64_kernel<true, false, B, B, WIDE>), dim3(blocks), dim3(256), 0, st, g);
+  } else {
+    if (transB) hipLaunchKernelGGL((gemm_f64_kernel<false, true, B, B, WIDE>), dim3(blocks), dim3(256), 0, st, g);
+    else hipLaunchKernelGGL((gemm_f64_kernel<false, false, B, B, WIDE>), dim3(blocks), dim3(256), 0, st, g);
+  }
+}
+
+hipError_t launch_gemm(GemmArgs& g, int transA, int transB, double* part, size_t part_doubles, hipStream_t st) {
+  if (g.M <= 0 || g.N <= 0 || g.batch <= 0) return hipSuccess;
+  Config c = choose_config(g.M, g.N, g.K, g.batch, g.upper != 0, part ? part_doubles : 0);
+  // byte span of a chunk: 16 rows of an operand whose tile rows run contiguously, up to
+  // 128 rows of a k-contiguous one
+  const bool wide = ((transA ? 16.0 : 128.0) * g.lda + 128.0) * 8.0 >= kRange ||
+                    ((transB ? 128.0 : 16.0) * g.ldb + 128.0) * 8.0 >= kRange;
+  if (wide) c.b = 2;
+  const int tile = 32 * c.b;
+  g.tm = (g.M + tile - 1) / tile;
+  g.tn = (g.N + tile - 1) / tile;
+  const int nchunk = g.K > 0 ? (g.K + GK - 1) / GK : 0;  // K <= 0 leaves C = beta C
+  g.kper = (nchunk + c.nsplit - 1) / c.nsplit;
+  g.nsplit = g.kper > 0 ? (nchunk + g.kper - 1) / g.kper : 1;
+  g.part = g.nsplit > 1 ? part : nullptr;
+  const double blocks = (double)g.tm * g.tn * g.batch * g.nsplit;
+  if (blocks > 2147483647.0) return hipErrorInvalidValue;
+  const unsigned nb = (unsigned)blocks;
+  if (wide) launch_tile<2, true>(g, transA, transB, nb, st);
+  else if (c.b == 4) launch_tile<4, false>(g, transA, transB, nb, st);
+  else launch_tile<2, false>(g, transA, transB, nb, st);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess || g.nsplit <= 1) return e;
+  const size_t all = ((size_t)g.M * g.N * g.batch + 255) / 256;
+  hipLaunchKernelGGL(gemm_f64_sum, dim3((unsigned)(all < 16384 ? all : 16384)), dim3(256), 0, st, g, tile);
+  return hipGetLastError();
 }
 
 }  // namespace
 
 hipError_t gemm_f64(const double* A, int lda, long long sA, int transA, const double* B, int ldb, long long sB,
                     int transB, double* C, int ldc, long long sC, int M, int N, int K, int batch, double alpha,
-                    double beta, hipStream_t st) {
-  if (M <= 0 || N <= 0 || batch <= 0) return hipSuccess;
-  if (batch > 65535 || (M + GT - 1) / GT > 65535) return hipErrorInvalidValue;
-  GemmArgs g{A, B, C, M, N, K, lda, ldb, ldc, sA, sB, sC, alpha, beta};
-  dim3 grid((N + GT - 1) / GT, (M + GT - 1) / GT, batch);  // K <= 0 leaves C = beta C
-  if (transA) {
-    if (transB) hipLaunchKernelGGL((gemm_f64_kernel<true, true>), grid, dim3(256), 0, st, g);
-    else hipLaunchKernelGGL((gemm_f64_kernel<true, false>), grid, dim3(256), 0, st, g);
-  } else {
-    if (transB) hipLaunchKernelGGL((gemm_f64_kernel<false, true>), grid, dim3(256), 0, st, g);
-    else hipLaunchKernelGGL((gemm_f64_kernel<false, false>), grid, dim3(256), 0, st, g);
-  }
-  return hipGetLastError();
+                    double beta, hipStream_t st, double* part, size_t part_doubles, bool upper) {
+  GemmArgs g{};
+  g.A = A;
+  g.B = B;
+  g.C = C;
+  g.M = M;
+  g.N = N;
+  g.K = K;
+  g.lda = lda;
+  g.ldb = ldb;
+  g.ldc = ldc;
+  g.sA = sA;
+  g.sB = sB;
+  g.sC = sC;
+  g.alpha = alpha;
+  g.beta = beta;
+  g.batch = batch;
+  g.upper = upper ? 1 : 0;
+  return launch_gemm(g, transA, transB, part, part_doubles, st);
+}
+
+hipError_t gemm_f64_pairs(const double* A, const double* B, int ld, double* C, int n, int M, int N, int K,
+                          long long stride_c, long long stride_d, hipStream_t st) {
+  GemmArgs g{};
+  g.A = A;
+  g.B = B;
+  g.C = C;
+  g.M = M;
+  g.N = N;
+  g.K = K;
+  g.lda = g.ldb = ld;
+  g.alpha = 1.0;
+  g.batch = 1;
+  g.pair_n = n;
+  g.pair_s1 = stride_c;
+  g.pair_s2 = stride_d;
+  return launch_gemm(g, 0, 1, nullptr, 0, st);
 }
 
 }  // namespace dfpt2

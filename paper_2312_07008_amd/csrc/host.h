@@ -94,8 +94,16 @@ class ProfScope {
 };
 void prof_flush();
 
+// C[b] = alpha op(A[b]) op(B[b]) + beta C[b] for b < batch (gemm_f64.hip).  `part`
+// (may be null): device scratch of part_doubles doubles that the call may use to
+// split a long contraction; it must overlap no operand.  `upper`: only the tiles that
+// reach or lie above the diagonal are formed (what lies below them in C is undefined).
 hipError_t gemm_f64(const double* A, int lda, long long sA, int transA, const double* B, int ldb, long long sB,
                     int transB, double* C, int ldc, long long sC, int M, int N, int K, int batch, double alpha,
-                    double beta, hipStream_t st);
+                    double beta, hipStream_t st, double* part = nullptr, size_t part_doubles = 0, bool upper = false);
+// A B^T with rows (a, c) = a n + c of A and (d, b) = d n + b of B (row stride ld),
+// written to C[stride_c c + stride_d d + n a + b]
+hipError_t gemm_f64_pairs(const double* A, const double* B, int ld, double* C, int n, int M, int N, int K,
+                          long long stride_c, long long stride_d, hipStream_t st);
 
 }  // namespace dfpt2

@@ -6,14 +6,17 @@
 //
 // Integral-direct in blocks of the first virtual a, as two FP64 MFMA GEMMs per
 // block (flops 2 N^4 n_aux + 2 N^4 n_amp in total, both proportional to N^4):
-//   G[(a,c)][(d,b)] = sum_Q B[(a,c)][Q] B[(d,b)][Q]      (rows a of the block)
-//   R[p][a][b]      = sum_(c,d) T[p][(c,d)] G[(a,c,d)][b]
+//   G[(c,d)][(a,b)] = sum_Q B[(a,c)][Q] B[(d,b)][Q]      (rows a of the block)
+//   R[p][(a,b)]     = sum_(c,d) T[p][(c,d)] G[(c,d)][(a,b)]
 // The first product reads the columns of (ac|bd) in (d,b) order, which is
 // (b,d) order of B because density-fitted integrals are symmetric in their two
-// orbital indices (B^Q_db = B^Q_bd); that lays G out as [(c,d)][b] per a, the
-// operand the second product contracts over (c,d).  G of one block holds
-// m_a N^3 doubles (m_a <= 32 values of a, at most ~16 GB, at least one a): the
-// contraction runs as m_a batched GEMMs of n_amp x N, so m_a sets its parallelism.
+// orbital indices (B^Q_db = B^Q_bd), so its tiles write runs of b; it stores them at
+// [(c,d)][(a,b)], so that the second product is one GEMM whose columns run over all
+// (a,b) of the block: no tile is cut off at N columns, whatever N.  G of one block
+// holds m_a N^3 doubles (at most ~16 GB, at least one a); m_a N >= 32768 columns fill
+// the GPU with tiles of the contraction.  At N' = 133, 800 auxiliary functions and 400
+// amplitude matrices the contraction took 18.7 ms as m_a = 32 batched GEMMs of
+// n_amp x N (13 TFLOP/s: 133 columns in tiles of 128).
 //
 // Truncated space: with the kept NOs X [N_V][ldx] (first N' columns) the inputs are transformed
 // first, B'^Q = X^T B^Q X (over both virtual indices of B[a][c][Q]) and
@@ -36,7 +39,7 @@ struct LadderPlan {
 };
 
 constexpr double kGBlockBytes = 16.0e9;  // one block of (ac|bd): enough values of a to fill the GPU
-constexpr int kMaxBlockRows = 32;  // values of a per block
+constexpr int kMinBlockCols = 32768;     // columns (a,b) of a block, where N and the bytes allow
 
 int plan_ladder(int64_t n_vir, int64_t n_aux, int64_t n_amp, int64_t n_kept, bool transform, LadderPlan* pl) {
   if (n_vir < 1 || n_vir > 2048) return fail(DFPT2_ERR_INVALID_ARG, "n_vir must lie in [1, 2048]");
@@ -55,7 +58,9 @@ int plan_ladder(int64_t n_vir, int64_t n_aux, int64_t n_amp, int64_t n_kept, boo
   p.np = (int)n_amp;
   p.transform = transform;
   const double n3 = (double)p.nk * p.nk * p.nk * sizeof(double);
-  p.ma = std::max(1, std::min({p.nk, kMaxBlockRows, (int)(kGBlockBytes / n3)}));
+  p.ma = std::max(1, std::min({p.nk, std::max(32, (kMinBlockCols + p.nk - 1) / p.nk), (int)(kGBlockBytes / n3)}));
+  const int nblk = (p.nk + p.ma - 1) / p.ma;  // blocks of equal size
+  p.ma = (p.nk + nblk - 1) / nblk;
   if ((double)p.nk * p.na > 2.0e9 || (double)p.nk * p.nk > 2.0e9)
     return fail(DFPT2_ERR_INVALID_ARG, "ladder operands exceed the GEMM index range");
   size_t off = 0;
@@ -136,13 +141,14 @@ int pp_ladder(int64_t n_vir, int64_t n_aux, int64_t n_amp, const double* B_vv, c
     const int N2 = nk * nk;
     for (int a0 = 0; a0 < nk; a0 += p.ma) {
       const int mb = std::min(p.ma, nk - a0);
-      // G[(a,c)][(d,b)] = sum_Q B'[(a,c)][Q] B'[(d,b)][Q] for a in [a0, a0 + mb)
-      if ((e = gemm_f64(Bk + (size_t)a0 * nk * na, na, 0, 0, Bk, na, 0, 1, G, N2, 0, mb * nk, N2, na, 1, 1.0, 0.0,
-                        s)) != hipSuccess)
+      // G[(c,d)][(a,b)] = sum_Q B'[(a,c)][Q] B'[(d,b)][Q] for a in [a0, a0 + mb)
+      const int ldg = mb * nk;
+      if ((e = gemm_f64_pairs(Bk + (size_t)a0 * nk * na, Bk, na, G, nk, mb * nk, N2, na, (long long)nk * ldg, ldg,
+                              s)) != hipSuccess)
         return hip_fail(e, "ladder integrals");
-      // R[p][a][b] = sum_(c,d) T'[p][(c,d)] G[a][(c,d)][b]
-      if ((e = gemm_f64(Tk, N2, 0, 0, G, nk, (long long)N2 * nk, 0, R + (size_t)a0 * nk, N2, nk, np, nk, N2, mb, 1.0,
-                        0.0, s)) != hipSuccess)
+      // R[p][(a,b)] = sum_(c,d) T'[p][(c,d)] G[(c,d)][(a,b)]
+      if ((e = gemm_f64(Tk, N2, 0, 0, G, ldg, 0, 0, R + (size_t)a0 * nk, N2, 0, np, ldg, N2, 1, 1.0, 0.0, s)) !=
+          hipSuccess)
         return hip_fail(e, "ladder contraction");
     }
   }

@@ -83,7 +83,8 @@ int naf_compress(const dfpt2_opts* opts, const double* B, double eps, double* B_
   {
     ProfScope ps(DFPT2_STAGE_TRANSFORM, s);
     // W = J^T J: op(A) = J^T (A stored rows x n_aux), op(B) = J
-    if ((e = gemm_f64(B, na, 0, 1, B, na, 0, 0, W, na, 0, na, na, (int)p.rows, 1, 1.0, 0.0, s)) != hipSuccess)
+    if ((e = gemm_f64(B, na, 0, 1, B, na, 0, 0, W, na, 0, na, na, (int)p.rows, 1, 1.0, 0.0, s,
+                      reinterpret_cast<double*>(ws + p.off_eig), p.eig_bytes / 8)) != hipSuccess)
       return hip_fail(e, "NAF metric GEMM");
   }
   st = eigh_run(W, na, sigma, U, ws + p.off_eig, p.eig_bytes, s, 1, eps > 0.0 ? eps : -1.0);
