@@ -1,25 +1,31 @@
 // FP64 symmetric eigensolver on the GPU, for the natural-orbital problem of
 // Eq. 8 (Gamma V = n V) and for the recanonicalization of the kept space.
 //
-//   1. Householder reduction to tridiagonal form, one column per step on the
-//      full symmetric matrix: the reflector (formed redundantly in every
-//      workgroup), p = tau A v and the rank-2 update A -= v w^T + w v^T with
-//      w = p - (tau/2)(p.v) v.  Up to n = 2731 one launch per column applies the
-//      previous column's update lazily while forming p; above, two launches.
+//   1. Householder reduction to tridiagonal form, one column per step on the full
+//      symmetric matrix: the reflector, p = tau A v and the rank-2 update
+//      A -= v w^T + w v^T with w = p - (tau/2)(p.v) v, applied lazily with the next
+//      column's product.  Up to n = 2048 in one launch, the matrix in registers (one
+//      workgroup up to n = 128, cooperating workgroups above); then one launch per column,
+//      two above n = 2731.
 //   2. Splitting at negligible off-diagonal entries, then every eigenvalue by
-//      multisection on Sturm counts (one wave per eigenvalue, 64 points a round).
-//   3. Eigenvectors of the tridiagonal matrix by inverse iteration with a
-//      partially pivoted LU of T - lambda I; eigenvalues closer than a small
-//      multiple of ||T|| form a group that one thread handles in order,
-//      orthogonalizing every iterate against the group's earlier vectors.
-//   4. Back-transformation Z <- H_0 H_1 ... H_{n-3} Z in compact-WY blocks of 8
-//      reflectors, one workgroup per 4 (2, 1 for large n) columns held in LDS,
-//      all blocks in one launch.
+//      multisection on Sturm counts (one wave per eigenvalue, 128 points a round).
+//   3. Eigenvectors of the tridiagonal matrix: isolated eigenvalues by twisted
+//      factorizations of T - lambda I; the others by inverse iteration with a partially
+//      pivoted LU.  Eigenvalues closer than a small multiple of ||T|| form a group that
+//      one thread handles in order, orthogonalizing every iterate against the group's
+//      earlier vectors.
+//   4. Back-transformation Z <- H_0 H_1 ... H_{n-3} Z in compact-WY blocks of 16
+//      reflectors on the matrix pipe, 16 columns of Z in a workgroup's registers (above
+//      n = 2048 blocks of 8, one workgroup per 2 or 1 columns held in LDS).
 //   5. One first-order orthonormalization of all columns (two FP64 GEMMs): it
-//      restores orthogonality between vectors of close eigenvalues that inverse
-//      iteration did not group.
+//      restores orthogonality between vectors of close eigenvalues that were formed apart.
 //   6. Columns sorted by eigenvalue and oriented so that the largest-magnitude
 //      component is positive.
+// n = 1200, ms before and after the resident reduction, the product-form counts, the
+// twisted factorizations and the matrix-pipe back-transformation: reduction 11.6 -> 5.0,
+// eigenvalues 1.8 -> 0.66, vectors 5.9 -> 0.28, back-transformation 2.0 -> 0.45, the whole
+// call 22.5 -> 6.8.
+#include <algorithm>
 #include <cmath>
 #include <cfloat>
 
@@ -188,6 +194,394 @@ __global__ __launch_bounds__(256) void tridiag_step_lazy(double* A, int n, int k
   }
 }
 
+// ---------------------------------------------------------------- resident form
+// The whole reduction in one launch, the matrix in registers (n <= kResidentMax).  The
+// launch-per-column form above pays ~10 us a column at n = 1200 for a launch, two passes
+// of vectors through memory and the row's way to and from L2; the arithmetic is 1 us.
+// Per column, every workgroup needs two vectors: p of the previous column and the row k
+// as its update by the column before left it (its owner hands it out).  It forms w and the
+// reflector for itself (each thread a few entries, two workgroup sums), and every wave
+// updates its row and multiplies it by the reflector in the same pass.  All workgroups run
+// the same operations on the same numbers, so that they agree to the bit.
+//
+// kResRows rows per wave (lane l holds columns l, l + 64, ...), 4 waves per workgroup, row
+// r on workgroup r mod G.  The two vectors go through memory, one slot per column and entry that
+// starts as kEmpty (a NaN pattern that no arithmetic here produces) and is written once, by
+// a 64-bit atomic store at device scope; readers poll the entry itself, so that a column
+// costs one trip through memory and no grid barrier.  All workgroups have to be resident:
+// the launch is cooperative, and every wait is bounded (kWaitTicks, or as soon as another
+// workgroup has given up): then *status = 2 and the caller starts again with the
+// launch-per-column form.  A column takes 2.5 us at n = 130 (the trip through memory, two
+// workgroup sums, a square root and a division) and 4.2 us at n = 1200.
+constexpr int kResidentMax = 2048;
+constexpr int kSmallMax = 128;
+constexpr unsigned long long kEmpty = ~0ull;
+constexpr unsigned long long kWaitTicks = 100000000ull;  // of the 100 MHz counter: 1 s
+
+template <int CTRL, int ROWS>
+__device__ inline double dpp_add(double x) {
+  const unsigned long long u = __builtin_bit_cast(unsigned long long, x);
+  const unsigned lo = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)u, CTRL, ROWS, 0xf, false);
+  const unsigned hi = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)(u >> 32), CTRL, ROWS, 0xf, false);
+  return x + __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
+}
+
+__device__ inline double read_lane(double x, int lane) {  // lane uniform
+  const unsigned long long u = __builtin_bit_cast(unsigned long long, x);
+  const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)u, lane);
+  const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(u >> 32), lane);
+  return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
+}
+
+// sum over the wave by DPP (rows of 16, then across rows), on every lane
+__device__ inline double wave_sum_dpp(double v) {
+  v = dpp_add<0x111, 0xf>(v);  // row_shr:1
+  v = dpp_add<0x112, 0xf>(v);
+  v = dpp_add<0x114, 0xf>(v);
+  v = dpp_add<0x118, 0xf>(v);
+  v = dpp_add<0x142, 0xa>(v);  // row_bcast:15 into rows 1 and 3
+  v = dpp_add<0x143, 0xc>(v);  // row_bcast:31 into rows 2 and 3
+  return read_lane(v, 63);
+}
+
+// reflector of a column from alpha = x_0 and s2 = sum of the other x_i^2: v = (1, scale x_i)
+__device__ inline void reflector(double alpha, double s2, double& beta, double& t, double& scale) {
+  t = scale = 0.0;
+  beta = alpha;
+  if (s2 > 0.0) {
+    const double mu = sqrt(alpha * alpha + s2);
+    beta = (alpha > 0.0) ? -mu : mu;
+    t = (beta - alpha) / beta;
+    scale = 1.0 / (alpha - beta);
+  }
+}
+
+__device__ inline void publish(unsigned long long* p, double v) {
+  const unsigned long long u = __builtin_bit_cast(unsigned long long, v);
+  __hip_atomic_store(p, u == kEmpty ? 0x7ff8000000000000ull : u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+constexpr int kResThreads = 256;
+constexpr int kResRows = 2;  // rows per wave: 1200 rows 7.9, 6.8, 7.7, 10.3 ms in all with 1, 2, 4, 8
+
+// J 64-wide column groups (n <= 64 J), RW rows per wave
+template <int J, int RW>
+__global__ __launch_bounds__(kResThreads) void tridiag_resident(const double* A_in, int n, double* A_out, double* Vs,
+                                                        double* tau, double* d, double* e, unsigned long long* P,
+                                                        unsigned long long* R, double* p_last, int* status) {
+  constexpr int NC = 64 * J, NT = kResThreads, NW = NT / 64, Q = (NC + NT - 1) / NT;
+  __shared__ double ws[NC], vs[NC], xs[NC];  // w, v of the previous column, x of this one (0 up to k + 1)
+  __shared__ double part1[NW], part2[NW], sc[3];
+  __shared__ int dead;
+  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int G = gridDim.x, wg = blockIdx.x;
+  int row[RW];
+#pragma unroll
+  for (int r = 0; r < RW; ++r) row[r] = wg + G * (wv + NW * r);
+  const bool writer = wg == (n - 1) % G;            // owns row n - 1, runs to the end
+  const int last = wg + (n - 1 - wg) / G * G;       // largest row of the workgroup
+  double a[RW][J], vo[Q], v_row[RW];
+#pragma unroll
+  for (int r = 0; r < RW; ++r) {
+    v_row[r] = 0.0;
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+      const int c = lane + 64 * j;
+      a[r][j] = (row[r] < n && c < n) ? A_in[(size_t)row[r] * n + c] : 0.0;
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < Q; ++q) vo[q] = 0.0;
+  for (int c = tid; c < NC; c += NT) ws[c] = vs[c] = xs[c] = 0.0;
+  if (tid == 0) dead = 0;
+  double t_prev = 0.0;
+  __syncthreads();
+  for (int k = 0; k + 2 < n; ++k) {
+    if (k >= last) break;  // workgroup-uniform: nothing left to update
+    // p of column k - 1 and row k, entries c = tid + 512 q
+    double p[Q], x[Q];
+    if (k == 0) {
+#pragma unroll
+      for (int q = 0; q < Q; ++q) {
+        const int c = tid + NT * q;
+        p[q] = 0.0;
+        x[q] = c < n ? A_in[c] : 0.0;
+      }
+    } else {
+      unsigned long long pv[Q], rv[Q];
+      unsigned long long t0 = 0;
+      for (int spin = 0;; ++spin) {
+        bool ok = true;
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+          const int c = tid + NT * q;
+          pv[q] = rv[q] = 0;
+          if (c >= k && c < n) {
+            pv[q] = __hip_atomic_load(P + (size_t)(k - 1) * n + c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            rv[q] = __hip_atomic_load(R + (size_t)k * n + c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          }
+        }
+#pragma unroll
+        for (int q = 0; q < Q; ++q) ok = ok && pv[q] != kEmpty && rv[q] != kEmpty;
+        if (ok) break;
+        if ((spin & 255) == 255) {
+          const unsigned long long now = wall_clock64();
+          if (spin == 255) t0 = now;
+          if (now - t0 > kWaitTicks || __hip_atomic_load(status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) {
+            dead = 1;
+            break;
+          }
+        }
+      }
+#pragma unroll
+      for (int q = 0; q < Q; ++q) {
+        p[q] = __builtin_bit_cast(double, pv[q]);
+        x[q] = __builtin_bit_cast(double, rv[q]);
+      }
+    }
+    // K = tau / 2 p . v of the previous column (p and v are zero at c < k and c >= n)
+    double dot = 0.0;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      dot = fma(p[q], vo[q], dot);
+      if (tid + NT * q == k) {
+        sc[0] = p[q];
+        sc[1] = x[q];
+      }
+    }
+    dot = wave_sum_dpp(dot);
+    if (lane == 0) part1[wv] = dot;
+    __syncthreads();
+    if (dead) {  // workgroup-uniform
+      if (tid == 0) __hip_atomic_store(status, 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      return;
+    }
+    dot = 0.0;
+#pragma unroll
+    for (int q = 0; q < NW; ++q) dot += part1[q];
+    const double K = 0.5 * t_prev * dot;
+    const double v0 = k > 0 ? 1.0 : 0.0, w0 = k > 0 ? sc[0] - K : 0.0, dk = sc[1] - 2.0 * v0 * w0;
+    // w, and x = row k with the update of column k - 1 (kept beyond k + 1; alpha = x_{k+1})
+    double s2 = 0.0;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      const int c = tid + NT * q;
+      const double w = fma(-K, vo[q], p[q]);
+      x[q] -= fma(v0, w, w0 * vo[q]);
+      if (c == k + 1) sc[2] = x[q];
+      if (c <= k + 1 || c >= n) x[q] = 0.0;
+      s2 = fma(x[q], x[q], s2);
+      if (c < NC) {
+        ws[c] = w;
+        vs[c] = vo[q];
+        xs[c] = x[q];
+      }
+    }
+    s2 = wave_sum_dpp(s2);
+    if (lane == 0) part2[wv] = s2;
+    __syncthreads();
+    s2 = 0.0;
+#pragma unroll
+    for (int q = 0; q < NW; ++q) s2 += part2[q];
+    const double alpha = sc[2];
+    double beta, t, scale;
+    reflector(alpha, s2, beta, t, scale);
+    // the wave's rows: update by column k - 1, then their products with (1, scale x)
+    const int j0 = k >> 6, j1 = (k + 1) >> 6, l1 = (k + 1) & 63;
+    double acc[RW], ak[RW], w_row[RW];
+#pragma unroll
+    for (int r = 0; r < RW; ++r) {
+      acc[r] = ak[r] = 0.0;
+      w_row[r] = row[r] < n ? ws[row[r]] : 0.0;
+    }
+#pragma unroll
+    for (int j = 0; j < J; ++j)
+      if (j >= j0) {
+        const int c = lane + 64 * j;
+        const double wc = ws[c], vc = vs[c], xc = xs[c];
+#pragma unroll
+        for (int r = 0; r < RW; ++r) {
+          a[r][j] -= fma(v_row[r], wc, w_row[r] * vc);
+          acc[r] = fma(a[r][j], xc, acc[r]);
+          if (j == j1) ak[r] = read_lane(a[r][j], l1);
+        }
+      }
+#pragma unroll
+    for (int r = 0; r < RW; ++r) acc[r] = wave_sum_dpp(acc[r]);
+#pragma unroll
+    for (int r = 0; r < RW; ++r)
+      if (row[r] > k && row[r] < n) {  // wave-uniform
+        const double pr = t * fma(scale, acc[r], ak[r]);
+        if (lane == 0) {
+          publish(P + (size_t)k * n + row[r], pr);
+          if (k + 3 == n) p_last[row[r] - (k + 1)] = pr;
+        }
+        if (row[r] == k + 1) {
+#pragma unroll
+          for (int j = 0; j < J; ++j) {
+            const int c = lane + 64 * j;
+            if (c > k && c < n) publish(R + (size_t)(k + 1) * n + c, a[r][j]);
+          }
+        }
+        if (k + 3 == n) {  // the last 2 x 2 block, with the update of column n - 3 pending
+#pragma unroll
+          for (int j = 0; j < J; ++j) {
+            const int c = lane + 64 * j;
+            if (c >= n - 2 && c < n) A_out[(size_t)row[r] * n + c] = a[r][j];
+          }
+        }
+        v_row[r] = row[r] == k + 1 ? 1.0 : xs[row[r]] * scale;
+      }
+    t_prev = t;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      const int c = tid + NT * q;
+      vo[q] = c == k + 1 ? 1.0 : x[q] * scale;
+      if (writer && c > k && c < n) Vs[(size_t)k * n + (c - k - 1)] = vo[q];
+    }
+    if (writer && tid == 0) {
+      tau[k] = t;
+      e[k] = beta;
+      d[k] = dk;
+    }
+  }
+}
+
+// The same for n <= 4 N4 <= kSmallMax in one workgroup: four lanes per row (N4 columns
+// each, c = 4 i + lane), the two vectors in LDS, three barriers a column.  n = 60: 4.9 us
+// a column with a launch each, 1.5 us so.
+template <int N4>
+__global__ __launch_bounds__(16 * N4) void tridiag_small(const double* A_in, int n, double* A_out, double* Vs,
+                                                         double* tau, double* d, double* e, double* p_last) {
+  constexpr int NC = 4 * N4, NW = N4 / 4;
+  __shared__ double ps[NC], rs[NC];          // p of the previous column, row k
+  __shared__ double ws[NC], vs[NC], xs[NC];  // w, v of the previous column, x of this one (0 up to k + 1)
+  __shared__ double part1[NW], part2[NW], sc[1];
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, row = tid >> 2, q4 = tid & 3;
+  double a[N4], vo = 0.0, v_row = 0.0, t_prev = 0.0;
+#pragma unroll
+  for (int i = 0; i < N4; ++i) {
+    const int c = 4 * i + q4;
+    a[i] = (row < n && c < n) ? A_in[(size_t)row * n + c] : 0.0;
+  }
+  if (tid < NC) {
+    ps[tid] = 0.0;
+    rs[tid] = tid < n ? A_in[tid] : 0.0;
+  }
+  for (int k = 0; k + 2 < n; ++k) {
+    __syncthreads();
+    double p = 0.0, x = 0.0;  // thread c < NC: entry c (threads beyond hold zeros)
+    if (tid >= k && tid < n) {
+      p = ps[tid];
+      x = rs[tid];
+    }
+    double s = wave_sum_dpp(p * vo);
+    if (lane == 0) part1[wv] = s;
+    const double pk = ps[k], rk = rs[k];
+    __syncthreads();
+    double dot = 0.0;
+#pragma unroll
+    for (int q = 0; q < NW; ++q) dot += part1[q];
+    const double K = 0.5 * t_prev * dot, v0 = k > 0 ? 1.0 : 0.0, w0 = k > 0 ? pk - K : 0.0;
+    const double w = fma(-K, vo, p);
+    x -= fma(v0, w, w0 * vo);
+    if (tid == k + 1) sc[0] = x;
+    if (tid <= k + 1 || tid >= n) x = 0.0;
+    if (tid < NC) {
+      ws[tid] = w;
+      vs[tid] = vo;
+      xs[tid] = x;
+    }
+    s = wave_sum_dpp(x * x);
+    if (lane == 0) part2[wv] = s;
+    __syncthreads();
+    double s2 = 0.0;
+#pragma unroll
+    for (int q = 0; q < NW; ++q) s2 += part2[q];
+    double beta, t, scale;
+    reflector(sc[0], s2, beta, t, scale);
+    double acc = 0.0, ak = 0.0;
+    const double w_row = ws[row];
+#pragma unroll
+    for (int i = 0; i < N4; ++i) {
+      const int c = 4 * i + q4;
+      a[i] -= fma(v_row, ws[c], w_row * vs[c]);
+      acc = fma(a[i], xs[c], acc);
+      if (c == k + 1) ak = a[i];
+    }
+    acc = fma(scale, acc, ak);  // ak: on one of the row's lanes
+    acc += __shfl_xor(acc, 1, 64);
+    acc += __shfl_xor(acc, 2, 64);
+    if (row > k && row < n) {
+      if (q4 == 0) {
+        ps[row] = t * acc;
+        if (k + 3 == n) p_last[row - (k + 1)] = t * acc;
+      }
+      if (row == k + 1) {
+#pragma unroll
+        for (int i = 0; i < N4; ++i) {
+          const int c = 4 * i + q4;
+          if (c > k) rs[c] = a[i];
+        }
+      }
+      if (k + 3 == n) {  // the last 2 x 2 block, with the update of column n - 3 pending
+#pragma unroll
+        for (int i = 0; i < N4; ++i) {
+          const int c = 4 * i + q4;
+          if (c >= n - 2 && c < n) A_out[(size_t)row * n + c] = a[i];
+        }
+      }
+      v_row = row == k + 1 ? 1.0 : xs[row] * scale;
+    }
+    vo = tid == k + 1 ? 1.0 : x * scale;
+    if (tid > k && tid < n) Vs[(size_t)k * n + (tid - k - 1)] = vo;
+    if (tid == 0) {
+      tau[k] = t;
+      e[k] = beta;
+      d[k] = rk - 2.0 * v0 * w0;
+    }
+    t_prev = t;
+  }
+}
+
+// slots of the resident form
+__global__ void fill_empty(unsigned long long* p, size_t n) {
+  for (size_t k = blockIdx.x * (size_t)blockDim.x + threadIdx.x; k < n; k += (size_t)gridDim.x * blockDim.x) p[k] = kEmpty;
+}
+
+template <int J, int RW>
+hipError_t launch_resident_multi(const double* A_in, int n, double* A_out, double* Vs, double* tau, double* d, double* e,
+                                 unsigned long long* P, unsigned long long* R, double* p_last, int* status,
+                                 hipStream_t st) {
+  void* args[] = {&A_in, &n, &A_out, &Vs, &tau, &d, &e, &P, &R, &p_last, &status};
+  return hipLaunchCooperativeKernel(reinterpret_cast<const void*>(&tridiag_resident<J, RW>), dim3((n + 4 * RW - 1) / (4 * RW)),
+                                    dim3(kResThreads), args, 0, st);
+}
+
+// false: not launched (the caller takes the launch-per-column form)
+bool launch_resident(const double* A_in, int n, double* A_out, double* Vs, double* tau, double* d, double* e,
+                     unsigned long long* P, unsigned long long* R, double* p_last, int* status, hipStream_t st) {
+  if (n <= kSmallMax) {
+    if (n <= 64) hipLaunchKernelGGL(tridiag_small<16>, dim3(1), dim3(256), 0, st, A_in, n, A_out, Vs, tau, d, e, p_last);
+    else hipLaunchKernelGGL(tridiag_small<32>, dim3(1), dim3(512), 0, st, A_in, n, A_out, Vs, tau, d, e, p_last);
+    return true;
+  }
+  const size_t slots = 2 * (size_t)n * n;
+  hipLaunchKernelGGL(fill_empty, dim3((unsigned)std::min<size_t>(2048, (slots + 255) / 256)), dim3(256), 0, st, P, slots);
+  hipError_t err = hipErrorInvalidValue;
+#define DFPT2_RESIDENT(J) err = launch_resident_multi<J, kResRows>(A_in, n, A_out, Vs, tau, d, e, P, R, p_last, status, st)
+  if (n <= 256) DFPT2_RESIDENT(4);
+  else if (n <= 512) DFPT2_RESIDENT(8);
+  else if (n <= 768) DFPT2_RESIDENT(12);
+  else if (n <= 1024) DFPT2_RESIDENT(16);
+  else if (n <= 1280) DFPT2_RESIDENT(20);
+  else if (n <= 1664) DFPT2_RESIDENT(26);
+  else DFPT2_RESIDENT(32);
+#undef DFPT2_RESIDENT
+  if (err != hipSuccess) (void)hipGetLastError();
+  return err == hipSuccess;
+}
+
 // d[n-2], d[n-1], e[n-2] from the last 2 x 2 block, with the update of column n - 3
 // still pending when the lazy steps were used (p_last = p of column n - 3)
 __global__ void tridiag_tail_lazy(const double* A, int n, const double* Vs, const double* tau,
@@ -213,97 +607,348 @@ __global__ void tridiag_tail(const double* A, int n, double* d, double* e) {
 }
 
 // ---------------------------------------------------------------- splitting
-// Zero negligible off-diagonals, record unreduced blocks: blk_of[pos] = start of
-// the block containing pos; blk_end[pos] = one past its end.  Also the norm.
-__global__ void tridiag_split(int n, const double* d, double* e, int* blk_start, int* blk_end,
-                              double* tnorm) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
+// Zero negligible off-diagonals, record unreduced blocks: blk_start[pos], blk_end[pos]
+// = first and one past the last position of the block containing pos.  Also the norm.
+// One workgroup; every thread owns a run of positions, the starts are a prefix maximum
+// and the ends a suffix minimum over the runs (a single thread took 450 us at n = 1200).
+__global__ __launch_bounds__(1024) void tridiag_split(int n, const double* d, double* e, int* blk_start,
+                                                      int* blk_end, double* tnorm) {
+  __shared__ double shn[1024];
+  __shared__ int last[1024], first[1024];
+  const int tid = threadIdx.x, per = (n + 1023) / 1024;
+  const int i0 = min(n, tid * per), i1 = min(n, i0 + per);
   double nrm = 0.0;
-  for (int i = 0; i < n; ++i) {
-    double r = fabs(d[i]) + (i > 0 ? fabs(e[i - 1]) : 0.0) + (i + 1 < n ? fabs(e[i]) : 0.0);
-    nrm = fmax(nrm, r);
-  }
-  *tnorm = nrm;
-  const double eps = DBL_EPSILON;
-  int start = 0;
-  for (int i = 0; i < n; ++i) {
-    bool brk = (i == n - 1);
-    if (!brk) {
-      const double ee = fabs(e[i]);
-      if (ee <= eps * sqrt(fabs(d[i])) * sqrt(fabs(d[i + 1])) || ee <= DBL_MIN * 1e6 || ee <= 1e-300) {
-        e[i] = 0.0;
-        brk = true;
-      }
+  for (int i = i0; i < i1; ++i)
+    nrm = fmax(nrm, fabs(d[i]) + (i > 0 ? fabs(e[i - 1]) : 0.0) + (i + 1 < n ? fabs(e[i]) : 0.0));
+  shn[tid] = nrm;
+  __syncthreads();  // the neighbours have read e before it changes
+  auto breaks = [&](int i) {
+    if (i == n - 1) return true;
+    const double ee = fabs(e[i]);
+    return ee <= DBL_EPSILON * sqrt(fabs(d[i])) * sqrt(fabs(d[i + 1])) || ee <= DBL_MIN * 1e6 || ee <= 1e-300;
+  };
+  int lb = -1, fb = n;  // last and first break of the run
+  for (int i = i0; i < i1; ++i)
+    if (breaks(i)) {
+      if (i + 1 < n) e[i] = 0.0;
+      lb = i;
+      if (fb == n) fb = i;
     }
-    if (brk) {
-      for (int q = start; q <= i; ++q) {
-        blk_start[q] = start;
-        blk_end[q] = i + 1;
+  last[tid] = lb;
+  first[tid] = fb;
+  __syncthreads();
+  for (int o = 1; o < 1024; o <<= 1) {
+    const int l = tid >= o ? last[tid - o] : -1, f = tid + o < 1024 ? first[tid + o] : n;
+    const double q = tid >= o ? shn[tid - o] : 0.0;
+    __syncthreads();
+    last[tid] = max(last[tid], l);
+    first[tid] = min(first[tid], f);
+    shn[tid] = fmax(shn[tid], q);
+    __syncthreads();
+  }
+  if (tid == 1023) *tnorm = shn[1023];
+  int st = (tid > 0 ? last[tid - 1] : -1) + 1;
+  for (int i = i0; i < i1; ++i) {
+    blk_start[i] = st;
+    if (i + 1 < n ? e[i] == 0.0 : true) st = i + 1;
+  }
+  int en = tid + 1 < 1024 ? first[tid + 1] : n;
+  for (int i = i1 - 1; i >= i0; --i) {
+    if (i + 1 < n ? e[i] == 0.0 : true) en = i;
+    blk_end[i] = en + 1;
+  }
+}
+
+// 1 / q to within an ulp or two (finite, normal q): the hardware's estimate and two
+// Newton steps, a third of the latency of a correctly rounded division
+__device__ inline double fast_rcp(double q) {
+  double r = __builtin_amdgcn_rcp(q);
+  r = fma(fma(-q, r, 1.0), r, r);
+  return fma(fma(-q, r, 1.0), r, r);
+}
+
+// Sturm counts (eigenvalues of the block smaller than x) at two points in one pass over
+// the block, two chains in flight.  In the scaled form below (kProduct) T is scaled by a
+// power of two to ||T|| <= 1 and the count is the number of sign changes of
+//     p_{i+1} = (d_i - x) p_i - e_{i-1}^2 p_{i-1},
+// rescaled by a power of two every 8 steps: three FP64 operations a step instead of the
+// dozen of q_{i+1} = d_i - x - e_{i-1}^2 / q_i, and the same backward error (p_{i+1} / p_i
+// is q_i with d - x and e off by a few relative roundings).  A zero p_i takes either sign
+// for exactly one change between its neighbours, as it should.  It needs e^2 >= 1e-60 in
+// the scaled block, so that 8 steps cannot underflow; otherwise the q form runs.
+template <bool kProduct>
+__device__ inline void sturm_pair(const double* d, const double* e, int s, int t, double xa, double xb, double pivmin,
+                                  int& ca, int& cb) {
+  ca = cb = 0;
+  if (kProduct) {
+    double a0 = 1.0, b0 = 1.0, a1 = d[s] - xa, b1 = d[s] - xb;
+    ca = a1 < 0.0;
+    cb = b1 < 0.0;
+    auto hi = [](double v) { return (unsigned)(__builtin_bit_cast(unsigned long long, v) >> 32); };
+    for (int i0 = s + 1; i0 < t; i0 += 8) {
+      const int m = min(8, t - i0);
+      auto step = [&](int i) {
+        const double di = d[i], e2 = e[i - 1];  // LDS holds e^2
+        const double a2 = fma(di - xa, a1, -e2 * a0), b2 = fma(di - xb, b1, -e2 * b0);
+        ca += (hi(a2) ^ hi(a1)) >> 31;
+        cb += (hi(b2) ^ hi(b1)) >> 31;
+        a0 = a1;
+        b0 = b1;
+        a1 = a2;
+        b1 = b2;
+      };
+      if (m == 8) {
+#pragma unroll
+        for (int q = 0; q < 8; ++q) step(i0 + q);
+      } else {
+        for (int q = 0; q < m; ++q) step(i0 + q);
       }
-      start = i + 1;
+      const int ea = __builtin_amdgcn_frexp_exp(fmax(fabs(a0), fabs(a1))), eb = __builtin_amdgcn_frexp_exp(fmax(fabs(b0), fabs(b1)));
+      a0 = __builtin_amdgcn_ldexp(a0, -ea);
+      a1 = __builtin_amdgcn_ldexp(a1, -ea);
+      b0 = __builtin_amdgcn_ldexp(b0, -eb);
+      b1 = __builtin_amdgcn_ldexp(b1, -eb);
+    }
+  } else {
+    double qa = d[s] - xa, qb = d[s] - xb;
+    if (fabs(qa) < pivmin) qa = -pivmin;
+    if (fabs(qb) < pivmin) qb = -pivmin;
+    ca = qa < 0.0;
+    cb = qb < 0.0;
+    for (int i = s + 1; i < t; ++i) {
+      const double di = d[i], e2 = e[i - 1] * e[i - 1];
+      qa = fma(-e2, fast_rcp(qa), di - xa);
+      qb = fma(-e2, fast_rcp(qb), di - xb);
+      if (fabs(qa) < pivmin) qa = -pivmin;
+      if (fabs(qb) < pivmin) qb = -pivmin;
+      ca += qa < 0.0;
+      cb += qb < 0.0;
     }
   }
 }
 
-// Number of eigenvalues of the block [s, t) smaller than x (Sturm sequence).
-__device__ int sturm_count(const double* d, const double* e, int s, int t, double x, double pivmin) {
-  int cnt = 0;
-  double q = d[s] - x;
-  if (fabs(q) < pivmin) q = -pivmin;
-  if (q < 0.0) ++cnt;
-  for (int i = s + 1; i < t; ++i) {
-    q = d[i] - x - e[i - 1] * e[i - 1] / q;
-    if (fabs(q) < pivmin) q = -pivmin;
-    if (q < 0.0) ++cnt;
+// Bracket [lo, hi] of the j-th eigenvalue of the block [s, t) shrunk by a wave: each lane
+// takes the counts at two of 128 interior points, and the bracket becomes the interval
+// between the highest point whose count is <= j and the next one (129x per round, ~8
+// rounds).  The invariant count(lo) <= j < count(hi) holds whatever the rounding.
+template <bool kProduct>
+__device__ double multisect(const double* d, const double* e, int s, int t, int j, double lo, double hi,
+                            double pivmin, int lane) {
+  for (int it = 0; it < 64; ++it) {
+    if (hi - lo <= 2.0 * DBL_EPSILON * fmax(fabs(lo), fabs(hi)) + pivmin) break;
+    const double h = (hi - lo) / 129.0;
+    const double xa = fmin(fmax(lo + (double)(2 * lane + 1) * h, lo), hi);
+    const double xb = fmin(fmax(lo + (double)(2 * lane + 2) * h, lo), hi);
+    int ca, cb;
+    sturm_pair<kProduct>(d, e, s, t, xa, xb, pivmin, ca, cb);
+    const bool la = (xa <= lo) ? true : (xa >= hi) ? false : ca <= j;
+    const bool lb = (xb <= lo) ? true : (xb >= hi) ? false : cb <= j;
+    // points in order: 2 lane (a), 2 lane + 1 (b)
+    const unsigned long long ma = __ballot(la), mb = __ballot(lb);
+    const int klo = max(ma ? 2 * (63 - __clzll((long long)ma)) : -1, mb ? 2 * (63 - __clzll((long long)mb)) + 1 : -1);
+    const int khi = klo + 1;
+    const int l0 = (klo < 0 ? 0 : klo) >> 1, l1 = (khi > 127 ? 127 : khi) >> 1;
+    const double lo_a = __shfl(xa, l0, 64), lo_b = __shfl(xb, l0, 64), hi_a = __shfl(xa, l1, 64), hi_b = __shfl(xb, l1, 64);
+    const double nlo = klo >= 0 ? ((klo & 1) ? lo_b : lo_a) : lo;
+    const double nhi = khi < 128 ? ((khi & 1) ? hi_b : hi_a) : hi;
+    if (!(nlo > lo || nhi < hi)) break;  // the points no longer split the bracket
+    lo = nlo;
+    hi = nhi;
   }
-  return cnt;
+  return 0.5 * (lo + hi);
 }
 
-// Wave g (four per workgroup): the (g - start)-th eigenvalue of the block
-// containing position g, by multisection: each lane takes the Sturm count at one
-// of 64 interior points of the bracket, and the bracket shrinks to the interval
-// between the highest point whose count is <= j and the lowest point above it
-// whose count is > j (65x per round instead of 2x, so ~9 rounds of parallel
-// counts instead of ~55 sequential ones).  The invariant count(lo) <= j <
-// count(hi) holds whatever the rounding of the points or counts; the stopping
-// rule is that of the bisection below.
-__global__ __launch_bounds__(256) void tridiag_multisect(int n, const double* d, const double* e,
+// Wave g (four per workgroup): the (g - start)-th eigenvalue of the block containing
+// position g.  What bounds it is the issue of the counts' FP64 operations.  d and e^2 (or
+// e) come from LDS up to n = kSturmLds.  n = 1200: 1.8 ms with one point per lane, full
+// divisions and global reads; 1.3 ms with two points and fast reciprocals; 0.5 ms in the
+// product form.
+constexpr int kSturmLds = 4096;
+
+template <bool kLds>
+__global__ __launch_bounds__(256) void tridiag_multisect(int n, const double* dg, const double* eg,
                                                          const int* blk_start, const int* blk_end,
                                                          const double* tnorm, double* lam) {
+  extern __shared__ double msh[];
+  __shared__ int small;
   const int g = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const double nrm = fmax(*tnorm, DBL_MIN);
+  int ex = 0;
+  bool product = false;
+  if (kLds) {
+    ex = nrm < 1e300 ? __builtin_amdgcn_frexp_exp(nrm) : 0;
+    if (threadIdx.x == 0) small = nrm < 1e300 ? 0 : 1;
+    __syncthreads();
+    int sm = 0;
+    for (int i = threadIdx.x; i < n; i += blockDim.x) {
+      const double ei = i + 1 < n ? ldexp(eg[i], -ex) : 0.0;
+      msh[i] = ldexp(dg[i], -ex);
+      msh[n + i] = ei;
+      sm |= ei != 0.0 && !(ei * ei >= 1e-60);
+    }
+    if (sm) small = 1;
+    __syncthreads();
+    product = !small;
+    if (product)
+      for (int i = threadIdx.x; i < n; i += blockDim.x) msh[n + i] *= msh[n + i];  // e^2
+    __syncthreads();
+  }
   if (g >= n) return;  // wave-uniform
   const int s = blk_start[g], t = blk_end[g], j = g - s;
   double lo = DBL_MAX, hi = -DBL_MAX;
   for (int i = s + lane; i < t; i += 64) {
-    const double r = (i > s ? fabs(e[i - 1]) : 0.0) + (i + 1 < t ? fabs(e[i]) : 0.0);
-    lo = fmin(lo, d[i] - r);
-    hi = fmax(hi, d[i] + r);
+    const double r = (i > s ? fabs(eg[i - 1]) : 0.0) + (i + 1 < t ? fabs(eg[i]) : 0.0);
+    lo = fmin(lo, dg[i] - r);
+    hi = fmax(hi, dg[i] + r);
   }
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) {
     lo = fmin(lo, __shfl_xor(lo, o, 64));
     hi = fmax(hi, __shfl_xor(hi, o, 64));
   }
-  const double nrm = fmax(*tnorm, DBL_MIN);
   const double pivmin = DBL_MIN * fmax(1.0, nrm * nrm) * 4.0;
   const double pad = 2.0 * DBL_EPSILON * nrm * (t - s) + 2.0 * pivmin;
   lo -= pad;
   hi += pad;
-  for (int it = 0; it < 64; ++it) {
-    if (hi - lo <= 2.0 * DBL_EPSILON * fmax(fabs(lo), fabs(hi)) + pivmin) break;
-    const double x = fmin(fmax(lo + (double)(lane + 1) * ((hi - lo) / 65.0), lo), hi);
-    const bool le = (x <= lo) ? true : (x >= hi) ? false : (sturm_count(d, e, s, t, x, pivmin) <= j);
-    const unsigned long long m = __ballot(le);
-    const int klo = m ? 63 - __clzll((long long)m) : -1;
-    const unsigned long long above = ~m & (klo >= 63 ? 0ull : (~0ull << (klo + 1)));
-    const int khi = above ? __ffsll((long long)above) - 1 : 64;
-    const double nlo = klo >= 0 ? __shfl(x, klo, 64) : lo;
-    const double nhi = khi < 64 ? __shfl(x, khi, 64) : hi;
-    if (!(nlo > lo || nhi < hi)) break;  // the points no longer split the bracket
-    lo = nlo;
-    hi = nhi;
+  double x;
+  if (product)  // in units of 2^ex (exact)
+    x = ldexp(multisect<true>(msh, msh + n, s, t, j, ldexp(lo, -ex), ldexp(hi, -ex), 8.0 * DBL_MIN, lane), ex);
+  else
+    x = multisect<false>(dg, eg, s, t, j, lo, hi, pivmin, lane);
+  if (lane == 0) lam[g] = x;
+}
+
+// ------------------------------------------------------------ twisted factorization
+// Eigenvector of an eigenvalue that is isolated in its block (both gaps above
+// kIsolated ||T||), one thread each: T - lam = L D L^T from the top and U D U^T from the
+// bottom, z = 1 at the row r where they leave the smallest pivot, and z_i = -l_i z_{i+1}
+// above, z_{i+1} = -u_i z_i below.  Either factorization is exact for off-diagonals off
+// by a few ulps (as in the Sturm counts), so the residual is the twist pivot over ||z||
+// plus a few ulps of ||T||: the vector is as good as inverse iteration's, in three
+// passes over the block instead of thirteen, without pivoting.  A residual above
+// 50 eps ||T|| or a value that is not finite leaves done[g] = 0, and the vector to
+// inverse iteration.  What bounds it is the chain of a factorization (one reciprocal and
+// three operations a position).  A wave takes VW vectors, 64 / VW lanes each: lane 0 of a
+// group runs down the block and lane 1 up, each writing its multipliers to LDS, all lanes
+// search for the twist, lanes 0 and 1 run the two recurrences of z over the multipliers in
+// place, and all lanes scale and store.  n = 1200: 5.9 ms for inverse iteration (its LU
+// arrays stream through memory nine times), 1.4 ms with one thread per vector and l, u in
+// memory, 0.28 ms so.
+constexpr double kIsolated = 1e-8;
+// LDS of a wave of VW vectors: d, e and the multipliers l, u
+constexpr size_t twisted_bytes(int n, int vw) { return (size_t)n * 8 * (2 + 2 * vw); }
+constexpr size_t kTwistedLds = 160 * 1024 - 256;
+
+template <int VW>
+__global__ __launch_bounds__(64) void tridiag_twisted(int n, const double* dg, const double* eg, const int* blk_start,
+                                                      const int* blk_end, const double* tnorm, const double* lam,
+                                                      double* __restrict__ X, int* done, const double* vec_floor) {
+  extern __shared__ double msh[];
+  constexpr int G = 64 / VW;
+  double *d = msh, *e = msh + n, *Lm = msh + 2 * n, *Um = Lm + (size_t)VW * n;
+  const int lane = threadIdx.x, v = lane / G, q = lane - v * G, g = blockIdx.x * VW + v;
+  for (int i = lane; i < n; i += 64) {
+    d[i] = dg[i];
+    e[i] = i + 1 < n ? eg[i] : 0.0;
   }
-  if (lane == 0) lam[g] = 0.5 * (lo + hi);
+  __syncthreads();
+  const double nrm = fmax(*tnorm, DBL_MIN), pivmin = DBL_MIN * fmax(1.0, nrm * nrm) * 4.0;
+  int s = 0, t = 0;
+  double x = 0.0;
+  bool go = g < n;
+  if (go) {
+    s = blk_start[g];
+    t = blk_end[g];
+    x = lam[g];
+    go = t - s > 1 && !(vec_floor && !(x > *vec_floor)) && !(g > s && !(fabs(x - lam[g - 1]) > kIsolated * nrm)) &&
+         !(g + 1 < t && !(fabs(lam[g + 1] - x) > kIsolated * nrm));
+    if (!go && q == 0) done[g] = 0;
+  }
+  if (!go) s = t = 0;  // the group's lanes stay for the barriers
+  // factorizations: lane 0 downwards (l at v + VW i), lane 1 upwards (u)
+  if (q < 2 && t > s) {
+    const int st = q == 0 ? 1 : -1;
+    int i = q == 0 ? s : t - 1, o = q == 0 ? s : t - 2;  // position, off-diagonal towards the next one
+    double* M = (q == 0 ? Lm : Um) + v;
+    double piv = d[i] - x;
+#pragma unroll 4
+    for (int k = t - 1 - s; k > 0; --k, i += st, o += st) {
+      if (fabs(piv) < pivmin) piv = -pivmin;
+      const double eo = e[o], m = eo * fast_rcp(piv);
+      M[(size_t)o * VW] = m;
+      piv = fma(-eo, m, d[i + st] - x);
+    }
+  }
+  __syncthreads();
+  // twist where the pivot, with its rounding, is smallest
+  int r = 0x7fffffff;
+  double best = DBL_MAX, gam = 0.0;
+  for (int i = s + q; i < t; i += G) {
+    const double el = i > s ? e[i - 1] * Lm[(size_t)(i - 1) * VW + v] : 0.0;
+    const double eu = i + 1 < t ? e[i] * Um[(size_t)i * VW + v] : 0.0;
+    const double dx = d[i] - x, ga = (dx - el) - eu;
+    const double c = fabs(ga) + DBL_EPSILON * (fabs(dx) + fabs(el) + fabs(eu));
+    if (c < best) {
+      best = c;
+      r = i;
+      gam = ga;
+    }
+  }
+#pragma unroll
+  for (int o = G / 2; o >= 1; o >>= 1) {
+    const double ob = __shfl_xor(best, o, 64), og = __shfl_xor(gam, o, 64);
+    const int orr = __shfl_xor(r, o, 64);
+    if (ob < best || (ob == best && orr < r)) {
+      best = ob;
+      gam = og;
+      r = orr;
+    }
+  }
+  if (r < s || r >= t) r = s;  // no finite pivot (the residual test below fails)
+  __syncthreads();
+  // z_i over l_i for i < r (lane 0), z_{i+1} over u_i for i >= r (lane 1)
+  if (q == 0 && t > s) {
+    double z = 1.0;
+#pragma unroll 8
+    for (int i = r - 1; i >= s; --i) {
+      z = -Lm[(size_t)i * VW + v] * z;
+      Lm[(size_t)i * VW + v] = z;
+    }
+  }
+  if (q == 1 && t > s) {
+    double z = 1.0;
+#pragma unroll 8
+    for (int i = r; i < t - 1; ++i) {
+      z = -Um[(size_t)i * VW + v] * z;
+      Um[(size_t)i * VW + v] = z;
+    }
+  }
+  __syncthreads();
+  double nz = 0.0;
+  auto zat = [&](int i) {
+    return i < r ? Lm[(size_t)i * VW + v] : i > r ? Um[(size_t)(i - 1) * VW + v] : 1.0;
+  };
+  for (int i = s + q; i < t; i += G) {
+    const double z = zat(i);
+    nz = fma(z, z, nz);
+  }
+#pragma unroll
+  for (int o = G / 2; o >= 1; o >>= 1) nz += __shfl_xor(nz, o, 64);
+  if (!go) return;
+  const double nn = sqrt(nz);
+  if (!(nn < 1e150) || !(best < DBL_MAX) || !(fabs(gam) <= 50.0 * DBL_EPSILON * nrm * nn)) {
+    if (q == 0) done[g] = 0;
+    return;
+  }
+  const double inv = 1.0 / nn;
+  for (int i = q; i < n; i += G) X[(size_t)i * n + g] = (i >= s && i < t) ? zat(i) * inv : 0.0;
+  if (q == 0) done[g] = 1;
+}
+
+// no vector is formed by a twisted factorization (n beyond its LDS)
+__global__ void zero_done(int n, int* done) {
+  const int g = blockIdx.x * blockDim.x + threadIdx.x;
+  if (g < n) done[g] = 0;
 }
 
 // ------------------------------------------------------------ inverse iteration
@@ -409,9 +1054,11 @@ __device__ double lu_solve(int s, int t, const LuCols& L, int n, int g, double* 
 // eigenpairs, such as the NAF compression, skip the cost of large clusters).
 __global__ void tridiag_inverse_iteration(int n, const double* d, const double* e, const int* blk_start,
                                           const int* blk_end, const double* tnorm, const double* lam,
-                                          LuCols L, double* X, int* status, const double* vec_floor) {
+                                          LuCols L, double* X, int* status, const double* vec_floor,
+                                          const int* done) {
   const int g = blockIdx.x * blockDim.x + threadIdx.x;
-  if (g >= n) return;
+  // done: the twisted factorization formed this vector; 2: there is no tridiagonal matrix
+  if (g >= n || done[g] || *status == 2) return;
   const int s = blk_start[g], t = blk_end[g];
   if (vec_floor && !(lam[g] > *vec_floor)) {
     for (int i = 0; i < n; ++i) X[(size_t)i * n + g] = 0.0;
@@ -432,11 +1079,13 @@ __global__ void tridiag_inverse_iteration(int n, const double* d, const double* 
   int g1 = g + 1;
   while (g1 < t && fabs(lam[g1] - lam[g1 - 1]) <= grp_tol) ++g1;
   const double tiny = DBL_EPSILON * nrm;
+  double lq = 0.0;
   for (int q = g; q < g1; ++q) {
     // zero the column outside the block, random start inside
     for (int i = 0; i < n; ++i) X[(size_t)i * n + q] = (i >= s && i < t) ? hash_unit(q, i) : 0.0;
-    // eigenvalues of a group are spread by a few ulps so that the factors differ
-    const double lq = lam[q] + (double)(q - g) * 4.0 * DBL_EPSILON * nrm;
+    // shifts of a group are kept a few ulps apart so that the factors differ; no further,
+    // so that a shift stays with its own eigenvalue wherever the gaps are wider
+    lq = q == g ? lam[q] : fmax(lam[q], lq + 4.0 * DBL_EPSILON * nrm);
     lu_factor(d, e, s, t, lq, tiny, L, n, g);
     // the solves and the orthogonalization are linear, so between iterations the
     // vector is only rescaled against overflow (by 1 / max |x|, applied as the
@@ -460,7 +1109,7 @@ __global__ void tridiag_inverse_iteration(int n, const double* d, const double* 
         }
       }
       if (!(mx > 0.0) || !isfinite(mx)) {
-        atomicExch(status, 1);
+        atomicMax(status, 1);
         return;
       }
       scl = 1.0 / mx;
@@ -615,18 +1264,140 @@ __global__ __launch_bounds__(256) void tridiag_backtransform(int n, const double
   }
 }
 
+// The same back-transformation on the FP64 matrix pipe, in blocks of 16 reflectors, for
+// 8 <= n <= 2048.  A workgroup keeps 16 columns of Z in registers: the register r of a 16 x 16
+// block in the products' output layout (row 4 r + lane / 16) is the second operand of the
+// contraction step r, so Z is both the operand of P = V^T Z and the accumulator of
+// Z -= V (T P) and never moves.  Row blocks are dealt round-robin to the 8 waves (the
+// reflectors act below k0 only); the waves' partial P meet in LDS, one barrier per block.
+// What bounds it: two passes over V per block from L2 and the chain P -> T P -> Z.
+// n = 1200: 2.0 ms with blocks of 8 on vector instructions, Z in LDS and three barriers;
+// 0.45 ms so.
+constexpr int WY16 = 16;
+
+// V[i][j] of block k0, 0 outside
+__device__ inline double wy16_v(const double* Vs, int n, int k0, int nr, int i, int j) {
+  const int k = k0 + j;
+  return (j < nr && i > k && i < n) ? Vs[(size_t)k * n + (i - k - 1)] : 0.0;
+}
+
+// T of every block ([16][16], upper triangular): S = V^T V, then each row by itself
+__global__ __launch_bounds__(256) void wy16_build_t(int n, const double* Vs, const double* tau, double* Tout) {
+  __shared__ double part[4][256];
+  __shared__ double S[16][17];
+  const int k0 = blockIdx.x * WY16, nr = min(WY16, n - 2 - k0);  // reflectors 0 .. n - 3
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, r16 = lane & 15, kq = lane >> 4;
+  d4 acc = (d4){0.0, 0.0, 0.0, 0.0};
+  for (int rb = k0 / 16 * 16 + 16 * w; rb < n; rb += 64)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const double v = wy16_v(Vs, n, k0, nr, rb + 4 * r + kq, r16);
+      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(v, v, acc, 0, 0, 0);
+    }
+#pragma unroll
+  for (int r = 0; r < 4; ++r) part[w][(kq + 4 * r) * 16 + r16] = acc[r];
+  __syncthreads();
+  S[tid >> 4][tid & 15] = (part[0][tid] + part[1][tid]) + (part[2][tid] + part[3][tid]);
+  __syncthreads();
+  if (tid < 16) {  // T_cc = tau_c, T[i][c] = -tau_c sum_l T[i][l] S[l][c]
+    double T[16];
+#pragma unroll
+    for (int c = 0; c < 16; ++c) {
+      const double tc = c < nr ? tau[k0 + c] : 0.0;
+      double sum = 0.0;
+#pragma unroll
+      for (int l = 0; l < c; ++l) sum += (l >= tid ? T[l] : 0.0) * S[l][c];
+      T[c] = c < tid ? 0.0 : c == tid ? tc : -tc * sum;
+      Tout[(size_t)blockIdx.x * 256 + tid * 16 + c] = T[c];
+    }
+  }
+}
+
+template <int NB>
+__global__ __launch_bounds__(512) void backtransform16(int n, const double* Vs, const double* Tall, double* Z) {
+  __shared__ double part[2][8][256];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, r16 = lane & 15, kq = lane >> 4;
+  const int c = blockIdx.x * 16 + r16;
+  d4 z[NB];
+#pragma unroll
+  for (int b = 0; b < NB; ++b)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int i = 16 * (w + 8 * b) + 4 * r + kq;
+      z[b][r] = (i < n && c < n) ? Z[(size_t)i * n + c] : 0.0;
+    }
+  const int nblk = (n - 2 + WY16 - 1) / WY16;
+  for (int blk = nblk - 1; blk >= 0; --blk) {
+    const int k0 = blk * WY16, nr = min(WY16, n - 2 - k0), buf = blk & 1;
+    // V[i][j] = Vs[(k0 + j) n + i - (k0 + j) - 1] for j < nr and k0 + j < i < n: a buffer
+    // load from row k0, at an offset out of range (which reads zero) elsewhere: no branch
+    auto desc = __builtin_amdgcn_make_buffer_rsrc((void*)(Vs + (size_t)k0 * n), 0, 0x7fffffff, 0x00020000);
+    auto vload = [&](int i, int j) {
+      const int o = (j * (n - 1) + i - k0 - 1) * 8;
+      const bool in = j < nr && i > k0 + j && i < n;
+      typedef uint32_t u2 __attribute__((ext_vector_type(2)));
+      return __builtin_bit_cast(double, (u2)__builtin_amdgcn_raw_buffer_load_b64(desc, in ? o : (int)0x80000000, 0, 0));
+    };
+    d4 p = (d4){0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+      const int rb = 16 * (w + 8 * b);
+      if (rb + 15 > k0 && rb < n) {  // wave-uniform
+        double v[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) v[r] = vload(rb + 4 * r + kq, r16);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) p = __builtin_amdgcn_mfma_f64_16x16x4f64(v[r], z[b][r], p, 0, 0, 0);
+      }
+    }
+    double t[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) t[r] = Tall[(size_t)blk * 256 + r16 * 16 + 4 * r + kq];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) part[buf][w][r * 64 + lane] = p[r];
+    __syncthreads();
+    d4 wv = (d4){0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      double sum = 0.0;
+#pragma unroll
+      for (int q = 0; q < 8; ++q) sum += part[buf][q][r * 64 + lane];
+      wv = __builtin_amdgcn_mfma_f64_16x16x4f64(t[r], -sum, wv, 0, 0, 0);
+    }
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+      const int rb = 16 * (w + 8 * b);
+      if (rb + 15 > k0 && rb < n) {
+        double v[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) v[r] = vload(rb + r16, 4 * r + kq);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) z[b] = __builtin_amdgcn_mfma_f64_16x16x4f64(v[r], wv[r], z[b], 0, 0, 0);
+      }
+    }
+  }
+#pragma unroll
+  for (int b = 0; b < NB; ++b)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int i = 16 * (w + 8 * b) + 4 * r + kq;
+      if (i < n && c < n) Z[(size_t)i * n + c] = z[b][r];
+    }
+}
+
 // ------------------------------------------------------------ sort + orient
-// rank of eigenvalue g among all (ties by index), ascending
-__global__ void eig_rank(int n, const double* lam, int* rank) {
-  const int g = blockIdx.x * blockDim.x + threadIdx.x;
+// rank of eigenvalue g among all (ties by index), ascending; one wave per eigenvalue
+__global__ __launch_bounds__(256) void eig_rank(int n, const double* lam, int* rank) {
+  const int g = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
   if (g >= n) return;
   const double x = lam[g];
   int r = 0;
-  for (int q = 0; q < n; ++q) {
+  for (int q = lane; q < n; q += 64) {
     const double y = lam[q];
     r += (y < x || (y == x && q < g)) ? 1 : 0;
   }
-  rank[g] = r;
+  for (int o = 32; o > 0; o >>= 1) r += __shfl_xor(r, o, 64);
+  if (lane == 0) rank[g] = r;
 }
 
 // out column dst(g) = sign-oriented column g; descending: dst = n-1-rank
@@ -641,45 +1412,42 @@ __global__ void orth_correction(int n, double* M) {
   }
 }
 
-__global__ void eig_permute(int n, const double* lam, const int* rank, const double* Zin, double* w_out,
-                            double* Z_out, int descending) {
-  const int g = blockIdx.x;
-  __shared__ double bestv[4];
-  __shared__ int besti[4];
+// One workgroup per 16 columns (whole 128-byte lines), 64 rows at a time.
+__global__ __launch_bounds__(1024) void eig_permute(int n, const double* lam, const int* rank, const double* Zin,
+                                                    double* w_out, double* Z_out, int descending) {
+  __shared__ double bestv[64][17];
+  __shared__ int besti[64][17];
+  const int c = threadIdx.x & 15, q = threadIdx.x >> 4, g = blockIdx.x * 16 + c;
   double bv = -1.0;
   int bi = 0x7fffffff;
-  for (int i = threadIdx.x; i < n; i += blockDim.x) {
-    const double a = fabs(Zin[(size_t)i * n + g]);
-    if (a > bv || (a == bv && i < bi)) {
-      bv = a;
-      bi = i;
+  if (g < n)
+    for (int i = q; i < n; i += 64) {
+      const double a = fabs(Zin[(size_t)i * n + g]);
+      if (a > bv) {  // the lowest row of the largest magnitude
+        bv = a;
+        bi = i;
+      }
     }
-  }
-  for (int off = 32; off > 0; off >>= 1) {
-    const double ov = __shfl_xor(bv, off, 64);
-    const int oi = __shfl_xor(bi, off, 64);
-    if (ov > bv || (ov == bv && oi < bi)) {
-      bv = ov;
-      bi = oi;
-    }
-  }
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  if (lane == 0) {
-    bestv[w] = bv;
-    besti[w] = bi;
-  }
+  bestv[q][c] = bv;
+  besti[q][c] = bi;
   __syncthreads();
-  bv = bestv[0];
-  bi = besti[0];
-  for (int q = 1; q < (int)(blockDim.x >> 6); ++q)
-    if (bestv[q] > bv || (bestv[q] == bv && besti[q] < bi)) {
-      bv = bestv[q];
-      bi = besti[q];
+  for (int o = 32; o > 0; o >>= 1) {
+    if (q < o) {
+      const double ov = bestv[q + o][c];
+      const int oi = besti[q + o][c];
+      if (ov > bestv[q][c] || (ov == bestv[q][c] && oi < besti[q][c])) {
+        bestv[q][c] = ov;
+        besti[q][c] = oi;
+      }
     }
-  const double sgn = (Zin[(size_t)bi * n + g] < 0.0) ? -1.0 : 1.0;
+    __syncthreads();
+  }
+  if (g >= n) return;
+  bi = besti[0][c];
+  const double sgn = (bi < n && Zin[(size_t)bi * n + g] < 0.0) ? -1.0 : 1.0;
   const int dst = descending ? (n - 1 - rank[g]) : rank[g];
-  if (threadIdx.x == 0) w_out[dst] = lam[g];
-  for (int i = threadIdx.x; i < n; i += blockDim.x) Z_out[(size_t)i * n + dst] = sgn * Zin[(size_t)i * n + g];
+  if (q == 0) w_out[dst] = lam[g];
+  for (int i = q; i < n; i += 64) Z_out[(size_t)i * n + dst] = sgn * Zin[(size_t)i * n + g];
 }
 
 // *floor = rel * (largest eigenvalue magnitude)
@@ -716,8 +1484,9 @@ size_t eigh_workspace_bytes(int n) {
   return b;
 }
 
-int eigh_run(const double* A_in, int n, double* w_out, double* Z_out, char* ws, size_t ws_bytes, hipStream_t st,
-             int descending, double vec_floor_rel) {
+// resident: try the one-launch tridiagonalization
+static int eigh_attempt(const double* A_in, int n, double* w_out, double* Z_out, char* ws, size_t ws_bytes,
+                        hipStream_t st, int descending, double vec_floor_rel, bool resident, int* hs) {
   if (n < 1 || n > kEighMaxN) return fail(DFPT2_ERR_INVALID_ARG, "eigh: n=%d outside [1, %d]", n, kEighMaxN);
   if (ws_bytes < eigh_workspace_bytes(n)) return fail(DFPT2_ERR_WORKSPACE, "eigh workspace too small");
   const size_t nn = (size_t)n * n;
@@ -739,18 +1508,25 @@ int eigh_run(const double* A_in, int n, double* w_out, double* Z_out, char* ws, 
   int* blk_start = (int*)take((size_t)n * 4 * 3 + 64);
   int* blk_end = blk_start + n;
   int* rank = blk_end + n;
+  int* done = rank;  // until the ranks are formed
   int* status = rank + n;
   double* tnorm = (double*)take(64);
   double* Tall = (double*)take((size_t)((n + WY_NB - 1) / WY_NB + 1) * WY_NB * WY_NB * 8);
   hipError_t err;
   ProfScope prof_all(DFPT2_STAGE_EIGH, st);
-  if ((err = hipMemcpyAsync(A, A_in, nn * 8, hipMemcpyDeviceToDevice, st)) != hipSuccess)
-    return hip_fail(err, "eigh copy");
   hipLaunchKernelGGL(zero_int, dim3(1), dim3(64), 0, st, status, 1);
-  // 1. tridiagonalization: one lazy-update launch per column where its LDS
-  //    staging fits in 64 KB, else the two-launch form
-  if (n >= 3 && (size_t)(3 * (n - 1) + 2) * 8 <= 64 * 1024) {
-    double* pb[2] = {p, lam};  // p of consecutive columns alternate (lam is free until step 2)
+  // 1. tridiagonalization: in one launch up to kResidentMax (the slots of its vectors lie
+  //    in the LU columns); else one lazy-update launch per column where its LDS staging
+  //    fits in 64 KB; else the two-launch form
+  double* pb[2] = {p, lam};  // p of consecutive columns alternate (lam is free until step 2)
+  unsigned long long* slots = reinterpret_cast<unsigned long long*>(lu);
+  resident = resident && n >= 3 && n <= kResidentMax &&
+             launch_resident(A_in, n, A, Vs, tau, d, e, slots, slots + nn, pb[(n - 3) & 1], status, st);
+  if (!resident && (err = hipMemcpyAsync(A, A_in, nn * 8, hipMemcpyDeviceToDevice, st)) != hipSuccess)
+    return hip_fail(err, "eigh copy");
+  if (resident) {
+    hipLaunchKernelGGL(tridiag_tail_lazy, dim3(1), dim3(64), 0, st, A, n, Vs, tau, pb[(n - 3) & 1], d, e);
+  } else if (n >= 3 && (size_t)(3 * (n - 1) + 2) * 8 <= 64 * 1024) {
     for (int k = 0; k + 2 < n; ++k) {
       const int m = n - k - 1;
       int ga = (m + 3) / 4;
@@ -772,31 +1548,53 @@ int eigh_run(const double* A_in, int n, double* w_out, double* Z_out, char* ws, 
     }
     hipLaunchKernelGGL(tridiag_tail, dim3(1), dim3(64), 0, st, A, n, d, e);
   }
-  // 2. split + bisection
-  hipLaunchKernelGGL(tridiag_split, dim3(1), dim3(64), 0, st, n, d, e, blk_start, blk_end, tnorm);
-  hipLaunchKernelGGL(tridiag_multisect, dim3((n + 3) / 4), dim3(256), 0, st, n, d, e, blk_start, blk_end, tnorm,
-                     lam);
-  // 3. inverse iteration
+  // 2. split + multisection
+  hipLaunchKernelGGL(tridiag_split, dim3(1), dim3(1024), 0, st, n, d, e, blk_start, blk_end, tnorm);
+  const bool lds = n <= kSturmLds;
+  const size_t de_bytes = lds ? (size_t)n * 16 : 0;
+  const dim3 ms_grid((n + 3) / 4), tw_grid((n + 63) / 64);
+  if (lds)
+    hipLaunchKernelGGL(tridiag_multisect<true>, ms_grid, dim3(256), de_bytes, st, n, d, e, blk_start, blk_end, tnorm, lam);
+  else
+    hipLaunchKernelGGL(tridiag_multisect<false>, ms_grid, dim3(256), 0, st, n, d, e, blk_start, blk_end, tnorm, lam);
+  // 3. eigenvectors of isolated eigenvalues by twisted factorizations, the others by
+  //    inverse iteration
   LuCols L{lu, lu + nn, lu + 2 * nn, lu + 3 * nn, lu + 4 * nn};
   const double* floor_ptr = nullptr;
   if (vec_floor_rel > 0.0) {
     hipLaunchKernelGGL(lam_floor, dim3(1), dim3(64), 0, st, n, lam, vec_floor_rel, tnorm + 1);
     floor_ptr = tnorm + 1;
   }
-  hipLaunchKernelGGL(tridiag_inverse_iteration, dim3((n + 63) / 64), dim3(64), 0, st, n, d, e, blk_start, blk_end,
-                     tnorm, lam, L, X, status, floor_ptr);
-  // 4. back-transformation (compact-WY blocks)
-  if (n > 2) {
-    int cw = 4;  // columns per workgroup: as many as the LDS holds, up to 4
-    while (cw > 1 && (size_t)n * cw * 8 > 150 * 1024) cw >>= 1;
+  if (twisted_bytes(n, 4) <= kTwistedLds)
+    hipLaunchKernelGGL(tridiag_twisted<4>, dim3((n + 3) / 4), dim3(64), twisted_bytes(n, 4), st, n, d, e, blk_start,
+                       blk_end, tnorm, lam, X, done, floor_ptr);
+  else if (twisted_bytes(n, 1) <= kTwistedLds)
+    hipLaunchKernelGGL(tridiag_twisted<1>, dim3(n), dim3(64), twisted_bytes(n, 1), st, n, d, e, blk_start, blk_end,
+                       tnorm, lam, X, done, floor_ptr);
+  else
+    hipLaunchKernelGGL(zero_done, dim3((n + 255) / 256), dim3(256), 0, st, n, done);
+  hipLaunchKernelGGL(tridiag_inverse_iteration, tw_grid, dim3(64), 0, st, n, d, e, blk_start, blk_end, tnorm, lam, L, X,
+                     status, floor_ptr, done);
+  // 4. back-transformation (compact-WY blocks): on the matrix pipe while a workgroup's
+  //    16 columns fit its registers
+  if (n >= 8 && n <= 2048) {  // the T factors (nblk 16 x 16) go to the LU columns, free by now
+    const int nblk = (n - 2 + WY16 - 1) / WY16;
+    double* Tall = lu;
+    hipLaunchKernelGGL(wy16_build_t, dim3(nblk), dim3(256), 0, st, n, Vs, tau, Tall);
+    const dim3 grid((n + 15) / 16), block(512);
+    if (n <= 128) hipLaunchKernelGGL(backtransform16<1>, grid, block, 0, st, n, Vs, Tall, X);
+    else if (n <= 512) hipLaunchKernelGGL(backtransform16<4>, grid, block, 0, st, n, Vs, Tall, X);
+    else if (n <= 1280) hipLaunchKernelGGL(backtransform16<10>, grid, block, 0, st, n, Vs, Tall, X);
+    else hipLaunchKernelGGL(backtransform16<16>, grid, block, 0, st, n, Vs, Tall, X);
+  } else if (n > 2) {
+    const int cw = (size_t)n * 2 * 8 <= 150 * 1024 ? 2 : 1;  // columns per workgroup that the LDS holds
     if ((size_t)n * cw * 8 > 150 * 1024) return fail(DFPT2_ERR_UNSUPPORTED, "eigh: n=%d too large", n);
     const int nblk = (n - 2 + WY_NB - 1) / WY_NB;
     hipLaunchKernelGGL(wy_build_t, dim3(nblk), dim3(256), 0, st, n, Vs, tau, Tall);
     const dim3 grid((n + cw - 1) / cw), block(256);
-    const size_t lds = (size_t)n * cw * 8;
-    if (cw == 4) hipLaunchKernelGGL(tridiag_backtransform<4>, grid, block, lds, st, n, Vs, Tall, X);
-    else if (cw == 2) hipLaunchKernelGGL(tridiag_backtransform<2>, grid, block, lds, st, n, Vs, Tall, X);
-    else hipLaunchKernelGGL(tridiag_backtransform<1>, grid, block, lds, st, n, Vs, Tall, X);
+    const size_t bytes = (size_t)n * cw * 8;
+    if (cw == 2) hipLaunchKernelGGL(tridiag_backtransform<2>, grid, block, bytes, st, n, Vs, Tall, X);
+    else hipLaunchKernelGGL(tridiag_backtransform<1>, grid, block, bytes, st, n, Vs, Tall, X);
   }
   // 5. one first-order orthonormalization of all columns: with G = Z^T Z = I + E
   //    and E small, Z <- Z (I - U), U = strict upper part of E + diag(E) / 2, leaves
@@ -814,15 +1612,26 @@ int eigh_run(const double* A_in, int n, double* w_out, double* Z_out, char* ws, 
   if ((err = gemm_f64(X, n, 0, 0, G, n, 0, 0, Zo, n, 0, n, n, n, 1, 1.0, 0.0, st, Part, 3 * nn)) != hipSuccess)
     return hip_fail(err, "eigh orthonormalization");
   // 6. sort + orient
-  hipLaunchKernelGGL(eig_rank, dim3((n + 255) / 256), dim3(256), 0, st, n, lam, rank);
-  hipLaunchKernelGGL(eig_permute, dim3(n), dim3(256), 0, st, n, lam, rank, Zo, w_out, Z_out, descending);
+  hipLaunchKernelGGL(eig_rank, dim3((n + 3) / 4), dim3(256), 0, st, n, lam, rank);
+  hipLaunchKernelGGL(eig_permute, dim3((n + 15) / 16), dim3(1024), 0, st, n, lam, rank, Zo, w_out, Z_out, descending);
   if ((err = hipGetLastError()) != hipSuccess) return hip_fail(err, "eigh launch");
   prof_all.close();
-  int hs = 0;
-  if ((err = hipMemcpyAsync(&hs, status, sizeof(int), hipMemcpyDeviceToHost, st)) != hipSuccess)
+  if ((err = hipMemcpyAsync(hs, status, sizeof(int), hipMemcpyDeviceToHost, st)) != hipSuccess)
     return hip_fail(err, "eigh status copy");
   if ((err = hipStreamSynchronize(st)) != hipSuccess) return hip_fail(err, "eigh sync");
   prof_flush();
+  return DFPT2_OK;
+}
+
+int eigh_run(const double* A_in, int n, double* w_out, double* Z_out, char* ws, size_t ws_bytes, hipStream_t st,
+             int descending, double vec_floor_rel) {
+  int hs = 0;
+  int rc = eigh_attempt(A_in, n, w_out, Z_out, ws, ws_bytes, st, descending, vec_floor_rel, true, &hs);
+  // 2: the workgroups of the resident form did not meet in time (held off the GPU by
+  // other work); the launch-per-column form waits for nothing
+  if (rc == DFPT2_OK && hs == 2)
+    rc = eigh_attempt(A_in, n, w_out, Z_out, ws, ws_bytes, st, descending, vec_floor_rel, false, &hs);
+  if (rc != DFPT2_OK) return rc;
   if (hs != 0) return fail(DFPT2_ERR_NOT_CONVERGED, "inverse iteration produced a zero or non-finite vector");
   return DFPT2_OK;
 }

@@ -23,29 +23,67 @@ namespace {
 // rule (p_o - c(N'-1), c(N') - p_o) as fractions of the total occupation; for the
 // cutoff rule (n[N'-1] - n_kappa, n_kappa - n[N']); otherwise the occupations
 // either side of the cut, (n[N'-1], n[N']).  Missing neighbours give +inf.
-__global__ void rule_threshold_kernel(const double* occ, int n, int rule, double param, double degen,
-                                      int64_t* n_kept, double* margins, int* flag) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  int bad = 0;
-  double total = 0.0;
-  for (int k = 0; k < n; ++k) {
-    if (!isfinite(occ[k])) bad = 1;
-    total += occ[k];
+// One workgroup brings the occupations into LDS (kLds; they stay in global memory beyond
+// kOccLds); one thread sums them in order, sixteen loads in flight.
+constexpr int kOccLds = 8192;
+
+template <bool kLds>
+__global__ __launch_bounds__(256) void rule_threshold_kernel(const double* occ_g, int n, int rule, double param,
+                                                             double degen, int64_t* n_kept, double* margins,
+                                                             int* flag) {
+  extern __shared__ double occ_sh[];
+  __shared__ int sh_bad;
+  if (threadIdx.x == 0) sh_bad = 0;
+  __syncthreads();
+  int mine = 0;
+  for (int k = threadIdx.x; k < n; k += blockDim.x) {
+    const double o = occ_g[k];
+    if (!isfinite(o)) mine = 1;
+    if (kLds) occ_sh[k] = o;
   }
+  if (mine) sh_bad = 1;
+  __syncthreads();
+  if (threadIdx.x != 0 || blockIdx.x != 0) return;
+  auto occ = [&](int k) { return kLds ? occ_sh[k] : occ_g[k]; };
+  const int bad = sh_bad;
+  double total = 0.0;
+  int k16 = 0;
+  for (; k16 + 16 <= n; k16 += 16) {
+    double o[16];
+#pragma unroll
+    for (int q = 0; q < 16; ++q) o[q] = occ(k16 + q);
+#pragma unroll
+    for (int q = 0; q < 16; ++q) total += o[q];
+  }
+  for (; k16 < n; ++k16) total += occ(k16);
   const double inf = __builtin_huge_val();
   int kept = n;
   if (rule == DFPT2_TRUNC_CUMULATIVE) {
     const double target = param * total;
     double c = 0.0, cprev = 0.0;
-    int idx = n - 1;
-    for (int k = 0; k < n; ++k) {
+    int idx = n - 1, k = 0;
+    auto step = [&](double o) {  // true at the first k whose cumulative occupation reaches the target
       cprev = c;
-      c += occ[k];
-      if (c >= target) {
-        idx = k;
-        break;
-      }
+      c += o;
+      return c >= target;
+    };
+    bool found = false;
+    for (; !found && k + 16 <= n; k += 16) {
+      double o[16];
+#pragma unroll
+      for (int q = 0; q < 16; ++q) o[q] = occ(k + q);
+#pragma unroll
+      for (int q = 0; q < 16; ++q)
+        if (!found && step(o[q])) {
+          found = true;
+          idx = k + q;
+        }
     }
+    for (; !found && k < n; ++k)
+      if (step(occ(k))) {
+        found = true;
+        idx = k;
+      }
     kept = idx + 1;
     margins[0] = param - (idx >= 1 ? cprev / total : 0.0);
     margins[1] = c / total - param;
@@ -55,17 +93,17 @@ __global__ void rule_threshold_kernel(const double* occ, int n, int rule, double
       if (kept > n) kept = n;
     } else if (rule == DFPT2_TRUNC_CUTOFF) {
       kept = 0;
-      while (kept < n && occ[kept] >= param) ++kept;
+      while (kept < n && occ(kept) >= param) ++kept;
     } else {
       kept = (int)param;
     }
-    const double lo = kept >= 1 ? occ[kept - 1] : inf, hi = kept < n ? occ[kept] : inf;
+    const double lo = kept >= 1 ? occ(kept - 1) : inf, hi = kept < n ? occ(kept) : inf;
     margins[0] = rule == DFPT2_TRUNC_CUTOFF ? (kept >= 1 ? lo - param : inf) : lo;
     margins[1] = rule == DFPT2_TRUNC_CUTOFF ? (kept < n ? param - hi : inf) : hi;
   }
   if (degen > 0.0 && kept >= 1) {
-    const double last = occ[kept - 1];
-    while (kept < n && (last - occ[kept]) < degen * last) ++kept;
+    const double last = occ(kept - 1);
+    while (kept < n && (last - occ(kept)) < degen * last) ++kept;
   }
   *n_kept = kept;
   *flag = bad;
@@ -133,8 +171,12 @@ static int truncate_impl(const double* D_vv, int64_t n_vir, int rule, double par
   double* d_marg = reinterpret_cast<double*>(tail + 64);
   int* d_flag = reinterpret_cast<int*>(tail + 128);
   ProfScope ps_thr(DFPT2_STAGE_REDUCE, st);
-  hipLaunchKernelGGL(rule_threshold_kernel, dim3(1), dim3(64), 0, st, occ, (int)n_vir, rule, param, degen_rel_tol,
-                     d_kept, d_marg, d_flag);
+  if (n_vir <= kOccLds)
+    hipLaunchKernelGGL(rule_threshold_kernel<true>, dim3(1), dim3(256), (size_t)n_vir * 8, st, occ, (int)n_vir, rule,
+                       param, degen_rel_tol, d_kept, d_marg, d_flag);
+  else
+    hipLaunchKernelGGL(rule_threshold_kernel<false>, dim3(1), dim3(256), 0, st, occ, (int)n_vir, rule, param,
+                       degen_rel_tol, d_kept, d_marg, d_flag);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hip_fail(e, "threshold kernel");
   ps_thr.close();
