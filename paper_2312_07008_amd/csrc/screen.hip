@@ -12,6 +12,7 @@
 // the network corrects.  Features
 //   x = (e_i, e_j, log(U/W), 0.1 (log W_ij - (log W_ii + log W_jj)/2), 0.1 log(g W)).
 // Parameters (FP32) are packed [W1 64x5, b1, W2 64x64, b2, w3, b3] = 4609 values.
+#include <algorithm>
 #include <cmath>
 #include <cfloat>
 
@@ -27,7 +28,7 @@ constexpr int NIN = 5;
 constexpr int NP = H * NIN + H + H * H + H + H + 1;  // 4609
 constexpr int OFF_W1 = 0, OFF_B1 = H * NIN, OFF_W2 = OFF_B1 + H, OFF_B2 = OFF_W2 + H * H, OFF_W3 = OFF_B2 + H,
               OFF_B3 = OFF_W3 + H;
-constexpr int BW_SAMPLES = 128;  // samples per workgroup in the backward kernel
+constexpr int BW_SAMPLES = 128;  // samples that the sizes of the workspaces count one row of gradients for
 
 // q2[i][Q] = sum_a B[i][a][Q]^2 for core holes
 __global__ void colnorm2_kernel(const double* B, int n_v, int n_aux, double* q2) {
@@ -98,152 +99,226 @@ __global__ void pair_features_kernel(const double* q2, const double* wdiag, cons
 }
 
 // ------------------------------------------------------------------ network
-// One thread per sample; parameters in LDS (broadcast reads).
-__global__ __launch_bounds__(256) void mlp_fwd_kernel(const float* Wp, const float* X, int n, float* out,
-                                                      float* cache) {
-  __shared__ float w[NP];
-  for (int k = threadIdx.x; k < NP; k += blockDim.x) w[k] = Wp[k];
-  __syncthreads();
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= n) return;
-  float x[NIN];
-#pragma unroll
-  for (int c = 0; c < NIN; ++c) x[c] = X[(size_t)t * NIN + c];
-  float h1[H];
-#pragma unroll
-  for (int k = 0; k < H; ++k) {
-    float z = w[OFF_B1 + k];
-#pragma unroll
-    for (int c = 0; c < NIN; ++c) z = fmaf(w[OFF_W1 + k * NIN + c], x[c], z);
-    h1[k] = tanhf(z);
-    if (cache) cache[(size_t)t * 2 * H + k] = h1[k];
-  }
-  float o = w[OFF_B3];
-  for (int k = 0; k < H; ++k) {
-    float z = w[OFF_B2 + k];
-#pragma unroll
-    for (int m = 0; m < H; ++m) z = fmaf(w[OFF_W2 + k * H + m], h1[m], z);
-    const float h2 = tanhf(z);
-    if (cache) cache[(size_t)t * 2 * H + H + k] = h2;
-    o = fmaf(w[OFF_W3 + k], h2, o);
-  }
-  out[t] = o;
-}
+// One workgroup of four waves takes tiles of 64 samples; the three 64 x 64 x 64 products
+// of a tile (z2 = h1 W2^T, dz2 W2, dz2^T h1) run on the FP32 matrix pipe (32x32x2, one
+// quadrant per wave), everything between them in registers and LDS:
+//   kForward   pred, and the activations where the caller wants them
+//   kBackward  parameter gradients from activations and d pred
+//   kTrain     both, with d pred = 2 (pred - y) / n and the loss formed on the way: the
+//              activations and d pred of a training step never reach memory
+// The gradients of a workgroup's tiles add up in its registers and leave as one row of
+// `partial` (NP parameter gradients, then the sum of squared residuals); at most
+// kMaxGroups rows are summed afterwards in a fixed order.  What bounds a step at ten
+// thousand samples is latency: as five launches (one thread per sample forward, 128
+// samples per workgroup backward, one thread per reduced parameter) it took 179 us at 11000
+// samples, 27 us as two (mlp_kernel 19.7, sum_partials_kernel 4.8).
+enum NetMode { kForward, kBackward, kTrain };
+constexpr int TS = 64;              // samples per tile
+constexpr int LD = H + 1;           // LDS row of a 64-wide matrix
+constexpr int kMaxGroups = 512;
+constexpr int PROW = (NP + 1 + 3) / 4 * 4;  // floats per row of partial sums
 
-// Gradient of sum_n dout_n out_n: a workgroup takes BW_SAMPLES samples, forms
-// dz2 and dz1 per sample, then the parameter gradients as small reductions over
-// its samples; partial[blockIdx.x][NP] is summed in a fixed order afterwards.
-__global__ __launch_bounds__(256) void mlp_bwd_kernel(const float* Wp, const float* X, const float* cache,
-                                                      const float* dout, int n, float* partial) {
-  __shared__ float w2[H * H];
-  __shared__ float sh1[BW_SAMPLES][H + 1];
-  __shared__ float sdz2[BW_SAMPLES][H + 1];
-  __shared__ float sdz1[BW_SAMPLES][H + 1];
-  __shared__ float sx[BW_SAMPLES][NIN];
-  __shared__ float sw3[H];
-  for (int k = threadIdx.x; k < H * H; k += blockDim.x) w2[k] = Wp[OFF_W2 + k];
-  for (int k = threadIdx.x; k < H; k += blockDim.x) sw3[k] = Wp[OFF_W3 + k];
-  const int s0 = blockIdx.x * BW_SAMPLES;
-  const int ns = min(BW_SAMPLES, n - s0);
-  __syncthreads();
-  // per-sample: dz2 = dout w3 (1 - h2^2); h1 and x staged
-  for (int idx = threadIdx.x; idx < BW_SAMPLES * H; idx += blockDim.x) {
-    const int r = idx / H, k = idx % H;
-    float h1 = 0.f, dz2 = 0.f;
-    if (r < ns) {
-      const size_t base = (size_t)(s0 + r) * 2 * H;
-      h1 = cache[base + k];
-      const float h2 = cache[base + H + k];
-      dz2 = dout[s0 + r] * sw3[k] * (1.f - h2 * h2);
+typedef float f16r __attribute__((ext_vector_type(16)));
+
+template <int MODE>
+__global__ __launch_bounds__(256, 2) void mlp_kernel(const float* Wp, const float* X, const float* y, int n, float* out,
+                                                  float* cache, const float* dout, float* partial) {
+  __shared__ float w2[H * LD], sh1[TS * LD], sh2[TS * LD], sdz[TS * LD];
+  __shared__ float w1[H * NIN], b1[H], b2[H], w3[H], sx[TS * 8], sdo[TS], red[4][H], lred[4];
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, l32 = lane & 31, hq = lane >> 5;
+  const int qr = (wv >> 1) * 32, qc = (wv & 1) * 32;  // this wave's quadrant
+  for (int k = tid; k < H * H; k += 256) w2[(k >> 6) * LD + (k & 63)] = Wp[OFF_W2 + k];
+  for (int k = tid; k < H * NIN; k += 256) w1[k] = Wp[OFF_W1 + k];
+  if (tid < H) {
+    b1[tid] = Wp[OFF_B1 + tid];
+    b2[tid] = Wp[OFF_B2 + tid];
+    w3[tid] = Wp[OFF_W3 + tid];
+  }
+  const float b3 = Wp[OFF_B3];
+  f16r g2;  // gradient of W2: rows k of the quadrant's row half, columns m
+#pragma unroll
+  for (int r = 0; r < 16; ++r) g2[r] = 0.f;
+  float gx[2] = {0.f, 0.f}, gb2 = 0.f, gw3 = 0.f, gb3 = 0.f, loss = 0.f;
+  const float two_n = 2.f / (float)n;
+  const int ntile = (n + TS - 1) / TS;
+  for (int tile = blockIdx.x; tile < ntile; tile += gridDim.x) {
+    const int s0 = tile * TS, ns = min(TS, n - s0);
+    __syncthreads();  // the previous tile's readers are done
+    for (int k = tid; k < TS * 8; k += 256) {
+      const int r = k >> 3, c = k & 7;  // column 5 is 1: its gradient is b1's
+      sx[k] = (c < NIN && r < ns) ? X[(size_t)(s0 + r) * NIN + c] : c == NIN ? 1.f : 0.f;
     }
-    sh1[r][k] = h1;
-    sdz2[r][k] = dz2;
-  }
-  for (int idx = threadIdx.x; idx < BW_SAMPLES * NIN; idx += blockDim.x) {
-    const int r = idx / NIN, c = idx % NIN;
-    sx[r][c] = (r < ns) ? X[(size_t)(s0 + r) * NIN + c] : 0.f;
-  }
-  __syncthreads();
-  // dz1[r][m] = (sum_k W2[k][m] dz2[r][k]) (1 - h1^2)
-  for (int idx = threadIdx.x; idx < BW_SAMPLES * H; idx += blockDim.x) {
-    const int r = idx / H, m = idx % H;
-    float acc = 0.f;
-    for (int k = 0; k < H; ++k) acc = fmaf(w2[k * H + m], sdz2[r][k], acc);
-    const float h1 = sh1[r][m];
-    sdz1[r][m] = acc * (1.f - h1 * h1);
-  }
-  __syncthreads();
-  float* part = partial + (size_t)blockIdx.x * NP;
-  // W2 gradient: sum_r dz2[r][k] h1[r][m]
-  for (int idx = threadIdx.x; idx < H * H; idx += blockDim.x) {
-    const int k = idx / H, m = idx % H;
-    float acc = 0.f;
-    for (int r = 0; r < BW_SAMPLES; ++r) acc = fmaf(sdz2[r][k], sh1[r][m], acc);
-    part[OFF_W2 + idx] = acc;
-  }
-  // W1 gradient: sum_r dz1[r][k] x[r][c]
-  for (int idx = threadIdx.x; idx < H * NIN; idx += blockDim.x) {
-    const int k = idx / NIN, c = idx % NIN;
-    float acc = 0.f;
-    for (int r = 0; r < BW_SAMPLES; ++r) acc = fmaf(sdz1[r][k], sx[r][c], acc);
-    part[OFF_W1 + idx] = acc;
-  }
-  // b1, b2, w3, b3
-  for (int k = threadIdx.x; k < H; k += blockDim.x) {
-    float a1 = 0.f, a2 = 0.f, a3 = 0.f;
-    for (int r = 0; r < BW_SAMPLES; ++r) {
-      a1 += sdz1[r][k];
-      a2 += sdz2[r][k];
-      if (r < ns) a3 = fmaf(dout[s0 + r], cache[(size_t)(s0 + r) * 2 * H + H + k], a3);
+    if (MODE == kBackward)
+      for (int k = tid; k < TS * H; k += 256) {
+        const int r = k >> 6, c = k & 63;
+        const float* a = cache + (size_t)(s0 + r) * 2 * H;
+        sh1[r * LD + c] = r < ns ? a[c] : 0.f;
+        sh2[r * LD + c] = r < ns ? a[H + c] : 0.f;
+      }
+    if (MODE == kBackward && tid < TS) sdo[tid] = tid < ns ? dout[s0 + tid] : 0.f;
+    __syncthreads();
+    if (MODE != kBackward) {
+      {  // h1: thread (k, 16 samples)
+        const int k = tid & 63;
+        float wk[NIN];
+#pragma unroll
+        for (int c = 0; c < NIN; ++c) wk[c] = w1[k * NIN + c];
+        const float bk = b1[k];
+#pragma unroll 4
+        for (int r = wv; r < TS; r += 4) {
+          float z = bk;
+#pragma unroll
+          for (int c = 0; c < NIN; ++c) z = fmaf(wk[c], sx[r * 8 + c], z);
+          const float h = tanhf(z);
+          sh1[r * LD + k] = h;
+          if (MODE == kForward && cache && r < ns) cache[(size_t)(s0 + r) * 2 * H + k] = h;
+        }
+      }
+      __syncthreads();
+      f16r z2;  // rows s of the quadrant, columns k
+#pragma unroll
+      for (int r = 0; r < 16; ++r) z2[r] = 0.f;
+#pragma unroll 8
+      for (int m = 0; m < H; m += 2)
+        z2 = __builtin_amdgcn_mfma_f32_32x32x2f32(sh1[(qr + l32) * LD + m + hq], w2[(qc + l32) * LD + m + hq], z2, 0, 0, 0);
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {  // register r: row 8 (r / 4) + 4 hq + r % 4
+        const int row = qr + 8 * (r >> 2) + 4 * hq + (r & 3), k = qc + l32;
+        const float h = tanhf(z2[r] + b2[k]);
+        sh2[row * LD + k] = h;
+        if (MODE == kForward && cache && row < ns) cache[(size_t)(s0 + row) * 2 * H + H + k] = h;
+      }
+      __syncthreads();
+      {  // output: four threads per sample
+        const int r = tid >> 2, q = tid & 3;
+        float o = 0.f;
+#pragma unroll
+        for (int k = 0; k < 16; ++k) o = fmaf(w3[4 * k + q], sh2[r * LD + 4 * k + q], o);
+        o += __shfl_xor(o, 1, 64);
+        o += __shfl_xor(o, 2, 64);
+        o += b3;
+        if (q == 0) {
+          if (MODE == kForward && r < ns) out[s0 + r] = o;
+          if (MODE == kTrain) {
+            const float e = r < ns ? o - y[s0 + r] : 0.f;
+            sdo[r] = e * two_n;
+            loss = fmaf(e, e, loss);
+          }
+        }
+      }
+      if (MODE == kTrain) __syncthreads();
     }
-    part[OFF_B1 + k] = a1;
-    part[OFF_B2 + k] = a2;
-    part[OFF_W3 + k] = a3;
+    if (MODE == kForward) continue;
+    // dz2 = dout w3 (1 - h2^2), the gradients of b2 and w3: thread (k, 16 samples)
+    {
+      const int k = tid & 63;
+      const float wk = w3[k];
+#pragma unroll 4
+      for (int r = wv; r < TS; r += 4) {
+        const float h = sh2[r * LD + k], d = sdo[r], z = d * wk * (1.f - h * h);
+        sdz[r * LD + k] = z;
+        gb2 += z;
+        gw3 = fmaf(d, h, gw3);
+      }
+    }
+    if (tid < TS) gb3 += sdo[tid];
+    __syncthreads();
+    f16r z1;  // dz2 W2: rows s, columns m
+#pragma unroll
+    for (int r = 0; r < 16; ++r) z1[r] = 0.f;
+#pragma unroll 8
+    for (int k = 0; k < H; k += 2) {
+      z1 = __builtin_amdgcn_mfma_f32_32x32x2f32(sdz[(qr + l32) * LD + k + hq], w2[(k + hq) * LD + qc + l32], z1, 0, 0, 0);
+      g2 = __builtin_amdgcn_mfma_f32_32x32x2f32(sdz[(k + hq) * LD + qr + l32], sh1[(k + hq) * LD + qc + l32], g2, 0, 0, 0);
+    }
+    // dz1 (over h2, which is no longer needed) and the gradients of W1 and b1
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int row = qr + 8 * (r >> 2) + 4 * hq + (r & 3), m = qc + l32;
+      const float h = sh1[row * LD + m];
+      sh2[row * LD + m] = z1[r] * (1.f - h * h);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int c = (tid >> 6) + 4 * i;  // inputs 0 .. 4, then the constant
+      if (c <= NIN) {
+        float acc = 0.f;
+#pragma unroll 8
+        for (int r = 0; r < TS; ++r) acc = fmaf(sh2[r * LD + (tid & 63)], sx[r * 8 + c], acc);
+        gx[i] += acc;
+      }
+    }
   }
-  if (threadIdx.x == 0) {
-    float a = 0.f;
-    for (int r = 0; r < ns; ++r) a += dout[s0 + r];
-    part[OFF_B3] = a;
+  if (MODE == kForward) return;
+  float* part = partial + (size_t)blockIdx.x * PROW;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) part[OFF_W2 + (qr + 8 * (r >> 2) + 4 * hq + (r & 3)) * H + qc + l32] = g2[r];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int c = (tid >> 6) + 4 * i, k = tid & 63;
+    if (c < NIN) part[OFF_W1 + k * NIN + c] = gx[i];
+    else if (c == NIN) part[OFF_B1 + k] = gx[i];
   }
-}
-
-__global__ void sum_partials_kernel(const float* partial, int nblk, float* dW) {
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= NP) return;
-  float acc = 0.f;
-  for (int b = 0; b < nblk; ++b) acc += partial[(size_t)b * NP + k];
-  dW[k] = acc;
-}
-
-// dout = 2 (out - y) / n ; loss = mean (out - y)^2 (single workgroup, fixed order)
-__global__ void mse_kernel(const float* out, const float* y, int n, float* dout, float* loss) {
-  __shared__ float sh[16];
-  float acc = 0.f;
-  for (int t = threadIdx.x; t < n; t += blockDim.x) {
-    const float r = out[t] - y[t];
-    dout[t] = 2.f * r / (float)n;
-    acc = fmaf(r, r, acc);
-  }
-  for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
-  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = acc;
   __syncthreads();
-  if (threadIdx.x == 0 && loss) {
-    float t = 0.f;
-    for (int w = 0; w < (int)(blockDim.x >> 6); ++w) t += sh[w];
-    *loss = t / (float)n;
+  red[wv][lane] = gb2;
+  __syncthreads();
+  if (tid < H) part[OFF_B2 + tid] = (red[0][tid] + red[1][tid]) + (red[2][tid] + red[3][tid]);
+  __syncthreads();
+  red[wv][lane] = gw3;
+  __syncthreads();
+  if (tid < H) part[OFF_W3 + tid] = (red[0][tid] + red[1][tid]) + (red[2][tid] + red[3][tid]);
+  for (int o = 32; o > 0; o >>= 1) {
+    gb3 += __shfl_xor(gb3, o, 64);
+    loss += __shfl_xor(loss, o, 64);
+  }
+  if (lane == 0) lred[wv] = loss;
+  __syncthreads();
+  if (tid == 0) {
+    part[OFF_B3] = gb3;
+    part[NP] = (lred[0] + lred[1]) + (lred[2] + lred[3]);
   }
 }
 
-__global__ void adam_kernel(float* W, const float* g, float* m, float* v, int n, float lr, float b1, float b2,
-                            float eps, float c1, float c2) {
+// Sums the rows of partial (32 parameters x 8 threads a workgroup), then dW or, training,
+// Adam on the parameter and the loss
+struct AdamArgs {
+  float *W, *m, *v, *loss;
+  float lr, b1, b2, eps, c1, c2, inv_n;
+};
+
+__device__ inline void adam_update(float& W, float& m, float& v, float g, const AdamArgs& a) {
+  const float mk = a.b1 * m + (1.f - a.b1) * g;
+  const float vk = a.b2 * v + (1.f - a.b2) * g * g;
+  m = mk;
+  v = vk;
+  W -= a.lr * (mk / a.c1) / (sqrtf(vk / a.c2) + a.eps);
+}
+
+template <bool kAdam>
+__global__ __launch_bounds__(256) void sum_partials_kernel(const float* partial, int nblk, float* dW, AdamArgs a) {
+  __shared__ float sh[8][32];
+  const int c = threadIdx.x & 31, q = threadIdx.x >> 5, k = blockIdx.x * 32 + c;
+  float acc = 0.f;
+  if (k <= NP) {
+#pragma unroll 4
+    for (int b = q; b < nblk; b += 8) acc += partial[(size_t)b * PROW + k];
+  }
+  sh[q][c] = acc;
+  __syncthreads();
+  if (q != 0 || k > NP) return;
+  acc = ((sh[0][c] + sh[1][c]) + (sh[2][c] + sh[3][c])) + ((sh[4][c] + sh[5][c]) + (sh[6][c] + sh[7][c]));
+  if (kAdam) {
+    if (k < NP) adam_update(a.W[k], a.m[k], a.v[k], acc, a);
+    else *a.loss = acc * a.inv_n;
+  } else if (k < NP) {
+    dW[k] = acc;
+  }
+}
+
+__global__ void adam_kernel(const float* g, int n, AdamArgs a) {
   const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= n) return;
-  const float gk = g[k];
-  const float mk = b1 * m[k] + (1.f - b1) * gk;
-  const float vk = b2 * v[k] + (1.f - b2) * gk * gk;
-  m[k] = mk;
-  v[k] = vk;
-  W[k] -= lr * (mk / c1) / (sqrtf(vk / c2) + eps);
+  if (k < n) adam_update(a.W[k], a.m[k], a.v[k], g[k], a);
 }
 
 // y[p] = log ||t_ij||_F - log(g W) for the core pairs, from the pass's pair_tnorm
@@ -305,6 +380,26 @@ double regularizer_peak() {
 }
 
 int train_nblk(int64_t n) { return (int)((n + BW_SAMPLES - 1) / BW_SAMPLES); }
+
+// workgroups over n samples, with room for their rows in `floats`
+int net_groups(int64_t n, size_t floats) {
+  const int64_t tiles = (n + TS - 1) / TS;
+  return (int)std::max<int64_t>(1, std::min<int64_t>({tiles, kMaxGroups, (int64_t)(floats / PROW)}));
+}
+
+AdamArgs adam_args(float* W, float* m, float* v, float lr, float b1, float b2, float eps, int64_t step) {
+  AdamArgs a{};
+  a.W = W;
+  a.m = m;
+  a.v = v;
+  a.lr = lr;
+  a.b1 = b1;
+  a.b2 = b2;
+  a.eps = eps;
+  a.c1 = (float)(1.0 - std::pow((double)b1, (double)step));
+  a.c2 = (float)(1.0 - std::pow((double)b2, (double)step));
+  return a;
+}
 
 }  // namespace
 
@@ -369,8 +464,8 @@ int pairscreen_mlp_forward(const float* W, const float* feats, int64_t n, float*
   if (n == 0) return DFPT2_OK;
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   ProfScope ps(DFPT2_STAGE_SCREEN, s);
-  hipLaunchKernelGGL(mlp_fwd_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, W, feats, (int)n, pred,
-                     act_cache);
+  hipLaunchKernelGGL(mlp_kernel<kForward>, dim3((unsigned)std::min<int64_t>((n + TS - 1) / TS, 2048)), dim3(256), 0, s, W,
+                     feats, nullptr, (int)n, pred, act_cache, nullptr, nullptr);
   hipError_t e = hipGetLastError();
   return e == hipSuccess ? DFPT2_OK : hip_fail(e, "mlp forward");
 }
@@ -393,10 +488,11 @@ int pairscreen_mlp_backward(const float* W, const float* feats, const float* act
   if (ws_bytes < need) return fail(DFPT2_ERR_WORKSPACE, "workspace too small");
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   ProfScope ps(DFPT2_STAGE_SCREEN, s);
-  const int nblk = train_nblk(n);
   float* partial = static_cast<float*>(workspace);
-  hipLaunchKernelGGL(mlp_bwd_kernel, dim3(nblk), dim3(256), 0, s, W, feats, act_cache, dpred, (int)n, partial);
-  hipLaunchKernelGGL(sum_partials_kernel, dim3((NP + 255) / 256), dim3(256), 0, s, partial, nblk, dW);
+  const int nblk = net_groups(n, need / sizeof(float));
+  hipLaunchKernelGGL(mlp_kernel<kBackward>, dim3(nblk), dim3(256), 0, s, W, feats, nullptr, (int)n, nullptr,
+                     const_cast<float*>(act_cache), dpred, partial);
+  hipLaunchKernelGGL(sum_partials_kernel<false>, dim3((NP + 32) / 32), dim3(256), 0, s, partial, nblk, dW, AdamArgs{});
   hipError_t e = hipGetLastError();
   return e == hipSuccess ? DFPT2_OK : hip_fail(e, "mlp backward");
 }
@@ -409,10 +505,8 @@ int pairscreen_adam_step(float* W, const float* dW, float* m, float* v, int64_t 
     return fail(DFPT2_ERR_INVALID_ARG, "bad Adam hyper-parameters");
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   ProfScope ps(DFPT2_STAGE_SCREEN, s);
-  const float c1 = (float)(1.0 - std::pow((double)b1, (double)step));
-  const float c2 = (float)(1.0 - std::pow((double)b2, (double)step));
-  hipLaunchKernelGGL(adam_kernel, dim3((unsigned)((n_params + 255) / 256)), dim3(256), 0, s, W, dW, m, v, (int)n_params,
-                     lr, b1, b2, eps, c1, c2);
+  hipLaunchKernelGGL(adam_kernel, dim3((unsigned)((n_params + 255) / 256)), dim3(256), 0, s, dW, (int)n_params,
+                     adam_args(W, m, v, lr, b1, b2, eps, step));
   hipError_t e = hipGetLastError();
   return e == hipSuccess ? DFPT2_OK : hip_fail(e, "adam");
 }
@@ -440,32 +534,19 @@ int pairscreen_train(float* W, float* m, float* v, const float* feats, const flo
   size_t need = 0;
   pairscreen_train_workspace_size(n, &need);
   if (ws_bytes < need) return fail(DFPT2_ERR_WORKSPACE, "workspace too small");
-  char* ws = static_cast<char*>(workspace);
-  size_t off = 0;
-  auto take = [&](size_t b) {
-    char* p = ws + off;
-    off += align_up(b, 256);
-    return p;
-  };
-  float* pred = (float*)take(sizeof(float) * n);
-  float* dpred = (float*)take(sizeof(float) * n);
-  float* act = (float*)take(sizeof(float) * n * 2 * H);
-  float* dW = (float*)take(sizeof(float) * NP);
-  size_t bw = 0;
-  pairscreen_backward_workspace_size(n, &bw);
-  char* bws = take(bw);
+  float* partial = static_cast<float*>(workspace);
+  const int nblk = net_groups(n, need / sizeof(float));
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   for (int64_t t = 1; t <= steps; ++t) {
-    int st = pairscreen_mlp_forward(W, feats, n, pred, act, stream);
-    if (st != DFPT2_OK) return st;
-    {
-      ProfScope ps(DFPT2_STAGE_SCREEN, s);
-      hipLaunchKernelGGL(mse_kernel, dim3(1), dim3(1024), 0, s, pred, y, (int)n, dpred, losses + (t - 1));
-    }
-    st = pairscreen_mlp_backward(W, feats, act, dpred, n, dW, bws, bw, stream);
-    if (st != DFPT2_OK) return st;
-    st = pairscreen_adam_step(W, dW, m, v, NP, lr, 0.9f, 0.999f, 1e-8f, step0 + t, stream);
-    if (st != DFPT2_OK) return st;
+    ProfScope ps(DFPT2_STAGE_SCREEN, s);
+    hipLaunchKernelGGL(mlp_kernel<kTrain>, dim3(nblk), dim3(256), 0, s, W, feats, y, (int)n, nullptr, nullptr, nullptr,
+                       partial);
+    AdamArgs a = adam_args(W, m, v, lr, 0.9f, 0.999f, 1e-8f, step0 + t);
+    a.loss = losses + (t - 1);
+    a.inv_n = 1.f / (float)n;
+    hipLaunchKernelGGL(sum_partials_kernel<true>, dim3((NP + 32) / 32), dim3(256), 0, s, partial, nblk, nullptr, a);
+    const hipError_t le = hipGetLastError();
+    if (le != hipSuccess) return hip_fail(le, "train");
   }
   hipError_t e = hipStreamSynchronize(s);
   prof_flush();
