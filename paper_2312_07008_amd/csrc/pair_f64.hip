@@ -18,6 +18,8 @@
 // T^{ij}: T_P at [a][b] and, for I < J, T_Q at the mirrored position [b][a]
 // (T^{ij}_{ba} = T^{ji}_{ab}).  Optionally the renormalized integrals
 // Vr = V (1 + x) are stored the same way (used when active holes are rotated).
+#include <type_traits>
+
 #include "common.h"
 #include "kernels.h"
 
@@ -26,122 +28,178 @@ namespace dfpt2 {
 namespace {
 constexpr int TM = 64;        // tile edge
 constexpr int KC = 16;        // aux chunk per pipeline stage
-constexpr int LDK = KC + 1;   // padded LDS row (doubles)
-}
+constexpr int PANEL = KC * TM;
+typedef uint32_t u2 __attribute__((ext_vector_type(2)));
 
+// place of (k, row) in a panel, k-major: the row is XOR-swizzled by the bits of k so that
+// the 16 lanes along k of a store (times two rows) and the 16 + 16 lanes of a fragment
+// read (rows of one block, k and k + 1) hit distinct banks without padding
+__device__ inline int slot(int k, int row) { return k * TM + (row ^ (((k & 1) << 4) | ((k >> 1) << 1))); }
+}  // namespace
+
+// What bounds it: the FP64 matrix pipe (64 cycles a product, 78 TFLOP/s), as long as
+// nothing else holds the SIMD.  Per 16-deep chunk a wave has 16 products of a 32 x 32
+// quadrant, 16 fragment reads, 8 loads and 8 LDS stores:
+//  * P and Q are formed one after the other, so that two panels in two LDS buffers are
+//    32 KB and three workgroups share a unit: the others fill one's waits at its barriers
+//    (both at once, four panels, two workgroups: 14.1 instead of 12.4 ms).
+//  * loads are 8-byte buffer loads (any n_aux) at byte offsets that never change, from
+//    descriptors whose base moves with the chunk; they run two chunks ahead in two register
+//    stages, so that a launch with one workgroup per unit (a small molecule) is not paced
+//    by the memory's latency.  Rows beyond n_v read a clamped row and reach no stored
+//    element; the partial chunk of the contraction comes first, outside the loop, with its
+//    missing columns read out of the descriptor's range, as zeros.
+//  * the products of 16 x 16 blocks that lie wholly beyond n_v are skipped (wave-uniform).
+//  * on a diagonal tile Q is P^T, exchanged through LDS instead of computed again.
+// 40 cores + 8 active, 400 virtuals, 1600 auxiliary functions, ms per pass: 12.4, 18.0 before
+// (predicated 16-byte loads one chunk ahead, padded LDS rows, whole tiles computed).
+//
 // STORE = false: energy-only variant (kept-space pass) that writes no amplitudes.
-template <bool VEC, bool STORE>
-__global__ __launch_bounds__(256, 2) void pair_gemm_f64_kernel(PairKernelArgs a) {
-  __shared__ double lds[2][4][TM][LDK];
+// WIDE: rows so long that a panel spans more than the 2 GB of a buffer load's offsets.
+template <bool STORE, bool WIDE>
+__global__ __launch_bounds__(256, 3) void pair_gemm_f64_kernel(PairKernelArgs a) {
+  __shared__ double lds[2][2][PANEL];
   __shared__ double red[2][4];
-  const int tp = blockIdx.x;
-  const int p = blockIdx.y;
+  int tp, p;
+  {  // XCD-aware order: each XCD walks a contiguous range of (pair, tile pair)
+    const uint64_t id = (uint64_t)blockIdx.y * gridDim.x + blockIdx.x, nblk = (uint64_t)gridDim.x * gridDim.y;
+    const uint64_t x = id & 7, q = id >> 3, per = nblk >> 3, rem = nblk & 7;
+    const uint64_t L = (x < rem) ? x * (per + 1) + q : rem * (per + 1) + (x - rem) * per + q;
+    p = (int)(L / a.nTP);
+    tp = (int)(L - (uint64_t)p * a.nTP);
+  }
   int I, J;
   tile_pair(tp, a.nt, I, J);
   const int2 pr = a.pairs[p];
   const int hi_i = pr.x, hi_j = pr.y;
-  const bool same = (hi_i == hi_j);
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const bool same = (hi_i == hi_j), two = !same && I != J;  // two: Q is a product of its own
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wr = w >> 1, wc = w & 1;
   const int n_v = a.n_v, n_aux = a.n_aux;
-
-  // panel sources: 0 = B_i rows I, 1 = B_j rows J, 2 = B_j rows I, 3 = B_i rows J
-  const int hole_of[4] = {hi_i, hi_j, hi_j, hi_i};
-  const int blk_of[4] = {I, J, I, J};
-  const int npanel = same ? 2 : 4;
-
-  // register staging of the next chunk: 4 panels x 2 double2 per thread
-  double2 stage[4][2];
-
-  auto load_chunk = [&](int k0) {
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      if (q >= npanel) break;
-      const double* base = a.B + (size_t)hole_of[q] * n_v * n_aux;
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const int e = tid + 256 * h;  // 0..511
-        const int row = e >> 3;
-        const int kk = (e & 7) * 2;
-        const int grow = blk_of[q] * TM + row;
-        const int gk = k0 + kk;
-        double2 v = make_double2(0.0, 0.0);
-        if (grow < n_v) {
-          const double* src = base + (size_t)grow * n_aux + gk;
-          if (VEC) {
-            if (gk + 1 < n_aux) v = *reinterpret_cast<const double2*>(src);
-            else if (gk < n_aux) v.x = src[0];
-          } else {
-            if (gk < n_aux) v.x = src[0];
-            if (gk + 1 < n_aux) v.y = src[1];
-          }
-        }
-        stage[q][h] = v;
-      }
-    }
-  };
-  auto store_chunk = [&](int buf) {
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      if (q >= npanel) break;
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const int e = tid + 256 * h;
-        const int row = e >> 3;
-        const int kk = (e & 7) * 2;
-        lds[buf][q][row][kk] = stage[q][h].x;
-        lds[buf][q][row][kk + 1] = stage[q][h].y;
-      }
-    }
-  };
-
-  d4 P[2][2], Q[2][2];
-#pragma unroll
-  for (int x = 0; x < 2; ++x)
-#pragma unroll
-    for (int y = 0; y < 2; ++y) {
-      P[x][y] = (d4){0.0, 0.0, 0.0, 0.0};
-      Q[x][y] = (d4){0.0, 0.0, 0.0, 0.0};
-    }
-
-  const int nchunk = (n_aux + KC - 1) / KC;
-  load_chunk(0);
-  store_chunk(0);
-  __syncthreads();
   const int r16 = lane & 15, kq = lane >> 4;
-  for (int c = 0; c < nchunk; ++c) {
-    const int buf = c & 1;
-    if (c + 1 < nchunk) load_chunk((c + 1) * KC);
+
+  // thread: column ka of the chunk, rows lr + 16 h of a panel
+  const int ka = tid & 15, lr = tid >> 4;
+  typename std::conditional<WIDE, uint64_t, uint32_t>::type off[2][4];
 #pragma unroll
-    for (int k4 = 0; k4 < KC / 4; ++k4) {
-      const int k = k4 * 4 + kq;
-      const double a0 = lds[buf][0][wr * 32 + r16][k];
-      const double a1 = lds[buf][0][wr * 32 + 16 + r16][k];
-      const double b0 = lds[buf][1][wc * 32 + r16][k];
-      const double b1 = lds[buf][1][wc * 32 + 16 + r16][k];
-      P[0][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b0, P[0][0], 0, 0, 0);
-      P[0][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b1, P[0][1], 0, 0, 0);
-      P[1][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b0, P[1][0], 0, 0, 0);
-      P[1][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b1, P[1][1], 0, 0, 0);
-      if (!same) {
-        const double c0 = lds[buf][2][wr * 32 + r16][k];
-        const double c1 = lds[buf][2][wr * 32 + 16 + r16][k];
-        const double d0 = lds[buf][3][wc * 32 + r16][k];
-        const double d1 = lds[buf][3][wc * 32 + 16 + r16][k];
-        Q[0][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(c0, d0, Q[0][0], 0, 0, 0);
-        Q[0][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(c0, d1, Q[0][1], 0, 0, 0);
-        Q[1][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(c1, d0, Q[1][0], 0, 0, 0);
-        Q[1][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(c1, d1, Q[1][1], 0, 0, 0);
-      }
-    }
-    if (c + 1 < nchunk) store_chunk(buf ^ 1);
-    __syncthreads();
+  for (int h = 0; h < 4; ++h) {
+    off[0][h] = ((decltype(off[0][0] + 0))min(lr + 16 * h, n_v - 1 - I * TM) * n_aux + ka) * 8u;
+    off[1][h] = ((decltype(off[0][0] + 0))min(lr + 16 * h, n_v - 1 - J * TM) * n_aux + ka) * 8u;
   }
+  // 16 x 16 blocks of this wave that reach into n_v
+  const int nbi = min(2, max(0, (n_v - I * TM - wr * 32 + 15) / 16)), nbj = min(2, max(0, (n_v - J * TM - wc * 32 + 15) / 16));
+  const int nfull = n_aux / KC, tail = n_aux - nfull * KC, n = nfull + (tail ? 1 : 0);
+  auto chunk_at = [&](int i) { return (tail ? i - 1 : i) * KC; };  // i > 0, or no tail
+
+  // acc = rows I of hole x times rows J of hole y, over all auxiliary functions, for the
+  // first NI x NJ blocks of the wave: no branch in the loop, whose merges would copy the
+  // accumulators and wait for the products in flight (the pass of the size below: 17.9 ms, 19.8 with a branch).
+  // Waves of a workgroup may run different instances: the same loads, stores and barriers.
+  auto contract = [&](auto NI, auto NJ, d4 (&acc)[2][2], int x, int y) __attribute__((always_inline)) {
+    const double* base[2] = {a.B + ((size_t)x * n_v + (size_t)I * TM) * n_aux,
+                             a.B + ((size_t)y * n_v + (size_t)J * TM) * n_aux};
+    // chunk at k0 into a register stage; `mask` is or'ed into the offsets (out of range: zero)
+    auto load = [&](double (&st)[2][4], int k0, uint32_t mask) __attribute__((always_inline)) {
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        if constexpr (WIDE) {
+#pragma unroll
+          for (int h = 0; h < 4; ++h) {
+            const char* src = reinterpret_cast<const char*>(base[q] + k0) + off[q][h];
+            st[q][h] = mask ? 0.0 : *reinterpret_cast<const double*>(src);
+          }
+        } else {
+          auto desc = __builtin_amdgcn_make_buffer_rsrc((void*)(base[q] + k0), 0, 0x7fffffff, 0x00020000);
+#pragma unroll
+          for (int h = 0; h < 4; ++h)
+            st[q][h] = __builtin_bit_cast(
+                double, (u2)__builtin_amdgcn_raw_buffer_load_b64(desc, (uint32_t)off[q][h] | mask, 0, 0));
+        }
+      }
+    };
+    auto store = [&](double (&st)[2][4], int buf) __attribute__((always_inline)) {
+#pragma unroll
+      for (int q = 0; q < 2; ++q)
+#pragma unroll
+        for (int h = 0; h < 4; ++h) lds[buf][q][slot(ka, lr + 16 * h)] = st[q][h];
+    };
+    auto products = [&](int buf) __attribute__((always_inline)) {
+#pragma unroll
+      for (int k4 = 0; k4 < KC / 4; ++k4) {
+        const int k = k4 * 4 + kq;
+        double u[2], v[2];
+#pragma unroll
+        for (int b = 0; b < NI(); ++b) u[b] = lds[buf][0][slot(k, wr * 32 + b * 16 + r16)];
+#pragma unroll
+        for (int b = 0; b < NJ(); ++b) v[b] = lds[buf][1][slot(k, wc * 32 + b * 16 + r16)];
+#pragma unroll
+        for (int bi = 0; bi < NI(); ++bi)
+#pragma unroll
+          for (int bj = 0; bj < NJ(); ++bj)
+            acc[bi][bj] = __builtin_amdgcn_mfma_f64_16x16x4f64(u[bi], v[bj], acc[bi][bj], 0, 0, 0);
+      }
+    };
+#pragma unroll
+    for (int bi = 0; bi < 2; ++bi)
+#pragma unroll
+      for (int bj = 0; bj < 2; ++bj) acc[bi][bj] = (d4){0.0, 0.0, 0.0, 0.0};
+    double s0[2][4], s1[2][4];
+    if (tail) load(s0, nfull * KC, ka < tail ? 0u : 0x80000000u);
+    else load(s0, 0, 0u);
+    if (n > 1) load(s1, chunk_at(1), 0u);
+    __syncthreads();  // the readers of an earlier contraction are done
+    store(s0, 0);
+    __syncthreads();
+    for (int i = 0; i + 1 < n; i += 2) {
+      load(s0, chunk_at(min(i + 2, n - 1)), 0u);
+      products(0);
+      store(s1, 1);
+      __syncthreads();
+      load(s1, chunk_at(min(i + 3, n - 1)), 0u);
+      products(1);
+      store(s0, 0);
+      __syncthreads();
+    }
+    if (n & 1) products(0);
+  };
+  d4 P[2][2], Q[2][2];
+  auto both = [&](auto NI, auto NJ) __attribute__((always_inline)) {
+    contract(NI, NJ, P, hi_i, hi_j);
+    if (two) contract(NI, NJ, Q, hi_j, hi_i);
+  };
+  using N0 = std::integral_constant<int, 0>;
+  using N1 = std::integral_constant<int, 1>;
+  using N2 = std::integral_constant<int, 2>;
+  if (nbi == 0 || nbj == 0) both(N0{}, N0{});
+  else if (nbi == 1) nbj == 1 ? both(N1{}, N1{}) : both(N1{}, N2{});
+  else nbj == 1 ? both(N2{}, N1{}) : both(N2{}, N2{});
   if (same) {
 #pragma unroll
     for (int x = 0; x < 2; ++x)
 #pragma unroll
       for (int y = 0; y < 2; ++y) Q[x][y] = P[x][y];
+  } else if (!two) {  // diagonal tile: Q = P^T through LDS (columns XOR-swizzled by the row)
+    __syncthreads();
+    double* ex = &lds[0][0][0];
+#pragma unroll
+    for (int bi = 0; bi < 2; ++bi)
+#pragma unroll
+      for (int bj = 0; bj < 2; ++bj)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int row = wr * 32 + bi * 16 + kq + 4 * r;
+          ex[row * TM + ((wc * 32 + bj * 16 + r16) ^ (row & 31))] = P[bi][bj][r];
+        }
+    __syncthreads();
+#pragma unroll
+    for (int bi = 0; bi < 2; ++bi)
+#pragma unroll
+      for (int bj = 0; bj < 2; ++bj)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int row = wc * 32 + bj * 16 + r16;
+          Q[bi][bj][r] = ex[row * TM + ((wr * 32 + bi * 16 + kq + 4 * r) ^ (row & 31))];
+        }
   }
 
   // ---- epilogue
@@ -200,17 +258,15 @@ __global__ __launch_bounds__(256, 2) void pair_gemm_f64_kernel(PairKernelArgs a)
 
 hipError_t launch_pair_gemm_f64(const PairKernelArgs& a, int n_pairs, hipStream_t st) {
   if (n_pairs <= 0) return hipSuccess;
-  dim3 grid(a.nTP, n_pairs), block(256);
-  const bool vec = (a.n_aux % 2) == 0;
-  const bool store = (a.T != nullptr) || (a.Vr != nullptr);
-  if (vec && store)
-    hipLaunchKernelGGL((pair_gemm_f64_kernel<true, true>), grid, block, 0, st, a);
-  else if (vec)
-    hipLaunchKernelGGL((pair_gemm_f64_kernel<true, false>), grid, block, 0, st, a);
-  else if (store)
-    hipLaunchKernelGGL((pair_gemm_f64_kernel<false, true>), grid, block, 0, st, a);
-  else
-    hipLaunchKernelGGL((pair_gemm_f64_kernel<false, false>), grid, block, 0, st, a);
+  const dim3 grid(a.nTP, n_pairs), block(256);
+  const bool store = a.T != nullptr || a.Vr != nullptr;
+  if ((double)TM * a.n_aux * 8.0 >= 2147483647.0) {
+    if (store) hipLaunchKernelGGL((pair_gemm_f64_kernel<true, true>), grid, block, 0, st, a);
+    else hipLaunchKernelGGL((pair_gemm_f64_kernel<false, true>), grid, block, 0, st, a);
+  } else {
+    if (store) hipLaunchKernelGGL((pair_gemm_f64_kernel<true, false>), grid, block, 0, st, a);
+    else hipLaunchKernelGGL((pair_gemm_f64_kernel<false, false>), grid, block, 0, st, a);
+  }
   return hipGetLastError();
 }
 
