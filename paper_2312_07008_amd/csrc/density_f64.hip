@@ -2,20 +2,32 @@
 // accumulated over hole pairs on FP64 MFMA.
 //
 // For an unordered pair {i < j} with amplitude matrix T = T^{ij} the two
-// ordered pairs contribute
-//     T (2T - T^T)^T + T^T (2T - T^T)   =   X1 Y1^T + X2 Y2^T
-// with, for a virtual c running along the contraction,
-//     X1[a][c] = T[a][c],  Y1[b][c] = 2 T[b][c] - T[c][b],
-//     X2[a][c] = T[c][a],  Y2[b][c] = 2 T[c][b] - T[b][c].
-// For i == j (T symmetric) the same expression is twice T T^T and gets half the
-// weight.  The result is symmetric, so only tiles (A <= B) of D are formed.
+// ordered pairs contribute T (2T - T^T)^T + T^T (2T - T^T).  With the symmetric and
+// antisymmetric parts T = S + A this is 2 S S^T + 6 A A^T: two products of one operand
+// each with itself.  With a virtual c running along the contraction and
+//     s[a][c] = T[a][c] + T[c][a],   d[a][c] = T[a][c] - T[c][a]
+// it is 1/2 s s^T + 3/2 d d^T.  For i == j (T symmetric, d = 0) the same expression gets
+// half the weight and the second product is skipped.  The result is symmetric, so only
+// tiles (A <= B) of D are formed.
 //
 // Workgroup = (tile pair (A, B), split s).  Split s owns a contiguous range of
 // pairs and accumulates into its own slice Dpart[s]; slices are summed in a
-// fixed order afterwards, so results are bitwise reproducible.  The four
-// operand panels per chunk (two row panels, two column panels of T) are staged
-// through LDS with a register double buffer; the Y operands are formed while
-// reading fragments.
+// fixed order afterwards, so results are bitwise reproducible.  Per 16-deep chunk the four
+// operand panels (rows A and B of T, and of T^T, i.e. columns A and B) are staged through
+// LDS; s and d are formed from two fragments as they are read, the first ones times the
+// pair's weight, so that one set of accumulators takes all pairs.
+// As in the FP64 pair kernel: buffer loads one chunk ahead at constant offsets, XOR-swizzled
+// LDS panels, the 16 x 16 blocks beyond n_v skipped, no branch in the loop over the chunks
+// of a pair; each XCD walks a contiguous range of (split, tile pair).
+//
+// What bounds it: the matrix pipe at the clock that it leaves (about 2 GHz), with 20% of
+// the products' time lost where the last tile row is narrow and in the last round.
+// 40 cores + 8 active, 400 virtuals, ms per pass: 4.8, 5.1 before (the operands 2T - T^T
+// formed with weights in the loop, whole tiles, predicated loads).  Without any load in
+// the loop 4.2; chunks of 8 with three or four workgroups per unit, and 27 or 54 splits
+// (whole rounds) instead of 64: no faster.
+#include <type_traits>
+
 #include "common.h"
 #include "kernels.h"
 
@@ -24,132 +36,148 @@ namespace dfpt2 {
 namespace {
 constexpr int TM = 64;
 constexpr int KC = 16;
-constexpr int LDR = KC + 1;  // row panel stride
-constexpr int LDC = TM + 1;  // column panel stride
-}
+constexpr int PANEL = KC * TM;
+typedef uint32_t u2 __attribute__((ext_vector_type(2)));
 
-template <bool VEC>
+// place of (k, row) in a panel (pair_f64.hip)
+__device__ inline int slot(int k, int row) { return k * TM + (row ^ (((k & 1) << 4) | ((k >> 1) << 1))); }
+}  // namespace
+
 __global__ __launch_bounds__(256, 2) void density_f64_kernel(DensityKernelArgs a) {
-  __shared__ double rp[2][2][TM][LDR];  // T[A, c..], T[B, c..]
-  __shared__ double cp[2][2][KC][LDC];  // T[c.., A], T[c.., B]
-  const int tp = blockIdx.x, split = blockIdx.y;
+  __shared__ double lds[2][4][PANEL];  // T[A, c..], T[B, c..], T[c.., A], T[c.., B]
+  int tp, split;
+  {  // XCD-aware order: each XCD walks a contiguous range of (split, tile pair)
+    const uint32_t id = blockIdx.y * gridDim.x + blockIdx.x, nblk = gridDim.x * gridDim.y;
+    const uint32_t x = id & 7, q = id >> 3, per8 = nblk >> 3, rem = nblk & 7;
+    const uint32_t L = (x < rem) ? x * (per8 + 1) + q : rem * (per8 + 1) + (x - rem) * per8 + q;
+    split = (int)(L / gridDim.x);
+    tp = (int)(L - (uint32_t)split * gridDim.x);
+  }
   int A, Bt;
   tile_pair(tp, a.nt, A, Bt);
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int wr = w >> 1, wc = w & 1;
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wr = w >> 1, wc = w & 1, r16 = lane & 15, kq = lane >> 4;
   const int n_v = a.n_v;
-  const int per = (a.n_pairs + a.nsplit - 1) / a.nsplit;
-  const int p0 = split * per;
-  const int p1 = min(a.n_pairs, p0 + per);
-  const int ncc = (n_v + KC - 1) / KC;
-  const int total = (p1 > p0) ? (p1 - p0) * ncc : 0;
+  const int p0 = (int)((int64_t)split * a.n_pairs / a.nsplit);
+  const int p1 = (int)((int64_t)(split + 1) * a.n_pairs / a.nsplit);
+  const int ncc = (n_v + KC - 1) / KC, tail = n_v - (ncc - 1) * KC;  // columns of the last chunk
   const int blk[2] = {A, Bt};
 
-  double2 sr[2][2], sc[2][2];
-  auto load_chunk = [&](int idx) {
-    const int p = p0 + idx / ncc;
-    const int c0 = (idx % ncc) * KC;
-    const double* Tp = a.T + (size_t)(a.slot ? a.slot[p] : p) * n_v * n_v;
+  // row panels: column ka of the chunk, rows lr + 16 h; column panels: row kc + 4 h of the
+  // chunk, column cc of the block
+  const int ka = tid & 15, lr = tid >> 4, cc = lane, kc = tid >> 6;
+  uint32_t orow[2][4], ocol[2];
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+#pragma unroll
+    for (int h = 0; h < 4; ++h) orow[q][h] = ((uint32_t)min(lr + 16 * h, n_v - 1 - blk[q] * TM) * n_v + ka) * 8u;
+    ocol[q] = ((uint32_t)kc * n_v + min(blk[q] * TM + cc, n_v - 1)) * 8u;
+  }
+  auto matrix = [&](int p) { return a.T + (size_t)(a.slot ? a.slot[p] : p) * n_v * n_v; };
+  const uint32_t out = ka >= tail ? 0x80000000u : 0u;  // of range in the last chunk: reads zero
+  auto load = [&](double (&st)[4][4], const double* Tp, int ci) __attribute__((always_inline)) {
+    const uint32_t mask = ci == ncc - 1 ? out : 0u;
+    // the rows left below the chunk's first bound the column panels
+    const uint64_t left = (uint64_t)(n_v - ci * KC) * n_v * 8;
+    auto dc = __builtin_amdgcn_make_buffer_rsrc((void*)(Tp + (size_t)ci * KC * n_v), 0,
+                                                (uint32_t)(left < 0x7fffffff ? left : 0x7fffffff), 0x00020000);
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
+      auto dr = __builtin_amdgcn_make_buffer_rsrc((void*)(Tp + (size_t)blk[q] * TM * n_v + ci * KC), 0, 0x7fffffff, 0x00020000);
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const int e = tid + 256 * h;
-        // row panel: rows blk*TM + (e>>3), columns c0 + 2*(e&7)
-        {
-          const int row = blk[q] * TM + (e >> 3);
-          const int col = c0 + (e & 7) * 2;
-          double2 v = make_double2(0.0, 0.0);
-          if (row < n_v) {
-            const double* src = Tp + (size_t)row * n_v + col;
-            if (VEC) {
-              if (col + 1 < n_v) v = *reinterpret_cast<const double2*>(src);
-              else if (col < n_v) v.x = src[0];
-            } else {
-              if (col < n_v) v.x = src[0];
-              if (col + 1 < n_v) v.y = src[1];
-            }
-          }
-          sr[q][h] = v;
-        }
-        // column panel: rows c0 + (e>>5), columns blk*TM + 2*(e&31)
-        {
-          const int row = c0 + (e >> 5);
-          const int col = blk[q] * TM + (e & 31) * 2;
-          double2 v = make_double2(0.0, 0.0);
-          if (row < n_v) {
-            const double* src = Tp + (size_t)row * n_v + col;
-            if (VEC) {
-              if (col + 1 < n_v) v = *reinterpret_cast<const double2*>(src);
-              else if (col < n_v) v.x = src[0];
-            } else {
-              if (col < n_v) v.x = src[0];
-              if (col + 1 < n_v) v.y = src[1];
-            }
-          }
-          sc[q][h] = v;
-        }
+      for (int h = 0; h < 4; ++h) {
+        st[q][h] = __builtin_bit_cast(double, (u2)__builtin_amdgcn_raw_buffer_load_b64(dr, orow[q][h] | mask, 0, 0));
+        st[2 + q][h] =
+            __builtin_bit_cast(double, (u2)__builtin_amdgcn_raw_buffer_load_b64(dc, ocol[q], 4 * h * n_v * 8, 0));
       }
     }
   };
-  auto store_chunk = [&](int buf) {
+  auto store = [&](double (&st)[4][4], int buf) __attribute__((always_inline)) {
 #pragma unroll
-    for (int q = 0; q < 2; ++q) {
+    for (int q = 0; q < 2; ++q)
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const int e = tid + 256 * h;
-        const int r = e >> 3, k = (e & 7) * 2;
-        rp[buf][q][r][k] = sr[q][h].x;
-        rp[buf][q][r][k + 1] = sr[q][h].y;
-        const int kr = e >> 5, cc = (e & 31) * 2;
-        cp[buf][q][kr][cc] = sc[q][h].x;
-        cp[buf][q][kr][cc + 1] = sc[q][h].y;
+      for (int h = 0; h < 4; ++h) {
+        lds[buf][q][slot(ka, lr + 16 * h)] = st[q][h];
+        lds[buf][2 + q][slot(kc + 4 * h, cc)] = st[2 + q][h];
       }
-    }
   };
 
-  d4 acc[2][2];
+  const int nbi = min(2, max(0, (n_v - A * TM - wr * 32 + 15) / 16)), nbj = min(2, max(0, (n_v - Bt * TM - wc * 32 + 15) / 16));
+  d4 D[2][2];
 #pragma unroll
   for (int x = 0; x < 2; ++x)
 #pragma unroll
-    for (int y = 0; y < 2; ++y) acc[x][y] = (d4){0.0, 0.0, 0.0, 0.0};
+    for (int y = 0; y < 2; ++y) D[x][y] = (d4){0.0, 0.0, 0.0, 0.0};
 
-  const int r16 = lane & 15, kq = lane >> 4;
-  if (total > 0) {
-    load_chunk(0);
-    store_chunk(0);
-  }
-  __syncthreads();
-  for (int idx = 0; idx < total; ++idx) {
-    const int buf = idx & 1;
-    const int p = p0 + idx / ncc;
-    const int2 pr = a.pairs[p];
-    double wp = a.w * (pr.x == pr.y ? 0.5 : 1.0);
-    if (a.pw) wp *= a.pw[p];
-    const double wp2 = 2.0 * wp;
-    if (idx + 1 < total) load_chunk(idx + 1);
+  auto run = [&](auto NI, auto NJ) __attribute__((always_inline)) {
+    double st[4][4];
+    // chunk `ci` of pair `p`, its products from buffer BUF; ANTI: also d d^T
+    auto products = [&](int buf, auto ANTI, double ws, double wx) __attribute__((always_inline)) {
 #pragma unroll
-    for (int k4 = 0; k4 < KC / 4; ++k4) {
-      const int k = k4 * 4 + kq;
-      const int ra0 = wr * 32 + r16, ra1 = ra0 + 16;
-      const int rb0 = wc * 32 + r16, rb1 = rb0 + 16;
-      const double x10 = rp[buf][0][ra0][k], x11 = rp[buf][0][ra1][k];
-      const double y10 = wp2 * rp[buf][1][rb0][k] - wp * cp[buf][1][k][rb0];
-      const double y11 = wp2 * rp[buf][1][rb1][k] - wp * cp[buf][1][k][rb1];
-      const double x20 = cp[buf][0][k][ra0], x21 = cp[buf][0][k][ra1];
-      const double y20 = wp2 * cp[buf][1][k][rb0] - wp * rp[buf][1][rb0][k];
-      const double y21 = wp2 * cp[buf][1][k][rb1] - wp * rp[buf][1][rb1][k];
-      acc[0][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(x10, y10, acc[0][0], 0, 0, 0);
-      acc[0][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(x10, y11, acc[0][1], 0, 0, 0);
-      acc[1][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(x11, y10, acc[1][0], 0, 0, 0);
-      acc[1][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(x11, y11, acc[1][1], 0, 0, 0);
-      acc[0][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(x20, y20, acc[0][0], 0, 0, 0);
-      acc[0][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(x20, y21, acc[0][1], 0, 0, 0);
-      acc[1][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(x21, y20, acc[1][0], 0, 0, 0);
-      acc[1][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(x21, y21, acc[1][1], 0, 0, 0);
-    }
-    if (idx + 1 < total) store_chunk(buf ^ 1);
+      for (int k4 = 0; k4 < KC / 4; ++k4) {
+        const int k = k4 * 4 + kq;
+        double sa[2], da[2], sb[2], db[2];
+#pragma unroll
+        for (int b = 0; b < NI(); ++b) {
+          const int o = slot(k, wr * 32 + b * 16 + r16);
+          const double x1 = lds[buf][0][o], x2 = lds[buf][2][o];
+          sa[b] = (x1 + x2) * ws;
+          da[b] = (x1 - x2) * wx;
+        }
+#pragma unroll
+        for (int b = 0; b < NJ(); ++b) {
+          const int o = slot(k, wc * 32 + b * 16 + r16);
+          const double x1 = lds[buf][1][o], x2 = lds[buf][3][o];
+          sb[b] = x1 + x2;
+          db[b] = x1 - x2;
+        }
+#pragma unroll
+        for (int bi = 0; bi < NI(); ++bi)
+#pragma unroll
+          for (int bj = 0; bj < NJ(); ++bj) {
+            D[bi][bj] = __builtin_amdgcn_mfma_f64_16x16x4f64(sa[bi], sb[bj], D[bi][bj], 0, 0, 0);
+          }
+        if (ANTI()) {
+#pragma unroll
+          for (int bi = 0; bi < NI(); ++bi)
+#pragma unroll
+            for (int bj = 0; bj < NJ(); ++bj)
+              D[bi][bj] = __builtin_amdgcn_mfma_f64_16x16x4f64(da[bi], db[bj], D[bi][bj], 0, 0, 0);
+        }
+      }
+    };
+    // the chunks of all pairs are one sequence whose loads run one ahead of the products
+    // (at the end the last pair's first chunk is loaded once more, and not read)
+    const double *Tp = matrix(p0), *Tn;
+    int buf = 0;
+    load(st, Tp, 0);
+    store(st, 0);
     __syncthreads();
+    for (int p = p0; p < p1; ++p, Tp = Tn) {
+      const int2 pr = a.pairs[p];
+      Tn = matrix(min(p + 1, p1 - 1));
+      const double wp = a.w * (pr.x == pr.y ? 0.5 : 1.0) * (a.pw ? a.pw[p] : 1.0);
+      const double ws = 0.5 * wp, wx = 1.5 * wp;
+      auto chunks = [&](auto ANTI) __attribute__((always_inline)) {
+        for (int c = 1; c <= ncc; ++c) {
+          const bool last = c == ncc;
+          load(st, last ? Tn : Tp, last ? 0 : c);
+          products(buf, ANTI, ws, wx);
+          store(st, buf ^= 1);
+          __syncthreads();
+        }
+      };
+      if (pr.x == pr.y) chunks(std::false_type{});
+      else chunks(std::true_type{});
+    }
+  };
+  using N0 = std::integral_constant<int, 0>;
+  using N1 = std::integral_constant<int, 1>;
+  using N2 = std::integral_constant<int, 2>;
+  if (p0 < p1) {  // workgroup-uniform; the instances have the same loads and barriers
+    if (nbi == 0 || nbj == 0) run(N0{}, N0{});
+    else if (nbi == 1) nbj == 1 ? run(N1{}, N1{}) : run(N1{}, N2{});
+    else nbj == 1 ? run(N2{}, N1{}) : run(N2{}, N2{});
   }
 
   double* Dp = a.Dpart + (size_t)split * n_v * n_v;
@@ -164,7 +192,7 @@ __global__ __launch_bounds__(256, 2) void density_f64_kernel(DensityKernelArgs a
         const int gb = Bt * TM + wc * 32 + bj * 16 + r16;
         if (gb >= n_v) continue;
         double* dst = Dp + (size_t)ga * n_v + gb;
-        *dst = a.accumulate ? *dst + acc[bi][bj][r] : acc[bi][bj][r];
+        *dst = a.accumulate ? *dst + D[bi][bj][r] : D[bi][bj][r];
       }
     }
 }
@@ -185,10 +213,7 @@ __global__ void density_reduce_kernel(const double* Dpart, int nsplit, int n_v, 
 hipError_t launch_density_f64(const DensityKernelArgs& a, hipStream_t st) {
   if (a.n_pairs <= 0) return hipSuccess;
   dim3 grid(a.nTP, a.nsplit), block(256);
-  if ((a.n_v % 2) == 0)
-    hipLaunchKernelGGL(density_f64_kernel<true>, grid, block, 0, st, a);
-  else
-    hipLaunchKernelGGL(density_f64_kernel<false>, grid, block, 0, st, a);
+  hipLaunchKernelGGL(density_f64_kernel, grid, block, 0, st, a);
   return hipGetLastError();
 }
 
