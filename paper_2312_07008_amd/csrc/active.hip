@@ -226,37 +226,6 @@ hipError_t launch_weighted_pair_reduce(const double* part, int ntile, int n_pair
   return hipGetLastError();
 }
 
-// E = sum of core-core pair energies (count on the device) + the rotated-pair
-// energies pe_act[0 .. n_act_pairs), in double-double, written to e_out[2].
-// Rotated pairs write their ||T||_F into pair_tnorm (semicanonical, ordered).
-__global__ void energy_finalize_active_kernel(const double* pe, const int* count, const double* pe_act,
-                                              int n_act_pairs, double* e_out) {
-  __shared__ double sh[2][16];
-  const int n = *count;
-  double hi = 0.0, lo = 0.0;
-  for (int p = threadIdx.x; p < n; p += blockDim.x) dd_add_dd(hi, lo, pe[2 * p], pe[2 * p + 1]);
-  for (int p = threadIdx.x; p < n_act_pairs; p += blockDim.x) dd_add_dd(hi, lo, pe_act[2 * p], pe_act[2 * p + 1]);
-  wave_sum_dd(hi, lo);
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = blockDim.x >> 6;
-  if (lane == 0) {
-    sh[0][w] = hi;
-    sh[1][w] = lo;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    double h = 0.0, l = 0.0;
-    for (int k = 0; k < nw; ++k) dd_add_dd(h, l, sh[0][k], sh[1][k]);
-    e_out[0] = h;
-    e_out[1] = l;
-  }
-}
-
-hipError_t launch_energy_finalize_active(const double* pe, const int* count, const double* pe_act, int n_act_pairs,
-                                         double* e_out, hipStream_t st) {
-  hipLaunchKernelGGL(energy_finalize_active_kernel, dim3(1), dim3(1024), 0, st, pe, count, pe_act, n_act_pairs, e_out);
-  return hipGetLastError();
-}
-
 // pair_energy = NaN and pair_tnorm = ||T||_F for pairs with an active hole
 __global__ void scatter_active_pair_info_kernel(const int2* pairs, const double* tn2, int n, int n_h,
                                                 double* pair_energy, float* pair_tnorm) {

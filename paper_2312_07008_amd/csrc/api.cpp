@@ -606,7 +606,8 @@ static int run_active_blocks(const PassPlan& pl, const dfpt2_opts& o, const doub
 
 int run_pass(const PassPlan& pl, const dfpt2_opts& o, const double* eps_h, const double* eps_v,
              const double* gamma_act, const double* B, const uint8_t* mask, double* D, double* e_out,
-             double* pair_energy, float* pair_tnorm, char* ws, hipStream_t s) {
+             double* pair_energy, float* pair_tnorm, char* ws, hipStream_t s, const double* e_full,
+             double* correction) {
   hipError_t e;
   int2* pairs = reinterpret_cast<int2*>(ws + pl.off_pairs);
   int* d_count = reinterpret_cast<int*>(ws + pl.off_count);
@@ -627,9 +628,15 @@ int run_pass(const PassPlan& pl, const dfpt2_opts& o, const double* eps_h, const
     L.ns2 = pl.ns2;
     L.rows_t = pl.n_v_rows_t;
   }
-  // d_count[0]: pairs of the mask; d_count[1]: set by the BF16 split when a row of B
-  // lies below the range its slices need (both read back with one copy below)
-  if ((e = launch_fill(reinterpret_cast<double*>(d_count), 2, 0.0, s)) != hipSuccess) return hip_fail(e, "fill");
+  {  // pairs with an active hole get their values later (NaN energies)
+    ProfScope ps(DFPT2_STAGE_REDUCE, s);
+    const bool diag = !pl.energy_only && pl.ns2 >= 2;
+    if ((e = launch_pass_begin(mask, pl.n_core, pl.n_h, pairs, d_count, pair_energy, pair_tnorm,
+                               pl.energy_only ? nullptr : Dpart, pl.energy_only ? 0 : mat * pl.nsplit_all,
+                               diag ? reinterpret_cast<double*>(ws + pl.off_diag) : nullptr, diag ? pl.n_v : 0, s)) !=
+        hipSuccess)
+      return hip_fail(e, "pass start");
+  }
   if (pl.precision != DFPT2_FP64) {
     ProfScope ps(DFPT2_STAGE_SPLIT, s);
     double* nrm = reinterpret_cast<double*>(ws + pl.off_norm2);
@@ -653,15 +660,13 @@ int run_pass(const PassPlan& pl, const dfpt2_opts& o, const double* eps_h, const
         return hip_fail(e, "split");
     }
   }
-  {
-    ProfScope ps(DFPT2_STAGE_REDUCE, s);
-    if ((e = launch_build_pairs(mask, pl.n_core, pl.n_h, pairs, d_count, s)) != hipSuccess)
-      return hip_fail(e, "build_pairs");
+  // read back only what the host cannot know: the pairs left by a mask, the BF16 split's flag
+  int cnt[2] = {pl.n_up, 0};
+  if (mask || pl.precision == DFPT2_BF16_SLICED) {
+    if ((e = hipMemcpyAsync(cnt, d_count, sizeof(cnt), hipMemcpyDeviceToHost, s)) != hipSuccess)
+      return hip_fail(e, "count copy");
+    if ((e = hipStreamSynchronize(s)) != hipSuccess) return hip_fail(e, "stream sync");
   }
-  int cnt[2] = {0, 0};
-  if ((e = hipMemcpyAsync(cnt, d_count, sizeof(cnt), hipMemcpyDeviceToHost, s)) != hipSuccess)
-    return hip_fail(e, "count copy");
-  if ((e = hipStreamSynchronize(s)) != hipSuccess) return hip_fail(e, "stream sync");
   const int count = cnt[0];
   if (cnt[1] != 0)
     return fail(DFPT2_ERR_UNSUPPORTED,
@@ -669,22 +674,6 @@ int run_pass(const PassPlan& pl, const dfpt2_opts& o, const double* eps_h, const
                 "normal FP32 range; rescale the integrals or use FP64 or INT8 digits",
                 bf16_min_row_exponent(pl.ns1) - 1, pl.ns1);
 
-  if (pair_energy) {
-    // core-core entries start at 0 (masked pairs stay 0); pairs with an active hole are NaN
-    if ((e = launch_fill(pair_energy, (size_t)pl.n_h * pl.n_h, 0.0, s)) != hipSuccess)
-      return hip_fail(e, "fill");
-  }
-  if (pair_tnorm) {
-    if ((e = launch_fill_f32(pair_tnorm, (size_t)pl.n_h * pl.n_h, 0.0f, s)) != hipSuccess)
-      return hip_fail(e, "fill");
-  }
-
-  if (!pl.energy_only) {
-    ProfScope ps(DFPT2_STAGE_REDUCE, s);
-    if ((e = launch_fill(Dpart, mat * pl.nsplit_all, 0.0, s)) != hipSuccess) return hip_fail(e, "fill");
-    if (pl.ns2 >= 2 && (e = launch_fill(reinterpret_cast<double*>(ws + pl.off_diag), pl.n_v, 0.0, s)) != hipSuccess)
-      return hip_fail(e, "fill");
-  }
   const int stage_pair = pl.energy_only ? DFPT2_STAGE_KEPT_PAIR : DFPT2_STAGE_PAIR;
   PairKernelArgs pa{};
   pa.B = B;
@@ -707,6 +696,11 @@ int run_pass(const PassPlan& pl, const dfpt2_opts& o, const double* eps_h, const
   da.nTP = pl.nTP;
   da.w = pl.w_density;
 
+  // One batch of at most 8 tile partials a pair (up to 192 virtuals) is reduced by the last
+  // kernel, whose single workgroup takes a pair per thread, instead of a launch of its own:
+  // 4.1 + 4.8 us in two launches, 5 in one, at 55 pairs of one partial.  More partials are
+  // left to a wave per pair over the whole chip.
+  const bool fused = count <= pl.batch && pl.nTP1 <= 8;
   for (int p0 = 0, b = 0; p0 < count; p0 += pl.batch, ++b) {
     const int np = (count - p0 < pl.batch) ? count - p0 : pl.batch;
     pa.pairs = pairs + p0;
@@ -721,7 +715,7 @@ int run_pass(const PassPlan& pl, const dfpt2_opts& o, const double* eps_h, const
       ProfScope ps(stage_pair, s);
       if ((e = launch_pair(L, pa, np, s, &ps)) != hipSuccess) return hip_fail(e, "pair kernel");
     }
-    {
+    if (!fused) {
       ProfScope ps(DFPT2_STAGE_REDUCE, s);
       if ((e = launch_pair_reduce(epart, tpart, pl.nTP1, np, pe + 2 * (size_t)p0, tn2 + p0, s)) != hipSuccess)
         return hip_fail(e, "pair reduce");
@@ -804,14 +798,25 @@ int run_pass(const PassPlan& pl, const dfpt2_opts& o, const double* eps_h, const
       if ((e = launch_density_reduce(Dpart, pl.nsplit_all, pl.n_v, diag, D, s)) != hipSuccess)
         return hip_fail(e, "density reduce");
     }
-    if ((e = launch_energy_finalize(pe, tn2, pairs, d_count, pl.n_up, pl.n_h, e_out, pair_energy, pair_tnorm,
-                                    s)) != hipSuccess)
-      return hip_fail(e, "energy finalize");
+    EnergyFinalizeArgs fa{};
+    fa.pe = pe;
+    fa.tn2 = tn2;
+    fa.epart = epart;
+    fa.tpart = tpart;
+    fa.pairs = pairs;
+    fa.count = d_count;
+    fa.nTP = fused ? pl.nTP1 : 0;
+    fa.n_h = pl.n_h;
     if (pl.n_act > 0) {
-      const double* pe_act = reinterpret_cast<const double*>(ws + pl.off_act_pe);
-      if ((e = launch_energy_finalize_active(pe, d_count, pe_act, pl.n_ca + pl.n_aa_un, e_out, s)) != hipSuccess)
-        return hip_fail(e, "energy finalize (active)");
+      fa.pe_act = reinterpret_cast<const double*>(ws + pl.off_act_pe);
+      fa.n_act_pairs = pl.n_ca + pl.n_aa_un;
     }
+    fa.e_out = e_out;
+    fa.e_full = e_full;
+    fa.correction = correction;
+    fa.pair_energy = pair_energy;
+    fa.pair_tnorm = pair_tnorm;
+    if ((e = launch_energy_finalize(fa, s)) != hipSuccess) return hip_fail(e, "energy finalize");
   }
   double eh[2];
   if ((e = hipMemcpyAsync(eh, e_out, sizeof(eh), hipMemcpyDeviceToHost, s)) != hipSuccess)

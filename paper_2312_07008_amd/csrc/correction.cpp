@@ -74,14 +74,6 @@ __global__ void symmetrize_kernel(double* F, int n) {
   F[(size_t)j * n + i] = v;
 }
 
-__global__ void dd_sub_kernel(const double* a, const double* b, double* out) {
-  if (threadIdx.x != 0) return;
-  double h = a[0], l = a[1];
-  dd_add_dd(h, l, -b[0], -b[1]);
-  out[0] = h;
-  out[1] = l;
-}
-
 }  // namespace
 
 }  // namespace dfpt2
@@ -145,18 +137,8 @@ int pt2_energy_correction(const dfpt2_opts* opts, const double* eps_hole, const 
   ps_u.close();
   // kept-space pass (energy only) in the recanonicalized basis (eps~, B~)
   st = run_pass(cp.kp, cp.ko, eps_hole, et, gamma_act, Bt, nullptr, nullptr, e_kept, nullptr, nullptr,
-                ws + cp.off_kp, s);
-  if (st != DFPT2_OK) return st;
-  ProfScope ps_sub(DFPT2_STAGE_REDUCE, s);
-  hipLaunchKernelGGL(dd_sub_kernel, dim3(1), dim3(64), 0, s, e_full, e_kept, correction);
-  if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "dd_sub");
-  ps_sub.close();
-  double h[2];
-  if ((e = hipMemcpyAsync(h, e_kept, 16, hipMemcpyDeviceToHost, s)) != hipSuccess) return hip_fail(e, "copy");
-  if ((e = hipStreamSynchronize(s)) != hipSuccess) return hip_fail(e, "sync");
-  prof_flush();
-  if (!std::isfinite(h[0]) || !std::isfinite(h[1])) return fail(DFPT2_ERR_NONFINITE, "kept-space energy is not finite");
-  return DFPT2_OK;
+                ws + cp.off_kp, s, e_full, correction);
+  return st;
 }
 
 }  // extern "C"

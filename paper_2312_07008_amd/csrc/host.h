@@ -48,7 +48,8 @@ int plan_pass(const dfpt2_opts* o, PassPlan* pl, bool energy_only = false);
 
 int run_pass(const PassPlan& pl, const dfpt2_opts& o, const double* eps_h, const double* eps_v,
              const double* gamma_act, const double* B, const uint8_t* mask, double* D, double* e_out,
-             double* pair_energy, float* pair_tnorm, char* ws, hipStream_t s);
+             double* pair_energy, float* pair_tnorm, char* ws, hipStream_t s, const double* e_full = nullptr,
+             double* correction = nullptr);  // correction[2] = e_full - e_out, unless null
 
 // Pair-kernel launcher shared by the pass and the kept-space energy: FP64, or
 // split BF16 / FP8 / INT8 from the slices in `Bs` (and FP8 block scales in

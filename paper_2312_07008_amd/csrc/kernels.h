@@ -144,16 +144,29 @@ hipError_t launch_density_reduce(const double* Dpart, int nsplit, int n_v, const
 
 // ------------------------------------------------------------ small kernels
 hipError_t launch_fill(double* p, size_t n, double v, hipStream_t st);
-hipError_t launch_fill_f32(float* p, size_t n, float v, hipStream_t st);
-hipError_t launch_build_pairs(const uint8_t* mask, int n_core, int n_h, int2* pairs, int* count,
-                              hipStream_t st);
+// start of a pass: pair list of the mask (count[0] pairs; count[1] = 0) and zeros into the
+// results (null: skipped)
+hipError_t launch_pass_begin(const uint8_t* mask, int n_core, int n_h, int2* pairs, int* count, double* pair_energy,
+                             float* pair_tnorm, double* Dpart, size_t n_Dpart, double* diag, int n_diag,
+                             hipStream_t st);
 // per-pair reduction of tile partials into double-double pair energies and ||T||^2
 hipError_t launch_pair_reduce(const double* epart, const double* tpart, int nTP, int n_pairs,
                               double* pe /*[n][2]*/, double* tn2 /*[n]*/, hipStream_t st);
-// sum of pair energies (double-double) -> e[2]; optional scatter to n_h x n_h outputs
-hipError_t launch_energy_finalize(const double* pe, const double* tn2, const int2* pairs,
-                                  const int* count, int max_pairs, int n_h, double* e_out,
-                                  double* pair_energy, float* pair_tnorm, hipStream_t st);
+// end of a pass: sum of pair energies (double-double) -> e_out[2]; optional scatter to
+// n_h x n_h outputs
+struct EnergyFinalizeArgs {
+  double *pe, *tn2;            // [n][2], [n]: reduced here first if nTP > 0
+  const double *epart, *tpart; // tile partials [n][nTP]
+  const int2* pairs;
+  const int* count;            // n, on the device
+  const double* pe_act;        // [n_act_pairs][2] energies of rotated pairs, summed with the others
+  int nTP, n_act_pairs, n_h;
+  double* e_out;
+  const double* e_full;        // correction[2] = e_full - e_out, unless null
+  double *correction, *pair_energy;
+  float* pair_tnorm;
+};
+hipError_t launch_energy_finalize(const EnergyFinalizeArgs& a, hipStream_t st);
 
 // ------------------------------------------------------------ active holes
 hipError_t launch_kron_uu(const double* U, int na, double* W, hipStream_t st);
@@ -169,8 +182,6 @@ hipError_t launch_rotated_energy(const double* T, const double* Vr, const int* s
                                  double* part, hipStream_t st);
 hipError_t launch_weighted_pair_reduce(const double* part, int ntile, int n_pairs, const double* we, double* pe,
                                        hipStream_t st);
-hipError_t launch_energy_finalize_active(const double* pe, const int* count, const double* pe_act, int n_act_pairs,
-                                         double* e_out, hipStream_t st);
 hipError_t launch_scatter_active_pair_info(const int2* pairs, const double* tn2, int n, int n_h, double* pair_energy,
                                            float* pair_tnorm, hipStream_t st);
 

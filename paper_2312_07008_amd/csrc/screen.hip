@@ -31,34 +31,35 @@ constexpr int OFF_W1 = 0, OFF_B1 = H * NIN, OFF_W2 = OFF_B1 + H, OFF_B2 = OFF_W2
 constexpr int BW_SAMPLES = 128;  // samples that the sizes of the workspaces count one row of gradients for
 
 // q2[i][Q] = sum_a B[i][a][Q]^2 for core holes
-__global__ void colnorm2_kernel(const double* B, int n_v, int n_aux, double* q2) {
-  const int Q = blockIdx.x * blockDim.x + threadIdx.x;
+// Bound by the latency of its loads (60 virtuals: 11 us with one thread per column, all rows
+// one after the other): a workgroup takes 64 columns, its 16 waves the rows w, w + 16, ...
+__global__ __launch_bounds__(1024) void colnorm2_kernel(const double* B, int n_v, int n_aux, double* q2) {
+  __shared__ double sh[16][64];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int Q = blockIdx.x * 64 + lane;
   const int i = blockIdx.y;
-  if (Q >= n_aux) return;
-  const double* Bi = B + (size_t)i * n_v * n_aux;
+  const double* Bi = B + (size_t)i * n_v * n_aux + min(Q, n_aux - 1);
   double acc = 0.0;
-  for (int a = 0; a < n_v; ++a) {
-    const double x = Bi[(size_t)a * n_aux + Q];
+#pragma unroll 4
+  for (int a = w; a < n_v; a += 16) {
+    const double x = Bi[(size_t)a * n_aux];
     acc += x * x;
   }
+  sh[w][lane] = acc;
+  __syncthreads();
+  if (w > 0 || Q >= n_aux) return;
+  for (int g = 1; g < 16; ++g) acc += sh[g][lane];
   q2[(size_t)i * n_aux + Q] = acc;
-}
-
-// wdiag[i] = W_ii^2 = sum_Q q2_iQ^2
-__global__ void wdiag_kernel(const double* q2, int n_aux, double* wdiag) {
-  const int i = blockIdx.x;
-  double acc = 0.0;
-  for (int Q = threadIdx.x; Q < n_aux; Q += 64) acc += q2[(size_t)i * n_aux + Q] * q2[(size_t)i * n_aux + Q];
-  acc = wave_sum(acc);
-  if (threadIdx.x == 0) wdiag[i] = acc;
 }
 
 __device__ double reg_fun(double s, double x) { return x > 0.0 ? -expm1(-s * x * x) / x : 0.0; }
 
-// one wave per pair
-__global__ void pair_features_kernel(const double* q2, const double* wdiag, const double* eps_h, double e_vmin,
-                                     double e_vmax, int n_core, int n_aux, double s, double x_star, float* feats,
-                                     double* log_scale, int n_pairs) {
+// one wave per pair; W_ii^2 = sum_Q q2_iQ^2 and W_jj^2 come along with the pair's own sums, and
+// lanes 0 to 4 take one regularizer value and one logarithm each.  The virtual energies are
+// ascending: the denominator range uses the first and last.
+__global__ void pair_features_kernel(const double* q2, const double* eps_h, const double* eps_v, int n_v, int n_core,
+                                     int n_aux, double s, double x_star, float* feats, double* log_scale,
+                                     int n_pairs) {
   const int lane = threadIdx.x & 63;
   const int p = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
   if (p >= n_pairs) return;
@@ -68,31 +69,38 @@ __global__ void pair_features_kernel(const double* q2, const double* wdiag, cons
     ++i;
   }
   const int j = i + rem;
-  double u = 0.0, w2 = 0.0;
+  double u = 0.0, w2 = 0.0, wi = 0.0, wj = 0.0;
   for (int Q = lane; Q < n_aux; Q += 64) {
     const double a = q2[(size_t)i * n_aux + Q], b = q2[(size_t)j * n_aux + Q];
     u += sqrt(a) * sqrt(b);
     w2 += a * b;
+    wi += a * a;
+    wj += b * b;
   }
   u = wave_sum(u);
   w2 = wave_sum(w2);
-  if (lane != 0) return;
+  wi = wave_sum(wi);
+  wj = wave_sum(wj);
   const double ei = eps_h[i], ej = eps_h[j];
-  double lo = fabs(ei + ej - 2.0 * e_vmin), hi = fabs(ei + ej - 2.0 * e_vmax);
+  double lo = fabs(ei + ej - 2.0 * eps_v[0]), hi = fabs(ei + ej - 2.0 * eps_v[n_v - 1]);
   if (lo > hi) {
     const double t = lo;
     lo = hi;
     hi = t;
   }
-  const double g = (lo <= x_star && x_star <= hi) ? reg_fun(s, x_star) : fmax(reg_fun(s, lo), reg_fun(s, hi));
+  const double r = reg_fun(s, lane == 0 ? x_star : lane == 1 ? lo : hi);
+  const double r0 = __shfl(r, 0, 64), r1 = __shfl(r, 1, 64), r2 = __shfl(r, 2, 64);
+  const double g = (lo <= x_star && x_star <= hi) ? r0 : fmax(r1, r2);
   const double w = sqrt(w2);
-  const double lw = log(w), lu = log(u);
-  const double lg = log(g);
+  const double l = log(lane == 0 ? w : lane == 1 ? u : lane == 2 ? g : lane == 3 ? wi : wj);
+  const double lw = __shfl(l, 0, 64), lu = __shfl(l, 1, 64), lg = __shfl(l, 2, 64);
+  const double li = __shfl(l, 3, 64), lj = __shfl(l, 4, 64);
+  if (lane != 0) return;
   float* f = feats + (size_t)p * NIN;
   f[0] = (float)ei;
   f[1] = (float)ej;
   f[2] = (float)(lu - lw);
-  f[3] = (float)(0.1 * (lw - 0.25 * (log(wdiag[i]) + log(wdiag[j]))));
+  f[3] = (float)(0.1 * (lw - 0.25 * (li + lj)));
   f[4] = (float)(0.1 * (lg + lw));
   log_scale[2 * (size_t)p] = lg + lw;
   log_scale[2 * (size_t)p + 1] = lg + lu;
@@ -437,23 +445,14 @@ int pairscreen_features(const dfpt2_opts* opts, const double* eps_hole, const do
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   char* ws = static_cast<char*>(workspace);
   double* q2 = reinterpret_cast<double*>(ws);
-  double* wd = reinterpret_cast<double*>(ws + align_up(sizeof(double) * (size_t)pl.n_core * pl.n_aux, 256));
-  // the virtual energies are ascending: the denominator range uses the first and last
-  double ev[2];
-  hipError_t e;
-  if ((e = hipMemcpyAsync(&ev[0], eps_vir, 8, hipMemcpyDeviceToHost, s)) != hipSuccess) return hip_fail(e, "copy");
-  if ((e = hipMemcpyAsync(&ev[1], eps_vir + pl.n_v - 1, 8, hipMemcpyDeviceToHost, s)) != hipSuccess)
-    return hip_fail(e, "copy");
-  if ((e = hipStreamSynchronize(s)) != hipSuccess) return hip_fail(e, "sync");
   ProfScope ps(DFPT2_STAGE_SCREEN, s);
-  hipLaunchKernelGGL(colnorm2_kernel, dim3((pl.n_aux + 255) / 256, pl.n_core), dim3(256), 0, s, B, pl.n_v, pl.n_aux,
+  hipLaunchKernelGGL(colnorm2_kernel, dim3((pl.n_aux + 63) / 64, pl.n_core), dim3(1024), 0, s, B, pl.n_v, pl.n_aux,
                      q2);
-  hipLaunchKernelGGL(wdiag_kernel, dim3(pl.n_core), dim3(64), 0, s, q2, pl.n_aux, wd);
   const double x_star = regularizer_peak() / std::sqrt(opts->s);
-  hipLaunchKernelGGL(pair_features_kernel, dim3((pl.n_up + 3) / 4), dim3(256), 0, s, q2, wd, eps_hole, ev[0], ev[1],
+  hipLaunchKernelGGL(pair_features_kernel, dim3((pl.n_up + 3) / 4), dim3(256), 0, s, q2, eps_hole, eps_vir, pl.n_v,
                      pl.n_core, pl.n_aux, opts->s, x_star, feats, log_scale, pl.n_up);
-  if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "features");
-  return DFPT2_OK;
+  const hipError_t e = hipGetLastError();
+  return e == hipSuccess ? DFPT2_OK : hip_fail(e, "features");
 }
 
 int pairscreen_mlp_forward(const float* W, const float* feats, int64_t n, float* pred, float* act_cache,
