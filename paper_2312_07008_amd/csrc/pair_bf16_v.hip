@@ -123,8 +123,8 @@ __global__ __launch_bounds__(128 * WC, 4 / WC) void pair_v_bf16_kernel(PairSlice
   static_assert(NBUF >= 2 && NBUF <= 4, "ring of 2 to 4 buffers");
   constexpr int TJ = 32 * WC;                     // V tile columns
   constexpr int KB_A = TV / 8, KB_B = TJ / 8;     // kilobytes of the two panels per chunk
-  constexpr int KB_W = (KB_A + KB_B) / (2 * WC);  // kilobytes per wave per chunk
-  static_assert(KB_W * 2 * WC == KB_A + KB_B, "whole kilobytes per wave");
+  constexpr int KB_F = (KB_A + KB_B) / (2 * WC);  // kilobytes per wave per chunk
+  static_assert(KB_F * 2 * WC == KB_A + KB_B && WC == 4, "whole kilobytes per wave; the edge forms deal 8 waves");
   // distinct arrays per ring slot and panel: the compiler's alias scopes then
   // tell the slots apart, so a read of one slot does not wait for the loads into
   // another; the panel-A slots (and the panel-B slots) lie within the 64 KB reach
@@ -132,13 +132,13 @@ __global__ __launch_bounds__(128 * WC, 4 / WC) void pair_v_bf16_kernel(PairSlice
   __shared__ u4 la0[KB_A * 64], la1[KB_A * 64], la2[NBUF > 2 ? KB_A * 64 : 1], la3[NBUF > 3 ? KB_A * 64 : 1];
   __shared__ u4 lb0[KB_B * 64], lb1[KB_B * 64], lb2[NBUF > 2 ? KB_B * 64 : 1], lb3[NBUF > 3 ? KB_B * 64 : 1];
   // ring slot K as a compile-time index (no pointer to a slot is ever stored)
-  auto slot_a = [&](auto K) -> u4* {
+  auto slot_a = [&](auto K) __attribute__((always_inline)) -> u4* {
     if constexpr (K() == 0) return la0;
     else if constexpr (K() == 1) return la1;
     else if constexpr (K() == 2) return la2;
     else return la3;
   };
-  auto slot_b = [&](auto K) -> u4* {
+  auto slot_b = [&](auto K) __attribute__((always_inline)) -> u4* {
     if constexpr (K() == 0) return lb0;
     else if constexpr (K() == 1) return lb1;
     else if constexpr (K() == 2) return lb2;
@@ -158,182 +158,194 @@ __global__ __launch_bounds__(128 * WC, 4 / WC) void pair_v_bf16_kernel(PairSlice
   // the diagonal are never read (the whole workgroup leaves before any barrier)
   if (pr.x == pr.y && I * TV >= (J + 1) * TJ) return;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int wr = w / WC, wc = w - (w / WC) * WC;
-
-  // kilobyte kb < KB_A of a chunk is rows 8 kb .. + 7 of panel A (B_i rows of tile I),
-  // kilobyte KB_A + kb rows 8 kb .. + 7 of panel B (B_j rows of tile J); wave w moves
-  // kilobytes KB_W w .. + KB_W - 1; lane l fills physical slot l % 8 of row l / 8
   const int q_w = __builtin_amdgcn_readfirstlane(w);
+  const int n_v = a.n_v;
   const int row_bytes = a.n_aux_pad * NS * 2;
   const char* panelA = static_cast<const char*>(a.Bs) + ((size_t)pr.x * a.n_v_pad + (size_t)I * TV) * row_bytes;
   const char* panelB = static_cast<const char*>(a.Bs) + ((size_t)pr.y * a.n_v_pad + (size_t)J * TJ) * row_bytes;
   const int l3 = lane >> 3, l7 = lane & 7;
-  auto src_off = [&](int kb) -> uint32_t {  // kb within its panel
+  auto src_off = [&](int kb) __attribute__((always_inline)) -> uint32_t {  // kb within its panel
     const int row = 8 * kb + l3;
     const int sl = l7 ^ swz_v(row);
     const int ts = sl >> 1, h = sl & 1;
     return (uint32_t)(row * row_bytes + (ts < NS ? ts * 32 + h * 16 : 0));
   };
   const int nchunk = a.n_aux_pad / KC;
-  auto load_chunk = [&](int chunk, auto K) {  // chunk < nchunk; into slot K
-    const size_t coff = (size_t)chunk * (KC * NS * 2);
-#pragma unroll
-    for (int m = 0; m < KB_W; ++m) {
-      const int kb = KB_W * q_w + m;  // wave-uniform
-      if (kb < KB_A)
-        __builtin_amdgcn_global_load_lds((gbl_void*)(panelA + coff + src_off(kb)), (lds_void*)(slot_a(K) + kb * 64), 16,
-                                         0, 0);
-      else
-        __builtin_amdgcn_global_load_lds((gbl_void*)(panelB + coff + src_off(kb - KB_A)),
-                                         (lds_void*)(slot_b(K) + (kb - KB_A) * 64), 16, 0, 0);
-    }
-  };
-
-  f16v acc[2][3];
-  double dV[2][16];
-#pragma unroll
-  for (int b = 0; b < 2; ++b) {
-#pragma unroll
-    for (int l = 0; l < 3; ++l)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[b][l][r] = 0.f;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) dV[b][r] = 0.0;
-  }
-
   const int r32 = lane & 31, hq = lane >> 5;
-  // per-lane u4 index of every fragment within a slot (row, swizzled logical slot);
-  // passed through an empty asm in every step, so that the compiler forms each
-  // slot's addresses at the read instead of holding NBUF x 3 NS of them in registers
-  int offB[NS], offA[2][NS];
-  {
-    const int rowB = wc * 32 + r32, fB = swz_v(rowB);
-#pragma unroll
-    for (int s = 0; s < NS; ++s) offB[s] = rowB * SLOTS + ((2 * s + hq) ^ fB);
-#pragma unroll
-    for (int b = 0; b < 2; ++b) {
-      const int rowA = wr * 64 + b * 32 + r32, fA = swz_v(rowA);
-#pragma unroll
-      for (int s = 0; s < NS; ++s) offA[b][s] = rowA * SLOTS + ((2 * s + hq) ^ fA);
-    }
-  }
-
-  auto compute = [&](auto K, int c) {  // chunk c from slot K
-#pragma unroll
-    for (int s = 0; s < NS; ++s) {
-      asm volatile("" : "+v"(offB[s]));
-      asm volatile("" : "+v"(offA[0][s]));
-      asm volatile("" : "+v"(offA[1][s]));
-    }
-    bf8v fb[NS];
-#pragma unroll
-    for (int s = 0; s < NS; ++s) fb[s] = __builtin_bit_cast(bf8v, slot_b(K)[offB[s]]);
-#pragma unroll
-    for (int b = 0; b < 2; ++b) {
-      bf8v fa[NS];
-#pragma unroll
-      for (int s = 0; s < NS; ++s) fa[s] = __builtin_bit_cast(bf8v, slot_a(K)[offA[b][s]]);
-#pragma unroll
-      for (int s = 0; s < NS; ++s)
-#pragma unroll
-        for (int u = 0; u + s < NS; ++u) {
-          const int lv = (s + u) < 2 ? (s + u) : 2;
-          acc[b][lv] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[s], fb[u], acc[b][lv], 0, 0, 0);
-        }
-    }
-    if ((c + 1) % FLUSH_CHUNKS == 0 || c + 1 == nchunk) {
-#pragma unroll
-      for (int b = 0; b < 2; ++b)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          dV[b][r] += (double)acc[b][0][r] + (double)acc[b][1][r];
-          acc[b][0][r] = 0.f;
-          acc[b][1][r] = 0.f;
-        }
-    }
-  };
-  // the workgroup barrier without the memory fence of __syncthreads (whose
-  // release waits for every outstanding load, vmcnt(0)); the empty asm keeps the
-  // compiler from moving memory accesses across it
-  auto barrier = [] {
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-  };
-  // step c: the loads of chunk c + NBUF - 1 go into the slot chunk c - 1 was read
-  // from (every wave finished those reads before the last barrier), the products
-  // of chunk c follow, then each wave waits for its own loads of chunk c + 1 --
-  // the KB_W (NBUF - 2) loads issued after them may stay in flight -- and the
-  // barrier makes every wave's part of chunk c + 1 visible.  The steady-state loop
-  // has no branch around a load or a wait (a merge of paths with different
-  // outstanding loads makes the compiler wait for all of them); the last
-  // 2 NBUF - 2 or fewer steps run in a tail that checks each load and waits for
-  // everything.
-  auto step = [&](int c, auto cur, auto nxt) {
-    load_chunk(c + NBUF - 1, nxt);
-    compute(cur, c);
-    __builtin_amdgcn_s_waitcnt(vm_wait_imm(KB_W * (NBUF - 2)));
-    barrier();
-  };
-  auto tail_step = [&](int c, auto cur, auto nxt) {
-    if (c >= nchunk) return;  // uniform
-    if (c + NBUF - 1 < nchunk) load_chunk(c + NBUF - 1, nxt);
-    compute(cur, c);
-    __builtin_amdgcn_s_waitcnt(vm_wait_imm(0));
-    barrier();
-  };
-  using S0 = std::integral_constant<int, 0>;
-  using S1 = std::integral_constant<int, 1>;
-  using S2 = std::integral_constant<int, 2>;
-  using S3 = std::integral_constant<int, 3>;
-  auto ring = [&](int c, auto&& f) {
-    if constexpr (NBUF == 2) {
-      f(c, S0{}, S1{});
-      f(c + 1, S1{}, S0{});
-    } else if constexpr (NBUF == 3) {
-      f(c, S0{}, S2{});
-      f(c + 1, S1{}, S0{});
-      f(c + 2, S2{}, S1{});
-    } else {
-      f(c, S0{}, S3{});
-      f(c + 1, S1{}, S0{});
-      f(c + 2, S2{}, S1{});
-      f(c + 3, S3{}, S2{});
-    }
-  };
-
-  // chunks 0 .. NBUF - 2 before the first step (chunk k lives in slot k % NBUF)
-  if (nchunk >= 2 * NBUF - 1) {
-    load_chunk(0, S0{});
-    if constexpr (NBUF > 2) load_chunk(1, S1{});
-    if constexpr (NBUF > 3) load_chunk(2, S2{});
-    __builtin_amdgcn_s_waitcnt(vm_wait_imm(KB_W * (NBUF - 2)));  // chunk 0 has landed
-  } else {
-    if (nchunk > 0) load_chunk(0, S0{});
-    if (NBUF > 2 && nchunk > 1) load_chunk(1, S1{});
-    if (NBUF > 3 && nchunk > 2) load_chunk(2, S2{});
-    __builtin_amdgcn_s_waitcnt(vm_wait_imm(0));
-  }
-  barrier();
-  int c = 0;
-  // steady state: every step of a revolution loads a chunk that exists
-  for (; c + 2 * NBUF - 2 < nchunk; c += NBUF) ring(c, step);
-  ring(c, tail_step);
-  if (c + NBUF < nchunk) ring(c + NBUF, tail_step);
-
-  // V^{ij}[ga][gb] in FP64 (register r of lane l: row 8(r/4) + 4(l/32) + r%4, column l%32)
-  const int n_v = a.n_v;
-  double* Vp = a.T + (size_t)p * n_v * n_v;
-  const int gb = J * TJ + wc * 32 + r32;
-  if (gb < n_v) {
-#pragma unroll
-    for (int b = 0; b < 2; ++b)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int ga = I * TV + wr * 64 + b * 32 + 8 * (r >> 2) + 4 * hq + (r & 3);
-        if (ga < n_v) Vp[(size_t)ga * n_v + gb] = dV[b][r] + (double)acc[b][2][r];
+  // The wave's NB 32 x 32 blocks from (row0, col0), KB_W kilobytes of loads per chunk:
+  // kilobyte kb < kb_a of a chunk is rows 8 kb .. + 7 of panel A (B_i rows of tile I),
+  // kilobyte kb_a + kb rows 8 kb .. + 7 of panel B (B_j rows of tile J); wave w moves
+  // kilobytes KB_W w .. + KB_W - 1; lane l fills physical slot l % 8 of row l / 8
+  auto run = [&](auto NB, auto KB_W, const int kb_a, const int row0, const int col0) __attribute__((always_inline)) {
+    auto load_chunk = [&](int chunk, auto K) __attribute__((always_inline)) {  // chunk < nchunk; into slot K
+      const size_t coff = (size_t)chunk * (KC * NS * 2);
+  #pragma unroll
+      for (int m = 0; m < KB_W(); ++m) {
+        const int kb = KB_W() * q_w + m;  // wave-uniform
+        if (kb < kb_a)
+          __builtin_amdgcn_global_load_lds((gbl_void*)(panelA + coff + src_off(kb)), (lds_void*)(slot_a(K) + kb * 64), 16,
+                                           0, 0);
+        else
+          __builtin_amdgcn_global_load_lds((gbl_void*)(panelB + coff + src_off(kb - kb_a)),
+                                           (lds_void*)(slot_b(K) + (kb - kb_a) * 64), 16, 0, 0);
       }
-  }
+    };
+
+    f16v acc[NB()][3];
+    double dV[NB()][16];
+  #pragma unroll
+    for (int b = 0; b < NB(); ++b) {
+  #pragma unroll
+      for (int l = 0; l < 3; ++l)
+  #pragma unroll
+        for (int r = 0; r < 16; ++r) acc[b][l][r] = 0.f;
+  #pragma unroll
+      for (int r = 0; r < 16; ++r) dV[b][r] = 0.0;
+    }
+
+    // per-lane u4 index of every fragment within a slot (row, swizzled logical slot);
+    // passed through an empty asm in every step, so that the compiler forms each
+    // slot's addresses at the read instead of holding NBUF x 3 NS of them in registers
+    int offB[NS], offA[NB()][NS];
+    {
+      const int rowB = col0 + r32, fB = swz_v(rowB);
+  #pragma unroll
+      for (int s = 0; s < NS; ++s) offB[s] = rowB * SLOTS + ((2 * s + hq) ^ fB);
+  #pragma unroll
+      for (int b = 0; b < NB(); ++b) {
+        const int rowA = row0 + b * 32 + r32, fA = swz_v(rowA);
+  #pragma unroll
+        for (int s = 0; s < NS; ++s) offA[b][s] = rowA * SLOTS + ((2 * s + hq) ^ fA);
+      }
+    }
+
+    auto compute = [&](auto K, int c) __attribute__((always_inline)) {  // chunk c from slot K
+  #pragma unroll
+      for (int s = 0; s < NS; ++s) {
+        asm volatile("" : "+v"(offB[s]));
+        asm volatile("" : "+v"(offA[0][s]));
+        if constexpr (NB() > 1) asm volatile("" : "+v"(offA[NB() - 1][s]));
+      }
+      bf8v fb[NS];
+  #pragma unroll
+      for (int s = 0; s < NS; ++s) fb[s] = __builtin_bit_cast(bf8v, slot_b(K)[offB[s]]);
+  #pragma unroll
+      for (int b = 0; b < NB(); ++b) {
+        bf8v fa[NS];
+  #pragma unroll
+        for (int s = 0; s < NS; ++s) fa[s] = __builtin_bit_cast(bf8v, slot_a(K)[offA[b][s]]);
+  #pragma unroll
+        for (int s = 0; s < NS; ++s)
+  #pragma unroll
+          for (int u = 0; u + s < NS; ++u) {
+            const int lv = (s + u) < 2 ? (s + u) : 2;
+            acc[b][lv] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[s], fb[u], acc[b][lv], 0, 0, 0);
+          }
+      }
+      if ((c + 1) % FLUSH_CHUNKS == 0 || c + 1 == nchunk) {
+  #pragma unroll
+        for (int b = 0; b < NB(); ++b)
+  #pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            dV[b][r] += (double)acc[b][0][r] + (double)acc[b][1][r];
+            acc[b][0][r] = 0.f;
+            acc[b][1][r] = 0.f;
+          }
+      }
+    };
+    // the workgroup barrier without the memory fence of __syncthreads (whose
+    // release waits for every outstanding load, vmcnt(0)); the empty asm keeps the
+    // compiler from moving memory accesses across it
+    auto barrier = []() __attribute__((always_inline)) {
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+    };
+    // step c: the loads of chunk c + NBUF - 1 go into the slot chunk c - 1 was read
+    // from (every wave finished those reads before the last barrier), the products
+    // of chunk c follow, then each wave waits for its own loads of chunk c + 1 --
+    // the KB_W (NBUF - 2) loads issued after them may stay in flight -- and the
+    // barrier makes every wave's part of chunk c + 1 visible.  The steady-state loop
+    // has no branch around a load or a wait (a merge of paths with different
+    // outstanding loads makes the compiler wait for all of them); the last
+    // 2 NBUF - 2 or fewer steps run in a tail that checks each load and waits for
+    // everything.
+    auto step = [&](int c, auto cur, auto nxt) __attribute__((always_inline)) {
+      load_chunk(c + NBUF - 1, nxt);
+      compute(cur, c);
+      __builtin_amdgcn_s_waitcnt(vm_wait_imm(KB_W() * (NBUF - 2)));
+      barrier();
+    };
+    auto tail_step = [&](int c, auto cur, auto nxt) __attribute__((always_inline)) {
+      if (c >= nchunk) return;  // uniform
+      if (c + NBUF - 1 < nchunk) load_chunk(c + NBUF - 1, nxt);
+      compute(cur, c);
+      __builtin_amdgcn_s_waitcnt(vm_wait_imm(0));
+      barrier();
+    };
+    using S0 = std::integral_constant<int, 0>;
+    using S1 = std::integral_constant<int, 1>;
+    using S2 = std::integral_constant<int, 2>;
+    using S3 = std::integral_constant<int, 3>;
+    auto ring = [&](int c, auto&& f) __attribute__((always_inline)) {
+      if constexpr (NBUF == 2) {
+        f(c, S0{}, S1{});
+        f(c + 1, S1{}, S0{});
+      } else if constexpr (NBUF == 3) {
+        f(c, S0{}, S2{});
+        f(c + 1, S1{}, S0{});
+        f(c + 2, S2{}, S1{});
+      } else {
+        f(c, S0{}, S3{});
+        f(c + 1, S1{}, S0{});
+        f(c + 2, S2{}, S1{});
+        f(c + 3, S3{}, S2{});
+      }
+    };
+
+    // chunks 0 .. NBUF - 2 before the first step (chunk k lives in slot k % NBUF)
+    if (nchunk >= 2 * NBUF - 1) {
+      load_chunk(0, S0{});
+      if constexpr (NBUF > 2) load_chunk(1, S1{});
+      if constexpr (NBUF > 3) load_chunk(2, S2{});
+      __builtin_amdgcn_s_waitcnt(vm_wait_imm(KB_W() * (NBUF - 2)));  // chunk 0 has landed
+    } else {
+      if (nchunk > 0) load_chunk(0, S0{});
+      if (NBUF > 2 && nchunk > 1) load_chunk(1, S1{});
+      if (NBUF > 3 && nchunk > 2) load_chunk(2, S2{});
+      __builtin_amdgcn_s_waitcnt(vm_wait_imm(0));
+    }
+    barrier();
+    int c = 0;
+    // steady state: every step of a revolution loads a chunk that exists
+    for (; c + 2 * NBUF - 2 < nchunk; c += NBUF) ring(c, step);
+    ring(c, tail_step);
+    if (c + NBUF < nchunk) ring(c + NBUF, tail_step);
+
+    // V^{ij}[ga][gb] in FP64 (register r of lane l: row 8(r/4) + 4(l/32) + r%4, column l%32)
+    double* Vp = a.T + (size_t)p * n_v * n_v;
+    const int gb = J * TJ + col0 + r32;
+    if (gb < n_v) {
+  #pragma unroll
+      for (int b = 0; b < NB(); ++b)
+  #pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int ga = I * TV + row0 + b * 32 + 8 * (r >> 2) + 4 * hq + (r & 3);
+          if (ga < n_v) Vp[(size_t)ga * n_v + gb] = dV[b][r] + (double)acc[b][2][r];
+        }
+    }
+  };
+  using N1 = std::integral_constant<int, 1>;
+  using N2 = std::integral_constant<int, 2>;
+  // A tile whose last 64 columns (or rows) lie beyond n_v: half the blocks, dealt evenly to
+  // the waves, and three quarters of the loads.  ms per batch: 31 holes, 539 virtuals (27 of
+  // the last 128 columns) 4.23, 4.68 with whole tiles; 512 pairs of 1200 virtuals (48 of 128)
+  // 55.1 and 55.8: there the chip is at its power limit, and products of zeros cost little.
+  using KB = std::integral_constant<int, KB_F>;
+  using KB_E = std::integral_constant<int, (KB_A + KB_B / 2) / (2 * WC)>;
+  if (n_v - J * TJ <= TJ / 2) run(N1{}, KB_E{}, KB_A, (w >> 1) * 32, (w & 1) * 32);
+  else if (n_v - I * TV <= TV / 2) run(N1{}, KB_E{}, KB_A / 2, (w / WC) * 32, (w % WC) * 32);
+  else run(N2{}, KB{}, KB_A, (w / WC) * 64, (w % WC) * 32);
 }
 
 // Epilogue pass over 64 x 64 tile pairs (I <= J) of the V written above; without

@@ -59,8 +59,7 @@ __global__ __launch_bounds__(512, 1) void pair_v_i8_kernel(PairSlicedArgs a, int
   constexpr int PANEL_U4 = TV * SLOTS;  // u4 per 128-row panel
   constexpr int ROWB = 32 * NS;         // bytes of one row of one chunk
   constexpr int LOADS = PANEL_U4 / 64;  // 1 KB direct loads per panel and chunk
-  constexpr int LPW = 2 * LOADS / 8;    // loads per wave per chunk
-  static_assert(LPW * 8 == 2 * LOADS, "whole loads per wave");
+  static_assert(2 * LOADS % 8 == 0, "whole loads per wave");
   // distinct arrays per ring slot and panel, so that the compiler's alias scopes
   // tell the slots apart (a read of one slot does not wait for loads into another)
   __shared__ u4 la0[PANEL_U4], la1[PANEL_U4], la2[PANEL_U4];
@@ -86,7 +85,8 @@ __global__ __launch_bounds__(512, 1) void pair_v_i8_kernel(PairSlicedArgs a, int
   // the diagonal are never read (the whole workgroup leaves before any barrier)
   if (pr.x == pr.y && I > J) return;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int wr = w >> 2, wc = w & 3;
+  const int r32 = lane & 31, hq = lane >> 5;
+  const int n_v = a.n_v;
 
   const int q_w = __builtin_amdgcn_readfirstlane(w);
   const size_t chunk_stride = (size_t)a.n_v_pad * ROWB;
@@ -100,137 +100,151 @@ __global__ __launch_bounds__(512, 1) void pair_v_i8_kernel(PairSlicedArgs a, int
     return (uint32_t)(rr * ROWB + 16 * i8l::logical_slot<NS>(rr, ps));
   };
   const int nchunk = a.n_aux_pad / KC;
-  auto load_chunk = [&](int chunk, auto K) __attribute__((always_inline)) {  // chunk < nchunk; into slot K
-    const size_t coff = (size_t)chunk * chunk_stride;
-#pragma unroll
-    for (int m = 0; m < LPW; ++m) {
-      const int g = LPW * q_w + m;  // wave-uniform
-      if (g < LOADS)
-        __builtin_amdgcn_global_load_lds((gbl_void*)(panelA + coff + src_off(g)), (lds_void*)(slot_a(K) + 64 * g), 16,
-                                         0, 0);
-      else
-        __builtin_amdgcn_global_load_lds((gbl_void*)(panelB + coff + src_off(g - LOADS)),
-                                         (lds_void*)(slot_b(K) + 64 * (g - LOADS)), 16, 0, 0);
-    }
-  };
-
-  v16i acc[2][NS];
-#pragma unroll
-  for (int b = 0; b < 2; ++b)
-#pragma unroll
-    for (int l = 0; l < NS; ++l)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) acc[b][l][e] = 0;
-
-  const int r32 = lane & 31, hq = lane >> 5;
-  // per-lane u4 index of every fragment within a slot; passed through an empty asm
-  // in every step, so that the compiler forms each slot's addresses at the read
-  int offB[NS], offA[2][NS];
-  {
-    const int rowB = wc * 32 + r32;
-#pragma unroll
-    for (int s = 0; s < NS; ++s) offB[s] = rowB * SLOTS + i8l::phys_slot<NS>(rowB, 2 * s + hq);
-#pragma unroll
-    for (int b = 0; b < 2; ++b) {
-      const int rowA = wr * 64 + b * 32 + r32;
-#pragma unroll
-      for (int s = 0; s < NS; ++s) offA[b][s] = rowA * SLOTS + i8l::phys_slot<NS>(rowA, 2 * s + hq);
-    }
-  }
-  auto compute = [&](auto K) __attribute__((always_inline)) {
-#pragma unroll
-    for (int s = 0; s < NS; ++s) {
-      asm volatile("" : "+v"(offB[s]));
-      asm volatile("" : "+v"(offA[0][s]));
-      asm volatile("" : "+v"(offA[1][s]));
-    }
-    v4i fb[NS];
-#pragma unroll
-    for (int s = 0; s < NS; ++s) fb[s] = __builtin_bit_cast(v4i, slot_b(K)[offB[s]]);
-#pragma unroll
-    for (int b = 0; b < 2; ++b) {
-      v4i fa[NS];
-#pragma unroll
-      for (int s = 0; s < NS; ++s) fa[s] = __builtin_bit_cast(v4i, slot_a(K)[offA[b][s]]);
-#pragma unroll
-      for (int s = 0; s < NS; ++s)
-#pragma unroll
-        for (int u = 0; u + s < NS; ++u)
-          acc[b][s + u] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[s], fb[u], acc[b][s + u], 0, 0, 0);
-    }
-  };
-  // the workgroup barrier without the memory fence of __syncthreads; the empty
-  // asm keeps the compiler from moving memory accesses across it
-  auto barrier = []() __attribute__((always_inline)) {
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-  };
-  // step c: the loads of chunk c + 2 go into the slot chunk c - 1 was read from,
-  // the products of chunk c follow, then each wave waits for its own loads of
-  // chunk c + 1 (those of chunk c + 2 stay in flight) and the barrier makes every
-  // wave's part of chunk c + 1 visible; no branch around a load or a wait in the
-  // steady state, the last steps run as tail steps that wait for everything
-  auto step = [&](int c, auto cur, auto nxt) __attribute__((always_inline)) {
-    load_chunk(c + NBUF - 1, nxt);
-    compute(cur);
-    __builtin_amdgcn_s_waitcnt(vm_wait_imm(LPW * (NBUF - 2)));
-    barrier();
-  };
-  auto tail_step = [&](int c, auto cur, auto nxt) __attribute__((always_inline)) {
-    if (c >= nchunk) return;  // uniform
-    if (c + NBUF - 1 < nchunk) load_chunk(c + NBUF - 1, nxt);
-    compute(cur);
-    __builtin_amdgcn_s_waitcnt(vm_wait_imm(0));
-    barrier();
-  };
-  using S0 = std::integral_constant<int, 0>;
-  using S1 = std::integral_constant<int, 1>;
-  using S2 = std::integral_constant<int, 2>;
-  auto ring = [&](int c, auto&& f) __attribute__((always_inline)) {
-    f(c, S0{}, S2{});
-    f(c + 1, S1{}, S0{});
-    f(c + 2, S2{}, S1{});
-  };
-
-  if (nchunk >= 2 * NBUF - 1) {
-    load_chunk(0, S0{});
-    load_chunk(1, S1{});
-    __builtin_amdgcn_s_waitcnt(vm_wait_imm(LPW * (NBUF - 2)));  // chunk 0 has landed
-  } else {
-    if (nchunk > 0) load_chunk(0, S0{});
-    if (nchunk > 1) load_chunk(1, S1{});
-    __builtin_amdgcn_s_waitcnt(vm_wait_imm(0));
-  }
-  barrier();
-  int c = 0;
-  // steady state: every step of a revolution loads a chunk that exists
-  for (; c + 2 * NBUF - 2 < nchunk; c += NBUF) ring(c, step);
-  ring(c, tail_step);
-  if (c + NBUF < nchunk) ring(c + NBUF, tail_step);
-
-  // levels -> FP64 (Horner in 2^-8, exact up to the final rounding), times the row
-  // scales; register e of lane l of a 32 x 32 block is row 8(e/4) + 4(l/32) + e%4,
-  // column l%32
-  const int n_v = a.n_v;
-  double* Vp = a.T + (size_t)p * n_v * n_v;
-  const int* ei = a.rexp + (size_t)pr.x * a.n_v_pad;
-  const int* ej = a.rexp + (size_t)pr.y * a.n_v_pad;
-  const int gb = J * TV + wc * 32 + r32;
-  if (gb < n_v) {
-    const int eb = ej[gb];
-#pragma unroll
-    for (int b = 0; b < 2; ++b)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const int ga = I * TV + wr * 64 + b * 32 + 8 * (e >> 2) + 4 * hq + (e & 3);
-        if (ga >= n_v) continue;
-        double v = (double)acc[b][NS - 1][e];
-#pragma unroll
-        for (int l = NS - 2; l >= 0; --l) v = v * 0.00390625 + (double)acc[b][l][e];
-        Vp[(size_t)ga * n_v + gb] = ldexp(v, ei[ga] + eb);
+  // The wave's NB 32 x 32 blocks from (row0, col0); LPW direct loads per chunk and wave of
+  // the loads_a + loads_b kilobytes of the two panels
+  auto run = [&](auto NB, auto LPW, const int loads_a, const int loads_b, const int row0, const int col0)
+      __attribute__((always_inline)) {
+    auto load_chunk = [&](int chunk, auto K) __attribute__((always_inline)) {  // chunk < nchunk; into slot K
+      const size_t coff = (size_t)chunk * chunk_stride;
+  #pragma unroll
+      for (int m = 0; m < LPW(); ++m) {
+        // wave-uniform; beyond the chunk's last load the same bytes go to the same place again
+        const int g = min(LPW() * q_w + m, loads_a + loads_b - 1);
+        if (g < loads_a)
+          __builtin_amdgcn_global_load_lds((gbl_void*)(panelA + coff + src_off(g)), (lds_void*)(slot_a(K) + 64 * g), 16,
+                                           0, 0);
+        else
+          __builtin_amdgcn_global_load_lds((gbl_void*)(panelB + coff + src_off(g - loads_a)),
+                                           (lds_void*)(slot_b(K) + 64 * (g - loads_a)), 16, 0, 0);
       }
-  }
+    };
+
+    v16i acc[NB()][NS];
+  #pragma unroll
+    for (int b = 0; b < NB(); ++b)
+  #pragma unroll
+      for (int l = 0; l < NS; ++l)
+  #pragma unroll
+        for (int e = 0; e < 16; ++e) acc[b][l][e] = 0;
+
+    // per-lane u4 index of every fragment within a slot; passed through an empty asm
+    // in every step, so that the compiler forms each slot's addresses at the read
+    int offB[NS], offA[NB()][NS];
+    {
+      const int rowB = col0 + r32;
+  #pragma unroll
+      for (int s = 0; s < NS; ++s) offB[s] = rowB * SLOTS + i8l::phys_slot<NS>(rowB, 2 * s + hq);
+  #pragma unroll
+      for (int b = 0; b < NB(); ++b) {
+        const int rowA = row0 + b * 32 + r32;
+  #pragma unroll
+        for (int s = 0; s < NS; ++s) offA[b][s] = rowA * SLOTS + i8l::phys_slot<NS>(rowA, 2 * s + hq);
+      }
+    }
+    auto compute = [&](auto K) __attribute__((always_inline)) {
+  #pragma unroll
+      for (int s = 0; s < NS; ++s) {
+        asm volatile("" : "+v"(offB[s]));
+        asm volatile("" : "+v"(offA[0][s]));
+        if constexpr (NB() > 1) asm volatile("" : "+v"(offA[NB() - 1][s]));
+      }
+      v4i fb[NS];
+  #pragma unroll
+      for (int s = 0; s < NS; ++s) fb[s] = __builtin_bit_cast(v4i, slot_b(K)[offB[s]]);
+  #pragma unroll
+      for (int b = 0; b < NB(); ++b) {
+        v4i fa[NS];
+  #pragma unroll
+        for (int s = 0; s < NS; ++s) fa[s] = __builtin_bit_cast(v4i, slot_a(K)[offA[b][s]]);
+  #pragma unroll
+        for (int s = 0; s < NS; ++s)
+  #pragma unroll
+          for (int u = 0; u + s < NS; ++u)
+            acc[b][s + u] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[s], fb[u], acc[b][s + u], 0, 0, 0);
+      }
+    };
+    // the workgroup barrier without the memory fence of __syncthreads; the empty
+    // asm keeps the compiler from moving memory accesses across it
+    auto barrier = []() __attribute__((always_inline)) {
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+    };
+    // step c: the loads of chunk c + 2 go into the slot chunk c - 1 was read from,
+    // the products of chunk c follow, then each wave waits for its own loads of
+    // chunk c + 1 (those of chunk c + 2 stay in flight) and the barrier makes every
+    // wave's part of chunk c + 1 visible; no branch around a load or a wait in the
+    // steady state, the last steps run as tail steps that wait for everything
+    auto step = [&](int c, auto cur, auto nxt) __attribute__((always_inline)) {
+      load_chunk(c + NBUF - 1, nxt);
+      compute(cur);
+      __builtin_amdgcn_s_waitcnt(vm_wait_imm(LPW() * (NBUF - 2)));
+      barrier();
+    };
+    auto tail_step = [&](int c, auto cur, auto nxt) __attribute__((always_inline)) {
+      if (c >= nchunk) return;  // uniform
+      if (c + NBUF - 1 < nchunk) load_chunk(c + NBUF - 1, nxt);
+      compute(cur);
+      __builtin_amdgcn_s_waitcnt(vm_wait_imm(0));
+      barrier();
+    };
+    using S0 = std::integral_constant<int, 0>;
+    using S1 = std::integral_constant<int, 1>;
+    using S2 = std::integral_constant<int, 2>;
+    auto ring = [&](int c, auto&& f) __attribute__((always_inline)) {
+      f(c, S0{}, S2{});
+      f(c + 1, S1{}, S0{});
+      f(c + 2, S2{}, S1{});
+    };
+
+    if (nchunk >= 2 * NBUF - 1) {
+      load_chunk(0, S0{});
+      load_chunk(1, S1{});
+      __builtin_amdgcn_s_waitcnt(vm_wait_imm(LPW() * (NBUF - 2)));  // chunk 0 has landed
+    } else {
+      if (nchunk > 0) load_chunk(0, S0{});
+      if (nchunk > 1) load_chunk(1, S1{});
+      __builtin_amdgcn_s_waitcnt(vm_wait_imm(0));
+    }
+    barrier();
+    int c = 0;
+    // steady state: every step of a revolution loads a chunk that exists
+    for (; c + 2 * NBUF - 2 < nchunk; c += NBUF) ring(c, step);
+    ring(c, tail_step);
+    if (c + NBUF < nchunk) ring(c + NBUF, tail_step);
+
+    // levels -> FP64 (Horner in 2^-8, exact up to the final rounding), times the row
+    // scales; register e of lane l of a 32 x 32 block is row 8(e/4) + 4(l/32) + e%4,
+    // column l%32
+    double* Vp = a.T + (size_t)p * n_v * n_v;
+    const int* ei = a.rexp + (size_t)pr.x * a.n_v_pad;
+    const int* ej = a.rexp + (size_t)pr.y * a.n_v_pad;
+    const int gb = J * TV + col0 + r32;
+    if (gb < n_v) {
+      const int eb = ej[gb];
+  #pragma unroll
+      for (int b = 0; b < NB(); ++b)
+  #pragma unroll
+        for (int e = 0; e < 16; ++e) {
+          const int ga = I * TV + row0 + b * 32 + 8 * (e >> 2) + 4 * hq + (e & 3);
+          if (ga >= n_v) continue;
+          double v = (double)acc[b][NS - 1][e];
+  #pragma unroll
+          for (int l = NS - 2; l >= 0; --l) v = v * 0.00390625 + (double)acc[b][l][e];
+          Vp[(size_t)ga * n_v + gb] = ldexp(v, ei[ga] + eb);
+        }
+    }
+  };
+  using N1 = std::integral_constant<int, 1>;
+  using N2 = std::integral_constant<int, 2>;
+  // A tile whose last 64 columns (or rows) lie beyond n_v: half the blocks, dealt evenly to
+  // the waves, and three quarters of the loads.  40 holes, 800 virtuals (32 of the last 128
+  // columns), ms per pass: 20.0, 22.6 with whole tiles.
+  using LF = std::integral_constant<int, 2 * LOADS / 8>;
+  using LE = std::integral_constant<int, (3 * LOADS / 2 + 7) / 8>;
+  if (n_v - J * TV <= TV / 2) run(N1{}, LE{}, LOADS, LOADS / 2, (w >> 1) * 32, (w & 1) * 32);
+  else if (n_v - I * TV <= TV / 2) run(N1{}, LE{}, LOADS / 2, LOADS, (w >> 2) * 32, (w & 3) * 32);
+  else run(N2{}, LF{}, LOADS, LOADS, (w >> 2) * 64, (w & 3) * 32);
 }
 
 hipError_t launch_pair_v_i8(const PairSlicedArgs& a, int ns, int n_pairs, hipStream_t st) {
