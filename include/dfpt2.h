@@ -286,14 +286,14 @@ int naf_compress(const dfpt2_opts* opts, const double* B, double eps, double* B_
  * truncated space.
  *   B_vv   [n_vir][n_vir][n_aux] density-fitted virtual-virtual integrals; must be
  *          symmetric in the two virtual indices (B^Q_ac = B^Q_ca), as such
- *          integrals are: the library reads (ac|bd) as (ac|db)
+ *          integrals are
  *   T      [n_amp][n_vir][n_vir]
  *   X      [n_vir][ldx] or NULL: the first n_kept columns are the kept NOs (fno_truncate's
  *          no_vecs with ldx = n_vir); NULL = full space (n_kept = 0 or n_vir, ldx ignored)
  *   R      [n_amp][m][m] out, m = n_kept with X, else n_vir
  * Limits: n_vir <= 2048, n_amp <= 65535.  Workspace (pp_ladder_workspace_size,
  * n_kept = 0 for the full space): one block of (ac|bd) of up to ~16 GB plus the
- * transformed inputs.  Asynchronous on the stream.
+ * transformed inputs and n_amp m^2 doubles.  Asynchronous on the stream.
  * Errors: INVALID_ARG, WORKSPACE, HIP.
  */
 int pp_ladder_workspace_size(int64_t n_vir, int64_t n_aux, int64_t n_amp, int64_t n_kept, size_t* bytes);

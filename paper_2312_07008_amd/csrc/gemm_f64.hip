@@ -43,12 +43,46 @@ struct GemmArgs {
   long long sA, sB, sC;
   double alpha, beta;
   int batch, tm, tn;  // tiles along M and N
+  int per;            // tiles of a product
   int nsplit, kper;   // splits of the contraction, chunks per split
   double* part;       // [nsplit][batch][M][N] partial products, or null (nsplit == 1)
   int upper;          // only the tiles that reach the diagonal or lie above it
-  int pair_n;         // > 0: row (a, c) and column (d, b) of C go to pair_s1 c + pair_s2 d + pair_n a + b
-  long long pair_s1, pair_s2;
+  int mode;           // 0, or a form of the ladder (LadderBlock in host.h):
+                      // kIntegrals: row (a, c), column (b, d) -> C[packed (a, b)][c][d], b <= a only
+                      // kPlus:  column j = (a, b): v/2 to C[row][a][b] and C[row][b][a]
+                      // kMinus: column j = (a, b): v/2 added to C[row][a][b], subtracted from C[row][b][a]
+  LadderBlock lad;    // kIntegrals; else n, and the triangle's index of column 0 in a0
 };
+enum { kIntegrals = 1, kPlus, kMinus };
+
+// pair (a, b), b <= a, of index t of the triangle
+__device__ inline void ladder_pair(int t, int& a, int& b) {
+  a = (int)((sqrt(8.0 * (double)t + 1.0) - 1.0) * 0.5);  // off by at most one
+  if ((long long)a * (a + 1) / 2 > t) --a;
+  if ((long long)(a + 1) * (a + 2) / 2 <= t) ++a;
+  b = (int)(t - (long long)a * (a + 1) / 2);
+}
+
+__device__ inline void ladder_store(double* R, int n, int a, int b, double v, bool plus) {
+  double *ab = R + (size_t)a * n + b, *ba = R + (size_t)b * n + a;
+  if (plus) {
+    *ab = *ba = 0.5 * v;
+  } else if (a != b) {
+    *ab += 0.5 * v;
+    *ba -= 0.5 * v;
+  }
+}
+
+constexpr int BAND = 8;  // tile rows of a band
+
+// tile columns that a band of an integral block reaches: those with a b <= a
+__host__ __device__ inline int band_columns(const GemmArgs& g, int band, int tm_edge, int tn_edge) {
+  if (g.mode != kIntegrals) return g.tn;
+  const int m1 = (band + 1) * BAND * tm_edge, last = (m1 < g.M ? m1 : g.M) - 1;
+  const long long cols = (long long)(g.lad.a0 + last / g.lad.n + 1 - g.lad.b0) * g.lad.n;  // b0 <= a0
+  const long long t = (cols + tn_edge - 1) / tn_edge;
+  return t < g.tn ? (int)t : g.tn;
+}
 
 constexpr int GK = 16;  // contraction chunk
 
@@ -89,14 +123,21 @@ __global__ __launch_bounds__(256, 2) void gemm_f64_kernel(GemmArgs g) {
     const int x = L & 7, k = L >> 3, q = nblk >> 3, rem = nblk & 7;
     L = (x < rem) ? x * (q + 1) + k : rem * (q + 1) + (x - rem) * q + k;
   }
-  const int per = g.tm * g.tn;
+  const int per = g.per;
   const int outer = L / per, t = L - outer * per;
   const int b = outer / g.nsplit, split = outer - b * g.nsplit;
-  constexpr int BAND = 8;
-  const int band = t / (BAND * g.tn), h = min(BAND, g.tm - band * BAND), tr = t - band * BAND * g.tn;
+  int band = 0, tr = t;
+  if (g.mode == kIntegrals)
+    for (int c; tr >= (c = BAND * band_columns(g, band, TM, TN)); ++band) tr -= c;
+  else {
+    band = t / (BAND * g.tn);
+    tr = t - band * BAND * g.tn;
+  }
+  const int h = min(BAND, g.tm - band * BAND);
   const int jt = tr / h, it = band * BAND + (tr - jt * h);
   const int m0 = it * TM, n0 = jt * TN;
   if (g.upper && m0 >= n0 + TN) return;  // workgroup-uniform, before any barrier
+  if (g.mode == kIntegrals && g.lad.b0 + n0 / g.lad.n > g.lad.a0 + (min(m0 + TM, g.M) - 1) / g.lad.n) return;
   const double* A = g.A + b * g.sA;
   const double* Bm = g.B + b * g.sB;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
@@ -223,6 +264,40 @@ __global__ __launch_bounds__(256, 2) void gemm_f64_kernel(GemmArgs g) {
     products(buf);
   }
   // register r of lane l holds row l / 16 + 4 r and column l % 16 of a 16 x 16 block
+  if (g.mode && !g.part) {
+    const LadderBlock q = g.lad;
+    int x[BN], y[BN];  // kIntegrals: b and d of the column; else a and b
+#pragma unroll
+    for (int j = 0; j < BN; ++j) {
+      const int gn = n0 + (wc * BN + j) * 16 + r16;
+      if (g.mode == kIntegrals) {
+        const int bl = gn / q.n;
+        y[j] = gn - bl * q.n;
+        x[j] = gn < g.N ? q.b0 + bl : 0x7fffffff;
+      } else {
+        ladder_pair(q.a0 + min(gn, g.N - 1), x[j], y[j]);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < BM; ++i)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int gm = m0 + (wr * BM + i) * 16 + kq + 4 * r;
+        if (gm >= g.M) continue;
+        const int a = q.a0 + gm / q.n, c = gm % q.n;
+        double* row = g.mode == kIntegrals ? g.C + (q.first(a) * q.n + c) * q.n : g.C + (size_t)gm * q.n * q.n;
+#pragma unroll
+        for (int j = 0; j < BN; ++j) {
+          const double v = acc[i][j][r];
+          if (g.mode == kIntegrals) {
+            if (x[j] <= a) row[(size_t)x[j] * q.n * q.n + y[j]] = v;
+          } else if (n0 + (wc * BN + j) * 16 + r16 < g.N) {
+            ladder_store(row, q.n, x[j], y[j], v, g.mode == kPlus);
+          }
+        }
+      }
+    return;
+  }
 #pragma unroll
   for (int i = 0; i < BM; ++i)
 #pragma unroll
@@ -235,8 +310,6 @@ __global__ __launch_bounds__(256, 2) void gemm_f64_kernel(GemmArgs g) {
         if (gn >= g.N) continue;
         double* dst;
         if (g.part) dst = g.part + (((size_t)split * g.batch + b) * g.M + gm) * g.N + gn;
-        else if (g.pair_n) dst = g.C + (long long)(gm / g.pair_n) * g.pair_n + (gm % g.pair_n) * g.pair_s1 +
-                                 (gn / g.pair_n) * g.pair_s2 + gn % g.pair_n;
         else dst = g.C + b * g.sC + (size_t)gm * g.ldc + gn;
         double v = acc[i][j][r];
         if (!g.part) {
@@ -260,6 +333,12 @@ __global__ __launch_bounds__(256) void gemm_f64_sum(GemmArgs g, int tile) {
     if (g.upper && m / tile > n / tile) continue;
     double v = 0.0;
     for (int k = 0; k < g.nsplit; ++k) v += g.part[((size_t)k * g.batch) * mn + q];
+    if (g.mode) {
+      int x, y;
+      ladder_pair(g.lad.a0 + n, x, y);
+      ladder_store(g.C + (size_t)m * g.lad.n * g.lad.n, g.lad.n, x, y, v, g.mode == kPlus);
+      continue;
+    }
     double* dst = g.C + b * g.sC + (size_t)m * g.ldc + n;
     v *= g.alpha;
     *dst = (g.beta != 0.0) ? v + g.beta * *dst : v;
@@ -277,7 +356,9 @@ struct Config {
 // memory.  Measured shares: 128 x 128 tiles 0.60 and 0.80 (18 TFLOP/s at 100 workgroups,
 // 63 at 4096), 64 x 64 tiles 0.42, 0.61 and 0.78 (34 TFLOP/s at 361 workgroups, 62 at
 // 16384): the larger tile leads only where it fills the units evenly, and 1200^3 goes
-// from 34 to 41 TFLOP/s with its contraction split in two.
+// from 34 to 41 TFLOP/s with its contraction split in two.  What is left after whole rounds
+// runs at the lower shares: A B^T 400 x 8911 x 8911 (980 smaller tiles, three rounds of 256 and
+// one alone on a unit) 43 TFLOP/s whole, 48 split in two.
 Config choose_config(int M, int N, int K, int batch, bool upper, size_t part_doubles) {
   static const struct {
     int b, wgs;
@@ -292,9 +373,11 @@ Config choose_config(int M, int N, int K, int batch, bool upper, size_t part_dou
     const double n = tm * tn * batch * (upper ? 0.5 * (1.0 + 1.0 / tn) : 1.0);
     for (int s = 1; s <= 64; s *= 2) {
       if (s > 1 && ((size_t)s * batch * M * N > part_doubles || nchunk < 8 * s)) break;
-      const double per_unit = std::ceil(n * s / 256.0);
+      const int per_unit = (int)std::min(std::ceil(n * s / 256.0), 1e8), rest = per_unit % t.wgs;
+      // rounds of as many as fit, then the rest at the rate that fewer reach
+      const double eff = (per_unit - rest) / t.rate[t.wgs - 1] + (rest ? rest / t.rate[rest - 1] : 0.0);
       const double flops = 2.0 * 1024 * t.b * t.b * GK * std::ceil((double)nchunk / s);
-      const double us = per_unit * flops / (flop_us * t.rate[(int)std::min(per_unit, (double)t.wgs) - 1]) +
+      const double us = eff * flops / flop_us +
                         (s > 1 ? 5.0 + (double)s * batch * M * N * 16.0 / 4e6 : 0.0);
       if (us < best_t * 0.999) {
         best_t = us;
@@ -331,9 +414,15 @@ hipError_t launch_gemm(GemmArgs& g, int transA, int transB, double* part, size_t
   g.kper = (nchunk + c.nsplit - 1) / c.nsplit;
   g.nsplit = g.kper > 0 ? (nchunk + g.kper - 1) / g.kper : 1;
   g.part = g.nsplit > 1 ? part : nullptr;
-  const double blocks = (double)g.tm * g.tn * g.batch * g.nsplit;
+  double per = 0.0;
+  if (g.mode == kIntegrals)
+    for (int band = 0; band * BAND < g.tm; ++band)
+      per += (double)std::min(BAND, g.tm - band * BAND) * band_columns(g, band, tile, tile);
+  else per = (double)g.tm * g.tn;
+  const double blocks = per * g.batch * g.nsplit;
   if (blocks > 2147483647.0) return hipErrorInvalidValue;
   const unsigned nb = (unsigned)blocks;
+  g.per = (int)per;
   if (wide) launch_tile<2, true>(g, transA, transB, nb, st);
   else if (c.b == 4) launch_tile<4, false>(g, transA, transB, nb, st);
   else launch_tile<2, false>(g, transA, transB, nb, st);
@@ -369,22 +458,38 @@ hipError_t gemm_f64(const double* A, int lda, long long sA, int transA, const do
   return launch_gemm(g, transA, transB, part, part_doubles, st);
 }
 
-hipError_t gemm_f64_pairs(const double* A, const double* B, int ld, double* C, int n, int M, int N, int K,
-                          long long stride_c, long long stride_d, hipStream_t st) {
+hipError_t ladder_integrals(const double* Bk, int n_aux, const LadderBlock& q, double* V, hipStream_t st) {
   GemmArgs g{};
-  g.A = A;
-  g.B = B;
-  g.C = C;
-  g.M = M;
-  g.N = N;
-  g.K = K;
-  g.lda = g.ldb = ld;
+  g.A = Bk + (size_t)q.a0 * q.n * n_aux;
+  g.B = Bk + (size_t)q.b0 * q.n * n_aux;
+  g.C = V;
+  g.M = (q.a1 - q.a0) * q.n;
+  g.N = (q.b1 - q.b0) * q.n;
+  g.K = n_aux;
+  g.lda = g.ldb = n_aux;
   g.alpha = 1.0;
   g.batch = 1;
-  g.pair_n = n;
-  g.pair_s1 = stride_c;
-  g.pair_s2 = stride_d;
+  g.mode = kIntegrals;
+  g.lad = q;
   return launch_gemm(g, 0, 1, nullptr, 0, st);
+}
+
+hipError_t ladder_contract(const double* T, const double* G, int n_amp, int K, int n, int t0, int count, bool plus,
+                           double* R, double* part, size_t part_doubles, hipStream_t st) {
+  GemmArgs g{};
+  g.A = T;
+  g.B = G;
+  g.C = R;
+  g.M = n_amp;
+  g.N = count;
+  g.K = K;
+  g.lda = g.ldb = K;
+  g.alpha = 1.0;
+  g.batch = 1;
+  g.mode = plus ? kPlus : kMinus;
+  g.lad.n = n;
+  g.lad.a0 = t0;
+  return launch_gemm(g, 0, 1, part, part_doubles, st);
 }
 
 }  // namespace dfpt2

@@ -102,9 +102,23 @@ void prof_flush();
 hipError_t gemm_f64(const double* A, int lda, long long sA, int transA, const double* B, int ldb, long long sB,
                     int transB, double* C, int ldc, long long sC, int M, int N, int K, int batch, double alpha,
                     double beta, hipStream_t st, double* part = nullptr, size_t part_doubles = 0, bool upper = false);
-// A B^T with rows (a, c) = a n + c of A and (d, b) = d n + b of B (row stride ld),
-// written to C[stride_c c + stride_d d + n a + b]
-hipError_t gemm_f64_pairs(const double* A, const double* B, int ld, double* C, int n, int M, int N, int K,
-                          long long stride_c, long long stride_d, hipStream_t st);
+
+// Pairs (a, b), b <= a, of the particle-particle ladder: those of the rows a0 <= a < a1, or of
+// one row a0 the part b0 <= b < b1 (else b0 = 0, b1 = a1), packed row by row.
+struct LadderBlock {
+  int n, a0, a1, b0, b1;
+  // packed index of (a, 0)
+  __host__ __device__ long long first(int a) const {
+    return ((long long)a * (a + 1) - (long long)a0 * (a0 + 1)) / 2 - b0;
+  }
+  __host__ __device__ int columns() const { return (int)(a1 - a0 > 1 ? first(a1) : b1 - b0); }
+};
+// V[(a, b)][c][d] = sum_Q Bk[(a, c)][Q] Bk[(b, d)][Q] for the pairs of a block
+hipError_t ladder_integrals(const double* Bk, int n_aux, const LadderBlock& q, double* V, hipStream_t st);
+// with X = T G^T (T [n_amp][K]; G [count][K], one row per pair, the first being pair t0 of
+// the triangle): plus writes X/2 to R[p][a][b] and R[p][b][a], else X/2 is added to
+// R[p][a][b] and subtracted from R[p][b][a] (a != b); part as in gemm_f64
+hipError_t ladder_contract(const double* T, const double* G, int n_amp, int K, int n, int t0, int count, bool plus,
+                           double* R, double* part, size_t part_doubles, hipStream_t st);
 
 }  // namespace dfpt2

@@ -4,19 +4,19 @@
 // (N_V'/N_V)^4 (Sec. 2):
 //     (ac|bd) = sum_Q B^Q_ac B^Q_bd,     R^p_ab = sum_cd (ac|bd) T^p_cd.
 //
-// Integral-direct in blocks of the first virtual a, as two FP64 MFMA GEMMs per
-// block (flops 2 N^4 n_aux + 2 N^4 n_amp in total, both proportional to N^4):
-//   G[(c,d)][(a,b)] = sum_Q B[(a,c)][Q] B[(d,b)][Q]      (rows a of the block)
-//   R[p][(a,b)]     = sum_(c,d) T[p][(c,d)] G[(c,d)][(a,b)]
-// The first product reads the columns of (ac|bd) in (d,b) order, which is
-// (b,d) order of B because density-fitted integrals are symmetric in their two
-// orbital indices (B^Q_db = B^Q_bd), so its tiles write runs of b; it stores them at
-// [(c,d)][(a,b)], so that the second product is one GEMM whose columns run over all
-// (a,b) of the block: no tile is cut off at N columns, whatever N.  G of one block
-// holds m_a N^3 doubles (at most ~16 GB, at least one a); m_a N >= 32768 columns fill
-// the GPU with tiles of the contraction.  At N' = 133, 800 auxiliary functions and 400
-// amplitude matrices the contraction took 18.7 ms as m_a = 32 batched GEMMs of
-// n_amp x N (13 TFLOP/s: 133 columns in tiles of 128).
+// Integral-direct over blocks of the pairs (a, b), b <= a, whose matrices
+// V^{ab}_cd = (ac|bd) serve both orders, V^{ba}_cd = V^{ab}_dc:
+//     R^p_ab, R^p_ba = 1/2 sum_{c>=d} S^{ab}_cd T+^p_cd +- 1/2 sum_{c>d} A^{ab}_cd T-^p_cd
+// with S, A = V_cd +- V_dc and T+, T- = T_cd +- T_dc (T+_cc = T_cc).  Half the integrals
+// and half the contraction of R^p_ab = sum_cd (ac|bd) T^p_cd over all (a, b): N^4 n_aux +
+// N^4 n_amp operations.  Per block
+//   V[(a,b)][c][d] = sum_Q B[(a,c)][Q] B[(b,d)][Q]     (tiles with b <= a)
+//   S, A           packed triangles of each V[(a,b)]
+//   R              two GEMMs [p][triangle] x [triangle][(a,b)], stored to both (a,b), (b,a)
+// What bounds it is the FP64 matrix pipe in the three GEMMs.  V and S, A hold some pairs
+// at a time, ~16 GB in all (more only where 1024 pairs are).  N' = 133, 800 auxiliary functions, 400
+// amplitude matrices, ms: integrals 4.8, split 0.7, contraction 2.7; over all (a, b) and
+// (c, d) integrals 9.3, contraction 5.0.
 //
 // Truncated space: with the kept NOs X [N_V][ldx] (first N' columns) the inputs are transformed
 // first, B'^Q = X^T B^Q X (over both virtual indices of B[a][c][Q]) and
@@ -33,13 +33,15 @@ namespace dfpt2 {
 namespace {
 
 struct LadderPlan {
-  int n, nk, na, np, ma;
+  int n, nk, na, np, vcols, scols;
   bool transform;
-  size_t off_Y, off_Bk, off_Z, off_Tk, off_G, bytes;
+  size_t off_Y, off_Bk, off_Z, off_Tk, off_Tp, off_V, off_S, bytes;
 };
 
-constexpr double kGBlockBytes = 16.0e9;  // one block of (ac|bd): enough values of a to fill the GPU
-constexpr int kMinBlockCols = 32768;     // columns (a,b) of a block, where N and the bytes allow
+constexpr double kVBytes = 2.0e9;    // V of the pairs whose integrals are formed at a time
+constexpr double kSBytes = 14.0e9;   // S and A of the pairs that are contracted at a time
+constexpr int kBlockPairs = 16384;   // pairs of either, where the bytes allow: enough to fill the GPU
+constexpr int kMinPairs = 1024;      // pairs contracted at a time, whatever the bytes
 
 int plan_ladder(int64_t n_vir, int64_t n_aux, int64_t n_amp, int64_t n_kept, bool transform, LadderPlan* pl) {
   if (n_vir < 1 || n_vir > 2048) return fail(DFPT2_ERR_INVALID_ARG, "n_vir must lie in [1, 2048]");
@@ -57,10 +59,9 @@ int plan_ladder(int64_t n_vir, int64_t n_aux, int64_t n_amp, int64_t n_kept, boo
   p.na = (int)n_aux;
   p.np = (int)n_amp;
   p.transform = transform;
-  const double n3 = (double)p.nk * p.nk * p.nk * sizeof(double);
-  p.ma = std::max(1, std::min({p.nk, std::max(32, (kMinBlockCols + p.nk - 1) / p.nk), (int)(kGBlockBytes / n3)}));
-  const int nblk = (p.nk + p.ma - 1) / p.ma;  // blocks of equal size
-  p.ma = (p.nk + nblk - 1) / nblk;
+  const double pair = (double)p.nk * p.nk * sizeof(double), all = 0.5 * p.nk * (p.nk + 1.0);
+  p.vcols = (int)std::max(1.0, std::min({all, (double)kBlockPairs, kVBytes / pair}));
+  p.scols = (int)std::min(all, std::max((double)kMinPairs, std::min((double)kBlockPairs, kSBytes / pair)));
   if ((double)p.nk * p.na > 2.0e9 || (double)p.nk * p.nk > 2.0e9)
     return fail(DFPT2_ERR_INVALID_ARG, "ladder operands exceed the GEMM index range");
   size_t off = 0;
@@ -74,9 +75,48 @@ int plan_ladder(int64_t n_vir, int64_t n_aux, int64_t n_amp, int64_t n_kept, boo
   p.off_Bk = take(transform ? d * p.nk * p.nk * p.na : 0);
   p.off_Z = take(transform ? d * p.np * p.n * p.nk : 0);
   p.off_Tk = take(transform ? d * p.np * p.nk * p.nk : 0);
-  p.off_G = take(d * (size_t)p.ma * p.nk * p.nk * p.nk);
+  p.off_Tp = take(d * p.np * p.nk * p.nk);
+  p.off_V = take(d * p.vcols * p.nk * p.nk);
+  p.off_S = take(d * p.scols * p.nk * p.nk);
   p.bytes = off;
   return DFPT2_OK;
+}
+
+// plus[m][c (c + 1) / 2 + d] = in[m][c][d] + in[m][d][c] (d < c), diag in[m][c][c] (d = c);
+// minus[m][c (c - 1) / 2 + d] = in[m][c][d] - in[m][d][c] (d < c).  One workgroup per matrix
+// and pair of 32 x 32 tiles, the transposed one through LDS; bound by memory.
+__global__ __launch_bounds__(256) void sym_split_kernel(const double* in, int n, double diag, double* plus, double* minus) {
+  __shared__ double tr[32][33];
+  int J, I;
+  tile_pair(blockIdx.x, (n + 31) / 32, J, I);  // J <= I
+  const size_t m = blockIdx.y;
+  const double* M = in + m * n * n;
+  const int x = threadIdx.x & 31, y = threadIdx.x >> 5;
+#pragma unroll
+  for (int r = y; r < 32; r += 8) {
+    const int c = J * 32 + r, d = I * 32 + x;
+    tr[r][x] = c < n && d < n ? M[(size_t)c * n + d] : 0.0;
+  }
+  __syncthreads();
+  double* P = plus + m * ((size_t)n * (n + 1) / 2);
+  double* Q = minus + m * ((size_t)n * (n - 1) / 2);
+#pragma unroll
+  for (int r = y; r < 32; r += 8) {
+    const int c = I * 32 + r, d = J * 32 + x;
+    if (c >= n || d > c) continue;
+    const double v = M[(size_t)c * n + d], w = tr[x][r];
+    P[(size_t)c * (c + 1) / 2 + d] = c == d ? diag * v : v + w;
+    if (d < c) Q[(size_t)c * (c - 1) / 2 + d] = v - w;
+  }
+}
+
+void sym_split(const double* in, int n, int count, double diag, double* plus, double* minus, hipStream_t st) {
+  const int nt = (n + 31) / 32;
+  for (int m0 = 0; m0 < count; m0 += 65535) {
+    const int k = std::min(65535, count - m0);
+    hipLaunchKernelGGL(sym_split_kernel, dim3(nt * (nt + 1) / 2, k), dim3(256), 0, st, in + (size_t)m0 * n * n, n, diag,
+                       plus + (size_t)m0 * n * (n + 1) / 2, minus + (size_t)m0 * n * (n - 1) / 2);
+  }
 }
 
 }  // namespace
@@ -137,18 +177,43 @@ int pp_ladder(int64_t n_vir, int64_t n_aux, int64_t n_amp, const double* B_vv, c
   }
   {
     ProfScope ps(DFPT2_STAGE_LADDER, s);
-    double* G = reinterpret_cast<double*>(ws + p.off_G);
-    const int N2 = nk * nk;
-    for (int a0 = 0; a0 < nk; a0 += p.ma) {
-      const int mb = std::min(p.ma, nk - a0);
-      // G[(c,d)][(a,b)] = sum_Q B'[(a,c)][Q] B'[(d,b)][Q] for a in [a0, a0 + mb)
-      const int ldg = mb * nk;
-      if ((e = gemm_f64_pairs(Bk + (size_t)a0 * nk * na, Bk, na, G, nk, mb * nk, N2, na, (long long)nk * ldg, ldg,
-                              s)) != hipSuccess)
-        return hip_fail(e, "ladder integrals");
-      // R[p][(a,b)] = sum_(c,d) T'[p][(c,d)] G[(c,d)][(a,b)]
-      if ((e = gemm_f64(Tk, N2, 0, 0, G, ldg, 0, 0, R + (size_t)a0 * nk, N2, 0, np, ldg, N2, 1, 1.0, 0.0, s)) !=
-          hipSuccess)
+    double* V = reinterpret_cast<double*>(ws + p.off_V);
+    const int kp = nk * (nk + 1) / 2, km = nk * (nk - 1) / 2;
+    double* Tp = reinterpret_cast<double*>(ws + p.off_Tp);
+    double* Tm = Tp + (size_t)np * kp;
+    sym_split(Tk, nk, np, 1.0, Tp, Tm, s);
+    double* S = reinterpret_cast<double*>(ws + p.off_S);
+    double* A = S + (size_t)p.scols * kp;
+    const int all = nk * (nk + 1) / 2;
+    const size_t nv = (size_t)p.vcols * nk * nk;  // V is free while the pairs are contracted
+    LadderBlock q{nk, 0, 0, 0, 0};
+    for (int t = 0; t < all;) {
+      const int t0 = t;
+      while (t < all) {
+        // the next rows a that fit, or the next part of a row
+        const int room = p.scols - (t - t0), row = q.a0 + 1 - q.b0;
+        if (t > t0 && room < std::min(row, p.vcols)) break;
+        const int most = std::min(room, p.vcols);
+        q.a1 = q.a0 + 1;
+        if (q.b0 == 0 && row <= most) {
+          while (q.a1 < nk && q.first(q.a1 + 1) <= most) ++q.a1;
+          q.b1 = q.a1;
+        } else {
+          q.b1 = std::min(q.b0 + most, q.a1);
+        }
+        const int cols = q.columns();
+        if ((e = ladder_integrals(Bk, na, q, V, s)) != hipSuccess) return hip_fail(e, "ladder integrals");
+        sym_split(V, nk, cols, 2.0, S + (size_t)(t - t0) * kp, A + (size_t)(t - t0) * km, s);
+        t += cols;
+        if (q.b1 < q.a1) {
+          q.b0 = q.b1;
+        } else {
+          q.a0 = q.a1;
+          q.b0 = 0;
+        }
+      }
+      if ((e = ladder_contract(Tp, S, np, kp, nk, t0, t - t0, true, R, V, nv, s)) != hipSuccess ||
+          (km > 0 && (e = ladder_contract(Tm, A, np, km, nk, t0, t - t0, false, R, V, nv, s)) != hipSuccess))
         return hip_fail(e, "ladder contraction");
     }
   }
