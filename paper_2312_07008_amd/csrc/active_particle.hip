@@ -10,13 +10,14 @@
 //     D_ef += sum_{ij} [ X_ij eta Z_ij^T ]_ef,   Z_ij = sum_{kl} w_ik w_jl Tc_kl,
 // where X_ij[e][x] = t^{ex}_{ij}.  Every ordered hole pair and active particle
 // is one column of an n_v x (n_h^2 n_act) matrix, so the work is
-//   1. X[e][(i,j,x)] = sum_Q B^Q_ie B_act^Q_jx          (FP64 MFMA GEMM, batched over i)
+//   1. X[e][(i,j,x)] = sum_Q B^Q_ie B_act^Q_jx          (FP64 MFMA GEMM)
 //   2. regularizer (Eq. A7), then Tc = 2 X - X^(i<->j)    (elementwise)
-//   3. Z = (w x w) Tc over the hole pair, Y = Z eta       (small kernel, GEMM batched over e)
-//   4. E = X Y^T, D += (E + E^T) / 2                     (FP64 MFMA GEMM, symmetric add)
+//   3. Z = (w x w) Tc over the hole pair, Y = Z eta       (one kernel)
+//   4. E = X Y^T (symmetric), D += E                     (FP64 MFMA GEMM of its upper triangle)
 // The cost is O(n_h^2 n_act n_v (n_aux + n_v)): a few percent of the pass.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 
 #include "../../include/dfpt2.h"
@@ -26,36 +27,36 @@
 namespace dfpt2 {
 namespace {
 
+// The kernels over X take one e per grid row and index within it in 32 bits: the 64-bit
+// divisions by run-time sizes of one flat index cost more than the memory they go through
+// (400 virtuals, 48 holes, 8 of them active: 42 us with them, 31 without).
+
 // X[e][i][j][x] *= (1 - exp(-s D^2)) / D,  D = eps_i + eps_j - eps_e - eps_(n_core + x)
-__global__ void ap_regularize(double* X, const double* eps_h, const double* eps_v, int n_v, int n_h, int n_a,
-                              int n_core, double s) {
-  const size_t n = (size_t)n_v * n_h * n_h * n_a;
-  for (size_t k = blockIdx.x * (size_t)blockDim.x + threadIdx.x; k < n; k += (size_t)gridDim.x * blockDim.x) {
-    size_t r = k;
-    const int x = (int)(r % n_a);
-    r /= n_a;
-    const int j = (int)(r % n_h);
-    r /= n_h;
-    const int i = (int)(r % n_h);
-    const int e = (int)(r / n_h);
-    const double dl = eps_h[i] + eps_h[j] - eps_v[e] - eps_h[n_core + x];
-    X[k] = (dl != 0.0) ? X[k] * (1.0 - exp(-s * dl * dl)) / dl : 0.0;
+__global__ void ap_regularize(double* X, const double* eps_h, const double* eps_v, int n_h, int n_a, int n_core,
+                              double s) {
+  const unsigned per = (unsigned)n_h * n_h * n_a;
+  const double ee = eps_v[blockIdx.y];
+  double* Xe = X + (size_t)blockIdx.y * per;
+  for (unsigned k = blockIdx.x * blockDim.x + threadIdx.x; k < per; k += gridDim.x * blockDim.x) {
+    const unsigned ij = k / n_a, x = k - ij * n_a, i = ij / n_h, j = ij - i * n_h;
+    const double dl = eps_h[i] + eps_h[j] - ee - eps_h[n_core + x];
+    Xe[k] = (dl != 0.0) ? Xe[k] * (1.0 - exp(-s * dl * dl)) / dl : 0.0;
   }
 }
 
-// Z[e][i][j][x] = sum_{k,l} w_ik w_jl (2 X[e][k][l][x] - X[e][l][k][x]),
-// w = identity on core holes and Gamma / 2 on the active block
-__global__ void ap_pair_mix(const double* X, const double* gamma, double* Z, int n_v, int n_h, int n_a,
-                            int n_core) {
-  const size_t n = (size_t)n_v * n_h * n_h * n_a;
-  for (size_t k = blockIdx.x * (size_t)blockDim.x + threadIdx.x; k < n; k += (size_t)gridDim.x * blockDim.x) {
-    size_t r = k;
-    const int x = (int)(r % n_a);
-    r /= n_a;
-    const int j = (int)(r % n_h);
-    r /= n_h;
-    const int i = (int)(r % n_h);
-    const size_t base = (r / n_h) * (size_t)n_h * n_h * n_a;
+// Y[e][i][j][z] = sum_x Z[e][i][j][x] eta_xz, Z[e][i][j][x] = sum_{k,l} w_ik w_jl (2 X[e][k][l][x] -
+// X[e][l][k][x]), w = identity on core holes and Gamma / 2 on the active block, eta = 2 - Gamma.
+// A workgroup takes as many pairs (i, j) of one e as have 256 values of Z, which meet eta in
+// LDS (Z through memory and a batched product with eta: 124 + 98 us, 158 so: the active pairs, a 36th of them, sum 64 terms each).
+__global__ __launch_bounds__(256) void ap_pair_mix(const double* X, const double* gamma, double* Y, int n_h, int n_a,
+                                                   int n_core) {
+  __shared__ double z[256];
+  const int P = 256 / n_a, p = threadIdx.x / n_a, x = threadIdx.x - p * n_a;  // n_a <= 64
+  const unsigned ij = blockIdx.x * P + p, nn = (unsigned)n_h * n_h;
+  const double* Xe = X + (size_t)blockIdx.y * nn * n_a;
+  const bool in = p < P && ij < nn;
+  if (in) {
+    const int i = (int)(ij / n_h), j = (int)(ij - (unsigned)i * n_h);
     const int k0 = i < n_core ? i : n_core, k1 = i < n_core ? i + 1 : n_h;
     const int l0 = j < n_core ? j : n_core, l1 = j < n_core ? j + 1 : n_h;
     double acc = 0.0;
@@ -63,37 +64,36 @@ __global__ void ap_pair_mix(const double* X, const double* gamma, double* Z, int
       const double wi = i < n_core ? 1.0 : 0.5 * gamma[(i - n_core) * n_a + (kk - n_core)];
       if (wi == 0.0) continue;
       double inner = 0.0;
+#pragma unroll 4
       for (int ll = l0; ll < l1; ++ll) {
         const double wj = j < n_core ? 1.0 : 0.5 * gamma[(j - n_core) * n_a + (ll - n_core)];
-        const double tc = 2.0 * X[base + ((size_t)kk * n_h + ll) * n_a + x] - X[base + ((size_t)ll * n_h + kk) * n_a + x];
+        const double tc = 2.0 * Xe[((unsigned)kk * n_h + ll) * n_a + x] - Xe[((unsigned)ll * n_h + kk) * n_a + x];
         inner += wj * tc;
       }
       acc += wi * inner;
     }
-    Z[k] = acc;
+    z[threadIdx.x] = acc;
   }
+  __syncthreads();
+  if (!in) return;
+  double y = 0.0;
+  for (int q = 0; q < n_a; ++q) y += z[p * n_a + q] * ((q == x ? 2.0 : 0.0) - gamma[q * n_a + x]);
+  Y[((size_t)blockIdx.y * nn + ij) * n_a + x] = y;
 }
 
-__global__ void ap_eta(const double* gamma, int n_a, double* eta) {
-  for (int k = threadIdx.x; k < n_a * n_a; k += blockDim.x) {
-    const int u = k / n_a, v = k - u * n_a;
-    eta[k] = (u == v ? 2.0 : 0.0) - gamma[k];
-  }
-}
-
-// D += scale (E + E^T) / 2
+// D += scale E, from the upper triangle of the symmetric E
 __global__ void ap_sym_add(const double* E, double* D, int n_v, double scale) {
   const size_t n = (size_t)n_v * n_v;
   for (size_t k = blockIdx.x * (size_t)blockDim.x + threadIdx.x; k < n; k += (size_t)gridDim.x * blockDim.x) {
     const size_t a = k / n_v, b = k - a * n_v;
-    D[k] += 0.5 * scale * (E[k] + E[b * n_v + a]);
+    D[k] += scale * (a <= b ? E[k] : E[b * n_v + a]);
   }
 }
 
 struct ApPlan {
   int n_core, n_a, n_h, n_v, n_aux;
   size_t K;  // n_h^2 n_a
-  size_t off_X, off_Z, off_Y, off_E, off_eta, bytes;
+  size_t off_X, off_Z, off_Y, off_E, bytes;
 };
 
 int plan_ap(const dfpt2_opts* o, ApPlan* p) {
@@ -121,7 +121,6 @@ int plan_ap(const dfpt2_opts* o, ApPlan* p) {
   p->off_Z = take(big);
   p->off_Y = take(big);
   p->off_E = take(sizeof(double) * (size_t)p->n_v * p->n_v);
-  p->off_eta = take(sizeof(double) * (size_t)(p->n_a > 0 ? p->n_a * p->n_a : 1));
   p->bytes = off;
   return DFPT2_OK;
 }
@@ -165,29 +164,29 @@ int dfpt2_add_active_particle_density(const dfpt2_opts* opts, const double* eps_
   double* Z = reinterpret_cast<double*>(ws + p.off_Z);
   double* Y = reinterpret_cast<double*>(ws + p.off_Y);
   double* E = reinterpret_cast<double*>(ws + p.off_E);
-  double* eta = reinterpret_cast<double*>(ws + p.off_eta);
   const int n_v = p.n_v, n_h = p.n_h, n_a = p.n_a, na = p.n_aux;
   const int K = (int)p.K, NA = n_h * n_a;
   const size_t all = (size_t)n_v * p.K;
   hipError_t e;
   ProfScope ps(DFPT2_STAGE_ACTIVE, s);
   // 1. X[e][(i, j, x)] = sum_Q B[i][e][Q] B_act[(j, x)][Q]
-  if ((e = gemm_f64(B, na, (long long)n_v * na, 0, B_act, na, 0, 1, X, K, NA, n_v, NA, na, n_h, 1.0, 0.0, s)) !=
-      hipSuccess)
+  // (one product over all rows (i, e): batched over i, 400 rows fill no whole number of tiles)
+  if ((e = gemm_f64(B, na, 0, 0, B_act, na, 0, 1, X, K, 0, n_h * n_v, NA, na, 1, 1.0, 0.0, s, nullptr, 0, false, n_v,
+                    NA)) != hipSuccess)
     return hip_fail(e, "active-particle integrals");
   // 2. amplitudes
-  hipLaunchKernelGGL(ap_regularize, dim3(grid_for(all)), dim3(256), 0, s, X, eps_hole, eps_vir, n_v, n_h, n_a,
-                     p.n_core, opts->s);
-  // 3. Z = (w x w) Tc, Y = Z eta (batched over e: M = n_h^2, N = K = n_act)
-  hipLaunchKernelGGL(ap_pair_mix, dim3(grid_for(all)), dim3(256), 0, s, X, gamma_act, Z, n_v, n_h, n_a, p.n_core);
-  hipLaunchKernelGGL(ap_eta, dim3(1), dim3(256), 0, s, gamma_act, n_a, eta);
+  const dim3 over((unsigned)std::min<size_t>((p.K + 255) / 256, 4096), n_v);
+  hipLaunchKernelGGL(ap_regularize, over, dim3(256), 0, s, X, eps_hole, eps_vir, n_h, n_a, p.n_core, opts->s);
+  // 3. Z = (w x w) Tc, Y = Z eta
+  const int pairs = 256 / n_a;
+  hipLaunchKernelGGL(ap_pair_mix, dim3((unsigned)(((size_t)n_h * n_h + pairs - 1) / pairs), n_v), dim3(256), 0, s, X,
+                     gamma_act, Y, n_h, n_a, p.n_core);
   if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "active-particle kernels");
-  if ((e = gemm_f64(Z, n_a, (long long)p.K, 0, eta, n_a, 0, 0, Y, n_a, (long long)p.K, n_h * n_h, n_a, n_a, n_v, 1.0,
-                    0.0, s)) != hipSuccess)
-    return hip_fail(e, "active-particle eta");
-  // 4. E = X Y^T, D += (E + E^T) / 2 (per-spin convention: half)
-  // (n_v^2 outputs, a contraction of n_h^2 n_act: split over workgroups, Z is free)
-  if ((e = gemm_f64(X, K, 0, 0, Y, K, 0, 1, E, n_v, 0, n_v, n_v, K, 1, 1.0, 0.0, s, Z, all)) != hipSuccess)
+  // 4. E = X Y^T, D += E (per-spin convention: half).  w, eta and the exchange are symmetric
+  // and the latter two commute with w x w, so E is symmetric: its upper triangle is enough
+  // (n_v^2 outputs, a contraction of n_h^2 n_act: split over workgroups)
+  if ((e = gemm_f64(X, K, 0, 0, Y, K, 0, 1, E, n_v, 0, n_v, n_v, K, 1, 1.0, 0.0, s, Z, all, true)) !=
+      hipSuccess)
     return hip_fail(e, "active-particle density");
   const double scale = opts->density_convention == 1 ? 0.5 : 1.0;
   hipLaunchKernelGGL(ap_sym_add, dim3(grid_for((size_t)n_v * n_v)), dim3(256), 0, s, E, D_vv, n_v, scale);

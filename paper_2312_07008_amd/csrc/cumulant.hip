@@ -26,11 +26,12 @@
 //     Q4[f][h v y] = sum_{u x} X[f][x][h][u] lambda_uv^yx.
 // The K columns are [D4+D6 first half | second half | D5 | D1 | D2]; one FP64
 // MFMA GEMM forms E = L R^T.  D3 needs the virtual-virtual amplitudes of the
-// active hole pairs, T[e][uv][e'] (a GEMM per active hole), mixed with lambda
+// active hole pairs, T[e][uv][e'] (one GEMM), mixed with lambda
 // over the hole pair (a GEMM batched over e) and contracted over (uv, e') into
 // the same E.  Each term is symmetric in (e, f); D += (E + E^T) / 2.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 
 #include "../../include/dfpt2.h"
@@ -44,121 +45,158 @@ __device__ inline size_t xidx(int e, int i, int j, int x, int n_h, int n_a) {
   return (((size_t)e * n_h + i) * n_h + j) * n_a + x;
 }
 
+// The kernels over X take one e (or f) per grid row and index within it in 32 bits: the
+// 64-bit divisions by run-time sizes of one flat index cost more than the memory they go
+// through.  Measured below at 400 virtuals and 48 holes, 8 of them active.
+
 // X[e][i][j][x] *= (1 - exp(-s D^2)) / D,  D = eps_i + eps_j - eps_e - eps_(n_core + x)
-__global__ void cs_regularize_x(double* X, const double* eps_h, const double* eps_v, int n_v, int n_h, int n_a,
-                                int n_core, double s) {
-  const size_t n = (size_t)n_v * n_h * n_h * n_a;
-  for (size_t k = blockIdx.x * (size_t)blockDim.x + threadIdx.x; k < n; k += (size_t)gridDim.x * blockDim.x) {
-    size_t r = k;
-    const int x = (int)(r % n_a);
-    r /= n_a;
-    const int j = (int)(r % n_h);
-    r /= n_h;
-    const int i = (int)(r % n_h);
-    const int e = (int)(r / n_h);
-    const double dl = eps_h[i] + eps_h[j] - eps_v[e] - eps_h[n_core + x];
-    X[k] = (dl != 0.0) ? X[k] * (1.0 - exp(-s * dl * dl)) / dl : 0.0;
-  }
-}
-
-// T[e][u v][e'] *= (1 - exp(-s D^2)) / D,  D = eps_u + eps_v - eps_e - eps_e'
-__global__ void cs_regularize_t(double* T, const double* eps_h, const double* eps_v, int n_v, int n_a, int n_core,
+// (42 us with one flat index, 31 so)
+__global__ void cs_regularize_x(double* X, const double* eps_h, const double* eps_v, int n_h, int n_a, int n_core,
                                 double s) {
-  const size_t n = (size_t)n_v * n_a * n_a * n_v;
-  for (size_t k = blockIdx.x * (size_t)blockDim.x + threadIdx.x; k < n; k += (size_t)gridDim.x * blockDim.x) {
-    size_t r = k;
-    const int e2 = (int)(r % n_v);
-    r /= n_v;
-    const int v = (int)(r % n_a);
-    r /= n_a;
-    const int u = (int)(r % n_a);
-    const int e = (int)(r / n_a);
-    const double dl = eps_h[n_core + u] + eps_h[n_core + v] - eps_v[e] - eps_v[e2];
-    T[k] = (dl != 0.0) ? T[k] * (1.0 - exp(-s * dl * dl)) / dl : 0.0;
+  const unsigned per = (unsigned)n_h * n_h * n_a;
+  const double ee = eps_v[blockIdx.y];
+  double* Xe = X + (size_t)blockIdx.y * per;
+  for (unsigned k = blockIdx.x * blockDim.x + threadIdx.x; k < per; k += gridDim.x * blockDim.x) {
+    const unsigned ij = k / n_a, x = k - ij * n_a, i = ij / n_h, j = ij - i * n_h;
+    const double dl = eps_h[i] + eps_h[j] - ee - eps_h[n_core + x];
+    Xe[k] = (dl != 0.0) ? Xe[k] * (1.0 - exp(-s * dl * dl)) / dl : 0.0;
   }
 }
 
-// singles t1[i][e] (Eq. A6 with f = 0)
+// T[e][u v][e'] *= (1 - exp(-s D^2)) / D,  D = eps_u + eps_v - eps_e - eps_e'.  As a matrix
+// of rows r = (u, e) and columns c = (v, e') T is symmetric and only r <= c is read; a
+// workgroup takes a 32 x 32 tile (I <= J) and writes it and, through LDS, its transpose.
+__global__ __launch_bounds__(256) void cs_regularize_t(double* T, const double* eps_h, const double* eps_v, int n_v,
+                                                       int n_a, int n_core, double s) {
+  __shared__ double tr[32][33];
+  const unsigned m = (unsigned)n_a * n_v;
+  int I, J;
+  tile_pair(blockIdx.x, (int)((m + 31) / 32), I, J);
+  const size_t K3 = (size_t)n_a * m;
+  const unsigned x = threadIdx.x & 31, y = threadIdx.x >> 5;
+  const unsigned c = J * 32 + x, v = c / n_v;
+  const double ec = c < m ? eps_h[n_core + v] - eps_v[c - v * n_v] : 0.0;
+  for (unsigned q = y; q < 32; q += 8) {
+    const unsigned r = I * 32 + q, u = r / n_v, e = r - u * n_v;
+    if (r > c || c >= m) continue;
+    double* t = T + e * K3 + (size_t)u * m + c;
+    const double dl = (eps_h[n_core + u] - eps_v[e]) + ec;
+    const double z = (dl != 0.0) ? *t * (1.0 - exp(-s * dl * dl)) / dl : 0.0;
+    *t = z;
+    tr[q][x] = z;
+  }
+  __syncthreads();
+  for (unsigned q = y; q < 32; q += 8) {
+    const unsigned r = J * 32 + q, u = r / n_v, e = r - u * n_v, c2 = I * 32 + x;
+    if (r < m && c2 < r) T[e * K3 + (size_t)u * m + c2] = tr[x][q];
+  }
+}
+
+// singles t1[i][e] (Eq. A6 with f = 0): one wave per (e, i), lanes over (u, x)
 __global__ void cs_singles(const double* X, const double* eps_h, const double* eps_v, const double* gamma, int n_v,
                            int n_h, int n_a, int n_core, double s, double* t1) {
-  const size_t n = (size_t)n_h * n_v;
-  for (size_t k = blockIdx.x * (size_t)blockDim.x + threadIdx.x; k < n; k += (size_t)gridDim.x * blockDim.x) {
-    const int i = (int)(k / n_v), e = (int)(k - (size_t)i * n_v);
-    double src = 0.0;
-    for (int u = 0; u < n_a; ++u)
-      for (int x = 0; x < n_a; ++x) {
-        const double w = (eps_h[n_core + x] - eps_h[n_core + u]) * gamma[x * n_a + u];
-        if (w == 0.0) continue;
-        src += w * (2.0 * X[xidx(e, i, n_core + u, x, n_h, n_a)] - X[xidx(e, n_core + u, i, x, n_h, n_a)]);
+  const int e = blockIdx.y, i = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (i >= n_h) return;
+  double src = 0.0;
+  for (int k = lane; k < n_a * n_a; k += 64) {
+    const int u = k / n_a, x = k - u * n_a;
+    const double w = (eps_h[n_core + x] - eps_h[n_core + u]) * gamma[x * n_a + u];
+    if (w == 0.0) continue;
+    src += w * (2.0 * X[xidx(e, i, n_core + u, x, n_h, n_a)] - X[xidx(e, n_core + u, i, x, n_h, n_a)]);
+  }
+  src = wave_sum(src);
+  const double dl = eps_h[i] - eps_v[e];
+  if (lane == 0) t1[(size_t)i * n_v + e] = (dl != 0.0) ? 0.5 * src * (1.0 - exp(-s * dl * dl)) / dl : 0.0;
+}
+
+// Qa = 2 Q1 - Q2 and Qb = -(Q1 + Q4), [f][h][v][y].  A workgroup takes one f and 24 holes:
+// the amplitudes go through LDS (a few x at a time), a lane has one (v, y) of six holes, so
+// that each element of lambda read serves six sums (180 us with one output a thread and all
+// reads from memory, 36 so).
+constexpr int kQHoles = 6;
+__global__ __launch_bounds__(256) void cs_q(const double* X, const double* lam, int n_h, int n_a, int n_core, double* Qa,
+                                            double* Qb) {
+  constexpr int H = 4 * kQHoles;
+  __shared__ double a1[H][64], a2[H][64];
+  const int f = blockIdx.y, h0 = blockIdx.x * H, tid = threadIdx.x, lane = tid & 63, g = tid >> 6;
+  const int xc = n_a < 8 ? n_a : 64 / n_a, n2 = n_a * n_a;  // x at a time: xc n_a <= 64
+  for (int vy0 = 0; vy0 < n2; vy0 += 64) {
+    const int vy = min(vy0 + lane, n2 - 1), v = vy / n_a, y = vy - v * n_a;
+    double q1[kQHoles] = {}, q2[kQHoles] = {}, q4[kQHoles] = {};
+    for (int x0 = 0; x0 < n_a; x0 += xc) {
+      const int nx = min(xc, n_a - x0) * n_a;
+      __syncthreads();
+      for (int k = tid; k < H * 64; k += 256) {
+        const int h = min(h0 + (k >> 6), n_h - 1), q = k & 63, dx = q / n_a, u = q - dx * n_a;
+        if (q < nx) {
+          a1[k >> 6][q] = X[xidx(f, h, n_core + x0 + dx, u, n_h, n_a)];
+          a2[k >> 6][q] = X[xidx(f, n_core + x0 + dx, h, u, n_h, n_a)];
+        }
       }
-    const double dl = eps_h[i] - eps_v[e];
-    t1[k] = (dl != 0.0) ? 0.5 * src * (1.0 - exp(-s * dl * dl)) / dl : 0.0;
+      __syncthreads();
+      for (int q = 0; q < nx; ++q) {
+        const int dx = q / n_a, u = q - dx * n_a, x = x0 + dx;
+        const size_t uv = ((size_t)u * n_a + v) * n2;
+        const double l = lam[uv + x * n_a + y], lt = lam[uv + y * n_a + x];
+#pragma unroll
+        for (int k = 0; k < kQHoles; ++k) {
+          const double b1 = a1[g * kQHoles + k][q], b2 = a2[g * kQHoles + k][q];
+          q1[k] += b1 * l;
+          q2[k] += b2 * l;
+          q4[k] += b2 * lt;
+        }
+      }
+    }
+    if (vy0 + lane >= n2) continue;
+#pragma unroll
+    for (int k = 0; k < kQHoles; ++k) {
+      const int h = h0 + g * kQHoles + k;
+      if (h >= n_h) continue;
+      const size_t o = ((size_t)f * n_h + h) * n2 + vy;
+      Qa[o] = 2.0 * q1[k] - q2[k];
+      Qb[o] = -(q1[k] + q4[k]);
+    }
   }
 }
 
-// Qa = 2 Q1 - Q2 and Qb = -(Q1 + Q4), [f][h][v][y]
-__global__ void cs_q(const double* X, const double* lam, int n_v, int n_h, int n_a, int n_core, double* Qa,
-                     double* Qb) {
-  const size_t n = (size_t)n_v * n_h * n_a * n_a;
-  for (size_t k = blockIdx.x * (size_t)blockDim.x + threadIdx.x; k < n; k += (size_t)gridDim.x * blockDim.x) {
-    size_t r = k;
-    const int y = (int)(r % n_a);
-    r /= n_a;
-    const int v = (int)(r % n_a);
-    r /= n_a;
-    const int h = (int)(r % n_h);
-    const int f = (int)(r / n_h);
-    double q1 = 0.0, q2 = 0.0, q4 = 0.0;
-    for (int u = 0; u < n_a; ++u)
-      for (int x = 0; x < n_a; ++x) {
-        const double a1 = X[xidx(f, h, n_core + x, u, n_h, n_a)];
-        const double a2 = X[xidx(f, n_core + x, h, u, n_h, n_a)];
-        q1 += a1 * lam[((u * n_a + v) * n_a + x) * n_a + y];
-        q2 += a2 * lam[((u * n_a + v) * n_a + x) * n_a + y];
-        q4 += a2 * lam[((u * n_a + v) * n_a + y) * n_a + x];
-      }
-    Qa[k] = 2.0 * q1 - q2;
-    Qb[k] = -(q1 + q4);
-  }
-}
-
-// W1[f][u] = sum_{v x y} t_fv^xy lambda_uv^xy
-__global__ void cs_w1(const double* X, const double* lam, int n_v, int n_h, int n_a, int n_core, double* W1) {
-  const size_t n = (size_t)n_v * n_a;
-  for (size_t k = blockIdx.x * (size_t)blockDim.x + threadIdx.x; k < n; k += (size_t)gridDim.x * blockDim.x) {
-    const int f = (int)(k / n_a), u = (int)(k - (size_t)f * n_a);
+// W1[f][u] = sum_{v x y} t_fv^xy lambda_uv^xy and
+// R5[f][u v z] = 1/2 sum_{x y w} t_fw^xy eta_w^z lambda_uv^xy, one workgroup per f: a wave per
+// u, and t eta for a few z at a time in LDS (82 and 133 us with a thread per output, 17 so)
+__global__ __launch_bounds__(512) void cs_w1_r5(const double* X, const double* lam, const double* gamma, int n_h, int n_a,
+                                                int n_core, double* W1, double* R5) {
+  __shared__ double xe[4096];
+  const int f = blockIdx.x, tid = threadIdx.x, lane = tid & 63, n2 = n_a * n_a;
+  for (int u = tid >> 6; u < n_a; u += 8) {
     double acc = 0.0;
-    for (int v = 0; v < n_a; ++v)
-      for (int x = 0; x < n_a; ++x)
-        for (int y = 0; y < n_a; ++y)
-          acc += X[xidx(f, n_core + x, n_core + y, v, n_h, n_a)] * lam[((u * n_a + v) * n_a + x) * n_a + y];
-    W1[k] = acc;
+    for (int k = lane; k < n2 * n_a; k += 64) {
+      const int v = k / n2, xy = k - v * n2, x = xy / n_a, y = xy - x * n_a;
+      acc += X[xidx(f, n_core + x, n_core + y, v, n_h, n_a)] * lam[(size_t)u * n2 * n_a + k];
+    }
+    acc = wave_sum(acc);
+    if (lane == 0) W1[(size_t)f * n_a + u] = acc;
   }
-}
-
-// R5[f][u v z] = 1/2 sum_{x y w} t_fw^xy eta_w^z lambda_uv^xy
-__global__ void cs_r5(const double* X, const double* lam, const double* gamma, int n_v, int n_h, int n_a, int n_core,
-                      double* R5) {
-  const size_t n = (size_t)n_v * n_a * n_a * n_a;
-  for (size_t k = blockIdx.x * (size_t)blockDim.x + threadIdx.x; k < n; k += (size_t)gridDim.x * blockDim.x) {
-    size_t r = k;
-    const int z = (int)(r % n_a);
-    r /= n_a;
-    const int v = (int)(r % n_a);
-    r /= n_a;
-    const int u = (int)(r % n_a);
-    const int f = (int)(r / n_a);
-    double acc = 0.0;
-    for (int x = 0; x < n_a; ++x)
-      for (int y = 0; y < n_a; ++y) {
-        const double l = lam[((u * n_a + v) * n_a + x) * n_a + y];
-        if (l == 0.0) continue;
-        double xe = 0.0;
-        for (int w = 0; w < n_a; ++w)
-          xe += X[xidx(f, n_core + x, n_core + y, w, n_h, n_a)] * ((w == z ? 2.0 : 0.0) - gamma[w * n_a + z]);
-        acc += xe * l;
+  const int zc = min(n_a, 4096 / n2);
+  for (int z0 = 0; z0 < n_a; z0 += zc) {
+    const int nz = min(zc, n_a - z0);
+    __syncthreads();
+    for (int k = tid; k < n2 * nz; k += 512) {
+      const int xy = k / nz, z = z0 + k - xy * nz, x = xy / n_a, y = xy - x * n_a;
+      double acc = 0.0;
+      for (int w = 0; w < n_a; ++w)
+        acc += X[xidx(f, n_core + x, n_core + y, w, n_h, n_a)] * ((w == z ? 2.0 : 0.0) - gamma[w * n_a + z]);
+      xe[k] = acc;
+    }
+    __syncthreads();
+    for (int k = tid; k < n2 * nz; k += 512) {
+      const int uv = k / nz, dz = k - uv * nz;
+      double acc = 0.0;
+#pragma unroll 4
+      for (int xy = 0; xy < n2; ++xy) {
+        const double l = lam[(size_t)uv * n2 + xy];
+        acc += l == 0.0 ? 0.0 : xe[xy * nz + dz] * l;
       }
-    R5[k] = 0.5 * acc;
+      R5[((size_t)f * n2 + uv) * n_a + z0 + dz] = 0.5 * acc;
+    }
   }
 }
 
@@ -338,21 +376,18 @@ int dfpt2_add_cumulant_singles_density(const dfpt2_opts* opts, const double* eps
   hipError_t e;
   ProfScope ps(DFPT2_STAGE_ACTIVE, s);
   // amplitudes with one active particle, X[e][(i, j, x)] (as active_particle.hip)
-  if ((e = gemm_f64(B, na, (long long)n_v * na, 0, B_act, na, 0, 1, X, KX, NA, n_v, NA, na, n_h, 1.0, 0.0, s)) !=
-      hipSuccess)
+  if ((e = gemm_f64(B, na, 0, 0, B_act, na, 0, 1, X, KX, 0, n_h * n_v, NA, na, 1, 1.0, 0.0, s, nullptr, 0, false, n_v,
+                    NA)) != hipSuccess)
     return hip_fail(e, "active-particle integrals");
   const size_t nx = (size_t)n_v * KX;
-  hipLaunchKernelGGL(cs_regularize_x, dim3(grid_cs(nx)), dim3(256), 0, s, X, eps_hole, eps_vir, n_v, n_h, n_a, nc,
-                     sflow);
-  hipLaunchKernelGGL(cs_singles, dim3(grid_cs((size_t)n_h * n_v)), dim3(256), 0, s, X, eps_hole, eps_vir, gamma_act,
+  hipLaunchKernelGGL(cs_regularize_x, dim3((unsigned)std::min((KX + 255) / 256, 4096), n_v), dim3(256), 0, s, X,
+                     eps_hole, eps_vir, n_h, n_a, nc, sflow);
+  hipLaunchKernelGGL(cs_singles, dim3((n_h + 3) / 4, n_v), dim3(256), 0, s, X, eps_hole, eps_vir, gamma_act,
                      n_v, n_h, n_a, nc, sflow, t1);
   if (d.lam) {
-    hipLaunchKernelGGL(cs_q, dim3(grid_cs((size_t)n_v * n_h * n_a * n_a)), dim3(256), 0, s, X, lambda_act, n_v, n_h,
-                       n_a, nc, Qa, Qb);
-    hipLaunchKernelGGL(cs_w1, dim3(grid_cs((size_t)n_v * n_a)), dim3(256), 0, s, X, lambda_act, n_v, n_h, n_a, nc,
-                       W1);
-    hipLaunchKernelGGL(cs_r5, dim3(grid_cs((size_t)n_v * n_a * n_a * n_a)), dim3(256), 0, s, X, lambda_act,
-                       gamma_act, n_v, n_h, n_a, nc, R5);
+    hipLaunchKernelGGL(cs_q, dim3((n_h + 4 * kQHoles - 1) / (4 * kQHoles), n_v), dim3(256), 0, s, X, lambda_act, n_h, n_a,
+                       nc, Qa, Qb);
+    hipLaunchKernelGGL(cs_w1_r5, dim3(n_v), dim3(512), 0, s, X, lambda_act, gamma_act, n_h, n_a, nc, W1, R5);
   }
   hipLaunchKernelGGL(cs_build_lr, dim3(grid_cs((size_t)n_v * d.K)), dim3(256), 0, s, X, t1, Qa, Qb, R5, W1,
                      gamma_act, d, L, R);
@@ -361,14 +396,15 @@ int dfpt2_add_cumulant_singles_density(const dfpt2_opts* opts, const double* eps
   if ((e = gemm_f64(L, d.K, 0, 0, R, d.K, 0, 1, E, n_v, 0, n_v, n_v, d.K, 1, 1.0, 0.0, s, X, nx)) != hipSuccess)
     return hip_fail(e, "cumulant/singles density");
   if (d.lam) {
-    // T[e][(u, v)][e'] = sum_Q B_ue^Q B_ve'^Q, one GEMM per active hole u batched over v
-    const int K3 = n_a * n_a * n_v;
-    for (int u = 0; u < n_a; ++u) {
-      if ((e = gemm_f64(B + (size_t)(nc + u) * n_v * na, na, 0, 0, B + (size_t)nc * n_v * na, na, (long long)n_v * na,
-                        1, T + (size_t)u * n_a * n_v, K3, n_v, n_v, n_v, na, n_a, 1.0, 0.0, s)) != hipSuccess)
-        return hip_fail(e, "active-active integrals");
-    }
-    hipLaunchKernelGGL(cs_regularize_t, dim3(grid_cs((size_t)n_v * K3)), dim3(256), 0, s, T, eps_hole, eps_vir, n_v,
+    // T[e][(u, v)][e'] = sum_Q B_ue^Q B_ve'^Q: rows (u, e) times themselves, the tiles from
+    // the diagonal on (0.38 ms; 1.10 as a product per u batched over v)
+    const int K3 = n_a * n_a * n_v, NAV = n_a * n_v;
+    const double* Ba = B + (size_t)nc * n_v * na;
+    if ((e = gemm_f64(Ba, na, 0, 0, Ba, na, 0, 1, T, K3, 0, NAV, NAV, na, 1, 1.0, 0.0, s, nullptr, 0, true, n_v, NAV)) !=
+        hipSuccess)
+      return hip_fail(e, "active-active integrals");
+    const int nt = (NAV + 31) / 32;
+    hipLaunchKernelGGL(cs_regularize_t, dim3((unsigned)nt * (nt + 1) / 2), dim3(256), 0, s, T, eps_hole, eps_vir, n_v,
                        n_a, nc, sflow);
     if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "active-active amplitudes");
     // M[f][(u, v)][e'] = sum_(x, y) lambda_uv^xy T[f][(x, y)][e'], batched over f

@@ -41,6 +41,8 @@ struct GemmArgs {
   int M, N, K;
   int lda, ldb, ldc;
   long long sA, sB, sC;
+  int row_n;          // row m of C lies at (m % row_n) ldc + (m / row_n) row_s (no groups: row_n = M)
+  long long row_s;
   double alpha, beta;
   int batch, tm, tn;  // tiles along M and N
   int per;            // tiles of a product
@@ -73,14 +75,21 @@ __device__ inline void ladder_store(double* R, int n, int a, int b, double v, bo
   }
 }
 
+__device__ inline double* c_row(const GemmArgs& g, int b, int m) {
+  const int q = m / g.row_n;
+  return g.C + b * g.sC + (size_t)(m - q * g.row_n) * g.ldc + q * g.row_s;
+}
+
 constexpr int BAND = 8;  // tile rows of a band
 
-// tile columns that a band of an integral block reaches: those with a b <= a
-__host__ __device__ inline int band_columns(const GemmArgs& g, int band, int tm_edge, int tn_edge) {
-  if (g.mode != kIntegrals) return g.tn;
-  const int m1 = (band + 1) * BAND * tm_edge, last = (m1 < g.M ? m1 : g.M) - 1;
+// first tile column and number of tile columns that a band of tile rows (edge `tile`) has:
+// all; of an integral block those with a b <= a; of an upper triangle those from the diagonal on
+__host__ __device__ inline int band_columns(const GemmArgs& g, int band, int tile, int& first) {
+  first = g.upper ? band * BAND : 0;
+  if (g.mode != kIntegrals) return g.tn - first;
+  const int m1 = (band + 1) * BAND * tile, last = (m1 < g.M ? m1 : g.M) - 1;
   const long long cols = (long long)(g.lad.a0 + last / g.lad.n + 1 - g.lad.b0) * g.lad.n;  // b0 <= a0
-  const long long t = (cols + tn_edge - 1) / tn_edge;
+  const long long t = (cols + tile - 1) / tile;
   return t < g.tn ? (int)t : g.tn;
 }
 
@@ -126,15 +135,16 @@ __global__ __launch_bounds__(256, 2) void gemm_f64_kernel(GemmArgs g) {
   const int per = g.per;
   const int outer = L / per, t = L - outer * per;
   const int b = outer / g.nsplit, split = outer - b * g.nsplit;
-  int band = 0, tr = t;
-  if (g.mode == kIntegrals)
-    for (int c; tr >= (c = BAND * band_columns(g, band, TM, TN)); ++band) tr -= c;
+  static_assert(TM == TN, "square tiles");
+  int band = 0, tr = t, jt0 = 0;
+  if (g.mode == kIntegrals || g.upper)
+    for (int c; tr >= (c = BAND * band_columns(g, band, TM, jt0)); ++band) tr -= c;
   else {
     band = t / (BAND * g.tn);
     tr = t - band * BAND * g.tn;
   }
   const int h = min(BAND, g.tm - band * BAND);
-  const int jt = tr / h, it = band * BAND + (tr - jt * h);
+  const int jt = jt0 + tr / h, it = band * BAND + tr % h;
   const int m0 = it * TM, n0 = jt * TN;
   if (g.upper && m0 >= n0 + TN) return;  // workgroup-uniform, before any barrier
   if (g.mode == kIntegrals && g.lad.b0 + n0 / g.lad.n > g.lad.a0 + (min(m0 + TM, g.M) - 1) / g.lad.n) return;
@@ -304,13 +314,12 @@ __global__ __launch_bounds__(256, 2) void gemm_f64_kernel(GemmArgs g) {
     for (int r = 0; r < 4; ++r) {
       const int gm = m0 + (wr * BM + i) * 16 + kq + 4 * r;
       if (gm >= g.M) continue;
+      double* row = g.part ? g.part + (((size_t)split * g.batch + b) * g.M + gm) * g.N : c_row(g, b, gm);
 #pragma unroll
       for (int j = 0; j < BN; ++j) {
         const int gn = n0 + (wc * BN + j) * 16 + r16;
         if (gn >= g.N) continue;
-        double* dst;
-        if (g.part) dst = g.part + (((size_t)split * g.batch + b) * g.M + gm) * g.N + gn;
-        else dst = g.C + b * g.sC + (size_t)gm * g.ldc + gn;
+        double* dst = row + gn;
         double v = acc[i][j][r];
         if (!g.part) {
           v *= g.alpha;
@@ -339,7 +348,7 @@ __global__ __launch_bounds__(256) void gemm_f64_sum(GemmArgs g, int tile) {
       ladder_store(g.C + (size_t)m * g.lad.n * g.lad.n, g.lad.n, x, y, v, g.mode == kPlus);
       continue;
     }
-    double* dst = g.C + b * g.sC + (size_t)m * g.ldc + n;
+    double* dst = c_row(g, b, m) + n;
     v *= g.alpha;
     *dst = (g.beta != 0.0) ? v + g.beta * *dst : v;
   }
@@ -371,7 +380,7 @@ Config choose_config(int M, int N, int K, int batch, bool upper, size_t part_dou
   for (const auto& t : tiles) {
     const double tm = (M + 32 * t.b - 1) / (32 * t.b), tn = (N + 32 * t.b - 1) / (32 * t.b);
     const double n = tm * tn * batch * (upper ? 0.5 * (1.0 + 1.0 / tn) : 1.0);
-    for (int s = 1; s <= 64; s *= 2) {
+    for (int s = 1; s <= 64; ++s) {
       if (s > 1 && ((size_t)s * batch * M * N > part_doubles || nchunk < 8 * s)) break;
       const int per_unit = (int)std::min(std::ceil(n * s / 256.0), 1e8), rest = per_unit % t.wgs;
       // rounds of as many as fit, then the rest at the rate that fewer reach
@@ -415,9 +424,9 @@ hipError_t launch_gemm(GemmArgs& g, int transA, int transB, double* part, size_t
   g.nsplit = g.kper > 0 ? (nchunk + g.kper - 1) / g.kper : 1;
   g.part = g.nsplit > 1 ? part : nullptr;
   double per = 0.0;
-  if (g.mode == kIntegrals)
-    for (int band = 0; band * BAND < g.tm; ++band)
-      per += (double)std::min(BAND, g.tm - band * BAND) * band_columns(g, band, tile, tile);
+  if (g.mode == kIntegrals || g.upper)
+    for (int band = 0, first; band * BAND < g.tm; ++band)
+      per += (double)std::min(BAND, g.tm - band * BAND) * band_columns(g, band, tile, first);
   else per = (double)g.tm * g.tn;
   const double blocks = per * g.batch * g.nsplit;
   if (blocks > 2147483647.0) return hipErrorInvalidValue;
@@ -437,7 +446,8 @@ hipError_t launch_gemm(GemmArgs& g, int transA, int transB, double* part, size_t
 
 hipError_t gemm_f64(const double* A, int lda, long long sA, int transA, const double* B, int ldb, long long sB,
                     int transB, double* C, int ldc, long long sC, int M, int N, int K, int batch, double alpha,
-                    double beta, hipStream_t st, double* part, size_t part_doubles, bool upper) {
+                    double beta, hipStream_t st, double* part, size_t part_doubles, bool upper,
+                    int row_n, long long row_s) {
   GemmArgs g{};
   g.A = A;
   g.B = B;
@@ -455,6 +465,8 @@ hipError_t gemm_f64(const double* A, int lda, long long sA, int transA, const do
   g.beta = beta;
   g.batch = batch;
   g.upper = upper ? 1 : 0;
+  g.row_n = row_n > 0 ? row_n : (M > 0 ? M : 1);
+  g.row_s = row_s;
   return launch_gemm(g, transA, transB, part, part_doubles, st);
 }
 

@@ -99,9 +99,11 @@ void prof_flush();
 // (may be null): device scratch of part_doubles doubles that the call may use to
 // split a long contraction; it must overlap no operand.  `upper`: only the tiles that
 // reach or lie above the diagonal are formed (what lies below them in C is undefined).
+// row_n > 0: rows in groups, row m of C at (m % row_n) ldc + (m / row_n) row_s.
 hipError_t gemm_f64(const double* A, int lda, long long sA, int transA, const double* B, int ldb, long long sB,
                     int transB, double* C, int ldc, long long sC, int M, int N, int K, int batch, double alpha,
-                    double beta, hipStream_t st, double* part = nullptr, size_t part_doubles = 0, bool upper = false);
+                    double beta, hipStream_t st, double* part = nullptr, size_t part_doubles = 0, bool upper = false,
+                    int row_n = 0, long long row_s = 0);
 
 // Pairs (a, b), b <= a, of the particle-particle ladder: those of the rows a0 <= a < a1, or of
 // one row a0 the part b0 <= b < b1 (else b0 = 0, b1 = a1), packed row by row.
