@@ -107,9 +107,9 @@ __global__ void pair_features_kernel(const double* q2, const double* eps_h, cons
 }
 
 // ------------------------------------------------------------------ network
-// One workgroup of four waves takes tiles of 64 samples; the three 64 x 64 x 64 products
-// of a tile (z2 = h1 W2^T, dz2 W2, dz2^T h1) run on the FP32 matrix pipe (32x32x2, one
-// quadrant per wave), everything between them in registers and LDS:
+// One workgroup of eight waves takes tiles of 64 samples; the products of a tile (z2 = h1 W2^T,
+// dz2 W2, dz2^T h1, dz1^T inputs) run on the FP32 matrix pipe (16x16x4, 32 rows and 16 columns
+// per wave), everything between them in registers and LDS:
 //   kForward   pred, and the activations where the caller wants them
 //   kBackward  parameter gradients from activations and d pred
 //   kTrain     both, with d pred = 2 (pred - y) / n and the loss formed on the way: the
@@ -117,47 +117,66 @@ __global__ void pair_features_kernel(const double* q2, const double* eps_h, cons
 // The gradients of a workgroup's tiles add up in its registers and leave as one row of
 // `partial` (NP parameter gradients, then the sum of squared residuals); at most
 // kMaxGroups rows are summed afterwards in a fixed order.  What bounds a step at ten
-// thousand samples is latency: as five launches (one thread per sample forward, 128
-// samples per workgroup backward, one thread per reduced parameter) it took 179 us at 11000
-// samples, 27 us as two (mlp_kernel 19.7, sum_partials_kernel 4.8).
+// thousand samples is latency, hence two waves per SIMD, conflict-free LDS rows and every
+// read of memory in flight before the first barrier.  A step of 11000 samples: 179 us as
+// five launches (one thread per sample forward, 128 samples per workgroup backward, one
+// thread per reduced parameter), 27 us with four waves and 32x32x2 products (mlp_kernel 19.7),
+// 19 us so (mlp_kernel 12.7, sum_partials_kernel 4.1).  A tanh without branches: no faster.
 enum NetMode { kForward, kBackward, kTrain };
 constexpr int TS = 64;              // samples per tile
-constexpr int LD = H + 1;           // LDS row of a 64-wide matrix
-constexpr int kMaxGroups = 512;
+constexpr int kThreads = 512, kWaves = kThreads / 64;
+constexpr int LD = H + 20;          // LDS row of a 64-wide matrix: 16 rows of 4 columns hit distinct banks, 4 rows of 16 nearly
+constexpr int kMaxGroups = 256;
 constexpr int PROW = (NP + 1 + 3) / 4 * 4;  // floats per row of partial sums
 
-typedef float f16r __attribute__((ext_vector_type(16)));
+typedef float f4r __attribute__((ext_vector_type(4)));
 
 template <int MODE>
-__global__ __launch_bounds__(256, 2) void mlp_kernel(const float* Wp, const float* X, const float* y, int n, float* out,
-                                                  float* cache, const float* dout, float* partial) {
+__global__ __launch_bounds__(kThreads, 1) void mlp_kernel(const float* Wp, const float* X, const float* y, int n, float* out,
+                                                          float* cache, const float* dout, float* partial) {
   __shared__ float w2[H * LD], sh1[TS * LD], sh2[TS * LD], sdz[TS * LD];
-  __shared__ float w1[H * NIN], b1[H], b2[H], w3[H], sx[TS * 8], sdo[TS], red[4][H], lred[4];
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, l32 = lane & 31, hq = lane >> 5;
-  const int qr = (wv >> 1) * 32, qc = (wv & 1) * 32;  // this wave's quadrant
-  for (int k = tid; k < H * H; k += 256) w2[(k >> 6) * LD + (k & 63)] = Wp[OFF_W2 + k];
-  for (int k = tid; k < H * NIN; k += 256) w1[k] = Wp[OFF_W1 + k];
+  __shared__ float w1[H * NIN], b1[H], b2[H], w3[H], sx[TS * 8], sdo[TS], red[2][kWaves][H], lred[2][kWaves];
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, l16 = lane & 15, q4 = lane >> 4;
+  const int rh = (wv >> 2) * 32, cq = (wv & 3) * 16;  // this wave's rows (two blocks of 16) and columns
+  // everything that the first tile reads from memory is in flight at once
+  const int ntile = (n + TS - 1) / TS, xr = tid >> 3, xc = tid & 7;  // row and input of this thread
+  auto input = [&](int tile) {  // column 5 is 1: its gradient is b1's
+    const int s = tile * TS + xr;
+    return xc < NIN && s < n ? X[(size_t)s * NIN + xc] : xc == NIN ? 1.f : 0.f;
+  };
+  auto target = [&](int tile) {
+    const int s = tile * TS + xr;
+    return MODE == kTrain && s < n ? y[s] : 0.f;
+  };
+  static_assert(TS * 8 == kThreads, "an input and an eighth of an output per thread");
+  float wr[H * H / kThreads], xn = input(blockIdx.x), yn = target(blockIdx.x);
+#pragma unroll
+  for (int k = 0; k < H * H / kThreads; ++k) wr[k] = Wp[OFF_W2 + kThreads * k + tid];
+  const float b3 = Wp[OFF_B3];
+  for (int k = tid; k < H * NIN; k += kThreads) w1[k] = Wp[OFF_W1 + k];
   if (tid < H) {
     b1[tid] = Wp[OFF_B1 + tid];
     b2[tid] = Wp[OFF_B2 + tid];
     w3[tid] = Wp[OFF_W3 + tid];
   }
-  const float b3 = Wp[OFF_B3];
-  f16r g2;  // gradient of W2: rows k of the quadrant's row half, columns m
 #pragma unroll
-  for (int r = 0; r < 16; ++r) g2[r] = 0.f;
-  float gx[2] = {0.f, 0.f}, gb2 = 0.f, gw3 = 0.f, gb3 = 0.f, loss = 0.f;
+  for (int k = 0; k < H * H / kThreads; ++k) w2[(kWaves * k + wv) * LD + lane] = wr[k];
+  f4r g2[2], gx;  // gradients of W2 (rows k, columns m) and of W1 and b1 (rows m, columns inputs)
+#pragma unroll
+  for (int r = 0; r < 4; ++r) g2[0][r] = g2[1][r] = gx[r] = 0.f;
+  float gb2 = 0.f, gw3 = 0.f, gb3 = 0.f, loss = 0.f;
   const float two_n = 2.f / (float)n;
-  const int ntile = (n + TS - 1) / TS;
   for (int tile = blockIdx.x; tile < ntile; tile += gridDim.x) {
     const int s0 = tile * TS, ns = min(TS, n - s0);
     __syncthreads();  // the previous tile's readers are done
-    for (int k = tid; k < TS * 8; k += 256) {
-      const int r = k >> 3, c = k & 7;  // column 5 is 1: its gradient is b1's
-      sx[k] = (c < NIN && r < ns) ? X[(size_t)(s0 + r) * NIN + c] : c == NIN ? 1.f : 0.f;
+    sx[tid] = xn;
+    const float yr = yn;
+    if (tile + (int)gridDim.x < ntile) {
+      xn = input(tile + gridDim.x);
+      yn = target(tile + gridDim.x);
     }
     if (MODE == kBackward)
-      for (int k = tid; k < TS * H; k += 256) {
+      for (int k = tid; k < TS * H; k += kThreads) {
         const int r = k >> 6, c = k & 63;
         const float* a = cache + (size_t)(s0 + r) * 2 * H;
         sh1[r * LD + c] = r < ns ? a[c] : 0.f;
@@ -166,14 +185,14 @@ __global__ __launch_bounds__(256, 2) void mlp_kernel(const float* Wp, const floa
     if (MODE == kBackward && tid < TS) sdo[tid] = tid < ns ? dout[s0 + tid] : 0.f;
     __syncthreads();
     if (MODE != kBackward) {
-      {  // h1: thread (k, 16 samples)
-        const int k = tid & 63;
+      {  // h1: thread (k, 8 samples)
+        const int k = lane;
         float wk[NIN];
 #pragma unroll
         for (int c = 0; c < NIN; ++c) wk[c] = w1[k * NIN + c];
         const float bk = b1[k];
 #pragma unroll 4
-        for (int r = wv; r < TS; r += 4) {
+        for (int r = wv; r < TS; r += kWaves) {
           float z = bk;
 #pragma unroll
           for (int c = 0; c < NIN; ++c) z = fmaf(wk[c], sx[r * 8 + c], z);
@@ -183,32 +202,39 @@ __global__ __launch_bounds__(256, 2) void mlp_kernel(const float* Wp, const floa
         }
       }
       __syncthreads();
-      f16r z2;  // rows s of the quadrant, columns k
+      f4r z2[2];  // rows s, columns k
 #pragma unroll
-      for (int r = 0; r < 16; ++r) z2[r] = 0.f;
-#pragma unroll 8
-      for (int m = 0; m < H; m += 2)
-        z2 = __builtin_amdgcn_mfma_f32_32x32x2f32(sh1[(qr + l32) * LD + m + hq], w2[(qc + l32) * LD + m + hq], z2, 0, 0, 0);
+      for (int r = 0; r < 4; ++r) z2[0][r] = z2[1][r] = 0.f;
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {  // register r: row 8 (r / 4) + 4 hq + r % 4
-        const int row = qr + 8 * (r >> 2) + 4 * hq + (r & 3), k = qc + l32;
-        const float h = tanhf(z2[r] + b2[k]);
-        sh2[row * LD + k] = h;
-        if (MODE == kForward && cache && row < ns) cache[(size_t)(s0 + row) * 2 * H + H + k] = h;
+      for (int m = 0; m < H; m += 4) {
+        const float bw = w2[(cq + l16) * LD + m + q4];
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+          z2[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(sh1[(rh + 16 * i + l16) * LD + m + q4], bw, z2[i], 0, 0, 0);
       }
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {  // register r: row 4 (lane / 16) + r
+          const int row = rh + 16 * i + 4 * q4 + r, k = cq + l16;
+          const float h = tanhf(z2[i][r] + b2[k]);
+          sh2[row * LD + k] = h;
+          if (MODE == kForward && cache && row < ns) cache[(size_t)(s0 + row) * 2 * H + H + k] = h;
+        }
       __syncthreads();
-      {  // output: four threads per sample
-        const int r = tid >> 2, q = tid & 3;
+      {  // output: eight threads per sample
+        const int r = xr, q = xc;
         float o = 0.f;
 #pragma unroll
-        for (int k = 0; k < 16; ++k) o = fmaf(w3[4 * k + q], sh2[r * LD + 4 * k + q], o);
+        for (int k = 0; k < 8; ++k) o = fmaf(w3[8 * k + q], sh2[r * LD + 8 * k + q], o);
         o += __shfl_xor(o, 1, 64);
         o += __shfl_xor(o, 2, 64);
+        o += __shfl_xor(o, 4, 64);
         o += b3;
         if (q == 0) {
           if (MODE == kForward && r < ns) out[s0 + r] = o;
           if (MODE == kTrain) {
-            const float e = r < ns ? o - y[s0 + r] : 0.f;
+            const float e = r < ns ? o - yr : 0.f;
             sdo[r] = e * two_n;
             loss = fmaf(e, e, loss);
           }
@@ -217,12 +243,12 @@ __global__ __launch_bounds__(256, 2) void mlp_kernel(const float* Wp, const floa
       if (MODE == kTrain) __syncthreads();
     }
     if (MODE == kForward) continue;
-    // dz2 = dout w3 (1 - h2^2), the gradients of b2 and w3: thread (k, 16 samples)
+    // dz2 = dout w3 (1 - h2^2), the gradients of b2 and w3: thread (k, 8 samples)
     {
-      const int k = tid & 63;
+      const int k = lane;
       const float wk = w3[k];
-#pragma unroll 4
-      for (int r = wv; r < TS; r += 4) {
+#pragma unroll
+      for (int r = wv; r < TS; r += kWaves) {
         const float h = sh2[r * LD + k], d = sdo[r], z = d * wk * (1.f - h * h);
         sdz[r * LD + k] = z;
         gb2 += z;
@@ -231,64 +257,72 @@ __global__ __launch_bounds__(256, 2) void mlp_kernel(const float* Wp, const floa
     }
     if (tid < TS) gb3 += sdo[tid];
     __syncthreads();
-    f16r z1;  // dz2 W2: rows s, columns m
+    f4r z1[2];  // dz2 W2: rows s, columns m
 #pragma unroll
-    for (int r = 0; r < 16; ++r) z1[r] = 0.f;
-#pragma unroll 8
-    for (int k = 0; k < H; k += 2) {
-      z1 = __builtin_amdgcn_mfma_f32_32x32x2f32(sdz[(qr + l32) * LD + k + hq], w2[(k + hq) * LD + qc + l32], z1, 0, 0, 0);
-      g2 = __builtin_amdgcn_mfma_f32_32x32x2f32(sdz[(k + hq) * LD + qr + l32], sh1[(k + hq) * LD + qc + l32], g2, 0, 0, 0);
-    }
-    // dz1 (over h2, which is no longer needed) and the gradients of W1 and b1
+    for (int r = 0; r < 4; ++r) z1[0][r] = z1[1][r] = 0.f;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int row = qr + 8 * (r >> 2) + 4 * hq + (r & 3), m = qc + l32;
-      const float h = sh1[row * LD + m];
-      sh2[row * LD + m] = z1[r] * (1.f - h * h);
-    }
-    __syncthreads();
+    for (int k = 0; k < H; k += 4) {
+      const float bw = w2[(k + q4) * LD + cq + l16], bh = sh1[(k + q4) * LD + cq + l16];
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const int c = (tid >> 6) + 4 * i;  // inputs 0 .. 4, then the constant
-      if (c <= NIN) {
-        float acc = 0.f;
-#pragma unroll 8
-        for (int r = 0; r < TS; ++r) acc = fmaf(sh2[r * LD + (tid & 63)], sx[r * 8 + c], acc);
-        gx[i] += acc;
+      for (int i = 0; i < 2; ++i) {
+        z1[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(sdz[(rh + 16 * i + l16) * LD + k + q4], bw, z1[i], 0, 0, 0);
+        g2[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(sdz[(k + q4) * LD + rh + 16 * i + l16], bh, g2[i], 0, 0, 0);
       }
+    }
+    // dz1 (over h2, which is no longer needed), then the gradients of W1 and b1: dz1^T times
+    // the inputs, four waves with 16 rows m each (columns 8 to 15 repeat 0 to 7)
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int row = rh + 16 * i + 4 * q4 + r, m = cq + l16;
+        const float h = sh1[row * LD + m];
+        sh2[row * LD + m] = z1[i][r] * (1.f - h * h);
+      }
+    __syncthreads();
+    if (wv < 4) {
+#pragma unroll
+      for (int r = 0; r < TS; r += 4)
+        gx = __builtin_amdgcn_mfma_f32_16x16x4f32(sh2[(r + q4) * LD + cq + l16], sx[(r + q4) * 8 + (l16 & 7)], gx, 0, 0, 0);
     }
   }
   if (MODE == kForward) return;
   float* part = partial + (size_t)blockIdx.x * PROW;
 #pragma unroll
-  for (int r = 0; r < 16; ++r) part[OFF_W2 + (qr + 8 * (r >> 2) + 4 * hq + (r & 3)) * H + qc + l32] = g2[r];
+  for (int i = 0; i < 2; ++i)
 #pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const int c = (tid >> 6) + 4 * i, k = tid & 63;
-    if (c < NIN) part[OFF_W1 + k * NIN + c] = gx[i];
-    else if (c == NIN) part[OFF_B1 + k] = gx[i];
+    for (int r = 0; r < 4; ++r) part[OFF_W2 + (rh + 16 * i + 4 * q4 + r) * H + cq + l16] = g2[i][r];
+  if (wv < 4) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int m = cq + 4 * q4 + r;
+      if (l16 < NIN) part[OFF_W1 + m * NIN + l16] = gx[r];
+      else if (l16 == NIN) part[OFF_B1 + m] = gx[r];
+    }
   }
-  __syncthreads();
-  red[wv][lane] = gb2;
-  __syncthreads();
-  if (tid < H) part[OFF_B2 + tid] = (red[0][tid] + red[1][tid]) + (red[2][tid] + red[3][tid]);
-  __syncthreads();
-  red[wv][lane] = gw3;
-  __syncthreads();
-  if (tid < H) part[OFF_W3 + tid] = (red[0][tid] + red[1][tid]) + (red[2][tid] + red[3][tid]);
+  red[0][wv][lane] = gb2;
+  red[1][wv][lane] = gw3;
   for (int o = 32; o > 0; o >>= 1) {
     gb3 += __shfl_xor(gb3, o, 64);
     loss += __shfl_xor(loss, o, 64);
   }
-  if (lane == 0) lred[wv] = loss;
+  if (lane == 0) {
+    lred[0][wv] = gb3;
+    lred[1][wv] = loss;
+  }
   __syncthreads();
-  if (tid == 0) {
-    part[OFF_B3] = gb3;
-    part[NP] = (lred[0] + lred[1]) + (lred[2] + lred[3]);
+  if (tid < 2 * H + 2) {
+    const int which = tid < 2 * H ? tid >> 6 : tid & 1;
+    const float* v = tid < 2 * H ? &red[which][0][lane] : lred[which];
+    const int step = tid < 2 * H ? H : 1;
+    float acc = 0.f;
+#pragma unroll
+    for (int k = 0; k < kWaves; ++k) acc += v[k * step];
+    part[tid >= 2 * H ? (which ? NP : OFF_B3) : (which ? OFF_W3 : OFF_B2) + lane] = acc;
   }
 }
 
-// Sums the rows of partial (32 parameters x 8 threads a workgroup), then dW or, training,
+// Sums the rows of partial (32 parameters x 16 threads a workgroup), then dW or, training,
 // Adam on the parameter and the loss
 struct AdamArgs {
   float *W, *m, *v, *loss;
@@ -304,18 +338,18 @@ __device__ inline void adam_update(float& W, float& m, float& v, float g, const 
 }
 
 template <bool kAdam>
-__global__ __launch_bounds__(256) void sum_partials_kernel(const float* partial, int nblk, float* dW, AdamArgs a) {
-  __shared__ float sh[8][32];
+__global__ __launch_bounds__(512) void sum_partials_kernel(const float* partial, int nblk, float* dW, AdamArgs a) {
+  __shared__ float sh[16][32];
   const int c = threadIdx.x & 31, q = threadIdx.x >> 5, k = blockIdx.x * 32 + c;
   float acc = 0.f;
   if (k <= NP) {
 #pragma unroll 4
-    for (int b = q; b < nblk; b += 8) acc += partial[(size_t)b * PROW + k];
+    for (int b = q; b < nblk; b += 16) acc += partial[(size_t)b * PROW + k];
   }
   sh[q][c] = acc;
   __syncthreads();
   if (q != 0 || k > NP) return;
-  acc = ((sh[0][c] + sh[1][c]) + (sh[2][c] + sh[3][c])) + ((sh[4][c] + sh[5][c]) + (sh[6][c] + sh[7][c]));
+  for (int b = 1; b < 16; ++b) acc += sh[b][c];
   if (kAdam) {
     if (k < NP) adam_update(a.W[k], a.m[k], a.v[k], acc, a);
     else *a.loss = acc * a.inv_n;
@@ -463,7 +497,7 @@ int pairscreen_mlp_forward(const float* W, const float* feats, int64_t n, float*
   if (n == 0) return DFPT2_OK;
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   ProfScope ps(DFPT2_STAGE_SCREEN, s);
-  hipLaunchKernelGGL(mlp_kernel<kForward>, dim3((unsigned)std::min<int64_t>((n + TS - 1) / TS, 2048)), dim3(256), 0, s, W,
+  hipLaunchKernelGGL(mlp_kernel<kForward>, dim3((unsigned)std::min<int64_t>((n + TS - 1) / TS, 2048)), dim3(kThreads), 0, s, W,
                      feats, nullptr, (int)n, pred, act_cache, nullptr, nullptr);
   hipError_t e = hipGetLastError();
   return e == hipSuccess ? DFPT2_OK : hip_fail(e, "mlp forward");
@@ -489,9 +523,9 @@ int pairscreen_mlp_backward(const float* W, const float* feats, const float* act
   ProfScope ps(DFPT2_STAGE_SCREEN, s);
   float* partial = static_cast<float*>(workspace);
   const int nblk = net_groups(n, need / sizeof(float));
-  hipLaunchKernelGGL(mlp_kernel<kBackward>, dim3(nblk), dim3(256), 0, s, W, feats, nullptr, (int)n, nullptr,
+  hipLaunchKernelGGL(mlp_kernel<kBackward>, dim3(nblk), dim3(kThreads), 0, s, W, feats, nullptr, (int)n, nullptr,
                      const_cast<float*>(act_cache), dpred, partial);
-  hipLaunchKernelGGL(sum_partials_kernel<false>, dim3((NP + 32) / 32), dim3(256), 0, s, partial, nblk, dW, AdamArgs{});
+  hipLaunchKernelGGL(sum_partials_kernel<false>, dim3((NP + 32) / 32), dim3(512), 0, s, partial, nblk, dW, AdamArgs{});
   hipError_t e = hipGetLastError();
   return e == hipSuccess ? DFPT2_OK : hip_fail(e, "mlp backward");
 }
@@ -538,12 +572,12 @@ int pairscreen_train(float* W, float* m, float* v, const float* feats, const flo
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   for (int64_t t = 1; t <= steps; ++t) {
     ProfScope ps(DFPT2_STAGE_SCREEN, s);
-    hipLaunchKernelGGL(mlp_kernel<kTrain>, dim3(nblk), dim3(256), 0, s, W, feats, y, (int)n, nullptr, nullptr, nullptr,
+    hipLaunchKernelGGL(mlp_kernel<kTrain>, dim3(nblk), dim3(kThreads), 0, s, W, feats, y, (int)n, nullptr, nullptr, nullptr,
                        partial);
     AdamArgs a = adam_args(W, m, v, lr, 0.9f, 0.999f, 1e-8f, step0 + t);
     a.loss = losses + (t - 1);
     a.inv_n = 1.f / (float)n;
-    hipLaunchKernelGGL(sum_partials_kernel<true>, dim3((NP + 32) / 32), dim3(256), 0, s, partial, nblk, nullptr, a);
+    hipLaunchKernelGGL(sum_partials_kernel<true>, dim3((NP + 32) / 32), dim3(512), 0, s, partial, nblk, nullptr, a);
     const hipError_t le = hipGetLastError();
     if (le != hipSuccess) return hip_fail(le, "train");
   }
