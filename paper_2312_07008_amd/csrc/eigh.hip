@@ -452,13 +452,14 @@ __global__ __launch_bounds__(kResThreads) void tridiag_resident(const double* A_
 // a column with a launch each, 1.5 us so.
 template <int N4>
 __global__ __launch_bounds__(16 * N4) void tridiag_small(const double* A_in, int n, double* A_out, double* Vs,
-                                                         double* tau, double* d, double* e, double* p_last) {
+                                                         double* tau, double* d, double* e, double* p_last, int* status) {
   constexpr int NC = 4 * N4, NW = N4 / 4;
   __shared__ double ps[NC], rs[NC];          // p of the previous column, row k
   __shared__ double ws[NC], vs[NC], xs[NC];  // w, v of the previous column, x of this one (0 up to k + 1)
   __shared__ double part1[NW], part2[NW], sc[1];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, row = tid >> 2, q4 = tid & 3;
   double a[N4], vo = 0.0, v_row = 0.0, t_prev = 0.0;
+  if (tid == 0) *status = 0;
 #pragma unroll
   for (int i = 0; i < N4; ++i) {
     const int c = 4 * i + q4;
@@ -545,7 +546,8 @@ __global__ __launch_bounds__(16 * N4) void tridiag_small(const double* A_in, int
 }
 
 // slots of the resident form
-__global__ void fill_empty(unsigned long long* p, size_t n) {
+__global__ void fill_empty(unsigned long long* p, size_t n, int* status) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) *status = 0;
   for (size_t k = blockIdx.x * (size_t)blockDim.x + threadIdx.x; k < n; k += (size_t)gridDim.x * blockDim.x) p[k] = kEmpty;
 }
 
@@ -562,12 +564,12 @@ hipError_t launch_resident_multi(const double* A_in, int n, double* A_out, doubl
 bool launch_resident(const double* A_in, int n, double* A_out, double* Vs, double* tau, double* d, double* e,
                      unsigned long long* P, unsigned long long* R, double* p_last, int* status, hipStream_t st) {
   if (n <= kSmallMax) {
-    if (n <= 64) hipLaunchKernelGGL(tridiag_small<16>, dim3(1), dim3(256), 0, st, A_in, n, A_out, Vs, tau, d, e, p_last);
-    else hipLaunchKernelGGL(tridiag_small<32>, dim3(1), dim3(512), 0, st, A_in, n, A_out, Vs, tau, d, e, p_last);
+    if (n <= 64) hipLaunchKernelGGL(tridiag_small<16>, dim3(1), dim3(256), 0, st, A_in, n, A_out, Vs, tau, d, e, p_last, status);
+    else hipLaunchKernelGGL(tridiag_small<32>, dim3(1), dim3(512), 0, st, A_in, n, A_out, Vs, tau, d, e, p_last, status);
     return true;
   }
   const size_t slots = 2 * (size_t)n * n;
-  hipLaunchKernelGGL(fill_empty, dim3((unsigned)std::min<size_t>(2048, (slots + 255) / 256)), dim3(256), 0, st, P, slots);
+  hipLaunchKernelGGL(fill_empty, dim3((unsigned)std::min<size_t>(2048, (slots + 255) / 256)), dim3(256), 0, st, P, slots, status);
   hipError_t err = hipErrorInvalidValue;
 #define DFPT2_RESIDENT(J) err = launch_resident_multi<J, kResRows>(A_in, n, A_out, Vs, tau, d, e, P, R, p_last, status, st)
   if (n <= 256) DFPT2_RESIDENT(4);
@@ -584,20 +586,17 @@ bool launch_resident(const double* A_in, int n, double* A_out, double* Vs, doubl
 
 // d[n-2], d[n-1], e[n-2] from the last 2 x 2 block, with the update of column n - 3
 // still pending when the lazy steps were used (p_last = p of column n - 3)
-__global__ void tridiag_tail_lazy(const double* A, int n, const double* Vs, const double* tau,
-                                  const double* p_last, double* d, double* e) {
-  if (threadIdx.x != 0) return;
-  const double* v = Vs + (size_t)(n - 3) * n;  // entries 0, 1 <-> indices n - 2, n - 1
-  const double K = 0.5 * tau[n - 3] * (p_last[0] * v[0] + p_last[1] * v[1]);
-  const double w0 = p_last[0] - K * v[0], w1 = p_last[1] - K * v[1];
-  d[n - 2] = A[(size_t)(n - 2) * n + (n - 2)] - 2.0 * v[0] * w0;
-  d[n - 1] = A[(size_t)(n - 1) * n + (n - 1)] - 2.0 * v[1] * w1;
-  e[n - 2] = A[(size_t)(n - 1) * n + (n - 2)] - (v[1] * w0 + w1 * v[0]);
-}
-
-__global__ void tridiag_tail(const double* A, int n, double* d, double* e) {
-  if (threadIdx.x != 0) return;
-  if (n >= 2) {
+// the last 2 x 2 block of the reduced matrix (one thread)
+__device__ inline void tridiag_tail(const double* A, int n, const double* Vs, const double* tau, const double* p_last,
+                                    double* d, double* e) {
+  if (p_last) {  // with the update of column n - 3 pending
+    const double* v = Vs + (size_t)(n - 3) * n;  // entries 0, 1 <-> indices n - 2, n - 1
+    const double K = 0.5 * tau[n - 3] * (p_last[0] * v[0] + p_last[1] * v[1]);
+    const double w0 = p_last[0] - K * v[0], w1 = p_last[1] - K * v[1];
+    d[n - 2] = A[(size_t)(n - 2) * n + (n - 2)] - 2.0 * v[0] * w0;
+    d[n - 1] = A[(size_t)(n - 1) * n + (n - 1)] - 2.0 * v[1] * w1;
+    e[n - 2] = A[(size_t)(n - 1) * n + (n - 2)] - (v[1] * w0 + w1 * v[0]);
+  } else if (n >= 2) {
     d[n - 2] = A[(size_t)(n - 2) * n + (n - 2)];
     d[n - 1] = A[(size_t)(n - 1) * n + (n - 1)];
     e[n - 2] = A[(size_t)(n - 1) * n + (n - 2)];
@@ -611,12 +610,16 @@ __global__ void tridiag_tail(const double* A, int n, double* d, double* e) {
 // = first and one past the last position of the block containing pos.  Also the norm.
 // One workgroup; every thread owns a run of positions, the starts are a prefix maximum
 // and the ends a suffix minimum over the runs (a single thread took 450 us at n = 1200).
-__global__ __launch_bounds__(1024) void tridiag_split(int n, const double* d, double* e, int* blk_start,
-                                                      int* blk_end, double* tnorm) {
+// First the reduction's last 2 x 2 block (p_last: see tridiag_tail).
+__global__ __launch_bounds__(1024) void tridiag_split(int n, double* d, double* e, int* blk_start, int* blk_end,
+                                                      double* tnorm, const double* A, const double* Vs, const double* tau,
+                                                      const double* p_last) {
   __shared__ double shn[1024];
   __shared__ int last[1024], first[1024];
   const int tid = threadIdx.x, per = (n + 1023) / 1024;
   const int i0 = min(n, tid * per), i1 = min(n, i0 + per);
+  if (tid == 0) tridiag_tail(A, n, Vs, tau, p_last, d, e);
+  __syncthreads();
   double nrm = 0.0;
   for (int i = i0; i < i1; ++i)
     nrm = fmax(nrm, fabs(d[i]) + (i > 0 ? fabs(e[i - 1]) : 0.0) + (i + 1 < n ? fabs(e[i]) : 0.0));
@@ -667,8 +670,8 @@ __device__ inline double fast_rcp(double q) {
   return fma(fma(-q, r, 1.0), r, r);
 }
 
-// Sturm counts (eigenvalues of the block smaller than x) at two points in one pass over
-// the block, two chains in flight.  In the scaled form below (kProduct) T is scaled by a
+// Sturm counts (eigenvalues of the block smaller than x) at P points in one pass over
+// the block, P chains in flight.  In the scaled form below (kProduct) T is scaled by a
 // power of two to ||T|| <= 1 and the count is the number of sign changes of
 //     p_{i+1} = (d_i - x) p_i - e_{i-1}^2 p_{i-1},
 // rescaled by a power of two every 8 steps: three FP64 operations a step instead of the
@@ -676,81 +679,93 @@ __device__ inline double fast_rcp(double q) {
 // is q_i with d - x and e off by a few relative roundings).  A zero p_i takes either sign
 // for exactly one change between its neighbours, as it should.  It needs e^2 >= 1e-60 in
 // the scaled block, so that 8 steps cannot underflow; otherwise the q form runs.
-template <bool kProduct>
-__device__ inline void sturm_pair(const double* d, const double* e, int s, int t, double xa, double xb, double pivmin,
-                                  int& ca, int& cb) {
-  ca = cb = 0;
+template <bool kProduct, int P>
+__device__ inline void sturm(const double* d, const double* e, int s, int t, const double (&x)[P], double pivmin, int (&c)[P]) {
+  double q[P], q0[P];
+#pragma unroll
+  for (int k = 0; k < P; ++k) {
+    q[k] = d[s] - x[k];
+    if (!kProduct && fabs(q[k]) < pivmin) q[k] = -pivmin;
+    c[k] = q[k] < 0.0;
+    q0[k] = 1.0;
+  }
   if (kProduct) {
-    double a0 = 1.0, b0 = 1.0, a1 = d[s] - xa, b1 = d[s] - xb;
-    ca = a1 < 0.0;
-    cb = b1 < 0.0;
     auto hi = [](double v) { return (unsigned)(__builtin_bit_cast(unsigned long long, v) >> 32); };
     for (int i0 = s + 1; i0 < t; i0 += 8) {
       const int m = min(8, t - i0);
       auto step = [&](int i) {
         const double di = d[i], e2 = e[i - 1];  // LDS holds e^2
-        const double a2 = fma(di - xa, a1, -e2 * a0), b2 = fma(di - xb, b1, -e2 * b0);
-        ca += (hi(a2) ^ hi(a1)) >> 31;
-        cb += (hi(b2) ^ hi(b1)) >> 31;
-        a0 = a1;
-        b0 = b1;
-        a1 = a2;
-        b1 = b2;
+#pragma unroll
+        for (int k = 0; k < P; ++k) {
+          const double q2 = fma(di - x[k], q[k], -e2 * q0[k]);
+          c[k] += (hi(q2) ^ hi(q[k])) >> 31;
+          q0[k] = q[k];
+          q[k] = q2;
+        }
       };
       if (m == 8) {
 #pragma unroll
-        for (int q = 0; q < 8; ++q) step(i0 + q);
+        for (int r = 0; r < 8; ++r) step(i0 + r);
       } else {
-        for (int q = 0; q < m; ++q) step(i0 + q);
+        for (int r = 0; r < m; ++r) step(i0 + r);
       }
-      const int ea = __builtin_amdgcn_frexp_exp(fmax(fabs(a0), fabs(a1))), eb = __builtin_amdgcn_frexp_exp(fmax(fabs(b0), fabs(b1)));
-      a0 = __builtin_amdgcn_ldexp(a0, -ea);
-      a1 = __builtin_amdgcn_ldexp(a1, -ea);
-      b0 = __builtin_amdgcn_ldexp(b0, -eb);
-      b1 = __builtin_amdgcn_ldexp(b1, -eb);
+#pragma unroll
+      for (int k = 0; k < P; ++k) {
+        const int ex = __builtin_amdgcn_frexp_exp(fmax(fabs(q0[k]), fabs(q[k])));
+        q0[k] = __builtin_amdgcn_ldexp(q0[k], -ex);
+        q[k] = __builtin_amdgcn_ldexp(q[k], -ex);
+      }
     }
   } else {
-    double qa = d[s] - xa, qb = d[s] - xb;
-    if (fabs(qa) < pivmin) qa = -pivmin;
-    if (fabs(qb) < pivmin) qb = -pivmin;
-    ca = qa < 0.0;
-    cb = qb < 0.0;
     for (int i = s + 1; i < t; ++i) {
       const double di = d[i], e2 = e[i - 1] * e[i - 1];
-      qa = fma(-e2, fast_rcp(qa), di - xa);
-      qb = fma(-e2, fast_rcp(qb), di - xb);
-      if (fabs(qa) < pivmin) qa = -pivmin;
-      if (fabs(qb) < pivmin) qb = -pivmin;
-      ca += qa < 0.0;
-      cb += qb < 0.0;
+#pragma unroll
+      for (int k = 0; k < P; ++k) {
+        q[k] = fma(-e2, fast_rcp(q[k]), di - x[k]);
+        if (fabs(q[k]) < pivmin) q[k] = -pivmin;
+        c[k] += q[k] < 0.0;
+      }
     }
   }
 }
 
-// Bracket [lo, hi] of the j-th eigenvalue of the block [s, t) shrunk by a wave: each lane
-// takes the counts at two of 128 interior points, and the bracket becomes the interval
-// between the highest point whose count is <= j and the next one (129x per round, ~8
-// rounds).  The invariant count(lo) <= j < count(hi) holds whatever the rounding.
-template <bool kProduct>
+// Bracket [lo, hi] of the j-th eigenvalue of the block [s, t) shrunk by W waves of P points a
+// lane: the bracket becomes the interval between the highest point whose count is <= j and
+// the next one (64 W P + 1 times smaller per round, 7 to 8 rounds).  The invariant count(lo) <=
+// j < count(hi) holds whatever the rounding.
+template <bool kProduct, int W, int P>
 __device__ double multisect(const double* d, const double* e, int s, int t, int j, double lo, double hi,
-                            double pivmin, int lane) {
+                            double pivmin, int wv, int lane, unsigned long long (*masks)[W][P]) {
+  constexpr int N = 64 * W * P;
   for (int it = 0; it < 64; ++it) {
     if (hi - lo <= 2.0 * DBL_EPSILON * fmax(fabs(lo), fabs(hi)) + pivmin) break;
-    const double h = (hi - lo) / 129.0;
-    const double xa = fmin(fmax(lo + (double)(2 * lane + 1) * h, lo), hi);
-    const double xb = fmin(fmax(lo + (double)(2 * lane + 2) * h, lo), hi);
-    int ca, cb;
-    sturm_pair<kProduct>(d, e, s, t, xa, xb, pivmin, ca, cb);
-    const bool la = (xa <= lo) ? true : (xa >= hi) ? false : ca <= j;
-    const bool lb = (xb <= lo) ? true : (xb >= hi) ? false : cb <= j;
-    // points in order: 2 lane (a), 2 lane + 1 (b)
-    const unsigned long long ma = __ballot(la), mb = __ballot(lb);
-    const int klo = max(ma ? 2 * (63 - __clzll((long long)ma)) : -1, mb ? 2 * (63 - __clzll((long long)mb)) + 1 : -1);
-    const int khi = klo + 1;
-    const int l0 = (klo < 0 ? 0 : klo) >> 1, l1 = (khi > 127 ? 127 : khi) >> 1;
-    const double lo_a = __shfl(xa, l0, 64), lo_b = __shfl(xb, l0, 64), hi_a = __shfl(xa, l1, 64), hi_b = __shfl(xb, l1, 64);
-    const double nlo = klo >= 0 ? ((klo & 1) ? lo_b : lo_a) : lo;
-    const double nhi = khi < 128 ? ((khi & 1) ? hi_b : hi_a) : hi;
+    const double h = (hi - lo) / (N + 1.0);
+    auto point = [&](int k) { return fmin(fmax(fma((double)(k + 1), h, lo), lo), hi); };
+    double x[P];
+    int c[P], klo = -1;
+#pragma unroll
+    for (int k = 0; k < P; ++k) x[k] = point((wv * 64 + lane) * P + k);
+    sturm<kProduct, P>(d, e, s, t, x, pivmin, c);
+#pragma unroll
+    for (int k = 0; k < P; ++k) {
+      unsigned long long m = __ballot((x[k] <= lo) ? true : (x[k] >= hi) ? false : c[k] <= j);
+      if (W == 1) {
+        if (m) klo = max(klo, P * (63 - __clzll((long long)m)) + k);
+      } else if (lane == 0) {
+        masks[it & 1][wv][k] = m;
+      }
+    }
+    if (W > 1) {  // the same rounds in every wave: one barrier each, masks of two rounds
+      __syncthreads();
+#pragma unroll
+      for (int w = 0; w < W; ++w)
+#pragma unroll
+        for (int k = 0; k < P; ++k) {
+          const unsigned long long m = masks[it & 1][w][k];
+          if (m) klo = max(klo, P * (64 * w + 63 - __clzll((long long)m)) + k);
+        }
+    }
+    const double nlo = klo >= 0 ? point(klo) : lo, nhi = klo + 1 < N ? point(klo + 1) : hi;
     if (!(nlo > lo || nhi < hi)) break;  // the points no longer split the bracket
     lo = nlo;
     hi = nhi;
@@ -758,20 +773,35 @@ __device__ double multisect(const double* d, const double* e, int s, int t, int 
   return 0.5 * (lo + hi);
 }
 
-// Wave g (four per workgroup): the (g - start)-th eigenvalue of the block containing
-// position g.  What bounds it is the issue of the counts' FP64 operations.  d and e^2 (or
-// e) come from LDS up to n = kSturmLds.  n = 1200: 1.8 ms with one point per lane, full
-// divisions and global reads; 1.3 ms with two points and fast reciprocals; 0.5 ms in the
-// product form.
+// The (g - start)-th eigenvalue of the block containing position g: one wave of two points a
+// lane, four of them a workgroup (W = 1), or a workgroup of W waves of one point.  What
+// bounds it is the issue of the counts' FP64 operations, and up to 512 positions, which leave
+// SIMDs idle, the chain of one count.  d and e^2 (or e) come from LDS up to n = kSturmLds.
+// n = 1200: 1.8 ms with one point per lane, full divisions and global reads; 1.3 ms with two
+// points and fast reciprocals; 0.5 ms in the product form.  n = 60: 33 us with W = 1, 21 us
+// with W = 4.  The last blocks form the factors of the back-transformation (wy16_t), which
+// takes no time of its own here.
 constexpr int kSturmLds = 4096;
 
-template <bool kLds>
+__device__ void wy16_t(int blk, int n, const double* Vs, const double* tau, double* Tout, double* sh);
+constexpr int kWySh = 4 * 256 + 16 * 17;  // doubles of LDS
+
+template <bool kLds, int W>
 __global__ __launch_bounds__(256) void tridiag_multisect(int n, const double* dg, const double* eg,
                                                          const int* blk_start, const int* blk_end,
-                                                         const double* tnorm, double* lam) {
+                                                         const double* tnorm, double* lam, int nblk,
+                                                         const double* Vs, const double* tau, double* Tout) {
+  constexpr int G = W == 1 ? 4 : 1, P = W == 1 ? 2 : 1;  // eigenvalues per workgroup, points per lane
   extern __shared__ double msh[];
   __shared__ int small;
-  const int g = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  __shared__ unsigned long long masks[2][W][P];
+  const int first = (n + G - 1) / G;
+  if ((int)blockIdx.x >= first) {
+    if ((int)blockIdx.x - first < nblk) wy16_t(blockIdx.x - first, n, Vs, tau, Tout, msh);
+    return;
+  }
+  const int wv = W == 1 ? 0 : threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int g = W == 1 ? blockIdx.x * 4 + (threadIdx.x >> 6) : blockIdx.x;
   const double nrm = fmax(*tnorm, DBL_MIN);
   int ex = 0;
   bool product = false;
@@ -793,7 +823,7 @@ __global__ __launch_bounds__(256) void tridiag_multisect(int n, const double* dg
       for (int i = threadIdx.x; i < n; i += blockDim.x) msh[n + i] *= msh[n + i];  // e^2
     __syncthreads();
   }
-  if (g >= n) return;  // wave-uniform
+  if (g >= n) return;  // wave-uniform; only where W == 1
   const int s = blk_start[g], t = blk_end[g], j = g - s;
   double lo = DBL_MAX, hi = -DBL_MAX;
   for (int i = s + lane; i < t; i += 64) {
@@ -812,10 +842,10 @@ __global__ __launch_bounds__(256) void tridiag_multisect(int n, const double* dg
   hi += pad;
   double x;
   if (product)  // in units of 2^ex (exact)
-    x = ldexp(multisect<true>(msh, msh + n, s, t, j, ldexp(lo, -ex), ldexp(hi, -ex), 8.0 * DBL_MIN, lane), ex);
+    x = ldexp(multisect<true, W, P>(msh, msh + n, s, t, j, ldexp(lo, -ex), ldexp(hi, -ex), 8.0 * DBL_MIN, wv, lane, masks), ex);
   else
-    x = multisect<false>(dg, eg, s, t, j, lo, hi, pivmin, lane);
-  if (lane == 0) lam[g] = x;
+    x = multisect<false, W, P>(dg, eg, s, t, j, lo, hi, pivmin, wv, lane, masks);
+  if (lane == 0 && wv == 0) lam[g] = x;
 }
 
 // ------------------------------------------------------------ twisted factorization
@@ -1281,14 +1311,14 @@ __device__ inline double wy16_v(const double* Vs, int n, int k0, int nr, int i, 
   return (j < nr && i > k && i < n) ? Vs[(size_t)k * n + (i - k - 1)] : 0.0;
 }
 
-// T of every block ([16][16], upper triangular): S = V^T V, then each row by itself
-__global__ __launch_bounds__(256) void wy16_build_t(int n, const double* Vs, const double* tau, double* Tout) {
-  __shared__ double part[4][256];
-  __shared__ double S[16][17];
-  const int k0 = blockIdx.x * WY16, nr = min(WY16, n - 2 - k0);  // reflectors 0 .. n - 3
+// T of block blk ([16][16], upper triangular): S = V^T V, then each row by itself; 256 threads
+__device__ void wy16_t(int blk, int n, const double* Vs, const double* tau, double* Tout, double* sh) {
+  double(*part)[256] = reinterpret_cast<double(*)[256]>(sh);
+  double(*S)[17] = reinterpret_cast<double(*)[17]>(sh + 4 * 256);
+  const int k0 = blk * WY16, nr = min(WY16, n - 2 - k0);  // reflectors 0 .. n - 3
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, r16 = lane & 15, kq = lane >> 4;
   d4 acc = (d4){0.0, 0.0, 0.0, 0.0};
-  for (int rb = k0 / 16 * 16 + 16 * w; rb < n; rb += 64)
+  for (int rb = k0 / 16 * 16 + 16 * w; rb < n; rb += 16 * (blockDim.x >> 6))
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const double v = wy16_v(Vs, n, k0, nr, rb + 4 * r + kq, r16);
@@ -1297,7 +1327,11 @@ __global__ __launch_bounds__(256) void wy16_build_t(int n, const double* Vs, con
 #pragma unroll
   for (int r = 0; r < 4; ++r) part[w][(kq + 4 * r) * 16 + r16] = acc[r];
   __syncthreads();
-  S[tid >> 4][tid & 15] = (part[0][tid] + part[1][tid]) + (part[2][tid] + part[3][tid]);
+  for (int k = tid; k < 256; k += blockDim.x) {
+    double v = part[0][k];
+    for (int q = 1; q < (int)(blockDim.x >> 6); ++q) v += part[q][k];
+    S[k >> 4][k & 15] = v;
+  }
   __syncthreads();
   if (tid < 16) {  // T_cc = tau_c, T[i][c] = -tau_c sum_l T[i][l] S[l][c]
     double T[16];
@@ -1308,9 +1342,14 @@ __global__ __launch_bounds__(256) void wy16_build_t(int n, const double* Vs, con
 #pragma unroll
       for (int l = 0; l < c; ++l) sum += (l >= tid ? T[l] : 0.0) * S[l][c];
       T[c] = c < tid ? 0.0 : c == tid ? tc : -tc * sum;
-      Tout[(size_t)blockIdx.x * 256 + tid * 16 + c] = T[c];
+      Tout[(size_t)blk * 256 + tid * 16 + c] = T[c];
     }
   }
+}
+
+__global__ __launch_bounds__(256) void wy16_build_t(int n, const double* Vs, const double* tau, double* Tout) {
+  __shared__ double sh[kWySh];
+  wy16_t(blockIdx.x, n, Vs, tau, Tout, sh);
 }
 
 template <int NB>
@@ -1386,20 +1425,6 @@ __global__ __launch_bounds__(512) void backtransform16(int n, const double* Vs, 
 }
 
 // ------------------------------------------------------------ sort + orient
-// rank of eigenvalue g among all (ties by index), ascending; one wave per eigenvalue
-__global__ __launch_bounds__(256) void eig_rank(int n, const double* lam, int* rank) {
-  const int g = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-  if (g >= n) return;
-  const double x = lam[g];
-  int r = 0;
-  for (int q = lane; q < n; q += 64) {
-    const double y = lam[q];
-    r += (y < x || (y == x && q < g)) ? 1 : 0;
-  }
-  for (int o = 32; o > 0; o >>= 1) r += __shfl_xor(r, o, 64);
-  if (lane == 0) rank[g] = r;
-}
-
 // out column dst(g) = sign-oriented column g; descending: dst = n-1-rank
 // M = I - U with U = strictly upper part of E + diag(E) / 2, where E = Z^T Z - I
 // arrives as G = Z^T Z in M (in place)
@@ -1412,9 +1437,22 @@ __global__ void orth_correction(int n, double* M) {
   }
 }
 
-// One workgroup per 16 columns (whole 128-byte lines), 64 rows at a time.
-__global__ __launch_bounds__(1024) void eig_permute(int n, const double* lam, const int* rank, const double* Zin,
-                                                    double* w_out, double* Z_out, int descending) {
+// One workgroup per 16 columns (whole 128-byte lines), 64 rows at a time; wave w finds the
+// rank of column w among all eigenvalues (ascending, ties by index).
+__global__ __launch_bounds__(1024) void eig_permute(int n, const double* lam, const double* Zin, double* w_out,
+                                                    double* Z_out, int descending) {
+  __shared__ int rank[16];
+  {
+    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, g = min((int)blockIdx.x * 16 + w, n - 1);
+    const double x = lam[g];
+    int r = 0;
+    for (int q = lane; q < n; q += 64) {
+      const double y = lam[q];
+      r += (y < x || (y == x && q < g)) ? 1 : 0;
+    }
+    for (int o = 32; o > 0; o >>= 1) r += __shfl_xor(r, o, 64);
+    if (lane == 0) rank[w] = r;
+  }
   __shared__ double bestv[64][17];
   __shared__ int besti[64][17];
   const int c = threadIdx.x & 15, q = threadIdx.x >> 4, g = blockIdx.x * 16 + c;
@@ -1445,7 +1483,7 @@ __global__ __launch_bounds__(1024) void eig_permute(int n, const double* lam, co
   if (g >= n) return;
   bi = besti[0][c];
   const double sgn = (bi < n && Zin[(size_t)bi * n + g] < 0.0) ? -1.0 : 1.0;
-  const int dst = descending ? (n - 1 - rank[g]) : rank[g];
+  const int dst = descending ? (n - 1 - rank[c]) : rank[c];
   if (q == 0) w_out[dst] = lam[g];
   for (int i = q; i < n; i += 64) Z_out[(size_t)i * n + dst] = sgn * Zin[(size_t)i * n + g];
 }
@@ -1478,7 +1516,7 @@ size_t eigh_workspace_bytes(int n) {
   add(nn * 8);      // X (tridiagonal eigenvectors, then back-transformed)
   add(5 * nn * 8);  // LU columns
   add((size_t)n * 8 * 5);  // tau d e p lam
-  add((size_t)n * 4 * 3 + 64);  // blk_start blk_end rank status
+  add((size_t)n * 4 * 3 + 64);  // blk_start blk_end done status
   add(64);          // tnorm
   add((size_t)((n + WY_NB - 1) / WY_NB + 1) * WY_NB * WY_NB * 8);  // compact-WY T factors
   return b;
@@ -1507,14 +1545,12 @@ static int eigh_attempt(const double* A_in, int n, double* w_out, double* Z_out,
   double* lam = p + n;
   int* blk_start = (int*)take((size_t)n * 4 * 3 + 64);
   int* blk_end = blk_start + n;
-  int* rank = blk_end + n;
-  int* done = rank;  // until the ranks are formed
-  int* status = rank + n;
+  int* done = blk_end + n;
+  int* status = done + n;
   double* tnorm = (double*)take(64);
   double* Tall = (double*)take((size_t)((n + WY_NB - 1) / WY_NB + 1) * WY_NB * WY_NB * 8);
   hipError_t err;
   ProfScope prof_all(DFPT2_STAGE_EIGH, st);
-  hipLaunchKernelGGL(zero_int, dim3(1), dim3(64), 0, st, status, 1);
   // 1. tridiagonalization: in one launch up to kResidentMax (the slots of its vectors lie
   //    in the LU columns); else one lazy-update launch per column where its LDS staging
   //    fits in 64 KB; else the two-launch form
@@ -1522,10 +1558,12 @@ static int eigh_attempt(const double* A_in, int n, double* w_out, double* Z_out,
   unsigned long long* slots = reinterpret_cast<unsigned long long*>(lu);
   resident = resident && n >= 3 && n <= kResidentMax &&
              launch_resident(A_in, n, A, Vs, tau, d, e, slots, slots + nn, pb[(n - 3) & 1], status, st);
+  if (!resident) hipLaunchKernelGGL(zero_int, dim3(1), dim3(64), 0, st, status, 1);
   if (!resident && (err = hipMemcpyAsync(A, A_in, nn * 8, hipMemcpyDeviceToDevice, st)) != hipSuccess)
     return hip_fail(err, "eigh copy");
+  const double* p_last = nullptr;
   if (resident) {
-    hipLaunchKernelGGL(tridiag_tail_lazy, dim3(1), dim3(64), 0, st, A, n, Vs, tau, pb[(n - 3) & 1], d, e);
+    p_last = pb[(n - 3) & 1];
   } else if (n >= 3 && (size_t)(3 * (n - 1) + 2) * 8 <= 64 * 1024) {
     for (int k = 0; k + 2 < n; ++k) {
       const int m = n - k - 1;
@@ -1534,7 +1572,7 @@ static int eigh_attempt(const double* A_in, int n, double* w_out, double* Z_out,
       hipLaunchKernelGGL(tridiag_step_lazy, dim3(ga), dim3(256), (size_t)(3 * m + 2) * 8, st, A, n, k, Vs, tau, d,
                          e, pb[(k + 1) & 1], pb[k & 1]);
     }
-    hipLaunchKernelGGL(tridiag_tail_lazy, dim3(1), dim3(64), 0, st, A, n, Vs, tau, pb[(n - 3) & 1], d, e);
+    p_last = pb[(n - 3) & 1];
   } else {
     for (int k = 0; k + 2 < n; ++k) {
       const int m = n - k - 1;
@@ -1546,17 +1584,27 @@ static int eigh_attempt(const double* A_in, int n, double* w_out, double* Z_out,
       if (gy > 256) gy = 256;
       hipLaunchKernelGGL(tridiag_step_b, dim3(gx, gy), dim3(256), 0, st, A, n, k, Vs, tau, p);
     }
-    hipLaunchKernelGGL(tridiag_tail, dim3(1), dim3(64), 0, st, A, n, d, e);
   }
   // 2. split + multisection
-  hipLaunchKernelGGL(tridiag_split, dim3(1), dim3(1024), 0, st, n, d, e, blk_start, blk_end, tnorm);
-  const bool lds = n <= kSturmLds;
-  const size_t de_bytes = lds ? (size_t)n * 16 : 0;
-  const dim3 ms_grid((n + 3) / 4), tw_grid((n + 63) / 64);
-  if (lds)
-    hipLaunchKernelGGL(tridiag_multisect<true>, ms_grid, dim3(256), de_bytes, st, n, d, e, blk_start, blk_end, tnorm, lam);
+  hipLaunchKernelGGL(tridiag_split, dim3(1), dim3(1024), 0, st, n, d, e, blk_start, blk_end, tnorm, A, Vs, tau, p_last);
+  // (the factors T of the back-transformation's 16-blocks go to A, free by now, where it holds
+  // them: from n = 23 on; else later to the LU columns)
+  const bool wy16 = n >= 8 && n <= 2048, early = wy16 && n >= 23;
+  const int nblk16 = (n - 2 + WY16 - 1) / WY16, nb = early ? nblk16 : 0;
+  const size_t de_bytes = std::max((size_t)n * 16, early ? kWySh * sizeof(double) : 0);
+  if (n <= 256)
+    hipLaunchKernelGGL((tridiag_multisect<true, 4>), dim3(n + nb), dim3(256), de_bytes, st, n, d, e, blk_start, blk_end,
+                       tnorm, lam, nb, Vs, tau, A);
+  else if (n <= 512)
+    hipLaunchKernelGGL((tridiag_multisect<true, 2>), dim3(n + nb), dim3(128), de_bytes, st, n, d, e, blk_start, blk_end,
+                       tnorm, lam, nb, Vs, tau, A);
+  else if (n <= kSturmLds)
+    hipLaunchKernelGGL((tridiag_multisect<true, 1>), dim3((n + 3) / 4 + nb), dim3(256), de_bytes, st, n, d, e, blk_start,
+                       blk_end, tnorm, lam, nb, Vs, tau, A);
   else
-    hipLaunchKernelGGL(tridiag_multisect<false>, ms_grid, dim3(256), 0, st, n, d, e, blk_start, blk_end, tnorm, lam);
+    hipLaunchKernelGGL((tridiag_multisect<false, 1>), dim3((n + 3) / 4), dim3(256), 0, st, n, d, e, blk_start, blk_end,
+                       tnorm, lam, 0, Vs, tau, A);
+  const dim3 tw_grid((n + 63) / 64);
   // 3. eigenvectors of isolated eigenvalues by twisted factorizations, the others by
   //    inverse iteration
   LuCols L{lu, lu + nn, lu + 2 * nn, lu + 3 * nn, lu + 4 * nn};
@@ -1577,10 +1625,9 @@ static int eigh_attempt(const double* A_in, int n, double* w_out, double* Z_out,
                      status, floor_ptr, done);
   // 4. back-transformation (compact-WY blocks): on the matrix pipe while a workgroup's
   //    16 columns fit its registers
-  if (n >= 8 && n <= 2048) {  // the T factors (nblk 16 x 16) go to the LU columns, free by now
-    const int nblk = (n - 2 + WY16 - 1) / WY16;
-    double* Tall = lu;
-    hipLaunchKernelGGL(wy16_build_t, dim3(nblk), dim3(256), 0, st, n, Vs, tau, Tall);
+  if (wy16) {
+    double* Tall = early ? A : lu;
+    if (!early) hipLaunchKernelGGL(wy16_build_t, dim3(nblk16), dim3(256), 0, st, n, Vs, tau, Tall);
     const dim3 grid((n + 15) / 16), block(512);
     if (n <= 128) hipLaunchKernelGGL(backtransform16<1>, grid, block, 0, st, n, Vs, Tall, X);
     else if (n <= 512) hipLaunchKernelGGL(backtransform16<4>, grid, block, 0, st, n, Vs, Tall, X);
@@ -1605,15 +1652,18 @@ static int eigh_attempt(const double* A_in, int n, double* w_out, double* Z_out,
   double* G = lu;
   double* Zo = lu + nn;
   double* Part = lu + 2 * nn;  // partial products, 3 nn; only the upper triangle of G is read
-  if ((err = gemm_f64(X, n, 0, 1, X, n, 0, 0, G, n, 0, n, n, n, 1, 1.0, 0.0, st, Part, 3 * nn, true)) != hipSuccess)
-    return hip_fail(err, "eigh orthonormalization");
-  hipLaunchKernelGGL(orth_correction, dim3((unsigned)((nn + 255) / 256 < 65535 ? (nn + 255) / 256 : 65535)),
-                     dim3(256), 0, st, n, G);
+  if (n <= 512) {  // the whole of M at once: a launch less, few flops more
+    if ((err = gemm_f64_orth(X, n, G, Part, 3 * nn, st)) != hipSuccess) return hip_fail(err, "eigh orthonormalization");
+  } else {
+    if ((err = gemm_f64(X, n, 0, 1, X, n, 0, 0, G, n, 0, n, n, n, 1, 1.0, 0.0, st, Part, 3 * nn, true)) != hipSuccess)
+      return hip_fail(err, "eigh orthonormalization");
+    hipLaunchKernelGGL(orth_correction, dim3((unsigned)((nn + 255) / 256 < 65535 ? (nn + 255) / 256 : 65535)),
+                       dim3(256), 0, st, n, G);
+  }
   if ((err = gemm_f64(X, n, 0, 0, G, n, 0, 0, Zo, n, 0, n, n, n, 1, 1.0, 0.0, st, Part, 3 * nn)) != hipSuccess)
     return hip_fail(err, "eigh orthonormalization");
   // 6. sort + orient
-  hipLaunchKernelGGL(eig_rank, dim3((n + 3) / 4), dim3(256), 0, st, n, lam, rank);
-  hipLaunchKernelGGL(eig_permute, dim3((n + 15) / 16), dim3(1024), 0, st, n, lam, rank, Zo, w_out, Z_out, descending);
+  hipLaunchKernelGGL(eig_permute, dim3((n + 15) / 16), dim3(1024), 0, st, n, lam, Zo, w_out, Z_out, descending);
   if ((err = hipGetLastError()) != hipSuccess) return hip_fail(err, "eigh launch");
   prof_all.close();
   if ((err = hipMemcpyAsync(hs, status, sizeof(int), hipMemcpyDeviceToHost, st)) != hipSuccess)

@@ -168,8 +168,8 @@ static int truncate_impl(const double* D_vv, int64_t n_vir, int rule, double par
   int st_ = eigh_run(D_vv, (int)n_vir, occ, no_vecs, ws, need - 512, st, 1);
   if (st_ != DFPT2_OK) return st_;
   int64_t* d_kept = reinterpret_cast<int64_t*>(tail);
-  double* d_marg = reinterpret_cast<double*>(tail + 64);
-  int* d_flag = reinterpret_cast<int*>(tail + 128);
+  double* d_marg = reinterpret_cast<double*>(tail + 8);
+  int* d_flag = reinterpret_cast<int*>(tail + 24);
   ProfScope ps_thr(DFPT2_STAGE_REDUCE, st);
   if (n_vir <= kOccLds)
     hipLaunchKernelGGL(rule_threshold_kernel<true>, dim3(1), dim3(256), (size_t)n_vir * 8, st, occ, (int)n_vir, rule,
@@ -185,9 +185,8 @@ static int truncate_impl(const double* D_vv, int64_t n_vir, int rule, double par
     double marg[2];
     int flag;
   } h{};
-  if ((e = hipMemcpyAsync(&h.kept, d_kept, 8, hipMemcpyDeviceToHost, st)) != hipSuccess) return hip_fail(e, "copy");
-  if ((e = hipMemcpyAsync(h.marg, d_marg, 16, hipMemcpyDeviceToHost, st)) != hipSuccess) return hip_fail(e, "copy");
-  if ((e = hipMemcpyAsync(&h.flag, d_flag, 4, hipMemcpyDeviceToHost, st)) != hipSuccess) return hip_fail(e, "copy");
+  static_assert(sizeof(h) == 32, "as laid out at tail");
+  if ((e = hipMemcpyAsync(&h, tail, sizeof(h), hipMemcpyDeviceToHost, st)) != hipSuccess) return hip_fail(e, "copy");
   if ((e = hipStreamSynchronize(st)) != hipSuccess) return hip_fail(e, "sync");
   prof_flush();
   if (h.flag) return fail(DFPT2_ERR_NONFINITE, "non-finite occupation number");

@@ -49,6 +49,7 @@ struct GemmArgs {
   int nsplit, kper;   // splits of the contraction, chunks per split
   double* part;       // [nsplit][batch][M][N] partial products, or null (nsplit == 1)
   int upper;          // only the tiles that reach the diagonal or lie above it
+  int orth;           // the product P is written as I - (strict upper part of P - I) - diag(P - I) / 2
   int mode;           // 0, or a form of the ladder (LadderBlock in host.h):
                       // kIntegrals: row (a, c), column (b, d) -> C[packed (a, b)][c][d], b <= a only
                       // kPlus:  column j = (a, b): v/2 to C[row][a][b] and C[row][b][a]
@@ -79,6 +80,8 @@ __device__ inline double* c_row(const GemmArgs& g, int b, int m) {
   const int q = m / g.row_n;
   return g.C + b * g.sC + (size_t)(m - q * g.row_n) * g.ldc + q * g.row_s;
 }
+
+__device__ inline double orth_value(double v, int m, int n) { return m < n ? -v : m == n ? 1.0 - 0.5 * (v - 1.0) : 0.0; }
 
 constexpr int BAND = 8;  // tile rows of a band
 
@@ -324,6 +327,7 @@ __global__ __launch_bounds__(256, 2) void gemm_f64_kernel(GemmArgs g) {
         if (!g.part) {
           v *= g.alpha;
           if (g.beta != 0.0) v += g.beta * *dst;
+          if (g.orth) v = orth_value(v, gm, gn);
         }
         *dst = v;
       }
@@ -350,7 +354,8 @@ __global__ __launch_bounds__(256) void gemm_f64_sum(GemmArgs g, int tile) {
     }
     double* dst = c_row(g, b, m) + n;
     v *= g.alpha;
-    *dst = (g.beta != 0.0) ? v + g.beta * *dst : v;
+    if (g.beta != 0.0) v += g.beta * *dst;
+    *dst = g.orth ? orth_value(v, m, n) : v;
   }
 }
 
@@ -468,6 +473,17 @@ hipError_t gemm_f64(const double* A, int lda, long long sA, int transA, const do
   g.row_n = row_n > 0 ? row_n : (M > 0 ? M : 1);
   g.row_s = row_s;
   return launch_gemm(g, transA, transB, part, part_doubles, st);
+}
+
+hipError_t gemm_f64_orth(const double* X, int n, double* M, double* part, size_t part_doubles, hipStream_t st) {
+  GemmArgs g{};
+  g.A = g.B = X;
+  g.C = M;
+  g.M = g.N = g.K = g.lda = g.ldb = g.ldc = g.row_n = n;
+  g.alpha = 1.0;
+  g.batch = 1;
+  g.orth = 1;
+  return launch_gemm(g, 1, 0, part, part_doubles, st);
 }
 
 hipError_t ladder_integrals(const double* Bk, int n_aux, const LadderBlock& q, double* V, hipStream_t st) {

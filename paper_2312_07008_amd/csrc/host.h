@@ -105,6 +105,9 @@ hipError_t gemm_f64(const double* A, int lda, long long sA, int transA, const do
                     double beta, hipStream_t st, double* part = nullptr, size_t part_doubles = 0, bool upper = false,
                     int row_n = 0, long long row_s = 0);
 
+// M = I - U, U = strict upper part of E + diag(E) / 2, E = X^T X - I (X, M n x n)
+hipError_t gemm_f64_orth(const double* X, int n, double* M, double* part, size_t part_doubles, hipStream_t st);
+
 // Pairs (a, b), b <= a, of the particle-particle ladder: those of the rows a0 <= a < a1, or of
 // one row a0 the part b0 <= b < b1 (else b0 = 0, b1 = a1), packed row by row.
 struct LadderBlock {
