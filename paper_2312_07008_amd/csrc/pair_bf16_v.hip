@@ -76,16 +76,13 @@
 // fills one contiguous kilobyte (8 rows x 8 slots) with no conflict.  The slabs
 // must have a multiple of 128 rows.
 //
-// Block order: the hardware deals consecutive workgroups round-robin to the 8
-// XCDs, each with its own L2.  The launch is 1-D and the block index is remapped
-// so that every XCD walks a contiguous range of (pair, tile) in order: the
-// workgroups resident on one XCD then belong to one or two pairs and share the
-// same slabs B_i, B_j through that XCD's L2.
+// Block order: v_tiles.h.
 #include <type_traits>
 
 #include "common.h"
 #include "kernels.h"
 #include "pair_epilogue.h"
+#include "v_tiles.h"
 
 namespace dfpt2 {
 
@@ -118,7 +115,7 @@ constexpr int vm_wait_imm(int n) { return (n & 15) | (((n >> 4) & 3) << 14) | (7
 // 64 wr .. + 63 and columns 32 wc .. + 31.  NBUF LDS buffers form a ring: the
 // loads run NBUF - 1 chunks ahead of the products.
 template <int NS, int WC, int NBUF>
-__global__ __launch_bounds__(128 * WC, 4 / WC) void pair_v_bf16_kernel(PairSlicedArgs a, int nti, int ntj) {
+__global__ __launch_bounds__(128 * WC, 4 / WC) void pair_v_bf16_kernel(PairSlicedArgs a) {
   static_assert(2 * NS <= SLOTS, "slices per LDS row");
   static_assert(NBUF >= 2 && NBUF <= 4, "ring of 2 to 4 buffers");
   constexpr int TJ = 32 * WC;                     // V tile columns
@@ -144,15 +141,8 @@ __global__ __launch_bounds__(128 * WC, 4 / WC) void pair_v_bf16_kernel(PairSlice
     else if constexpr (K() == 2) return lb2;
     else return lb3;
   };
-  const int per_pair = nti * ntj;
-  const int L = xcd_block_v(blockIdx.x, per_pair * a.n_blk_pairs);
-  const int p = L / per_pair, t = L - p * per_pair;
-  // tiles of one pair in bands of HB tile rows, taken column by column within a
-  // band: the ~32 workgroups resident on one XCD then read about 6 + 5 panels
-  // instead of the 14 of 3-4 whole tile rows (1% faster than row order)
-  constexpr int HB = 6;
-  const int band = t / (HB * ntj), h = min(HB, nti - band * HB), r = t - band * HB * ntj;
-  const int J = r / h, I = band * HB + (r - (r / h) * h);
+  int p, I, J;
+  v_tile(blockIdx.x, a.n_v, a.n_blk_pairs, p, I, J);
   const int2 pr = a.pairs[p];
   // V^{ii} is symmetric and its epilogue takes Q from P: the tiles wholly below
   // the diagonal are never read (the whole workgroup leaves before any barrier)
@@ -383,15 +373,16 @@ hipError_t launch_pair_v_bf16(const PairSlicedArgs& a, int ns, int n_pairs, hipS
   if (n_pairs <= 0) return hipSuccess;
   if (!a.T || a.n_v_pad % TV != 0) return hipErrorInvalidValue;
   constexpr int WC = kVWaveCols;
-  const int nti = (a.n_v + TV - 1) / TV, ntj = (a.n_v + 32 * WC - 1) / (32 * WC);
-  if ((long long)nti * ntj * n_pairs > 0x7fffffffLL) return hipErrorInvalidValue;
+  static_assert(32 * WC == TV, "square tiles");
+  const int nti = (a.n_v + TV - 1) / TV;
+  if ((long long)nti * nti * n_pairs > 0x7fffffffLL) return hipErrorInvalidValue;
   PairSlicedArgs b = a;
   b.n_blk_pairs = n_pairs;
-  dim3 gv(nti * ntj * n_pairs), bv(128 * WC);
+  dim3 gv(nti * nti * n_pairs), bv(128 * WC);
   switch (ns) {
-    case 2: hipLaunchKernelGGL((pair_v_bf16_kernel<2, WC, kVRing>), gv, bv, 0, st, b, nti, ntj); break;
-    case 3: hipLaunchKernelGGL((pair_v_bf16_kernel<3, WC, kVRing>), gv, bv, 0, st, b, nti, ntj); break;
-    case 4: hipLaunchKernelGGL((pair_v_bf16_kernel<4, WC, kVRing>), gv, bv, 0, st, b, nti, ntj); break;
+    case 2: hipLaunchKernelGGL((pair_v_bf16_kernel<2, WC, kVRing>), gv, bv, 0, st, b); break;
+    case 3: hipLaunchKernelGGL((pair_v_bf16_kernel<3, WC, kVRing>), gv, bv, 0, st, b); break;
+    case 4: hipLaunchKernelGGL((pair_v_bf16_kernel<4, WC, kVRing>), gv, bv, 0, st, b); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();

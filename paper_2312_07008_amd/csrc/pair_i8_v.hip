@@ -23,13 +23,13 @@
 // i8_layout.h, through a ring of NBUF slots: step c issues the loads of chunk
 // c + NBUF - 1, runs the products of chunk c, waits for its own loads of chunk
 // c + 1 only and closes with a barrier that carries no memory fence.  Block
-// order: every XCD walks a contiguous range of (pair, tile), the tiles of one
-// pair in bands of 6 tile rows, as in the BF16 kernel.
+// order: v_tiles.h.
 #include <type_traits>
 
 #include "common.h"
 #include "i8_layout.h"
 #include "kernels.h"
+#include "v_tiles.h"
 
 namespace dfpt2 {
 
@@ -42,18 +42,13 @@ typedef int v16i __attribute__((ext_vector_type(16)));
 typedef __attribute__((address_space(3))) void lds_void;
 typedef __attribute__((address_space(1))) void gbl_void;
 
-__device__ inline int xcd_block_vi(int h, int nblk) {
-  const int x = h & 7, k = h >> 3, q = nblk >> 3, rem = nblk & 7;
-  return (x < rem) ? x * (q + 1) + k : rem * (q + 1) + (x - rem) * q + k;
-}
-
 // s_waitcnt immediate (gfx9 encoding): wait until at most n vector-memory
 // operations of this wave are outstanding, other counters untouched
 constexpr int vm_wait_imm(int n) { return (n & 15) | (((n >> 4) & 3) << 14) | (7 << 4) | (15 << 8); }
 }  // namespace
 
 template <int NS, int NBUF>
-__global__ __launch_bounds__(512, 1) void pair_v_i8_kernel(PairSlicedArgs a, int nti, int ntj) {
+__global__ __launch_bounds__(512, 1) void pair_v_i8_kernel(PairSlicedArgs a) {
   static_assert(NBUF == 3, "ring of 3 slots");
   constexpr int SLOTS = 2 * NS;         // 16-byte slots per LDS row
   constexpr int PANEL_U4 = TV * SLOTS;  // u4 per 128-row panel
@@ -74,12 +69,8 @@ __global__ __launch_bounds__(512, 1) void pair_v_i8_kernel(PairSlicedArgs a, int
     else if constexpr (K() == 1) return lb1;
     else return lb2;
   };
-  const int per_pair = nti * ntj;
-  const int L = xcd_block_vi(blockIdx.x, per_pair * a.n_blk_pairs);
-  const int p = L / per_pair, t = L - p * per_pair;
-  constexpr int HB = 6;
-  const int band = t / (HB * ntj), h = min(HB, nti - band * HB), r = t - band * HB * ntj;
-  const int J = r / h, I = band * HB + (r - (r / h) * h);
+  int p, I, J;
+  v_tile(blockIdx.x, a.n_v, a.n_blk_pairs, p, I, J);
   const int2 pr = a.pairs[p];
   // V^{ii} is symmetric and its epilogue takes Q from P: the tiles wholly below
   // the diagonal are never read (the whole workgroup leaves before any barrier)
@@ -251,15 +242,15 @@ hipError_t launch_pair_v_i8(const PairSlicedArgs& a, int ns, int n_pairs, hipStr
   if (n_pairs <= 0) return hipSuccess;
   if (!a.T || !a.rexp || a.n_v_pad % TV != 0 || a.n_aux_pad % KC != 0 || a.n_aux_pad > pair_i8_max_aux_pad(ns))
     return hipErrorInvalidValue;
-  const int nti = (a.n_v + TV - 1) / TV, ntj = nti;
-  if ((long long)nti * ntj * n_pairs > 0x7fffffffLL) return hipErrorInvalidValue;
+  const int nti = (a.n_v + TV - 1) / TV;
+  if ((long long)nti * nti * n_pairs > 0x7fffffffLL) return hipErrorInvalidValue;
   PairSlicedArgs b = a;
   b.n_blk_pairs = n_pairs;
-  const dim3 grid(nti * ntj * n_pairs), block(512);
+  const dim3 grid(nti * nti * n_pairs), block(512);
   switch (ns) {
-    case 3: hipLaunchKernelGGL((pair_v_i8_kernel<3, 3>), grid, block, 0, st, b, nti, ntj); break;
-    case 4: hipLaunchKernelGGL((pair_v_i8_kernel<4, 3>), grid, block, 0, st, b, nti, ntj); break;
-    case 5: hipLaunchKernelGGL((pair_v_i8_kernel<5, 3>), grid, block, 0, st, b, nti, ntj); break;
+    case 3: hipLaunchKernelGGL((pair_v_i8_kernel<3, 3>), grid, block, 0, st, b); break;
+    case 4: hipLaunchKernelGGL((pair_v_i8_kernel<4, 3>), grid, block, 0, st, b); break;
+    case 5: hipLaunchKernelGGL((pair_v_i8_kernel<5, 3>), grid, block, 0, st, b); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
