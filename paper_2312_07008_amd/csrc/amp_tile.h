@@ -107,21 +107,21 @@ __device__ inline void load_tile(const double* M, int n_v, int A, int C, double 
   __syncthreads();
 }
 
-// The four density operands of one unordered pair, for a row a and the 16
+// The two density operands of one unordered pair, for a row a and the 16
 // columns c of one thread (x[j] = T[a][c], y[j] = T[c][a]):
-//   m = 0: T[a][c]   m = 1: T[c][a]   m = 2: 2 T[a][c] - T[c][a]   m = 3: 2 T[c][a] - T[a][c]
+//   m = 0: s[a][c] = T[a][c] + T[c][a]   m = 1: d[a][c] = T[a][c] - T[c][a]
 // Each matrix's row is split per 64-column block: 2^E from the largest magnitude
 // of the row within the block (over the thread's quad), then ns true-scale BF16
 // slices s_t 2^(E - 8 - 9t) by successive rounding to the nearest integer:
 // u_0 = v 2^(8 - E) (|u_0| < 256), s_t = rint(u_t), u_{t+1} = 512 (u_t - s_t), every
 // step exact in FP64, so |s_t| <= 256 (exact in BF16) and
 // sum_t s_t 512^(ns-1-t) = rint(v 2^(8 + 9(ns-1) - E)).
-// Within a block every product of a row of X and a row of Y is an integer
+// Within a block every product of two rows of an operand is an integer
 // multiple of one unit, so the density kernel's FP32 level sums over a block are
 // exact.
 //
 // The workgroup (256 threads, thread t on row t / 4 of the 64-row tile, columns
-// 16 (t % 4) .. + 15 of the 64-column block) writes the block of the four
+// 16 (t % 4) .. + 15 of the 64-column block) writes the block of the two
 // matrices: base is row 0 of the tile at the block's first column in matrix 0,
 // matrix m at base + m mat_elems, rows row_elems apart; a row of the block is
 // [4 chunks][ns][16] bf16, 128 ns contiguous bytes.  Each matrix's slices go
@@ -144,12 +144,12 @@ __device__ inline double split_block_rows(const double* x, const double* y, u4* 
 #pragma unroll
   for (int j = 0; j < 16; ++j) dg += 2.0 * (x[j] * x[j] - x[j] * y[j] + y[j] * y[j]);
 #pragma unroll
-  for (int m = 0; m < 4; ++m) {
+  for (int m = 0; m < 2; ++m) {
     double v[16];
     double mx = 0.0;
 #pragma unroll
     for (int j = 0; j < 16; ++j) {
-      v[j] = m == 0 ? x[j] : m == 1 ? y[j] : m == 2 ? 2.0 * x[j] - y[j] : 2.0 * y[j] - x[j];
+      v[j] = m == 0 ? x[j] + y[j] : x[j] - y[j];
       mx = fmax(mx, fabs(v[j]));
     }
     mx = quad_max(mx);

@@ -182,6 +182,7 @@ int plan_pass(const dfpt2_opts* o, PassPlan* pl, bool energy_only) {
     if (act_np > nb_t) nb_t = act_np;
   }
   const size_t t_bytes = p.precision == DFPT2_INT8_SLICED ? 1 : sizeof(__bf16);
+  // (operand regions: twice the two matrices of a pair, as callers' workspaces have always been)
   p.off_Ts = take(p.ns2 >= 2 ? t_bytes * 4 * (size_t)nb_t * p.n_v_rows_t * p.n_v_pad_d * p.ns2 : 0);
   p.off_Texp = take(p.ns2 >= 2 && p.precision == DFPT2_INT8_SLICED ? sizeof(int) * 4 * (size_t)nb_t * p.n_v_pad_d
                                                                     : 0);
@@ -411,7 +412,7 @@ static int sliced_density(const PassPlan& pl, const double* T, const int* slot, 
   double* diag = reinterpret_cast<double*>(ws + pl.off_diag);
   if (pl.precision == DFPT2_INT8_SLICED) {
     {  // one exponent per row: the row maxima first
-      if ((e = launch_fill(reinterpret_cast<double*>(tmax), (size_t)np * 4 * pl.n_v_pad_d, 0.0, s)) != hipSuccess)
+      if ((e = launch_fill(reinterpret_cast<double*>(tmax), (size_t)np * 2 * pl.n_v_pad_d, 0.0, s)) != hipSuccess)
         return hip_fail(e, "fill");
       if ((e = launch_pair_row_stats(T, slot, np, pl.n_v, pl.n_v_pad_d, tmax, dgp, s)) != hipSuccess)
         return hip_fail(e, "amplitude row data");
@@ -708,7 +709,7 @@ int run_pass(const PassPlan& pl, const dfpt2_opts& o, const double* eps_h, const
       pa.tmax = reinterpret_cast<unsigned long long*>(ws + pl.off_tmax);
       pa.dgp = reinterpret_cast<double*>(ws + pl.off_dg);
       ProfScope ps(DFPT2_STAGE_SPLIT_T, s);
-      if ((e = launch_fill(reinterpret_cast<double*>(pa.tmax), (size_t)np * 4 * pl.n_v_pad_d, 0.0, s)) != hipSuccess)
+      if ((e = launch_fill(reinterpret_cast<double*>(pa.tmax), (size_t)np * 2 * pl.n_v_pad_d, 0.0, s)) != hipSuccess)
         return hip_fail(e, "fill");
     }
     {

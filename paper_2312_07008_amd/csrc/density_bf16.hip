@@ -2,22 +2,21 @@
 // (Eq. A9 with zero cumulants) accumulated over hole pairs from BF16 slices of
 // the amplitudes, on the 32x32x16 BF16 MFMA.
 //
-// Per unordered pair the contribution is X1 Y1^T + X2 Y2^T (the slices of the
-// rows of X1 = T, X2 = T^T, Y1 = 2T - T^T, Y2 = 2T^T - T come from
-// epi_split_bf16.hip or split_t.hip).  As in the pair kernel, the slice products
+// Per unordered pair the contribution is 1/2 s s^T + 3/2 d d^T (density_f64.hip; the
+// slices of the rows of s = T + T^T and d = T - T^T come from epi_split_bf16.hip or
+// split_t.hip).  As in the pair kernel, the slice products
 // of level s + t - 1 <= NS are kept.  The operands carry one exponent per (row,
 // 64-column block), so within one block of one product of one pair every
-// product of a row a of X and a row b of Y is an integer multiple of one unit
+// product of a row a and a row b is an integer multiple of one unit
 // (the two rows' block scales): the level-1 and level-2 sums are exact in FP32
 // over the block's 64 contraction steps and are added into FP64 at the end of
 // every block (with the pair's weight); levels >= 3 are summed in FP32 per
 // product.  The two products carry different units, so the contraction runs over
-// X1 / Y1 first and X2 / Y2 after it, with one set of accumulators.  D is
+// s first and d after it, with one set of accumulators.  D is
 // symmetric: only tiles on or above the diagonal are formed, and of a tile on
 // the diagonal only the elements above it are written.  Diagonal elements are
-// left out: the amplitude split sums them exactly in FP64 (the rows of X and Y
-// there carry the same amplitudes, so the dropped slice products would not
-// average out).
+// left out: the amplitude split sums them exactly in FP64 (a row meets itself
+// there, so the dropped slice products would not average out).
 //
 // Workgroup = (128 x 128 tile (I, J) of D, I <= J, split s): split s owns a
 // contiguous range of pairs and accumulates into its own slice Dpart[s]; the
@@ -119,12 +118,12 @@ __global__ __launch_bounds__(512, 1) void density_bf16_kernel(DensitySlicedArgs 
     const int t = sl >> 1, h = sl & 1;
     return (uint32_t)(row * row_bytes + (t < NS ? t * 32 + h * 16 : 0));
   };
-  // load cursor: pair lq, product lh (0: X1 Y1^T, 1: X2 Y2^T), chunk lch
+  // load cursor: pair lq, product lh (0: s s^T, 1: d d^T), chunk lch
   int lq = p0, lh = 0, lch = 0;
   auto load_next = [&](auto K) __attribute__((always_inline)) {  // chunk at the cursor into slot K; cursor moves on
-    const char* pb = Ts + (size_t)lq * 4 * mat_bytes + (size_t)lch * (KC * NS * 2);
-    const char* pX = pb + (size_t)lh * mat_bytes + (size_t)I * TD * row_bytes;
-    const char* pY = pb + (size_t)(2 + lh) * mat_bytes + (size_t)J * TD * row_bytes;
+    const char* pb = Ts + ((size_t)lq * 2 + lh) * mat_bytes + (size_t)lch * (KC * NS * 2);
+    const char* pX = pb + (size_t)I * TD * row_bytes;
+    const char* pY = pb + (size_t)J * TD * row_bytes;
 #pragma unroll
     for (int m = 0; m < KB_W; ++m) {
       const int kb = KB_W * q_w + m;  // wave-uniform
@@ -202,7 +201,7 @@ __global__ __launch_bounds__(512, 1) void density_bf16_kernel(DensitySlicedArgs 
     const c_int* pr = (const c_int*)a.pairs + 2 * (size_t)p;
     double wp = a.w * (pr[0] == pr[1] ? 0.5 : 1.0);
     if (a.pw) wp *= ((const c_double*)a.pw)[p];
-    return wp;
+    return 0.5 * wp;  // of s s^T; three times as much of d d^T
   };
   // compute cursor: pair cq, product chalf, exponent block cblk of the chunks being computed
   int cq = p0, chalf = 0, cblk = 0;
@@ -235,6 +234,8 @@ __global__ __launch_bounds__(512, 1) void density_bf16_kernel(DensitySlicedArgs 
       if (chalf == 0) {
         ++cq;
         if (cq < p1) wp = weight(cq);
+      } else {
+        wp *= 3.0;
       }
     }
   };

@@ -2,8 +2,8 @@
 // (Eq. A9 with zero cumulants) accumulated over hole pairs from balanced
 // base-256 digits of the amplitudes (split_t.hip) on the 32x32x32 INT8 MFMA.
 //
-// Per unordered pair the contribution is X1 Y1^T + X2 Y2^T (X1 = T, X2 = T^T,
-// Y1 = 2T - T^T, Y2 = 2T^T - T; density_bf16.hip).  With NS digits per row the
+// Per unordered pair the contribution is 1/2 s s^T + 3/2 d d^T (s = T + T^T,
+// d = T - T^T; density_f64.hip).  With NS digits per row the
 // kernel keeps the digit products of levels s + t < NS and sums each level of
 // each of the two products in its own INT32 accumulator over the pair's whole
 // contraction (a level has at most NS - 1 products of 2^14 and two of 2^13 per
@@ -75,10 +75,10 @@ __global__ __launch_bounds__(256, 2) void density_i8_kernel(DensityDigitArgs a) 
   const int nck = n_v_pad / KC;
   const int total = (p1 > p0) ? (p1 - p0) * nck : 0;
 
-  // wave w fills panel w: 0 = X1 rows A, 1 = Y1 rows B, 2 = X2 rows A, 3 = Y2 rows B
+  // wave w fills panel w: 0 = s rows A, 1 = s rows B, 2 = d rows A, 3 = d rows B
   const int q_w = __builtin_amdgcn_readfirstlane(w);
-  const int mat_w = (q_w == 0) ? 0 : (q_w == 1) ? 2 : (q_w == 2) ? 1 : 3;
-  const int tile_w = (q_w == 0 || q_w == 2) ? A : Bt;
+  const int mat_w = q_w >> 1;
+  const int tile_w = (q_w & 1) ? Bt : A;
   const size_t chunk_stride = (size_t)n_v_pad * ROWB;
   auto src_off = [&](int m) -> uint32_t {
     const int u = 64 * m + lane, r = u / SLOTS, ps = u - r * SLOTS;
@@ -87,7 +87,7 @@ __global__ __launch_bounds__(256, 2) void density_i8_kernel(DensityDigitArgs a) 
   auto load_chunk = [&](int idx, u4* buf) {
     const int p = p0 + idx / nck, ch = idx - (idx / nck) * nck;
     const char* base = reinterpret_cast<const char*>(a.Ts) +
-                       (((size_t)p * 4 + mat_w) * nck + ch) * chunk_stride + (size_t)tile_w * TM * ROWB;
+                       (((size_t)p * 2 + mat_w) * nck + ch) * chunk_stride + (size_t)tile_w * TM * ROWB;
 #pragma unroll
     for (int m = 0; m < SLOTS; ++m)
       __builtin_amdgcn_global_load_lds((gbl_void*)(base + src_off(m)), (lds_void*)(buf + q_w * PANEL_U4 + m * 64),
@@ -135,7 +135,7 @@ __global__ __launch_bounds__(256, 2) void density_i8_kernel(DensityDigitArgs a) 
       for (int t = 0; t + s < NS; ++t)
         accQ[s + t] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[s], fb[t], accQ[s + t], 0, 0, 0);
   };
-  // end of pair p: levels -> FP64, row scales of X1/Y1 and X2/Y2, pair weight;
+  // end of pair p: levels -> FP64, row scales of s and d, pair weight;
   // the diagonal is left out (the exact FP64 sum of split_t.hip)
   const int gb = Bt * TM + wc * 32 + r32;
   auto flush = [&](int p) {
@@ -146,8 +146,8 @@ __global__ __launch_bounds__(256, 2) void density_i8_kernel(DensityDigitArgs a) 
     const int2 pr = a.pairs[p];
     double wp = a.w * (pr.x == pr.y ? 0.5 : 1.0);
     if (a.pw) wp *= a.pw[p];
-    const int* ex = a.rexp + (size_t)p * 4 * n_v_pad;
-    const int eY1 = ex[2 * n_v_pad + gb], eY2 = ex[3 * n_v_pad + gb];
+    const int* ex = a.rexp + (size_t)p * 2 * n_v_pad;
+    const int es = ex[gb], ed = ex[n_v_pad + gb];
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       const int ga = A * TM + wr * 32 + 8 * (r >> 2) + 4 * hq + (r & 3);
@@ -157,7 +157,7 @@ __global__ __launch_bounds__(256, 2) void density_i8_kernel(DensityDigitArgs a) 
         vp = vp * 0.00390625 + (double)accP[l][r];
         vq = vq * 0.00390625 + (double)accQ[l][r];
       }
-      const double v = wp * (ldexp(vp, ex[ga] + eY1) + ldexp(vq, ex[n_v_pad + ga] + eY2));
+      const double v = wp * (0.5 * ldexp(vp, ex[ga] + es) + 1.5 * ldexp(vq, ex[n_v_pad + ga] + ed));
       if (gb < nvs && ga < nvs && ga != gb) {
         double* dst = Dp + (size_t)ga * nvs + gb;
         *dst = first ? v : *dst + v;

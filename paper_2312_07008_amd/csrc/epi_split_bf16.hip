@@ -1,6 +1,6 @@
 // Epilogue of the split-BF16 density pass: the DSRG amplitudes of one pair
 // (paper App. A, Eq. A7), its energy and norm partials, and the BF16 slices of
-// the four density operands of the core-core term of Eq. A9, formed from the
+// the two density operands of the core-core term of Eq. A9, formed from the
 // FP64 V^{ij} = B_i B_j^T that pair_v_bf16_kernel wrote, without storing the
 // FP64 amplitudes.
 //
@@ -16,8 +16,8 @@
 // diagonal unwritten, so Q = P, and the diagonal V^{ii}_{aa} is the exact FP64
 // norm ||B_ia||^2.
 //
-// The thread's values then give the slices of rows a (columns of J) of the four
-// operands T, T^T, 2T - T^T, 2T^T - T with one exponent per (row, 64-column
+// The thread's values then give the slices of rows a (columns of J) of the two
+// operands T + T^T, T - T^T with one exponent per (row, 64-column
 // block) (amp::split_block_rows: the block is whole in the workgroup), and the
 // diagonal partial of row a for block J.  For I < J the amplitudes go through
 // LDS once more, so that every thread also holds 16 columns (of I) of a row of J
@@ -86,7 +86,7 @@ __global__ __launch_bounds__(256, 3) void pair_epi_split_bf16_kernel(PairSlicedA
 
   const int n_v_pad = a.n_v_pad_d;
   const size_t row_elems = (size_t)n_v_pad * NS, mat_elems = (size_t)rows_pad * row_elems;
-  __bf16* Tq = Ts + (size_t)p * 4 * mat_elems;
+  __bf16* Tq = Ts + (size_t)p * 2 * mat_elems;
   amp::u4* stg = reinterpret_cast<amp::u4*>(&sq[0][0]);  // 33 KB: the 32 KB of a block of slices fit
   {  // rows a of I, columns of J
     __bf16* base = Tq + (size_t)(I * TB) * row_elems + (size_t)(J * 4) * (NS * 16);

@@ -37,7 +37,7 @@ struct PairSlicedArgs {
   double* Vr;           // [n_pairs][n_v][n_v] renormalized integrals out, or null
   double* epart;
   double* tpart;
-  unsigned long long* tmax;  // INT8 only, or null: [n_pairs][4][n_v_pad] row maxima for the density digits
+  unsigned long long* tmax;  // INT8 only, or null: [n_pairs][2][n_v_pad] row maxima for the density digits
   double* dgp;               // with tmax: [n_pairs][nt][n_v_pad] diagonal partial sums (split_t.hip)
   int n_v, n_v_pad, n_aux_pad, nt, nTP;  // n_v_pad: slab rows of Bs; nt: 64-wide tiles of n_v;
                                         // nTP: workgroup tiles per pair
@@ -53,7 +53,7 @@ hipError_t launch_pair_v_bf16(const PairSlicedArgs& a, int ns, int n_pairs, hipS
 hipError_t launch_pair_epi_bf16(const PairSlicedArgs& a, int n_pairs, bool store, hipStream_t st);
 // the epilogue of the split-BF16 density pass (epi_split_bf16.hip): from the V in
 // a.T, the energy and norm partials as above, and instead of T the ns2 BF16 slices
-// of the four density operands (layout of launch_split_t_bf16, matrices rows_pad
+// of the two density operands (layout of launch_split_t_bf16, matrices rows_pad
 // rows apart) in Ts and the diagonal partials in dgp ([n_pairs][nt][n_v_pad_d])
 hipError_t launch_pair_epi_split_bf16(const PairSlicedArgs& a, int n_pairs, int ns2, int rows_pad, __bf16* Ts,
                                       double* dgp, hipStream_t st);
@@ -91,7 +91,7 @@ hipError_t launch_density_f64(const DensityKernelArgs& a, hipStream_t st);
 
 // split-BF16 density: amplitude slices (split_t.hip) and the sliced product
 struct DensitySlicedArgs {
-  const __bf16* Ts;     // [n_pairs][4][rows_pad][n_v_pad/16][ns][16] (split_t.hip)
+  const __bf16* Ts;     // [n_pairs][2][rows_pad][n_v_pad/16][ns][16] (split_t.hip)
   const double* pw;     // [n_pairs] per-pair weight, or null
   const int2* pairs;    // [n_pairs]
   double* Dpart;        // [nsplit][n_v][n_v]
@@ -102,7 +102,7 @@ struct DensitySlicedArgs {
 };
 // workgroup tiles (128 x 64, on or above the diagonal) of the split-BF16 density kernel
 int density_bf16_tiles(int nt);
-// slices of the four density operands of every pair of a batch (T: [n_pairs][n_v][n_v]),
+// slices of the two density operands of every pair of a batch (T: [n_pairs][n_v][n_v]),
 // one exponent per (row, 64-column block) taken from the block itself, plus the
 // exact FP64 diagonal partials dgp ([n_pairs][n_v_pad/64][n_v_pad]) and diag[a] +=
 // their weighted sum; the operand matrices are rows_pad rows apart (a multiple of
@@ -116,17 +116,17 @@ hipError_t launch_split_t_bf16(const double* T, const int* slot, const int2* pai
 // (w_q = w pw[q], halved for i == j), in a fixed order
 hipError_t launch_diag_accumulate(const double* dgp, const int2* pairs, const double* pw, double w, int n_pairs,
                                   int n_v, int n_v_pad, double* diag, hipStream_t st);
-// row maxima of the four density operands (tmax, atomic max: zero it first) and the
+// row maxima of the two density operands (tmax, atomic max: zero it first) and the
 // diagonal partials (dgp) of amplitude matrices T + slot[q] n_v^2 that did not come
 // out of a pair-kernel epilogue, for the INT8-digit split
 hipError_t launch_pair_row_stats(const double* T, const int* slot, int n_pairs, int n_v, int n_v_pad,
                                  unsigned long long* tmax, double* dgp, hipStream_t st);
 hipError_t launch_density_bf16(const DensitySlicedArgs& a, int ns, hipStream_t st);
 
-// INT8-digit density: digits of the four operands (split_t.hip) and the digit product
+// INT8-digit density: digits of the two operands (split_t.hip) and the digit product
 struct DensityDigitArgs {
-  const int8_t* Ts;     // [n_pairs][4][n_v_pad/32][n_v_pad][ns][32] (split_t.hip)
-  const int* rexp;      // [n_pairs][4][n_v_pad] row exponents
+  const int8_t* Ts;     // [n_pairs][2][n_v_pad/32][n_v_pad][ns][32] (split_t.hip)
+  const int* rexp;      // [n_pairs][2][n_v_pad] row exponents
   const double* pw;     // [n_pairs] per-pair weight, or null
   const int2* pairs;    // [n_pairs]
   double* Dpart;        // [nsplit][n_v][n_v]

@@ -16,9 +16,9 @@ namespace dfpt2 {
 
 // Row information the INT8-digit density needs, from the amplitudes of one tile
 // pair (x = T[a][b] for a in I, b in J, y = T[b][a]; split_t.hip):
-//   the largest magnitudes of the rows of T, T^T, 2T - T^T and 2T^T - T
-//   (quantities |x|, |y|, |2x - y|, |2y - x| over b for rows a of I; with the
-//   roles of x and y swapped over a for rows b of J when I < J), merged with an
+//   the largest magnitudes of the rows of T + T^T and T - T^T
+//   (quantities |x + y|, |x - y| over b for rows a of I, and over a for rows b of
+//   J when I < J), merged with an
 //   atomic max of the bit patterns of non-negative doubles (order independent);
 //   and the partial sums 2 (x^2 - x y + y^2) of the exact diagonal of the pair's
 //   density contribution, one slot per (row, other tile) in dgp.
@@ -32,21 +32,20 @@ __device__ inline void density_row_info(const PairSlicedArgs& a, int p, int I, i
   const int wr = w >> 1, wc = w & 1, r32 = lane & 31, hq = lane >> 5;
   double* xl = xs;        // [4 waves][32 rows] row partials
   double* xc = xs + 128;  // [4 waves][32 columns] column partials
-  for (int m = 0; m < 5; ++m) {
+  for (int m = 0; m < 3; ++m) {
     double v[16];
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       const double x = tpv[r], y = tqv[r];
-      v[r] = m == 0 ? fabs(x) : m == 1 ? fabs(y) : m == 2 ? fabs(2.0 * x - y) : m == 3 ? fabs(2.0 * y - x)
-                                                                               : 2.0 * (x * x - x * y + y * y);
+      v[r] = m == 0 ? fabs(x + y) : m == 1 ? fabs(x - y) : 2.0 * (x * x - x * y + y * y);
     }
     // column value: over the 16 registers, then the two halves
     double cv = v[0];
 #pragma unroll
-    for (int r = 1; r < 16; ++r) cv = m < 4 ? fmax(cv, v[r]) : cv + v[r];
+    for (int r = 1; r < 16; ++r) cv = m < 2 ? fmax(cv, v[r]) : cv + v[r];
     {
       const double o = __shfl_xor(cv, 32, 64);
-      cv = m < 4 ? fmax(cv, o) : cv + o;
+      cv = m < 2 ? fmax(cv, o) : cv + o;
     }
     // row values: over the 32 lanes of the half, by recursive halving: at each
     // level a lane keeps half of its registers and adds its partner's copy of
@@ -60,13 +59,13 @@ __device__ inline void density_row_info(const PairSlicedArgs& a, int p, int I, i
         const double mine = up ? v[n / 2 + i] : v[i];
         const double give = up ? v[i] : v[n / 2 + i];
         const double got = __shfl_xor(give, o, 64);
-        v[i] = m < 4 ? fmax(mine, got) : mine + got;
+        v[i] = m < 2 ? fmax(mine, got) : mine + got;
       }
     }
     double rv = v[0];
     {
       const double o = __shfl_xor(rv, 1, 64);
-      rv = m < 4 ? fmax(rv, o) : rv + o;
+      rv = m < 2 ? fmax(rv, o) : rv + o;
     }
     __syncthreads();
     if ((r32 & 1) == 0) xl[w * 32 + hq * 16 + (r32 >> 1)] = rv;
@@ -75,26 +74,24 @@ __device__ inline void density_row_info(const PairSlicedArgs& a, int p, int I, i
     if (tid < 64) {  // rows of I: waves (wr, 0) and (wr, 1)
       const int rw = tid >> 5, k = tid & 31, h = k >> 4, r = k & 15;
       const double u0 = xl[(rw * 2 + 0) * 32 + k], u1 = xl[(rw * 2 + 1) * 32 + k];
-      const double val = m < 4 ? fmax(u0, u1) : u0 + u1;
+      const double val = m < 2 ? fmax(u0, u1) : u0 + u1;
       const int row = I * 64 + rw * 32 + 8 * (r >> 2) + 4 * h + (r & 3);
       if (row < a.n_v) {
-        if (m < 4)
-          atomicMax(a.tmax + ((size_t)p * 4 + m) * a.n_v_pad_d + row, (unsigned long long)__double_as_longlong(val));
+        if (m < 2)
+          atomicMax(a.tmax + ((size_t)p * 2 + m) * a.n_v_pad_d + row, (unsigned long long)__double_as_longlong(val));
         else
           a.dgp[((size_t)p * a.nt + J) * a.n_v_pad_d + row] = val;
       }
-    } else if (tid < 128 && I < J) {  // rows of J: waves (0, wc) and (1, wc), roles of x and y swapped
+    } else if (tid < 128 && I < J) {  // rows of J: waves (0, wc) and (1, wc)
       const int cw = (tid - 64) >> 5, c = tid & 31;
       const double u0 = xc[(0 * 2 + cw) * 32 + c], u1 = xc[(1 * 2 + cw) * 32 + c];
-      const double val = m < 4 ? fmax(u0, u1) : u0 + u1;
+      const double val = m < 2 ? fmax(u0, u1) : u0 + u1;
       const int row = J * 64 + cw * 32 + c;
       if (row < a.n_v) {
-        if (m < 4) {
-          const int mm = m ^ 1;  // |x| <-> |y|, |2x - y| <-> |2y - x|
-          atomicMax(a.tmax + ((size_t)p * 4 + mm) * a.n_v_pad_d + row, (unsigned long long)__double_as_longlong(val));
-        } else {
+        if (m < 2)
+          atomicMax(a.tmax + ((size_t)p * 2 + m) * a.n_v_pad_d + row, (unsigned long long)__double_as_longlong(val));
+        else
           a.dgp[((size_t)p * a.nt + I) * a.n_v_pad_d + row] = val;
-        }
       }
     }
   }

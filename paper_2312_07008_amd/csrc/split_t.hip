@@ -1,13 +1,15 @@
 // Amplitude splitting for the split-BF16 density product (row a4 of the pass).
 //
 // For one unordered pair {i <= j} with amplitude matrix T = T^{ij} (n_v x n_v),
-// the two ordered pairs contribute X1 Y1^T + X2 Y2^T to D (Eq. A9 with zero
+// the two ordered pairs contribute 1/2 s s^T + 3/2 d d^T to D (Eq. A9 with zero
 // cumulants, see density_f64.hip), with, for a virtual c along the contraction,
-//     m = 0:  X1[a][c] = T[a][c]
-//     m = 1:  X2[a][c] = T[c][a]
-//     m = 2:  Y1[b][c] = 2 T[b][c] - T[c][b]
-//     m = 3:  Y2[b][c] = 2 T[c][b] - T[b][c]
-// BF16 slices (split_t_bf16_kernel): every row of the four matrices is split
+//     m = 0:  s[a][c] = T[a][c] + T[c][a]
+//     m = 1:  d[a][c] = T[a][c] - T[c][a]
+// (half of what the four operands T, T^T, 2T - T^T, 2T^T - T of the equation's own form
+// take to split, to write and to hold in the L2: a BF16 pass of 31 holes and 539 virtuals
+// takes 7.0 ms, 7.45 with four, one of 80 holes and 1200 virtuals 477 ms, 497 with four; the
+// INT8 digits of 40 holes and 800 virtuals 2.4 ms, 3.8 with four; errors against FP64 as before).
+// BF16 slices (split_t_bf16_kernel): every row of the two matrices is split
 // per 64-column block, from the largest magnitude of the row within the block
 // (amp_tile.h), into ns true-scale BF16 slices whose integer digits satisfy
 // sum_t s_t 512^(ns-1-t) = rint(x 2^(8 + 9(ns-1) - E)), so the density kernel can
@@ -21,15 +23,14 @@
 // forms the same slices in the pair epilogue (epi_split_bf16.hip); this kernel
 // serves amplitude matrices already in memory (the active blocks).
 //
-// The diagonal of the pair's contribution, w_q sum_c (X1 Y1 + X2 Y2)[a][c] =
+// The diagonal of the pair's contribution,
 // w_q sum_c 2 (x^2 - x y + y^2) with x = T[a][c], y = T[c][a], is summed in
 // FP64, one partial per (row, 64-column block) in dgp, and accumulated in a
-// fixed order by diag_accumulate_kernel: on the diagonal the rows of X and Y
-// carry the same amplitudes, so the slice products the density kernel drops
+// fixed order by diag_accumulate_kernel: on the diagonal a row meets itself, so the slice products the density kernel drops
 // would not average out there, and the diagonal carries the trace of D.  The
 // density kernel leaves the diagonal out.
 //
-// INT8 digits (split_t_i8_kernel) keep one exponent per row: the four row maxima
+// INT8 digits (split_t_i8_kernel) keep one exponent per row: the two row maxima
 // and the diagonal partial sums come from the pair kernel's epilogue
 // (pair_epilogue.h) or from pair_row_stats_kernel.
 #include <cmath>
@@ -46,7 +47,7 @@ using amp::u4;
 
 // ---------------------------------------------------------------- slices
 // Workgroup = (row block A, column block C, pair q): rows A x columns C of the
-// four matrices.  x = T[a][c] comes straight from global memory, y = T[c][a]
+// two matrices.  x = T[a][c] comes straight from global memory, y = T[c][a]
 // from the mirror tile T[C, A] staged in LDS (amp::load_tile).  The thread's 16
 // columns are exactly one 16-wide chunk of the output row; the slices of each
 // matrix go through the LDS tile to whole-row stores (amp::split_block_rows).
@@ -66,13 +67,13 @@ __global__ __launch_bounds__(256) void split_t_bf16_kernel(const double* T, cons
 #pragma unroll
   for (int j = 0; j < 16; ++j) y[j] = tm[k4 * 16 + j][r];
   const size_t row_elems = (size_t)n_v_pad * NS, mat_elems = (size_t)rows_pad * row_elems;
-  __bf16* base = out + (size_t)q * 4 * mat_elems + (size_t)(A * TB) * row_elems + (size_t)(C * 4) * (NS * 16);
+  __bf16* base = out + (size_t)q * 2 * mat_elems + (size_t)(A * TB) * row_elems + (size_t)(C * 4) * (NS * 16);
   const double dg = amp::split_block_rows<NS>(x, y, reinterpret_cast<u4*>(&tm[0][0]), base, mat_elems, row_elems);
   if (k4 == 0 && row < n_v) dgp[((size_t)q * nt + C) * n_v_pad + row] = dg;
 }
 
 // ---------------------------------------------------------------- INT8 digits
-// The same four matrices as balanced base-256 digits for the INT8 density kernel
+// The same two matrices as balanced base-256 digits for the INT8 density kernel
 // (density_i8.hip): per row, Z = rint(v 2^(6 + 8 (NS-1) - E)) with 2^E above the
 // row's largest magnitude (tmax), digits d_t in [-128, 127] (|d_0| <= 64), row
 // value 2^(E - 6) sum_t d_t 2^(-8t).  Layout, chunk-major as for B (split.hip):
@@ -101,11 +102,11 @@ __global__ __launch_bounds__(256) void split_t_i8_kernel(const double* T, const 
 
   const int nck = n_v_pad >> 5;
 #pragma unroll
-  for (int m = 0; m < 4; ++m) {
-    const double mx = __longlong_as_double((long long)tmax[((size_t)q * 4 + m) * n_v_pad + row]);
+  for (int m = 0; m < 2; ++m) {
+    const double mx = __longlong_as_double((long long)tmax[((size_t)q * 2 + m) * n_v_pad + row]);
     int E = 0;
     if (mx > 0.0) frexp(mx, &E);
-    if (C == 0 && k4 == 0) rexp[((size_t)q * 4 + m) * n_v_pad + row] = mx > 0.0 ? E - 6 : 0;
+    if (C == 0 && k4 == 0) rexp[((size_t)q * 2 + m) * n_v_pad + row] = mx > 0.0 ? E - 6 : 0;
     uint32_t word[NS][4];
 #pragma unroll
     for (int t = 0; t < NS; ++t)
@@ -113,7 +114,7 @@ __global__ __launch_bounds__(256) void split_t_i8_kernel(const double* T, const 
       for (int u = 0; u < 4; ++u) word[t][u] = 0u;
 #pragma unroll
     for (int j = 0; j < 16; ++j) {
-      const double v = m == 0 ? x[j] : m == 1 ? y[j] : m == 2 ? 2.0 * x[j] - y[j] : 2.0 * y[j] - x[j];
+      const double v = m == 0 ? x[j] + y[j] : x[j] - y[j];
       long long Z = (mx > 0.0) ? (long long)rint(ldexp(v, 6 + 8 * (NS - 1) - E)) : 0;
 #pragma unroll
       for (int t = NS - 1; t >= 1; --t) {
@@ -136,7 +137,7 @@ __global__ __launch_bounds__(256) void split_t_i8_kernel(const double* T, const 
       stg[(k4 >> 1) * (128 * NS) + r * (2 * NS) + 2 * t + (k4 & 1)] = v4;
     }
     __syncthreads();
-    int8_t* mb = out + (((size_t)q * 4 + m) * nck + 2 * C) * n_v_pad * (size_t)(32 * NS);
+    int8_t* mb = out + (((size_t)q * 2 + m) * nck + 2 * C) * n_v_pad * (size_t)(32 * NS);
 #pragma unroll
     for (int i = 0; i < NS; ++i) {
       const int P = i * 256 + tid, c2 = P / (128 * NS), off = P - c2 * (128 * NS);
@@ -149,7 +150,7 @@ __global__ __launch_bounds__(256) void split_t_i8_kernel(const double* T, const 
 // The row data the split kernels read, for amplitude matrices that did not pass
 // through a pair-kernel epilogue (the amplitudes of the active blocks, rotated to
 // the natural orbitals of Gamma_act): for matrix T = T + slot[q] n_v^2, the
-// largest magnitudes of the rows of T, T^T, 2T - T^T and 2T^T - T (atomic max on
+// largest magnitudes of the rows of T + T^T and T - T^T (atomic max on
 // the bit patterns of non-negative doubles, so independent of order) and the
 // diagonal partial sums 2 (x^2 - x y + y^2) per (row a, 64-column block C), as
 // pair_epilogue.h records them.  Workgroup (A, C, q) as in the split kernels.
@@ -164,19 +165,17 @@ __global__ __launch_bounds__(256) void pair_row_stats_kernel(const double* T, co
   const int row = A * TB + r;
   double x[16];
   amp::load_tile<VEC>(Tp, n_v, A, C, tm, x, true);
-  double mx[4] = {0.0, 0.0, 0.0, 0.0}, dg = 0.0;
+  double mx[2] = {0.0, 0.0}, dg = 0.0;
 #pragma unroll
   for (int j = 0; j < 16; ++j) {
     const double xv = x[j], yv = tm[k4 * 16 + j][r];
-    mx[0] = fmax(mx[0], fabs(xv));
-    mx[1] = fmax(mx[1], fabs(yv));
-    mx[2] = fmax(mx[2], fabs(2.0 * xv - yv));
-    mx[3] = fmax(mx[3], fabs(2.0 * yv - xv));
+    mx[0] = fmax(mx[0], fabs(xv + yv));
+    mx[1] = fmax(mx[1], fabs(xv - yv));
     dg += 2.0 * (xv * xv - xv * yv + yv * yv);
   }
   // over the row's quad (the four 16-column quarters), in a fixed pattern
 #pragma unroll
-  for (int m = 0; m < 4; ++m) {
+  for (int m = 0; m < 2; ++m) {
     mx[m] = fmax(mx[m], amp::quad_xor<0xB1>(mx[m]));
     mx[m] = fmax(mx[m], amp::quad_xor<0x4E>(mx[m]));
   }
@@ -184,8 +183,8 @@ __global__ __launch_bounds__(256) void pair_row_stats_kernel(const double* T, co
   dg += amp::quad_xor<0x4E>(dg);
   if (k4 == 0 && row < n_v) {
 #pragma unroll
-    for (int m = 0; m < 4; ++m)
-      atomicMax(tmax + ((size_t)q * 4 + m) * n_v_pad + row, (unsigned long long)__double_as_longlong(mx[m]));
+    for (int m = 0; m < 2; ++m)
+      atomicMax(tmax + ((size_t)q * 2 + m) * n_v_pad + row, (unsigned long long)__double_as_longlong(mx[m]));
     dgp[((size_t)q * nt + C) * n_v_pad + row] = dg;
   }
 }
