@@ -22,7 +22,8 @@
 //
 // What bounds it: the matrix pipe at the clock that it leaves (about 2 GHz), with 20% of
 // the products' time lost where the last tile row is narrow and in the last round.
-// 40 cores + 8 active, 400 virtuals, ms per pass: 4.8, 5.1 before (the operands 2T - T^T
+// 40 cores + 8 active, 400 virtuals, ms per pass: 4.5, 4.8 with the narrow tile pairs among the
+// others, 5.1 before (the operands 2T - T^T
 // formed with weights in the loop, whole tiles, predicated loads).  Without any load in
 // the loop 4.2; chunks of 8 with three or four workgroups per unit, and 27 or 54 splits
 // (whole rounds) instead of 64: no faster.
@@ -45,16 +46,28 @@ __device__ inline int slot(int k, int row) { return k * TM + (row ^ (((k & 1) <<
 
 __global__ __launch_bounds__(256, 2) void density_f64_kernel(DensityKernelArgs a) {
   __shared__ double lds[2][4][PANEL];  // T[A, c..], T[B, c..], T[c.., A], T[c.., B]
-  int tp, split;
-  {  // XCD-aware order: each XCD walks a contiguous range of (split, tile pair)
-    const uint32_t id = blockIdx.y * gridDim.x + blockIdx.x, nblk = gridDim.x * gridDim.y;
-    const uint32_t x = id & 7, q = id >> 3, per8 = nblk >> 3, rem = nblk & 7;
-    const uint32_t L = (x < rem) ? x * (per8 + 1) + q : rem * (per8 + 1) + (x - rem) * per8 + q;
-    split = (int)(L / gridDim.x);
-    tp = (int)(L - (uint32_t)split * gridDim.x);
+  // Each XCD walks a contiguous range of (split, tile pair); tile pairs with at most 16 columns,
+  // which take half as long, come after the others of all splits (pair_f64.hip)
+  int split, A, Bt;
+  {
+    const int edge = a.n_v - (a.nt - 1) * TM, nf = edge <= 16 ? a.nt - 1 : a.nt;
+    const uint32_t full = nf * (nf + 1) / 2, rest = a.nTP - full, all = full * gridDim.y;
+    const uint32_t id = blockIdx.y * gridDim.x + blockIdx.x;
+    auto xcd = [](uint32_t h, uint32_t nblk) {
+      const uint32_t x = h & 7, k = h >> 3, q = nblk >> 3, rem = nblk & 7;
+      return (x < rem) ? x * (q + 1) + k : rem * (q + 1) + (x - rem) * q + k;
+    };
+    if (id < all) {
+      const uint32_t L = xcd(id, all);
+      split = (int)(L / full);
+      tile_pair((int)(L - split * full), nf, A, Bt);
+    } else {
+      const uint32_t L = xcd(id - all, rest * gridDim.y);
+      split = (int)(L / rest);
+      A = (int)(L - split * rest);
+      Bt = a.nt - 1;
+    }
   }
-  int A, Bt;
-  tile_pair(tp, a.nt, A, Bt);
   const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wr = w >> 1, wc = w & 1, r16 = lane & 15, kq = lane >> 4;
   const int n_v = a.n_v;
