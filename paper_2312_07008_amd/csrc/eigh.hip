@@ -698,8 +698,7 @@ __global__ __launch_bounds__(1024) void tridiag_split(int n, double* d, double* 
   }
 }
 
-// Sturm counts (eigenvalues of the block smaller than x) at P points in one pass over
-// the block, P chains in flight.  In the scaled form below (kProduct) T is scaled by a
+// Sturm counts (eigenvalues of the block smaller than x) at a point.  In the scaled form below (kProduct) T is scaled by a
 // power of two to ||T|| <= 1 and the count is the number of sign changes of
 //     p_{i+1} = (d_i - x) p_i - e_{i-1}^2 p_{i-1},
 // rescaled by a power of two every 8 steps: three FP64 operations a step instead of the
@@ -707,29 +706,20 @@ __global__ __launch_bounds__(1024) void tridiag_split(int n, double* d, double* 
 // is q_i with d - x and e off by a few relative roundings).  A zero p_i takes either sign
 // for exactly one change between its neighbours, as it should.  It needs e^2 >= 1e-60 in
 // the scaled block, so that 8 steps cannot underflow; otherwise the q form runs.
-template <bool kProduct, int P>
-__device__ inline void sturm(const double* d, const double* e, int s, int t, const double (&x)[P], double pivmin, int (&c)[P]) {
-  double q[P], q0[P];
-#pragma unroll
-  for (int k = 0; k < P; ++k) {
-    q[k] = d[s] - x[k];
-    if (!kProduct && fabs(q[k]) < pivmin) q[k] = -pivmin;
-    c[k] = q[k] < 0.0;
-    q0[k] = 1.0;
-  }
+template <bool kProduct>
+__device__ inline int sturm(const double* d, const double* e, int s, int t, double x, double pivmin) {
+  double q = d[s] - x, q0 = 1.0;
+  if (!kProduct && fabs(q) < pivmin) q = -pivmin;
+  int c = q < 0.0;
   if (kProduct) {
     auto hi = [](double v) { return (unsigned)(__builtin_bit_cast(unsigned long long, v) >> 32); };
     for (int i0 = s + 1; i0 < t; i0 += 8) {
       const int m = min(8, t - i0);
-      auto step = [&](int i) {
-        const double di = d[i], e2 = e[i - 1];  // LDS holds e^2
-#pragma unroll
-        for (int k = 0; k < P; ++k) {
-          const double q2 = fma(di - x[k], q[k], -e2 * q0[k]);
-          c[k] += (hi(q2) ^ hi(q[k])) >> 31;
-          q0[k] = q[k];
-          q[k] = q2;
-        }
+      auto step = [&](int i) {  // LDS holds e^2
+        const double q2 = fma(d[i] - x, q, -e[i - 1] * q0);
+        c += (hi(q2) ^ hi(q)) >> 31;
+        q0 = q;
+        q = q2;
       };
       if (m == 8) {
 #pragma unroll
@@ -737,61 +727,46 @@ __device__ inline void sturm(const double* d, const double* e, int s, int t, con
       } else {
         for (int r = 0; r < m; ++r) step(i0 + r);
       }
-#pragma unroll
-      for (int k = 0; k < P; ++k) {
-        const int ex = __builtin_amdgcn_frexp_exp(fmax(fabs(q0[k]), fabs(q[k])));
-        q0[k] = __builtin_amdgcn_ldexp(q0[k], -ex);
-        q[k] = __builtin_amdgcn_ldexp(q[k], -ex);
-      }
+      const int ex = __builtin_amdgcn_frexp_exp(fmax(fabs(q0), fabs(q)));
+      q0 = __builtin_amdgcn_ldexp(q0, -ex);
+      q = __builtin_amdgcn_ldexp(q, -ex);
     }
   } else {
     for (int i = s + 1; i < t; ++i) {
-      const double di = d[i], e2 = e[i - 1] * e[i - 1];
-#pragma unroll
-      for (int k = 0; k < P; ++k) {
-        q[k] = fma(-e2, fast_rcp(q[k]), di - x[k]);
-        if (fabs(q[k]) < pivmin) q[k] = -pivmin;
-        c[k] += q[k] < 0.0;
-      }
+      q = fma(-e[i - 1] * e[i - 1], fast_rcp(q), d[i] - x);
+      if (fabs(q) < pivmin) q = -pivmin;
+      c += q < 0.0;
     }
   }
+  return c;
 }
 
-// Bracket [lo, hi] of the j-th eigenvalue of the block [s, t) shrunk by W waves of P points a
+// Bracket [lo, hi] of the j-th eigenvalue of the block [s, t) shrunk by W waves of a point per
 // lane: the bracket becomes the interval between the highest point whose count is <= j and
-// the next one (64 W P + 1 times smaller per round, 7 to 8 rounds).  The invariant count(lo) <=
+// the next one (64 W + 1 times smaller per round, 7 to 9 rounds).  The invariant count(lo) <=
 // j < count(hi) holds whatever the rounding.
-template <bool kProduct, int W, int P>
+template <bool kProduct, int W>
 __device__ double multisect(const double* d, const double* e, int s, int t, int j, double lo, double hi,
-                            double pivmin, int wv, int lane, unsigned long long (*masks)[W][P]) {
-  constexpr int N = 64 * W * P;
+                            double pivmin, int wv, int lane, unsigned long long (*masks)[W]) {
+  constexpr int N = 64 * W;
   for (int it = 0; it < 64; ++it) {
     if (hi - lo <= 2.0 * DBL_EPSILON * fmax(fabs(lo), fabs(hi)) + pivmin) break;
     const double h = (hi - lo) / (N + 1.0);
     auto point = [&](int k) { return fmin(fmax(fma((double)(k + 1), h, lo), lo), hi); };
-    double x[P];
-    int c[P], klo = -1;
-#pragma unroll
-    for (int k = 0; k < P; ++k) x[k] = point((wv * 64 + lane) * P + k);
-    sturm<kProduct, P>(d, e, s, t, x, pivmin, c);
-#pragma unroll
-    for (int k = 0; k < P; ++k) {
-      unsigned long long m = __ballot((x[k] <= lo) ? true : (x[k] >= hi) ? false : c[k] <= j);
-      if (W == 1) {
-        if (m) klo = max(klo, P * (63 - __clzll((long long)m)) + k);
-      } else if (lane == 0) {
-        masks[it & 1][wv][k] = m;
-      }
-    }
-    if (W > 1) {  // the same rounds in every wave: one barrier each, masks of two rounds
+    const double x = point(wv * 64 + lane);
+    const int c = sturm<kProduct>(d, e, s, t, x, pivmin);
+    unsigned long long m = __ballot((x <= lo) ? true : (x >= hi) ? false : c <= j);
+    int klo = -1;
+    if (W == 1) {
+      if (m) klo = 63 - __clzll((long long)m);
+    } else {  // the same rounds in every wave: one barrier each, masks of two rounds
+      if (lane == 0) masks[it & 1][wv] = m;
       __syncthreads();
 #pragma unroll
-      for (int w = 0; w < W; ++w)
-#pragma unroll
-        for (int k = 0; k < P; ++k) {
-          const unsigned long long m = masks[it & 1][w][k];
-          if (m) klo = max(klo, P * (64 * w + 63 - __clzll((long long)m)) + k);
-        }
+      for (int w = 0; w < W; ++w) {
+        m = masks[it & 1][w];
+        if (m) klo = 64 * w + 63 - __clzll((long long)m);
+      }
     }
     const double nlo = klo >= 0 ? point(klo) : lo, nhi = klo + 1 < N ? point(klo + 1) : hi;
     if (!(nlo > lo || nhi < hi)) break;  // the points no longer split the bracket
@@ -801,12 +776,13 @@ __device__ double multisect(const double* d, const double* e, int s, int t, int 
   return 0.5 * (lo + hi);
 }
 
-// The (g - start)-th eigenvalue of the block containing position g: one wave of two points a
-// lane, four of them a workgroup (W = 1), or a workgroup of W waves of one point.  What
+// The (g - start)-th eigenvalue of the block containing position g: one wave, four of them a
+// workgroup (W = 1), or a workgroup of W waves.  What
 // bounds it is the issue of the counts' FP64 operations, and up to 512 positions, which leave
 // SIMDs idle, the chain of one count.  d and e^2 (or e) come from LDS up to n = kSturmLds.
-// n = 1200: 1.8 ms with one point per lane, full divisions and global reads; 1.3 ms with two
-// points and fast reciprocals; 0.5 ms in the product form.  n = 60: 33 us with W = 1, 21 us
+// n = 1200: 1.8 ms with full divisions and global reads, 1.3 ms with fast reciprocals (and two
+// points per lane, to fill their latency); in the product form 0.66 ms with two points and
+// 0.50 with one.  n = 60: 33 us with W = 1, 21 us
 // with W = 4.  The last blocks form the factors of the back-transformation (wy16_t), which
 // takes no time of its own here.
 constexpr int kSturmLds = 4096;
@@ -819,10 +795,10 @@ __global__ __launch_bounds__(256) void tridiag_multisect(int n, const double* dg
                                                          const int* blk_start, const int* blk_end,
                                                          const double* tnorm, double* lam, int nblk,
                                                          const double* Vs, const double* tau, double* Tout) {
-  constexpr int G = W == 1 ? 4 : 1, P = W == 1 ? 2 : 1;  // eigenvalues per workgroup, points per lane
+  constexpr int G = W == 1 ? 4 : 1;  // eigenvalues per workgroup
   extern __shared__ double msh[];
   __shared__ int small;
-  __shared__ unsigned long long masks[2][W][P];
+  __shared__ unsigned long long masks[2][W];
   const int first = (n + G - 1) / G;
   if ((int)blockIdx.x >= first) {
     if ((int)blockIdx.x - first < nblk) wy16_t(blockIdx.x - first, n, Vs, tau, Tout, msh);
@@ -870,9 +846,9 @@ __global__ __launch_bounds__(256) void tridiag_multisect(int n, const double* dg
   hi += pad;
   double x;
   if (product)  // in units of 2^ex (exact)
-    x = ldexp(multisect<true, W, P>(msh, msh + n, s, t, j, ldexp(lo, -ex), ldexp(hi, -ex), 8.0 * DBL_MIN, wv, lane, masks), ex);
+    x = ldexp(multisect<true, W>(msh, msh + n, s, t, j, ldexp(lo, -ex), ldexp(hi, -ex), 8.0 * DBL_MIN, wv, lane, masks), ex);
   else
-    x = multisect<false, W, P>(dg, eg, s, t, j, lo, hi, pivmin, wv, lane, masks);
+    x = multisect<false, W>(dg, eg, s, t, j, lo, hi, pivmin, wv, lane, masks);
   if (lane == 0 && wv == 0) lam[g] = x;
 }
 
