@@ -4,10 +4,10 @@
 //     C[b] = alpha op(A[b]) op(B[b]) + beta C[b],   op(A) M x K, op(B) K x N.
 //
 // What bounds it: the FP64 matrix pipe, 64 cycles per 16x16x4 product (78 TFLOP/s
-// sustained by a loop of products alone).  A 16-deep chunk of a 128 x 128 tile is 64
-// products per wave against 32 KB of operands, so LDS and L2 have slack; what costs
+// sustained by a loop of products alone).  A 16-deep chunk of a 64 x 64 tile is 16
+// products per wave against 16 KB of operands, so LDS and L2 have slack; what costs
 // time is whatever keeps a SIMD's waves from issuing products.  Hence:
-//  * the next chunk is fetched into registers (8 bytes per lane: any leading dimension
+//  * two chunks are fetched ahead into registers (8 bytes per lane: any leading dimension
 //    and alignment) by buffer loads whose descriptor base moves with the chunk (scalar
 //    arithmetic) at byte offsets that never change: no vector instruction and no branch
 //    but the loads (8192 x 8192 x 2048: 60.3 TFLOP/s with 64-bit addresses per load,
@@ -18,14 +18,18 @@
 //  * LDS holds both operands k-major ([k][m], [k][n]) with rows of 18 (mod 32) doubles:
 //    the 16 lanes along k that store a row of a k-contiguous operand and the 16 + 16
 //    lanes that read a fragment hit distinct banks.
-//  * the tile is 128 x 128 (64 x 64 per wave) or 64 x 64, and a contraction that is long
-//    for its number of tiles is split over workgroups whose partial tiles are summed in a
-//    fixed order (choose_config).
-// Measured against the kernel before (one 128 x 128 tile, predicated loads, no split), TFLOP/s:
+//  * three workgroups fit a unit and fill each other's waits at the barriers; a contraction
+//    that is long for its number of tiles is split over workgroups whose partial tiles are
+//    summed in a fixed order (choose_split).  128 x 128 tiles, two per unit: no faster at any
+//    size tried (ladder of 133 virtuals 8.34 ms with them where they looked better, 8.10
+//    without; 894 x 4000 x 1200 of 80 stacks the same).
+// Measured against the kernel before (128 x 128 tiles, predicated loads, no split), TFLOP/s:
 // A B^T 4256 x 17689 x 800 37 -> 56, A^T B 894 x 4000 x 1200 of 80 stacks 50 -> 61,
-// A B 1200^3 14 -> 41, A B^T 400 x 400 x 18432 1.5 -> 33.
+// A B 1200^3 14 -> 41, A B^T 400 x 400 x 18432 1.5 -> 33.  The second chunk in flight took the
+// density terms of 40 + 8 holes and 400 virtuals from 1.96 to 1.90 ms.
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 #include "common.h"
 #include "host.h"
@@ -58,6 +62,9 @@ struct GemmArgs {
 };
 enum { kIntegrals = 1, kPlus, kMinus };
 
+constexpr int GK = 16;     // contraction chunk
+constexpr int kTile = 64;  // tile edge
+
 // pair (a, b), b <= a, of index t of the triangle
 __device__ inline void ladder_pair(int t, int& a, int& b) {
   a = (int)((sqrt(8.0 * (double)t + 1.0) - 1.0) * 0.5);  // off by at most one
@@ -85,18 +92,17 @@ __device__ inline double orth_value(double v, int m, int n) { return m < n ? -v 
 
 constexpr int BAND = 8;  // tile rows of a band
 
-// first tile column and number of tile columns that a band of tile rows (edge `tile`) has:
+// first tile column and number of tile columns that a band of tile rows has:
 // all; of an integral block those with a b <= a; of an upper triangle those from the diagonal on
-__host__ __device__ inline int band_columns(const GemmArgs& g, int band, int tile, int& first) {
+__host__ __device__ inline int band_columns(const GemmArgs& g, int band, int& first) {
   first = g.upper ? band * BAND : 0;
   if (g.mode != kIntegrals) return g.tn - first;
-  const int m1 = (band + 1) * BAND * tile, last = (m1 < g.M ? m1 : g.M) - 1;
+  const int m1 = (band + 1) * BAND * kTile, last = (m1 < g.M ? m1 : g.M) - 1;
   const long long cols = (long long)(g.lad.a0 + last / g.lad.n + 1 - g.lad.b0) * g.lad.n;  // b0 <= a0
-  const long long t = (cols + tile - 1) / tile;
+  const long long t = (cols + kTile - 1) / kTile;
   return t < g.tn ? (int)t : g.tn;
 }
 
-constexpr int GK = 16;  // contraction chunk
 
 // LDS row of a T-wide operand tile: T + pad = 18 (mod 32) doubles
 constexpr int lds_row(int t) { return t + (18 - t % 32 + 32) % 32; }
@@ -119,9 +125,9 @@ constexpr uint32_t kRange = 0x80000000u;  // bytes a buffer load may reach past 
 
 // Four waves, 2 x 2; each owns BM x BN blocks of 16 x 16.  WIDE: the operands' rows are
 // so far apart that a chunk spans more than the 2 GB of a buffer load's offsets.
-template <bool TA, bool TB, int BM, int BN, bool WIDE>
+template <bool TA, bool TB, bool WIDE>
 __global__ __launch_bounds__(256, 2) void gemm_f64_kernel(GemmArgs g) {
-  constexpr int TM = 32 * BM, TN = 32 * BN;
+  constexpr int BM = 2, BN = 2, TM = kTile, TN = kTile;
   constexpr int LA = lds_row(TM), LB = lds_row(TN);
   constexpr int PA = TM * GK / 256, PB = TN * GK / 256;
   __shared__ double As[2][GK][LA];
@@ -138,10 +144,9 @@ __global__ __launch_bounds__(256, 2) void gemm_f64_kernel(GemmArgs g) {
   const int per = g.per;
   const int outer = L / per, t = L - outer * per;
   const int b = outer / g.nsplit, split = outer - b * g.nsplit;
-  static_assert(TM == TN, "square tiles");
   int band = 0, tr = t, jt0 = 0;
   if (g.mode == kIntegrals || g.upper)
-    for (int c; tr >= (c = BAND * band_columns(g, band, TM, jt0)); ++band) tr -= c;
+    for (int c; tr >= (c = BAND * band_columns(g, band, jt0)); ++band) tr -= c;
   else {
     band = t / (BAND * g.tn);
     tr = t - band * BAND * g.tn;
@@ -159,7 +164,7 @@ __global__ __launch_bounds__(256, 2) void gemm_f64_kernel(GemmArgs g) {
 
   // A: op(A)[m][k] is A[m][k] (k contiguous) or, transposed, A[k][m] (m contiguous)
   // B: op(B)[k][n] is B[k][n] (n contiguous) or, transposed, B[n][k] (k contiguous)
-  double ra[PA], rb[PB];
+  double ra[2][PA], rb[2][PB];  // two chunks in flight
   // Loads go through buffer descriptors whose base is the chunk's (scalar arithmetic),
   // at byte offsets that stay the same from chunk to chunk: no vector instruction but the
   // load itself, which matters because the FP64 products hold the vector pipe.
@@ -181,56 +186,56 @@ __global__ __launch_bounds__(256, 2) void gemm_f64_kernel(GemmArgs g) {
                  : ((uint32_t)kb * g.ldb + min(n0 + rowb, g.N - 1)) * 8u;
   }
   // whole chunk at k0
-  auto load = [&](int k0) {
+  auto load = [&](auto S, int k0) __attribute__((always_inline)) {
     if constexpr (WIDE) {
 #pragma unroll
       for (int r = 0; r < PA; ++r)
-        ra[r] = TA ? At[(size_t)(k0 + ka + SA * r) * g.lda + min(m0 + rowa, g.M - 1)]
+        ra[S()][r] = TA ? At[(size_t)(k0 + ka + SA * r) * g.lda + min(m0 + rowa, g.M - 1)]
                    : At[(size_t)min(rowa + 16 * r, g.M - 1 - m0) * g.lda + k0 + ka];
 #pragma unroll
       for (int r = 0; r < PB; ++r)
-        rb[r] = TB ? Bt[(size_t)min(rowb + 16 * r, g.N - 1 - n0) * g.ldb + k0 + kb]
+        rb[S()][r] = TB ? Bt[(size_t)min(rowb + 16 * r, g.N - 1 - n0) * g.ldb + k0 + kb]
                    : Bt[(size_t)(k0 + kb + SB * r) * g.ldb + min(n0 + rowb, g.N - 1)];
     } else {
       auto da = __builtin_amdgcn_make_buffer_rsrc((void*)(At + (TA ? (size_t)k0 * g.lda : (size_t)k0)), 0, kRange, 0x00020000);
       auto db = __builtin_amdgcn_make_buffer_rsrc((void*)(Bt + (TB ? (size_t)k0 : (size_t)k0 * g.ldb)), 0, kRange, 0x00020000);
 #pragma unroll
       for (int r = 0; r < PA; ++r)
-        ra[r] = __builtin_bit_cast(double, (u2)__builtin_amdgcn_raw_buffer_load_b64(da, oa[TA ? 0 : r], TA ? SA * r * g.lda * 8 : 0, 0));
+        ra[S()][r] = __builtin_bit_cast(double, (u2)__builtin_amdgcn_raw_buffer_load_b64(da, oa[TA ? 0 : r], TA ? SA * r * g.lda * 8 : 0, 0));
 #pragma unroll
       for (int r = 0; r < PB; ++r)
-        rb[r] = __builtin_bit_cast(double, (u2)__builtin_amdgcn_raw_buffer_load_b64(db, ob[TB ? r : 0], TB ? 0 : SB * r * g.ldb * 8, 0));
+        rb[S()][r] = __builtin_bit_cast(double, (u2)__builtin_amdgcn_raw_buffer_load_b64(db, ob[TB ? r : 0], TB ? 0 : SB * r * g.ldb * 8, 0));
     }
   };
   // the last `left` < GK steps of the contraction at k0; the others are zero
-  auto load_tail = [&](int k0, int left) {
+  auto load_tail = [&](int k0, int left) __attribute__((always_inline)) {
 #pragma unroll
     for (int r = 0; r < PA; ++r) {
       const int k = ka + (TA ? SA * r : 0), kk = k0 + min(k, left - 1);
       const double v = TA ? At[(size_t)kk * g.lda + min(m0 + rowa, g.M - 1)]
                           : At[(size_t)min(rowa + 16 * r, g.M - 1 - m0) * g.lda + kk];
-      ra[r] = k < left ? v : 0.0;
+      ra[0][r] = k < left ? v : 0.0;
     }
 #pragma unroll
     for (int r = 0; r < PB; ++r) {
       const int k = kb + (TB ? 0 : SB * r), kk = k0 + min(k, left - 1);
       const double v = TB ? Bt[(size_t)min(rowb + 16 * r, g.N - 1 - n0) * g.ldb + kk]
                           : Bt[(size_t)kk * g.ldb + min(n0 + rowb, g.N - 1)];
-      rb[r] = k < left ? v : 0.0;
+      rb[0][r] = k < left ? v : 0.0;
     }
   };
-  auto store = [&](int buf) {
+  auto store = [&](auto S, int buf) __attribute__((always_inline)) {
 #pragma unroll
     for (int r = 0; r < PA; ++r) {
       int row, k;
       stage_index<!TA, TM>(tid + 256 * r, row, k);
-      As[buf][k][row] = ra[r];
+      As[buf][k][row] = ra[S()][r];
     }
 #pragma unroll
     for (int r = 0; r < PB; ++r) {
       int col, k;
       stage_index<TB, TN>(tid + 256 * r, col, k);
-      Bs[buf][k][col] = rb[r];
+      Bs[buf][k][col] = rb[S()][r];
     }
   };
 
@@ -240,7 +245,7 @@ __global__ __launch_bounds__(256, 2) void gemm_f64_kernel(GemmArgs g) {
 #pragma unroll
     for (int j = 0; j < BN; ++j) acc[i][j] = (d4){0.0, 0.0, 0.0, 0.0};
 
-  auto products = [&](int buf) {
+  auto products = [&](int buf) __attribute__((always_inline)) {
 #pragma unroll
     for (int k4 = 0; k4 < GK / 4; ++k4) {
       const int k = k4 * 4 + kq;
@@ -256,23 +261,34 @@ __global__ __launch_bounds__(256, 2) void gemm_f64_kernel(GemmArgs g) {
     }
   };
   const int kfull = kbeg + (kend - kbeg) / GK * GK;
+  using S0 = std::integral_constant<int, 0>;
+  using S1 = std::integral_constant<int, 1>;
   int buf = 0;
-  if (kbeg < kfull) {
-    load(kbeg);
-    store(0);
+  if (kbeg < kfull) {  // loads two chunks ahead; past the end the last chunk again, not read
+    const int last = kfull - GK;
+    load(S0{}, kbeg);
+    load(S1{}, min(kbeg + GK, last));
+    store(S0{}, 0);
     __syncthreads();
-    for (int k0 = kbeg; k0 < kfull; k0 += GK) {
-      const bool more = k0 + GK < kfull;
-      if (more) load(k0 + GK);
-      products(buf);
-      if (more) store(buf ^ 1);
+    int k0 = kbeg;
+    for (; k0 + GK < kfull; k0 += 2 * GK) {
+      load(S0{}, min(k0 + 2 * GK, last));
+      products(0);
+      store(S1{}, 1);
       __syncthreads();
-      buf ^= 1;
+      load(S1{}, min(k0 + 3 * GK, last));
+      products(1);
+      store(S0{}, 0);
+      __syncthreads();
+    }
+    if (k0 < kfull) {
+      products(0);
+      buf = 1;
     }
   }
   if (kfull < kend) {  // workgroup-uniform
     load_tail(kfull, kend - kfull);
-    store(buf);
+    store(S0{}, buf);
     __syncthreads();
     products(buf);
   }
@@ -337,13 +353,13 @@ __global__ __launch_bounds__(256, 2) void gemm_f64_kernel(GemmArgs g) {
 
 // C = alpha sum over the splits of their partial products + beta C, in the order of
 // the splits; with `upper`, the tiles wholly below the diagonal were not formed
-__global__ __launch_bounds__(256) void gemm_f64_sum(GemmArgs g, int tile) {
+__global__ __launch_bounds__(256) void gemm_f64_sum(GemmArgs g) {
   const size_t mn = (size_t)g.M * g.N, all = mn * g.batch;
   for (size_t q = blockIdx.x * (size_t)blockDim.x + threadIdx.x; q < all; q += (size_t)gridDim.x * blockDim.x) {
     const int b = (int)(q / mn);
     const size_t o = q - b * mn;
     const int m = (int)(o / g.N), n = (int)(o - (size_t)m * g.N);
-    if (g.upper && m / tile > n / tile) continue;
+    if (g.upper && m / kTile > n / kTile) continue;
     double v = 0.0;
     for (int k = 0; k < g.nsplit; ++k) v += g.part[((size_t)k * g.batch) * mn + q];
     if (g.mode) {
@@ -359,91 +375,76 @@ __global__ __launch_bounds__(256) void gemm_f64_sum(GemmArgs g, int tile) {
   }
 }
 
-struct Config {
-  int b, nsplit;  // tile edge / 32, splits of the contraction
-};
-
-// Tile and split by the estimated time on 256 compute units: the products done (padding
-// included) by the busiest unit, at the share of the matrix rate that 1, 2, 3 workgroups
-// on a unit reach (LDS holds two of the larger and three of the smaller tile; one alone
-// has nothing to fill the waits at its barriers), plus the partial products' way through
-// memory.  Measured shares: 128 x 128 tiles 0.60 and 0.80 (18 TFLOP/s at 100 workgroups,
-// 63 at 4096), 64 x 64 tiles 0.42, 0.61 and 0.78 (34 TFLOP/s at 361 workgroups, 62 at
-// 16384): the larger tile leads only where it fills the units evenly, and 1200^3 goes
-// from 34 to 41 TFLOP/s with its contraction split in two.  What is left after whole rounds
-// runs at the lower shares: A B^T 400 x 8911 x 8911 (980 smaller tiles, three rounds of 256 and
-// one alone on a unit) 43 TFLOP/s whole, 48 split in two.
-Config choose_config(int M, int N, int K, int batch, bool upper, size_t part_doubles) {
-  static const struct {
-    int b, wgs;
-    double rate[3];
-  } tiles[] = {{4, 2, {0.60, 0.80, 0.80}}, {2, 3, {0.42, 0.61, 0.78}}};
+// Splits of the contraction by the estimated time on 256 compute units: the products done
+// (padding included) by the busiest unit, at the share of the matrix rate that 1, 2, 3
+// workgroups on a unit reach (LDS holds three; one alone has nothing to fill the waits at its
+// barriers), plus the partial products' way through memory.  Measured shares 0.42, 0.61 and
+// 0.78 (34 TFLOP/s at 361 workgroups, 62 at 16384): 1200^3 goes from 34 to 41 TFLOP/s split in
+// two.  What is left after whole rounds runs at the lower shares: A B^T 400 x 8911 x 8911 (980
+// tiles, three rounds of 256 and one alone on a unit) 43 TFLOP/s whole, 48 split in two.
+int choose_split(int M, int N, int K, int batch, bool upper, size_t part_doubles) {
+  constexpr int kFit = 3;
+  constexpr double kRate[kFit] = {0.42, 0.61, 0.78};
   const double flop_us = 305e3;  // per unit at 78 TFLOP/s
-  Config best{4, 1};
+  int best = 1;
   double best_t = 1e300;
   const int nchunk = (K + GK - 1) / GK;
-  for (const auto& t : tiles) {
-    const double tm = (M + 32 * t.b - 1) / (32 * t.b), tn = (N + 32 * t.b - 1) / (32 * t.b);
-    const double n = tm * tn * batch * (upper ? 0.5 * (1.0 + 1.0 / tn) : 1.0);
-    for (int s = 1; s <= 64; ++s) {
-      if (s > 1 && ((size_t)s * batch * M * N > part_doubles || nchunk < 8 * s)) break;
-      const int per_unit = (int)std::min(std::ceil(n * s / 256.0), 1e8), rest = per_unit % t.wgs;
-      // rounds of as many as fit, then the rest at the rate that fewer reach
-      const double eff = (per_unit - rest) / t.rate[t.wgs - 1] + (rest ? rest / t.rate[rest - 1] : 0.0);
-      const double flops = 2.0 * 1024 * t.b * t.b * GK * std::ceil((double)nchunk / s);
-      const double us = eff * flops / flop_us +
-                        (s > 1 ? 5.0 + (double)s * batch * M * N * 16.0 / 4e6 : 0.0);
-      if (us < best_t * 0.999) {
-        best_t = us;
-        best = Config{t.b, s};
-      }
+  const double tm = (M + kTile - 1) / kTile, tn = (N + kTile - 1) / kTile;
+  const double n = tm * tn * batch * (upper ? 0.5 * (1.0 + 1.0 / tn) : 1.0);
+  for (int s = 1; s <= 64; ++s) {
+    if (s > 1 && ((size_t)s * batch * M * N > part_doubles || nchunk < 8 * s)) break;
+    const int per_unit = (int)std::min(std::ceil(n * s / 256.0), 1e8), rest = per_unit % kFit;
+    // rounds of as many as fit, then the rest at the rate that fewer reach
+    const double eff = (per_unit - rest) / kRate[kFit - 1] + (rest ? rest / kRate[rest - 1] : 0.0);
+    const double us = eff * 2.0 * kTile * kTile * GK * std::ceil((double)nchunk / s) / flop_us +
+                      (s > 1 ? 5.0 + (double)s * batch * M * N * 16.0 / 4e6 : 0.0);
+    if (us < best_t * 0.999) {
+      best_t = us;
+      best = s;
     }
   }
   return best;
 }
 
-template <int B, bool WIDE>
-void launch_tile(const GemmArgs& g, int transA, int transB, unsigned blocks, hipStream_t st) {
+template <bool WIDE>
+void launch_kernel(const GemmArgs& g, int transA, int transB, unsigned blocks, hipStream_t st) {
   if (transA) {
-    if (transB) hipLaunchKernelGGL((gemm_f64_kernel<true, true, B, B, WIDE>), dim3(blocks), dim3(256), 0, st, g);
-    else hipLaunchKernelGGL((gemm_f64_kernel<true, false, B, B, WIDE>), dim3(blocks), dim3(256), 0, st, g);
+    if (transB) hipLaunchKernelGGL((gemm_f64_kernel<true, true, WIDE>), dim3(blocks), dim3(256), 0, st, g);
+    else hipLaunchKernelGGL((gemm_f64_kernel<true, false, WIDE>), dim3(blocks), dim3(256), 0, st, g);
   } else {
-    if (transB) hipLaunchKernelGGL((gemm_f64_kernel<false, true, B, B, WIDE>), dim3(blocks), dim3(256), 0, st, g);
-    else hipLaunchKernelGGL((gemm_f64_kernel<false, false, B, B, WIDE>), dim3(blocks), dim3(256), 0, st, g);
+    if (transB) hipLaunchKernelGGL((gemm_f64_kernel<false, true, WIDE>), dim3(blocks), dim3(256), 0, st, g);
+    else hipLaunchKernelGGL((gemm_f64_kernel<false, false, WIDE>), dim3(blocks), dim3(256), 0, st, g);
   }
 }
 
 hipError_t launch_gemm(GemmArgs& g, int transA, int transB, double* part, size_t part_doubles, hipStream_t st) {
   if (g.M <= 0 || g.N <= 0 || g.batch <= 0) return hipSuccess;
-  Config c = choose_config(g.M, g.N, g.K, g.batch, g.upper != 0, part ? part_doubles : 0);
+  const int nsplit = choose_split(g.M, g.N, g.K, g.batch, g.upper != 0, part ? part_doubles : 0);
   // byte span of a chunk: 16 rows of an operand whose tile rows run contiguously, up to
-  // 128 rows of a k-contiguous one
-  const bool wide = ((transA ? 16.0 : 128.0) * g.lda + 128.0) * 8.0 >= kRange ||
-                    ((transB ? 128.0 : 16.0) * g.ldb + 128.0) * 8.0 >= kRange;
-  if (wide) c.b = 2;
-  const int tile = 32 * c.b;
-  g.tm = (g.M + tile - 1) / tile;
-  g.tn = (g.N + tile - 1) / tile;
+  // 64 rows of a k-contiguous one
+  const bool wide = ((transA ? 16.0 : 64.0) * g.lda + 64.0) * 8.0 >= kRange ||
+                    ((transB ? 64.0 : 16.0) * g.ldb + 64.0) * 8.0 >= kRange;
+  g.tm = (g.M + kTile - 1) / kTile;
+  g.tn = (g.N + kTile - 1) / kTile;
   const int nchunk = g.K > 0 ? (g.K + GK - 1) / GK : 0;  // K <= 0 leaves C = beta C
-  g.kper = (nchunk + c.nsplit - 1) / c.nsplit;
+  g.kper = (nchunk + nsplit - 1) / nsplit;
   g.nsplit = g.kper > 0 ? (nchunk + g.kper - 1) / g.kper : 1;
   g.part = g.nsplit > 1 ? part : nullptr;
   double per = 0.0;
   if (g.mode == kIntegrals || g.upper)
     for (int band = 0, first; band * BAND < g.tm; ++band)
-      per += (double)std::min(BAND, g.tm - band * BAND) * band_columns(g, band, tile, first);
+      per += (double)std::min(BAND, g.tm - band * BAND) * band_columns(g, band, first);
   else per = (double)g.tm * g.tn;
   const double blocks = per * g.batch * g.nsplit;
   if (blocks > 2147483647.0) return hipErrorInvalidValue;
   const unsigned nb = (unsigned)blocks;
   g.per = (int)per;
-  if (wide) launch_tile<2, true>(g, transA, transB, nb, st);
-  else if (c.b == 4) launch_tile<4, false>(g, transA, transB, nb, st);
-  else launch_tile<2, false>(g, transA, transB, nb, st);
+  if (wide) launch_kernel<true>(g, transA, transB, nb, st);
+  else launch_kernel<false>(g, transA, transB, nb, st);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || g.nsplit <= 1) return e;
   const size_t all = ((size_t)g.M * g.N * g.batch + 255) / 256;
-  hipLaunchKernelGGL(gemm_f64_sum, dim3((unsigned)(all < 16384 ? all : 16384)), dim3(256), 0, st, g, tile);
+  hipLaunchKernelGGL(gemm_f64_sum, dim3((unsigned)(all < 16384 ? all : 16384)), dim3(256), 0, st, g);
   return hipGetLastError();
 }
 
