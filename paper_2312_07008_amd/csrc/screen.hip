@@ -107,7 +107,7 @@ __global__ void pair_features_kernel(const double* q2, const double* eps_h, cons
 }
 
 // ------------------------------------------------------------------ network
-// One workgroup of eight waves takes tiles of 64 samples; the products of a tile (z2 = h1 W2^T,
+// One workgroup of eight waves takes tiles of 64, 32 or 16 samples (net_plan); the products of a tile (z2 = h1 W2^T,
 // dz2 W2, dz2^T h1, dz1^T inputs) run on the FP32 matrix pipe (16x16x4, 32 rows and 16 columns
 // per wave), everything between them in registers and LDS:
 //   kForward   pred, and the activations where the caller wants them
@@ -123,7 +123,6 @@ __global__ void pair_features_kernel(const double* q2, const double* eps_h, cons
 // thread per reduced parameter), 27 us with four waves and 32x32x2 products (mlp_kernel 19.7),
 // 19 us so (mlp_kernel 12.7, sum_partials_kernel 4.1).  A tanh without branches: no faster.
 enum NetMode { kForward, kBackward, kTrain };
-constexpr int TS = 64;              // samples per tile
 constexpr int kThreads = 512, kWaves = kThreads / 64;
 constexpr int LD = H + 20;          // LDS row of a 64-wide matrix: 16 rows of 4 columns hit distinct banks, 4 rows of 16 nearly
 constexpr int kMaxGroups = 256;
@@ -131,24 +130,28 @@ constexpr int PROW = (NP + 1 + 3) / 4 * 4;  // floats per row of partial sums
 
 typedef float f4r __attribute__((ext_vector_type(4)));
 
-template <int MODE>
+template <int MODE, int TS>
 __global__ __launch_bounds__(kThreads, 1) void mlp_kernel(const float* Wp, const float* X, const float* y, int n, float* out,
                                                           float* cache, const float* dout, float* partial) {
   __shared__ float w2[H * LD], sh1[TS * LD], sh2[TS * LD], sdz[TS * LD];
   __shared__ float w1[H * NIN], b1[H], b2[H], w3[H], sx[TS * 8], sdo[TS], red[2][kWaves][H], lred[2][kWaves];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, l16 = lane & 15, q4 = lane >> 4;
-  const int rh = (wv >> 2) * 32, cq = (wv & 3) * 16;  // this wave's rows (two blocks of 16) and columns
+  // this wave's 16 x 16 blocks: columns cq, rows rh and, where there are more than 32, rh + 32
+  // (two waves of a SIMD share the blocks of its columns evenly)
+  constexpr int NI = TS > 32 ? 2 : 1;
+  static_assert(TS == 64 || TS == 32 || TS == 16, "whole blocks per wave, or one for half of them");
+  const int rh = __builtin_amdgcn_readfirstlane(wv >> 2) * 16, cq = (wv & 3) * 16;
   // everything that the first tile reads from memory is in flight at once
   const int ntile = (n + TS - 1) / TS, xr = tid >> 3, xc = tid & 7;  // row and input of this thread
   auto input = [&](int tile) {  // column 5 is 1: its gradient is b1's
     const int s = tile * TS + xr;
-    return xc < NIN && s < n ? X[(size_t)s * NIN + xc] : xc == NIN ? 1.f : 0.f;
+    return xc < NIN && xr < TS && s < n ? X[(size_t)s * NIN + xc] : xc == NIN ? 1.f : 0.f;
   };
   auto target = [&](int tile) {
     const int s = tile * TS + xr;
-    return MODE == kTrain && s < n ? y[s] : 0.f;
+    return MODE == kTrain && xr < TS && s < n ? y[s] : 0.f;
   };
-  static_assert(TS * 8 == kThreads, "an input and an eighth of an output per thread");
+  static_assert(TS * 8 <= kThreads, "an input and an eighth of an output per thread");
   float wr[H * H / kThreads], xn = input(blockIdx.x), yn = target(blockIdx.x);
 #pragma unroll
   for (int k = 0; k < H * H / kThreads; ++k) wr[k] = Wp[OFF_W2 + kThreads * k + tid];
@@ -169,7 +172,7 @@ __global__ __launch_bounds__(kThreads, 1) void mlp_kernel(const float* Wp, const
   for (int tile = blockIdx.x; tile < ntile; tile += gridDim.x) {
     const int s0 = tile * TS, ns = min(TS, n - s0);
     __syncthreads();  // the previous tile's readers are done
-    sx[tid] = xn;
+    if (xr < TS) sx[tid] = xn;
     const float yr = yn;
     if (tile + (int)gridDim.x < ntile) {
       xn = input(tile + gridDim.x);
@@ -202,27 +205,31 @@ __global__ __launch_bounds__(kThreads, 1) void mlp_kernel(const float* Wp, const
         }
       }
       __syncthreads();
-      f4r z2[2];  // rows s, columns k
+      f4r z2[NI];  // rows s, columns k
 #pragma unroll
-      for (int r = 0; r < 4; ++r) z2[0][r] = z2[1][r] = 0.f;
+      for (int i = 0; i < NI; ++i)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) z2[i][r] = 0.f;
 #pragma unroll
       for (int m = 0; m < H; m += 4) {
         const float bw = w2[(cq + l16) * LD + m + q4];
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
-          z2[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(sh1[(rh + 16 * i + l16) * LD + m + q4], bw, z2[i], 0, 0, 0);
+        for (int i = 0; i < NI; ++i)
+          if (TS > 16 || rh == 0)
+            z2[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(sh1[(rh + 32 * i + l16) * LD + m + q4], bw, z2[i], 0, 0, 0);
       }
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
+      for (int i = 0; i < NI; ++i)
+        if (TS > 16 || rh == 0)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {  // register r: row 4 (lane / 16) + r
-          const int row = rh + 16 * i + 4 * q4 + r, k = cq + l16;
-          const float h = tanhf(z2[i][r] + b2[k]);
-          sh2[row * LD + k] = h;
-          if (MODE == kForward && cache && row < ns) cache[(size_t)(s0 + row) * 2 * H + H + k] = h;
-        }
+          for (int r = 0; r < 4; ++r) {  // register r: row 4 (lane / 16) + r
+            const int row = rh + 32 * i + 4 * q4 + r, k = cq + l16;
+            const float h = tanhf(z2[i][r] + b2[k]);
+            sh2[row * LD + k] = h;
+            if (MODE == kForward && cache && row < ns) cache[(size_t)(s0 + row) * 2 * H + H + k] = h;
+          }
       __syncthreads();
-      {  // output: eight threads per sample
+      if (xr < TS) {  // output: eight threads per sample, whole waves
         const int r = xr, q = xc;
         float o = 0.f;
 #pragma unroll
@@ -257,28 +264,37 @@ __global__ __launch_bounds__(kThreads, 1) void mlp_kernel(const float* Wp, const
     }
     if (tid < TS) gb3 += sdo[tid];
     __syncthreads();
-    f4r z1[2];  // dz2 W2: rows s, columns m
+    f4r z1[NI];  // dz2 W2: rows s, columns m
 #pragma unroll
-    for (int r = 0; r < 4; ++r) z1[0][r] = z1[1][r] = 0.f;
+    for (int i = 0; i < NI; ++i)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) z1[i][r] = 0.f;
 #pragma unroll
     for (int k = 0; k < H; k += 4) {
-      const float bw = w2[(k + q4) * LD + cq + l16], bh = sh1[(k + q4) * LD + cq + l16];
+      const float bw = w2[(k + q4) * LD + cq + l16];
 #pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        z1[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(sdz[(rh + 16 * i + l16) * LD + k + q4], bw, z1[i], 0, 0, 0);
-        g2[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(sdz[(k + q4) * LD + rh + 16 * i + l16], bh, g2[i], 0, 0, 0);
-      }
+      for (int i = 0; i < NI; ++i)
+        if (TS > 16 || rh == 0)
+          z1[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(sdz[(rh + 32 * i + l16) * LD + k + q4], bw, z1[i], 0, 0, 0);
+    }
+#pragma unroll
+    for (int r = 0; r < TS; r += 4) {
+      const float bh = sh1[(r + q4) * LD + cq + l16];
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+        g2[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(sdz[(r + q4) * LD + rh + 32 * i + l16], bh, g2[i], 0, 0, 0);
     }
     // dz1 (over h2, which is no longer needed), then the gradients of W1 and b1: dz1^T times
     // the inputs, four waves with 16 rows m each (columns 8 to 15 repeat 0 to 7)
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < NI; ++i)
+      if (TS > 16 || rh == 0)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int row = rh + 16 * i + 4 * q4 + r, m = cq + l16;
-        const float h = sh1[row * LD + m];
-        sh2[row * LD + m] = z1[i][r] * (1.f - h * h);
-      }
+        for (int r = 0; r < 4; ++r) {
+          const int row = rh + 32 * i + 4 * q4 + r, m = cq + l16;
+          const float h = sh1[row * LD + m];
+          sh2[row * LD + m] = z1[i][r] * (1.f - h * h);
+        }
     __syncthreads();
     if (wv < 4) {
 #pragma unroll
@@ -291,7 +307,7 @@ __global__ __launch_bounds__(kThreads, 1) void mlp_kernel(const float* Wp, const
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int r = 0; r < 4; ++r) part[OFF_W2 + (rh + 16 * i + 4 * q4 + r) * H + cq + l16] = g2[i][r];
+    for (int r = 0; r < 4; ++r) part[OFF_W2 + (rh + 32 * i + 4 * q4 + r) * H + cq + l16] = g2[i][r];
   if (wv < 4) {
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
@@ -423,10 +439,35 @@ double regularizer_peak() {
 
 int train_nblk(int64_t n) { return (int)((n + BW_SAMPLES - 1) / BW_SAMPLES); }
 
-// workgroups over n samples, with room for their rows in `floats`
-int net_groups(int64_t n, size_t floats) {
-  const int64_t tiles = (n + TS - 1) / TS;
-  return (int)std::max<int64_t>(1, std::min<int64_t>({tiles, kMaxGroups, (int64_t)(floats / PROW)}));
+// Samples per tile and workgroups over n samples, with room for `rows` rows of partial sums:
+// the tile with the least work on the busiest unit, a tile costing its samples and about 32
+// more in fixed latency.  Twelve training steps, us: 200 samples 159, 194 with tiles of 64; 4096
+// samples 182 and 208; 8192 samples 211 and 217.  (Tiles of 48, whose blocks do not fill the
+// eight waves: 272 instead of 234 at 11000.)
+struct NetPlan {
+  int ts, groups;
+};
+NetPlan net_plan(int64_t n, int64_t rows) {
+  NetPlan best{64, 1};
+  int64_t least = INT64_MAX;
+  for (int ts : {64, 32, 16}) {
+    const int64_t tiles = (n + ts - 1) / ts, g = std::max<int64_t>(1, std::min<int64_t>({tiles, kMaxGroups, rows}));
+    const int64_t cost = (tiles + g - 1) / g * (ts + 32);
+    if (cost < least) {
+      least = cost;
+      best = NetPlan{ts, (int)g};
+    }
+  }
+  return best;
+}
+
+template <int MODE>
+void launch_mlp(const NetPlan& p, hipStream_t s, const float* W, const float* X, const float* y, int n, float* out,
+                float* cache, const float* dout, float* partial) {
+  const dim3 grid(p.groups), block(kThreads);
+  if (p.ts == 64) hipLaunchKernelGGL((mlp_kernel<MODE, 64>), grid, block, 0, s, W, X, y, n, out, cache, dout, partial);
+  else if (p.ts == 32) hipLaunchKernelGGL((mlp_kernel<MODE, 32>), grid, block, 0, s, W, X, y, n, out, cache, dout, partial);
+  else hipLaunchKernelGGL((mlp_kernel<MODE, 16>), grid, block, 0, s, W, X, y, n, out, cache, dout, partial);
 }
 
 AdamArgs adam_args(float* W, float* m, float* v, float lr, float b1, float b2, float eps, int64_t step) {
@@ -497,8 +538,9 @@ int pairscreen_mlp_forward(const float* W, const float* feats, int64_t n, float*
   if (n == 0) return DFPT2_OK;
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   ProfScope ps(DFPT2_STAGE_SCREEN, s);
-  hipLaunchKernelGGL(mlp_kernel<kForward>, dim3((unsigned)std::min<int64_t>((n + TS - 1) / TS, 2048)), dim3(kThreads), 0, s, W,
-                     feats, nullptr, (int)n, pred, act_cache, nullptr, nullptr);
+  NetPlan p = net_plan(n, kMaxGroups);
+  p.groups = (int)std::min<int64_t>((n + p.ts - 1) / p.ts, 2048);
+  launch_mlp<kForward>(p, s, W, feats, nullptr, (int)n, pred, act_cache, nullptr, nullptr);
   hipError_t e = hipGetLastError();
   return e == hipSuccess ? DFPT2_OK : hip_fail(e, "mlp forward");
 }
@@ -522,10 +564,9 @@ int pairscreen_mlp_backward(const float* W, const float* feats, const float* act
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   ProfScope ps(DFPT2_STAGE_SCREEN, s);
   float* partial = static_cast<float*>(workspace);
-  const int nblk = net_groups(n, need / sizeof(float));
-  hipLaunchKernelGGL(mlp_kernel<kBackward>, dim3(nblk), dim3(kThreads), 0, s, W, feats, nullptr, (int)n, nullptr,
-                     const_cast<float*>(act_cache), dpred, partial);
-  hipLaunchKernelGGL(sum_partials_kernel<false>, dim3((NP + 32) / 32), dim3(512), 0, s, partial, nblk, dW, AdamArgs{});
+  const NetPlan p = net_plan(n, (int64_t)(need / sizeof(float) / PROW));
+  launch_mlp<kBackward>(p, s, W, feats, nullptr, (int)n, nullptr, const_cast<float*>(act_cache), dpred, partial);
+  hipLaunchKernelGGL(sum_partials_kernel<false>, dim3((NP + 32) / 32), dim3(512), 0, s, partial, p.groups, dW, AdamArgs{});
   hipError_t e = hipGetLastError();
   return e == hipSuccess ? DFPT2_OK : hip_fail(e, "mlp backward");
 }
@@ -568,16 +609,15 @@ int pairscreen_train(float* W, float* m, float* v, const float* feats, const flo
   pairscreen_train_workspace_size(n, &need);
   if (ws_bytes < need) return fail(DFPT2_ERR_WORKSPACE, "workspace too small");
   float* partial = static_cast<float*>(workspace);
-  const int nblk = net_groups(n, need / sizeof(float));
+  const NetPlan p = net_plan(n, (int64_t)(need / sizeof(float) / PROW));
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   for (int64_t t = 1; t <= steps; ++t) {
     ProfScope ps(DFPT2_STAGE_SCREEN, s);
-    hipLaunchKernelGGL(mlp_kernel<kTrain>, dim3(nblk), dim3(kThreads), 0, s, W, feats, y, (int)n, nullptr, nullptr, nullptr,
-                       partial);
+    launch_mlp<kTrain>(p, s, W, feats, y, (int)n, nullptr, nullptr, nullptr, partial);
     AdamArgs a = adam_args(W, m, v, lr, 0.9f, 0.999f, 1e-8f, step0 + t);
     a.loss = losses + (t - 1);
     a.inv_n = 1.f / (float)n;
-    hipLaunchKernelGGL(sum_partials_kernel<true>, dim3((NP + 32) / 32), dim3(512), 0, s, partial, nblk, nullptr, a);
+    hipLaunchKernelGGL(sum_partials_kernel<true>, dim3((NP + 32) / 32), dim3(512), 0, s, partial, p.groups, nullptr, a);
     const hipError_t le = hipGetLastError();
     if (le != hipSuccess) return hip_fail(le, "train");
   }
