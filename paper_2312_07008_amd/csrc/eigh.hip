@@ -23,8 +23,8 @@
 //      component is positive.
 // n = 1200, ms before and after the resident reduction, the product-form counts, the
 // twisted factorizations and the matrix-pipe back-transformation: reduction 11.6 -> 5.0,
-// eigenvalues 1.8 -> 0.66, vectors 5.9 -> 0.28, back-transformation 2.0 -> 0.45, the whole
-// call 22.5 -> 6.8.
+// eigenvalues 1.8 -> 0.46, vectors 5.9 -> 0.44, back-transformation 2.0 -> 0.44, the whole
+// call 22.5 -> 6.6.
 #include <algorithm>
 #include <cmath>
 #include <cfloat>
@@ -854,24 +854,43 @@ __global__ __launch_bounds__(256) void tridiag_multisect(int n, const double* dg
 
 // ------------------------------------------------------------ twisted factorization
 // Eigenvector of an eigenvalue that is isolated in its block (both gaps above
-// kIsolated ||T||), one thread each: T - lam = L D L^T from the top and U D U^T from the
+// kIsolated ||T||): T - lam = L D L^T from the top and U D U^T from the
 // bottom, z = 1 at the row r where they leave the smallest pivot, and z_i = -l_i z_{i+1}
 // above, z_{i+1} = -u_i z_i below.  Either factorization is exact for off-diagonals off
 // by a few ulps (as in the Sturm counts), so the residual is the twist pivot over ||z||
-// plus a few ulps of ||T||: the vector is as good as inverse iteration's, in three
-// passes over the block instead of thirteen, without pivoting.  A residual above
-// 50 eps ||T|| or a value that is not finite leaves done[g] = 0, and the vector to
-// inverse iteration.  What bounds it is the chain of a factorization (one reciprocal and
+// plus a few ulps of ||T||.  That is a single solve, of the start vector e_r, and leaves
+// (lam's error) / gap of its neighbours in z; a second one with the same factors squares it
+// away, as inverse iteration's do.  Relative error of the vectors of random symmetric matrices of
+// 600 and 1200 rows, in units of inverse iteration's: 0.95 and 1.02, with one solve 1.55 and 2.31.
+// A residual of z above 50 eps ||T|| or a value that is not finite leaves done[g] = 0, and the
+// vector to inverse iteration.  What bounds it is the chain of a factorization (one reciprocal and
 // three operations a position).  A wave takes VW vectors, 64 / VW lanes each: lane 0 of a
 // group runs down the block and lane 1 up, each writing its multipliers to LDS, all lanes
-// search for the twist, lanes 0 and 1 run the two recurrences of z over the multipliers in
-// place, and all lanes scale and store.  n = 1200: 5.9 ms for inverse iteration (its LU
+// search for the twist, lanes 0 and 1 run the recurrences of the two solves, and all lanes
+// scale and store.  n = 1200: 5.9 ms for inverse iteration (its LU
 // arrays stream through memory nine times), 1.4 ms with one thread per vector and l, u in
-// memory, 0.28 ms so.
+// memory, 0.44 ms so (0.28 with one solve).
 constexpr double kIsolated = 1e-8;
 // LDS of a wave of VW vectors: d, e and the multipliers l, u
 constexpr size_t twisted_bytes(int n, int vw) { return (size_t)n * 8 * (2 + 2 * vw); }
 constexpr size_t kTwistedLds = 160 * 1024 - 256;
+
+// x <- b_k - c_k x (kAdd; else -c_k x) for k < n, each x stored over b_k; eight reads in flight
+template <bool kAdd>
+__device__ inline double recur(const double* c, double* b, int stride, int n, double x) {
+  for (; n >= 8; n -= 8, c += 8 * stride, b += 8 * stride) {
+    double cv[8], bv[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      cv[k] = c[k * stride];
+      bv[k] = kAdd ? b[k * stride] : 0.0;
+    }
+#pragma unroll
+    for (int k = 0; k < 8; ++k) b[k * stride] = x = kAdd ? fma(-cv[k], x, bv[k]) : -cv[k] * x;
+  }
+  for (; n > 0; --n, c += stride, b += stride) *b = x = kAdd ? fma(-*c, x, *b) : -*c * x;
+  return x;
+}
 
 template <int VW>
 __global__ __launch_bounds__(64) void tridiag_twisted(int n, const double* dg, const double* eg, const int* blk_start,
@@ -940,42 +959,59 @@ __global__ __launch_bounds__(64) void tridiag_twisted(int n, const double* dg, c
   }
   if (r < s || r >= t) r = s;  // no finite pivot (the residual test below fails)
   __syncthreads();
-  // z_i over l_i for i < r (lane 0), z_{i+1} over u_i for i >= r (lane 1)
-  if (q == 0 && t > s) {
-    double z = 1.0;
-#pragma unroll 8
-    for (int i = r - 1; i >= s; --i) {
-      z = -Lm[(size_t)i * VW + v] * z;
-      Lm[(size_t)i * VW + v] = z;
+  // From here on l_i counts for i < r only and u_i for i >= r; the vectors lie in the other
+  // halves: entry i < r over u_i, entry i + 1 > r over l_i.
+  const int cnt = q > 1 || t <= s ? 0 : q == 0 ? r - s : t - 1 - r, dir = q == 0 ? VW : -VW;
+  double* C = (q == 0 ? Lm : Um) + v;  // multipliers and vector of the lane's half
+  double* B = (q == 0 ? Um : Lm) + v;
+  // z_i (lane 0), z_{i+1} (lane 1), away from the twist
+  const int near = (q == 0 ? r - 1 : r) * VW, far = (q == 0 ? s : t - 2) * VW;
+  if (cnt > 0) recur<false>(C + near, B + near, -dir, cnt, 1.0);
+  __syncthreads();
+  auto entry = [&](int i) {
+    return i < r ? Um[(size_t)i * VW + v] : i > r ? Lm[(size_t)(i - 1) * VW + v] : 1.0;
+  };
+  auto norm = [&] {
+    double nz = 0.0;
+    for (int i = s + q; i < t; i += G) {
+      const double z = entry(i);
+      nz = fma(z, z, nz);
     }
-  }
-  if (q == 1 && t > s) {
-    double z = 1.0;
-#pragma unroll 8
-    for (int i = r; i < t - 1; ++i) {
-      z = -Um[(size_t)i * VW + v] * z;
-      Um[(size_t)i * VW + v] = z;
-    }
+#pragma unroll
+    for (int o = G / 2; o >= 1; o >>= 1) nz += __shfl_xor(nz, o, 64);
+    return sqrt(nz);
+  };
+  double nn = norm();
+  if (go && (!(nn < 1e150) || !(best < DBL_MAX) || !(fabs(gam) <= 50.0 * DBL_EPSILON * nrm * nn))) {
+    if (q == 0) done[g] = 0;
+    go = false;
+    s = t = 0;
   }
   __syncthreads();
-  double nz = 0.0;
-  auto zat = [&](int i) {
-    return i < r ? Lm[(size_t)i * VW + v] : i > r ? Um[(size_t)(i - 1) * VW + v] : 1.0;
-  };
+  // The second solve, (T - lam I) y = z, in place.  N D N^T with N's columns l, u: first N w = z,
+  // w_{i+1} = z_{i+1} - l_i w_i above the twist (lane 0), w_i = z_i - u_i w_{i+1} below (lane 1)
+  double a = 0.0;
+  if (cnt > 0 && t > s) a = C[near] * recur<true>(C + far, B + far + dir, dir, cnt - 1, B[far]);
+  a += __shfl_xor(a, 1, 64);
+  const double sc = gam / (1.0 - __shfl(a, lane - q, 64));  // scales y to y_r = 1
+  __syncthreads();
+  // w_i / D_i, with 1 / D_i = l_i / e_i above the twist and u_{i-1} / e_{i-1} below
   for (int i = s + q; i < t; i += G) {
-    const double z = zat(i);
-    nz = fma(z, z, nz);
+    if (i < r) Um[(size_t)i * VW + v] = sc * Um[(size_t)i * VW + v] * Lm[(size_t)i * VW + v] / e[i];
+    if (i > r) Lm[(size_t)(i - 1) * VW + v] = sc * Lm[(size_t)(i - 1) * VW + v] * Um[(size_t)(i - 1) * VW + v] / e[i - 1];
   }
-#pragma unroll
-  for (int o = G / 2; o >= 1; o >>= 1) nz += __shfl_xor(nz, o, 64);
+  __syncthreads();
+  // N^T y: y_i = w_i / D_i - l_i y_{i+1}, y_{i+1} = w_{i+1} / D_{i+1} - u_i y_i
+  if (cnt > 0 && t > s) recur<true>(C + near, B + near, -dir, cnt, 1.0);
+  __syncthreads();
+  nn = norm();
   if (!go) return;
-  const double nn = sqrt(nz);
-  if (!(nn < 1e150) || !(best < DBL_MAX) || !(fabs(gam) <= 50.0 * DBL_EPSILON * nrm * nn)) {
+  if (!(nn < 1e150)) {
     if (q == 0) done[g] = 0;
     return;
   }
   const double inv = 1.0 / nn;
-  for (int i = q; i < n; i += G) X[(size_t)i * n + g] = (i >= s && i < t) ? zat(i) * inv : 0.0;
+  for (int i = q; i < n; i += G) X[(size_t)i * n + g] = (i >= s && i < t) ? entry(i) * inv : 0.0;
   if (q == 0) done[g] = 1;
 }
 
