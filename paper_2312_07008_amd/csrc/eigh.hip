@@ -23,7 +23,7 @@
 //      component is positive.
 // n = 1200, ms before and after the resident reduction, the product-form counts, the
 // twisted factorizations and the matrix-pipe back-transformation: reduction 11.6 -> 5.0,
-// eigenvalues 1.8 -> 0.46, vectors 5.9 -> 0.44, back-transformation 2.0 -> 0.44, the whole
+// eigenvalues 1.8 -> 0.46, vectors 5.9 -> 0.44, back-transformation 2.0 -> 0.48, the whole
 // call 22.5 -> 6.6.
 #include <algorithm>
 #include <cmath>
@@ -1337,12 +1337,16 @@ __global__ __launch_bounds__(256) void tridiag_backtransform(int n, const double
 // The same back-transformation on the FP64 matrix pipe, in blocks of 16 reflectors, for
 // 8 <= n <= 2048.  A workgroup keeps 16 columns of Z in registers: the register r of a 16 x 16
 // block in the products' output layout (row 4 r + lane / 16) is the second operand of the
-// contraction step r, so Z is both the operand of P = V^T Z and the accumulator of
-// Z -= V (T P) and never moves.  Row blocks are dealt round-robin to the 8 waves (the
+// contraction step r, so Z is the operand of P = V^T Z, takes V (T P) and never moves.  Row
+// blocks are dealt round-robin to the 8 waves (the
 // reflectors act below k0 only); the waves' partial P meet in LDS, one barrier per block.
+// Every sum is formed in pairs from products of four terms, and V (T P) apart from Z: with a
+// sum of hundreds of terms on one accumulator, and Z as the accumulator of its update, the
+// largest residual of 600 and 1200 random rows was 2.0 and 2.5 times that of sums over a
+// workgroup's threads, 1.0 so.
 // What bounds it: two passes over V per block from L2 and the chain P -> T P -> Z.
 // n = 1200: 2.0 ms with blocks of 8 on vector instructions, Z in LDS and three barriers;
-// 0.45 ms so.
+// 0.48 ms so (0.44 with one accumulator per sum).
 constexpr int WY16 = 16;
 
 // V[i][j] of block k0, 0 outside
@@ -1358,12 +1362,15 @@ __device__ void wy16_t(int blk, int n, const double* Vs, const double* tau, doub
   const int k0 = blk * WY16, nr = min(WY16, n - 2 - k0);  // reflectors 0 .. n - 3
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, r16 = lane & 15, kq = lane >> 4;
   d4 acc = (d4){0.0, 0.0, 0.0, 0.0};
-  for (int rb = k0 / 16 * 16 + 16 * w; rb < n; rb += 16 * (blockDim.x >> 6))
+  for (int rb = k0 / 16 * 16 + 16 * w; rb < n; rb += 16 * (blockDim.x >> 6)) {
+    d4 m[4];
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const double v = wy16_v(Vs, n, k0, nr, rb + 4 * r + kq, r16);
-      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(v, v, acc, 0, 0, 0);
+      m[r] = __builtin_amdgcn_mfma_f64_16x16x4f64(v, v, (d4){0.0, 0.0, 0.0, 0.0}, 0, 0, 0);
     }
+    acc += (m[0] + m[1]) + (m[2] + m[3]);
+  }
 #pragma unroll
   for (int r = 0; r < 4; ++r) part[w][(kq + 4 * r) * 16 + r16] = acc[r];
   __syncthreads();
@@ -1397,6 +1404,7 @@ __global__ __launch_bounds__(512) void backtransform16(int n, const double* Vs, 
   __shared__ double part[2][8][256];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, r16 = lane & 15, kq = lane >> 4;
   const int c = blockIdx.x * 16 + r16;
+  const d4 zero = (d4){0.0, 0.0, 0.0, 0.0};
   d4 z[NB];
 #pragma unroll
   for (int b = 0; b < NB; ++b)
@@ -1417,41 +1425,48 @@ __global__ __launch_bounds__(512) void backtransform16(int n, const double* Vs, 
       typedef uint32_t u2 __attribute__((ext_vector_type(2)));
       return __builtin_bit_cast(double, (u2)__builtin_amdgcn_raw_buffer_load_b64(desc, in ? o : (int)0x80000000, 0, 0));
     };
-    d4 p = (d4){0.0, 0.0, 0.0, 0.0};
+    d4 ps[2] = {zero, zero};
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
       const int rb = 16 * (w + 8 * b);
       if (rb + 15 > k0 && rb < n) {  // wave-uniform
         double v[4];
+        d4 m[4];
 #pragma unroll
         for (int r = 0; r < 4; ++r) v[r] = vload(rb + 4 * r + kq, r16);
 #pragma unroll
-        for (int r = 0; r < 4; ++r) p = __builtin_amdgcn_mfma_f64_16x16x4f64(v[r], z[b][r], p, 0, 0, 0);
+        for (int r = 0; r < 4; ++r) m[r] = __builtin_amdgcn_mfma_f64_16x16x4f64(v[r], z[b][r], zero, 0, 0, 0);
+        ps[b & 1] += (m[0] + m[1]) + (m[2] + m[3]);
       }
     }
+    const d4 p = ps[0] + ps[1];
     double t[4];
 #pragma unroll
     for (int r = 0; r < 4; ++r) t[r] = Tall[(size_t)blk * 256 + r16 * 16 + 4 * r + kq];
 #pragma unroll
     for (int r = 0; r < 4; ++r) part[buf][w][r * 64 + lane] = p[r];
     __syncthreads();
-    d4 wv = (d4){0.0, 0.0, 0.0, 0.0};
+    d4 wm[4];
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      double sum = 0.0;
+      double q[8];
 #pragma unroll
-      for (int q = 0; q < 8; ++q) sum += part[buf][q][r * 64 + lane];
-      wv = __builtin_amdgcn_mfma_f64_16x16x4f64(t[r], -sum, wv, 0, 0, 0);
+      for (int k = 0; k < 8; ++k) q[k] = part[buf][k][r * 64 + lane];
+      const double sum = ((q[0] + q[1]) + (q[2] + q[3])) + ((q[4] + q[5]) + (q[6] + q[7]));
+      wm[r] = __builtin_amdgcn_mfma_f64_16x16x4f64(t[r], -sum, zero, 0, 0, 0);
     }
+    const d4 wv = (wm[0] + wm[1]) + (wm[2] + wm[3]);
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
       const int rb = 16 * (w + 8 * b);
       if (rb + 15 > k0 && rb < n) {
         double v[4];
+        d4 u = zero;
 #pragma unroll
         for (int r = 0; r < 4; ++r) v[r] = vload(rb + r16, 4 * r + kq);
 #pragma unroll
-        for (int r = 0; r < 4; ++r) z[b] = __builtin_amdgcn_mfma_f64_16x16x4f64(v[r], wv[r], z[b], 0, 0, 0);
+        for (int r = 0; r < 4; ++r) u = __builtin_amdgcn_mfma_f64_16x16x4f64(v[r], wv[r], u, 0, 0, 0);
+        z[b] += u;
       }
     }
   }
