@@ -302,13 +302,14 @@ constexpr int kResRows = 2;  // rows per wave: 1200 rows 7.9, 6.8, 7.7, 10.3 ms 
 template <int J, int RW>
 __global__ __launch_bounds__(kResThreads) void tridiag_resident(const double* A_in, int n, double* A_out, double* Vs,
                                                         double* tau, double* d, double* e, unsigned long long* P,
-                                                        unsigned long long* R, double* p_last, int* status) {
+                                                        unsigned long long* R, double* p_last, int* status, int G,
+                                                        unsigned long long wait) {
   constexpr int NC = 64 * J, NT = kResThreads, NW = NT / 64, Q = (NC + NT - 1) / NT;
   __shared__ double ws[NC], vs[NC], xs[NC];  // w, v of the previous column, x of this one (0 up to k + 1)
   __shared__ double part1[NW], part2[NW], sc[3];
   __shared__ int dead;
   const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int G = gridDim.x, wg = blockIdx.x;
+  const int wg = blockIdx.x;  // of G
   int row[RW];
 #pragma unroll
   for (int r = 0; r < RW; ++r) row[r] = wg + G * (wv + NW * r);
@@ -361,7 +362,7 @@ __global__ __launch_bounds__(kResThreads) void tridiag_resident(const double* A_
         if ((spin & 255) == 255) {
           const unsigned long long now = wall_clock64();
           if (spin == 255) t0 = now;
-          if (now - t0 > kWaitTicks || __hip_atomic_load(status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) {
+          if (now - t0 > wait || __hip_atomic_load(status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) {
             dead = 1;
             break;
           }
@@ -597,15 +598,19 @@ __global__ void fill_empty(unsigned long long* p, size_t n, int* status) {
 template <int J, int RW>
 hipError_t launch_resident_multi(const double* A_in, int n, double* A_out, double* Vs, double* tau, double* d, double* e,
                                  unsigned long long* P, unsigned long long* R, double* p_last, int* status,
-                                 hipStream_t st) {
-  void* args[] = {&A_in, &n, &A_out, &Vs, &tau, &d, &e, &P, &R, &p_last, &status};
-  return hipLaunchCooperativeKernel(reinterpret_cast<const void*>(&tridiag_resident<J, RW>), dim3((n + 4 * RW - 1) / (4 * RW)),
-                                    dim3(kResThreads), args, 0, st);
+                                 hipStream_t st, EighPath path) {
+  int G = (n + 4 * RW - 1) / (4 * RW);
+  unsigned long long wait = path == EighPath::kMissed ? kWaitTicks / 1000 : kWaitTicks;
+  void* args[] = {&A_in, &n, &A_out, &Vs, &tau, &d, &e, &P, &R, &p_last, &status, &G, &wait};
+  return hipLaunchCooperativeKernel(reinterpret_cast<const void*>(&tridiag_resident<J, RW>),
+                                    dim3(path == EighPath::kMissed ? G - 1 : G), dim3(kResThreads), args, 0, st);
 }
 
 // false: not launched (the caller takes the launch-per-column form)
 bool launch_resident(const double* A_in, int n, double* A_out, double* Vs, double* tau, double* d, double* e,
-                     unsigned long long* P, unsigned long long* R, double* p_last, int* status, hipStream_t st) {
+                     unsigned long long* P, unsigned long long* R, double* p_last, int* status, hipStream_t st,
+                     EighPath path) {
+  if (path == EighPath::kRefused) return false;
   if (n <= kSmallMax) {
     if (n <= 64) hipLaunchKernelGGL(tridiag_small<16>, dim3(1), dim3(256), 0, st, A_in, n, A_out, Vs, tau, d, e, p_last, status);
     else hipLaunchKernelGGL(tridiag_small<32>, dim3(1), dim3(512), 0, st, A_in, n, A_out, Vs, tau, d, e, p_last, status);
@@ -614,7 +619,7 @@ bool launch_resident(const double* A_in, int n, double* A_out, double* Vs, doubl
   const size_t slots = 2 * (size_t)n * n;
   hipLaunchKernelGGL(fill_empty, dim3((unsigned)std::min<size_t>(2048, (slots + 255) / 256)), dim3(256), 0, st, P, slots, status);
   hipError_t err = hipErrorInvalidValue;
-#define DFPT2_RESIDENT(J) err = launch_resident_multi<J, kResRows>(A_in, n, A_out, Vs, tau, d, e, P, R, p_last, status, st)
+#define DFPT2_RESIDENT(J) err = launch_resident_multi<J, kResRows>(A_in, n, A_out, Vs, tau, d, e, P, R, p_last, status, st, path)
   if (n <= 256) DFPT2_RESIDENT(4);
   else if (n <= 512) DFPT2_RESIDENT(8);
   else if (n <= 768) DFPT2_RESIDENT(12);
@@ -1501,8 +1506,11 @@ __global__ void orth_correction(int n, double* M) {
 
 // One workgroup per 16 columns (whole 128-byte lines), 64 rows at a time; wave w finds the
 // rank of column w among all eigenvalues (ascending, ties by index).
+// Nothing is written after a reduction that was given up: the next attempt reads the matrix
+// again, and a caller may have named one buffer for the matrix and the vectors.
 __global__ __launch_bounds__(1024) void eig_permute(int n, const double* lam, const double* Zin, double* w_out,
-                                                    double* Z_out, int descending) {
+                                                    double* Z_out, int descending, const int* status) {
+  if (*status == 2) return;
   __shared__ int rank[16];
   {
     const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, g = min((int)blockIdx.x * 16 + w, n - 1);
@@ -1586,7 +1594,7 @@ size_t eigh_workspace_bytes(int n) {
 
 // resident: try the one-launch tridiagonalization
 static int eigh_attempt(const double* A_in, int n, double* w_out, double* Z_out, char* ws, size_t ws_bytes,
-                        hipStream_t st, int descending, double vec_floor_rel, bool resident, int* hs) {
+                        hipStream_t st, int descending, double vec_floor_rel, bool resident, EighPath path, int* hs) {
   if (n < 1 || n > kEighMaxN) return fail(DFPT2_ERR_INVALID_ARG, "eigh: n=%d outside [1, %d]", n, kEighMaxN);
   if (ws_bytes < eigh_workspace_bytes(n)) return fail(DFPT2_ERR_WORKSPACE, "eigh workspace too small");
   const size_t nn = (size_t)n * n;
@@ -1619,7 +1627,8 @@ static int eigh_attempt(const double* A_in, int n, double* w_out, double* Z_out,
   double* pb[2] = {p, lam};  // p of consecutive columns alternate (lam is free until step 2)
   unsigned long long* slots = reinterpret_cast<unsigned long long*>(lu);
   resident = resident && n >= 3 && n <= kResidentMax &&
-             launch_resident(A_in, n, A, Vs, tau, d, e, slots, slots + nn, pb[(n - 3) & 1], status, st);
+             launch_resident(A_in, n, A, Vs, tau, d, e, slots, slots + nn, pb[(n - 3) & 1], status, st,
+                             path);
   if (!resident) hipLaunchKernelGGL(zero_int, dim3(1), dim3(64), 0, st, status, 1);
   if (!resident && (err = hipMemcpyAsync(A, A_in, nn * 8, hipMemcpyDeviceToDevice, st)) != hipSuccess)
     return hip_fail(err, "eigh copy");
@@ -1725,7 +1734,8 @@ static int eigh_attempt(const double* A_in, int n, double* w_out, double* Z_out,
   if ((err = gemm_f64(X, n, 0, 0, G, n, 0, 0, Zo, n, 0, n, n, n, 1, 1.0, 0.0, st, Part, 3 * nn)) != hipSuccess)
     return hip_fail(err, "eigh orthonormalization");
   // 6. sort + orient
-  hipLaunchKernelGGL(eig_permute, dim3((n + 15) / 16), dim3(1024), 0, st, n, lam, Zo, w_out, Z_out, descending);
+  hipLaunchKernelGGL(eig_permute, dim3((n + 15) / 16), dim3(1024), 0, st, n, lam, Zo, w_out, Z_out, descending,
+                     status);
   if ((err = hipGetLastError()) != hipSuccess) return hip_fail(err, "eigh launch");
   prof_all.close();
   if ((err = hipMemcpyAsync(hs, status, sizeof(int), hipMemcpyDeviceToHost, st)) != hipSuccess)
@@ -1736,16 +1746,29 @@ static int eigh_attempt(const double* A_in, int n, double* w_out, double* Z_out,
 }
 
 int eigh_run(const double* A_in, int n, double* w_out, double* Z_out, char* ws, size_t ws_bytes, hipStream_t st,
-             int descending, double vec_floor_rel) {
+             int descending, double vec_floor_rel, EighPath path, int* attempts) {
   int hs = 0;
-  int rc = eigh_attempt(A_in, n, w_out, Z_out, ws, ws_bytes, st, descending, vec_floor_rel, true, &hs);
+  int rc = eigh_attempt(A_in, n, w_out, Z_out, ws, ws_bytes, st, descending, vec_floor_rel, true, path, &hs);
+  if (attempts) *attempts = 1;
   // 2: the workgroups of the resident form did not meet in time (held off the GPU by
   // other work); the launch-per-column form waits for nothing
-  if (rc == DFPT2_OK && hs == 2)
-    rc = eigh_attempt(A_in, n, w_out, Z_out, ws, ws_bytes, st, descending, vec_floor_rel, false, &hs);
+  if (rc == DFPT2_OK && hs == 2) {
+    rc = eigh_attempt(A_in, n, w_out, Z_out, ws, ws_bytes, st, descending, vec_floor_rel, false, path, &hs);
+    if (attempts) *attempts = 2;
+  }
   if (rc != DFPT2_OK) return rc;
   if (hs != 0) return fail(DFPT2_ERR_NOT_CONVERGED, "inverse iteration produced a zero or non-finite vector");
   return DFPT2_OK;
 }
 
 }  // namespace dfpt2
+
+extern "C" int dfpt2_eigh_sym_path(const double* A, int64_t n, double* w, double* Z, void* workspace, size_t ws_bytes,
+                                   dfpt2_stream_t stream, int path, int* attempts) {
+  using namespace dfpt2;
+  g_last_error.clear();
+  if (!A || !w || !Z || !workspace) return fail(DFPT2_ERR_INVALID_ARG, "null pointer argument");
+  if (n < 1 || n > kEighMaxN || path < 0 || path > 2) return fail(DFPT2_ERR_INVALID_ARG, "bad argument");
+  return eigh_run(A, (int)n, w, Z, static_cast<char*>(workspace), ws_bytes, reinterpret_cast<hipStream_t>(stream), 0,
+                  -1.0, static_cast<EighPath>(path), attempts);
+}
