@@ -697,11 +697,16 @@ int run_pass(const PassPlan& pl, const dfpt2_opts& o, const double* eps_h, const
   da.nTP = pl.nTP;
   da.w = pl.w_density;
 
-  // One batch of at most 8 tile partials a pair (up to 192 virtuals) is reduced by the last
-  // kernel, whose single workgroup takes a pair per thread, instead of a launch of its own:
-  // 4.1 + 4.8 us in two launches, 5 in one, at 55 pairs of one partial.  More partials are
-  // left to a wave per pair over the whole chip.
-  const bool fused = count <= pl.batch && pl.nTP1 <= 8;
+  // Few tile partials, of one batch, are reduced by the last kernel, whose single workgroup takes
+  // a pair per thread, instead of a launch of a wave per pair over the whole chip.  Up to 8
+  // partials a pair (192 virtuals).  Whole FP64 passes, us, one kernel and two, on two boxes: 60
+  // virtuals (1 partial a pair), 55 pairs 64.5 and 66.4, 63.5 and 66.8; 2080 pairs 323 and 324, 321 and 325;
+  // 4095 pairs 574 and 575, 571 and 574; 128 virtuals (3), 300 pairs 149.4 and 150.6, 148.1 and 151.3; 1035 pairs
+  // 356 and 357, 355 and 357; 4095 pairs 1203 and 1199, 1199 and 1197; 20100 pairs 5830 and 5790, 5797 and 5769;
+  // 192 virtuals (6), 528 pairs 414.7 and 415.8, 412.4 and 414.8; 1035 pairs 762 and 760, 761 and 760;
+  // 64980 pairs 45300 and 44900, 45190 and 44780: even at 4000 to 6000 partials.
+  constexpr int kFusedPartials = 4096;
+  const bool fused = count <= pl.batch && pl.nTP1 <= 8 && (long long)count * pl.nTP1 <= kFusedPartials;
   for (int p0 = 0, b = 0; p0 < count; p0 += pl.batch, ++b) {
     const int np = (count - p0 < pl.batch) ? count - p0 : pl.batch;
     pa.pairs = pairs + p0;
