@@ -292,8 +292,9 @@ int naf_compress(const dfpt2_opts* opts, const double* B, double eps, double* B_
  *          no_vecs with ldx = n_vir); NULL = full space (n_kept = 0 or n_vir, ldx ignored)
  *   R      [n_amp][m][m] out, m = n_kept with X, else n_vir
  * Limits: n_vir <= 2048, n_amp <= 65535.  Workspace (pp_ladder_workspace_size,
- * n_kept = 0 for the full space): one block of (ac|bd) of up to ~16 GB plus the
- * transformed inputs and n_amp m^2 doubles.  Asynchronous on the stream.
+ * n_kept = 0 for the full space): blocks of (ac|bd) of up to ~16 GB, or 1024 m^2 doubles
+ * and 2 GB where that is more (m > 1300; 36 GB at 2048), plus the transformed inputs with X or
+ * at most 2 GB for the amplitudes without.  Asynchronous on the stream.
  * Errors: INVALID_ARG, WORKSPACE, HIP.
  */
 int pp_ladder_workspace_size(int64_t n_vir, int64_t n_aux, int64_t n_amp, int64_t n_kept, size_t* bytes);

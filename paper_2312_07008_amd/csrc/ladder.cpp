@@ -33,7 +33,7 @@ namespace dfpt2 {
 namespace {
 
 struct LadderPlan {
-  int n, nk, na, np, vcols, scols;
+  int n, nk, na, np, vcols, scols, tp;
   bool transform;
   size_t off_Y, off_Bk, off_Z, off_Tk, off_Tp, off_V, off_S, bytes;
 };
@@ -42,6 +42,7 @@ constexpr double kVBytes = 2.0e9;    // V of the pairs whose integrals are forme
 constexpr double kSBytes = 14.0e9;   // S and A of the pairs that are contracted at a time
 constexpr int kBlockPairs = 16384;   // pairs of either, where the bytes allow: enough to fill the GPU
 constexpr int kMinPairs = 1024;      // pairs contracted at a time, whatever the bytes
+constexpr double kTBytes = 2.0e9;    // T+ and T- of the amplitudes that are contracted at a time in the full space
 
 int plan_ladder(int64_t n_vir, int64_t n_aux, int64_t n_amp, int64_t n_kept, bool transform, LadderPlan* pl) {
   if (n_vir < 1 || n_vir > 2048) return fail(DFPT2_ERR_INVALID_ARG, "n_vir must lie in [1, 2048]");
@@ -75,7 +76,11 @@ int plan_ladder(int64_t n_vir, int64_t n_aux, int64_t n_amp, int64_t n_kept, boo
   p.off_Bk = take(transform ? d * p.nk * p.nk * p.na : 0);
   p.off_Z = take(transform ? d * p.np * p.n * p.nk : 0);
   p.off_Tk = take(transform ? d * p.np * p.nk * p.nk : 0);
-  p.off_Tp = take(d * p.np * p.nk * p.nk);
+  // T+ and T-: of all amplitudes where T' was formed, over the half-transformed Z (n >= nk);
+  // in the full space of kTBytes at a time, split again for every block of pairs (a few percent of its
+  // contraction at worst), so that the workspace does not grow with the amplitudes
+  p.tp = transform ? p.np : (int)std::max(1.0, std::min((double)p.np, kTBytes / pair));
+  p.off_Tp = transform ? p.off_Z : take(d * p.tp * p.nk * p.nk);
   p.off_V = take(d * p.vcols * p.nk * p.nk);
   p.off_S = take(d * p.scols * p.nk * p.nk);
   p.bytes = off;
@@ -180,8 +185,8 @@ int pp_ladder(int64_t n_vir, int64_t n_aux, int64_t n_amp, const double* B_vv, c
     double* V = reinterpret_cast<double*>(ws + p.off_V);
     const int kp = nk * (nk + 1) / 2, km = nk * (nk - 1) / 2;
     double* Tp = reinterpret_cast<double*>(ws + p.off_Tp);
-    double* Tm = Tp + (size_t)np * kp;
-    sym_split(Tk, nk, np, 1.0, Tp, Tm, s);
+    double* Tm = Tp + (size_t)p.tp * kp;
+    if (p.tp == np) sym_split(Tk, nk, np, 1.0, Tp, Tm, s);
     double* S = reinterpret_cast<double*>(ws + p.off_S);
     double* A = S + (size_t)p.scols * kp;
     const int all = nk * (nk + 1) / 2;
@@ -212,9 +217,14 @@ int pp_ladder(int64_t n_vir, int64_t n_aux, int64_t n_amp, const double* B_vv, c
           q.b0 = 0;
         }
       }
-      if ((e = ladder_contract(Tp, S, np, kp, nk, t0, t - t0, true, R, V, nv, s)) != hipSuccess ||
-          (km > 0 && (e = ladder_contract(Tm, A, np, km, nk, t0, t - t0, false, R, V, nv, s)) != hipSuccess))
-        return hip_fail(e, "ladder contraction");
+      for (int p0 = 0; p0 < np; p0 += p.tp) {
+        const int m = std::min(p.tp, np - p0);
+        double* Rp = R + (size_t)p0 * nk * nk;
+        if (p.tp < np) sym_split(Tk + (size_t)p0 * nk * nk, nk, m, 1.0, Tp, Tm, s);
+        if ((e = ladder_contract(Tp, S, m, kp, nk, t0, t - t0, true, Rp, V, nv, s)) != hipSuccess ||
+            (km > 0 && (e = ladder_contract(Tm, A, m, km, nk, t0, t - t0, false, Rp, V, nv, s)) != hipSuccess))
+          return hip_fail(e, "ladder contraction");
+      }
     }
   }
   if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "ladder launch");
