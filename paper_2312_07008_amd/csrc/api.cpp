@@ -182,7 +182,8 @@ int plan_pass(const dfpt2_opts* o, PassPlan* pl, bool energy_only) {
     if (act_np > nb_t) nb_t = act_np;
   }
   const size_t t_bytes = p.precision == DFPT2_INT8_SLICED ? 1 : sizeof(__bf16);
-  // (operand regions: twice the two matrices of a pair, as callers' workspaces have always been)
+  // (the operand, exponent and row-maximum regions hold four matrices a pair, of which the two
+  // operands s and d use half: the sizes that callers are told, and with them what is refused, stay)
   p.off_Ts = take(p.ns2 >= 2 ? t_bytes * 4 * (size_t)nb_t * p.n_v_rows_t * p.n_v_pad_d * p.ns2 : 0);
   p.off_Texp = take(p.ns2 >= 2 && p.precision == DFPT2_INT8_SLICED ? sizeof(int) * 4 * (size_t)nb_t * p.n_v_pad_d
                                                                     : 0);

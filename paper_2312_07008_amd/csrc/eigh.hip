@@ -8,9 +8,9 @@
 //      workgroup up to n = 128, cooperating workgroups above); then one launch per column,
 //      two above n = 2731.
 //   2. Splitting at negligible off-diagonal entries, then every eigenvalue by
-//      multisection on Sturm counts (one wave per eigenvalue, 128 points a round).
+//      multisection on Sturm counts (one, two or four waves per eigenvalue, a point per lane).
 //   3. Eigenvectors of the tridiagonal matrix: isolated eigenvalues by twisted
-//      factorizations of T - lambda I; the others by inverse iteration with a partially
+//      factorizations of T - lambda I, two solves each; the others by inverse iteration with a partially
 //      pivoted LU.  Eigenvalues closer than a small multiple of ||T|| form a group that
 //      one thread handles in order, orthogonalizing every iterate against the group's
 //      earlier vectors.
@@ -333,7 +333,7 @@ __global__ __launch_bounds__(kResThreads) void tridiag_resident(const double* A_
   __syncthreads();
   for (int k = 0; k + 2 < n; ++k) {
     if (k >= last) break;  // workgroup-uniform: nothing left to update
-    // p of column k - 1 and row k, entries c = tid + 512 q
+    // p of column k - 1 and row k, entries c = tid + NT q
     double p[Q], x[Q];
     if (k == 0) {
 #pragma unroll
@@ -632,9 +632,8 @@ bool launch_resident(const double* A_in, int n, double* A_out, double* Vs, doubl
   return err == hipSuccess;
 }
 
-// d[n-2], d[n-1], e[n-2] from the last 2 x 2 block, with the update of column n - 3
-// still pending when the lazy steps were used (p_last = p of column n - 3)
-// the last 2 x 2 block of the reduced matrix (one thread)
+// d[n-2], d[n-1], e[n-2] from the last 2 x 2 block of the reduced matrix, with the update of column
+// n - 3 still pending unless p_last (p of that column) is null; one thread
 __device__ inline void tridiag_tail(const double* A, int n, const double* Vs, const double* tau, const double* p_last,
                                     double* d, double* e) {
   if (p_last) {  // with the update of column n - 3 pending
@@ -1492,7 +1491,6 @@ __global__ __launch_bounds__(512) void backtransform16(int n, const double* Vs, 
 }
 
 // ------------------------------------------------------------ sort + orient
-// out column dst(g) = sign-oriented column g; descending: dst = n-1-rank
 // M = I - U with U = strictly upper part of E + diag(E) / 2, where E = Z^T Z - I
 // arrives as G = Z^T Z in M (in place)
 __global__ void orth_correction(int n, double* M) {
@@ -1504,8 +1502,9 @@ __global__ void orth_correction(int n, double* M) {
   }
 }
 
-// One workgroup per 16 columns (whole 128-byte lines), 64 rows at a time; wave w finds the
-// rank of column w among all eigenvalues (ascending, ties by index).
+// Out column dst(g) = sign-oriented column g; descending: dst = n - 1 - rank.  One workgroup per
+// 16 columns (whole 128-byte lines), 64 rows at a time; wave w finds the rank of column w among
+// all eigenvalues (ascending, ties by index).
 // Nothing is written after a reduction that was given up: the next attempt reads the matrix
 // again, and a caller may have named one buffer for the matrix and the vectors.
 __global__ __launch_bounds__(1024) void eig_permute(int n, const double* lam, const double* Zin, double* w_out,

@@ -500,6 +500,7 @@ int pairscreen_workspace_size(const dfpt2_opts* opts, size_t* bytes) {
   PassPlan pl;
   int st = plan_pass(opts, &pl);
   if (st != DFPT2_OK) return st;
+  // the second term is not used: each wave of pair_features_kernel forms the diagonal values itself
   *bytes = align_up(sizeof(double) * (size_t)(pl.n_core > 0 ? pl.n_core : 1) * pl.n_aux, 256) +
            align_up(sizeof(double) * (size_t)(pl.n_core > 0 ? pl.n_core : 1), 256) + 256;
   return DFPT2_OK;
@@ -588,11 +589,13 @@ int pairscreen_adam_step(float* W, const float* dW, float* m, float* v, int64_t 
 int pairscreen_train_workspace_size(int64_t n, size_t* bytes) {
   g_last_error.clear();
   if (!bytes || n <= 0) return fail(DFPT2_ERR_INVALID_ARG, "bad argument");
+  // Room for predictions, their gradients, activations and dW, none of which a step writes any more:
+  // rows of partial sums take it (net_plan), and the size that callers are told stays.
   size_t b = 0;
-  b += align_up(sizeof(float) * n, 256);          // pred
-  b += align_up(sizeof(float) * n, 256);          // dpred
-  b += align_up(sizeof(float) * n * 2 * H, 256);  // activations
-  b += align_up(sizeof(float) * NP, 256);         // dW
+  b += align_up(sizeof(float) * n, 256);
+  b += align_up(sizeof(float) * n, 256);
+  b += align_up(sizeof(float) * n * 2 * H, 256);
+  b += align_up(sizeof(float) * NP, 256);
   size_t bw = 0;
   pairscreen_backward_workspace_size(n, &bw);
   b += align_up(bw, 256);

@@ -8,10 +8,11 @@ namespace dfpt2 {
 // (pair, tile).  Tiles of one pair go in bands of 6 tile rows, column by column within a
 // band: the ~32 workgroups resident on one XCD then read about 6 + 5 panels instead of the
 // 14 of 3-4 whole tile rows (1% faster than row order).  Tiles with at most half their columns
-// or rows, which take half as long, come after the whole tiles of all pairs: workgroups of
-// equal length stay at the same chunks of the panels that they share and find them in the L2.
-// 31 holes, 539 virtuals, BF16: 57 -> 29% of the requests miss the L2, product 4.30 -> 4.22 ms;
-// 80 holes, 1200 virtuals, 4000 auxiliary functions: 47.4 -> 46.2 ms per launch.
+// or rows, which take half as long, come after the whole tiles of all pairs.  31 holes, 539
+// virtuals, BF16: product 4.30 -> 4.22 ms; workgroups of equal length stay at the same chunks of the
+// panels that they share and find them in the L2 (57 -> 29% of the requests miss).  80 holes, 1200
+// virtuals, 4000 auxiliary functions: 47.4 -> 46.2 ms per launch, though the misses rise there (24 -> 31% of
+// the requests: strips of half tiles share fewer panels); what the gain comes from is not shown.
 __device__ inline void v_tile(int h0, int n_v, int n_pairs, int& p, int& I, int& J) {
   constexpr int TV = 128, HB = 6;
   auto xcd = [](int h, int nblk) {
