@@ -266,9 +266,8 @@ __device__ inline double fast_sqrt(double a) {
 // reflector of a column from alpha = x_0 and s2 = sum of the other x_i^2: v = (1, scale x_i).
 // Every column's chain goes through it: with rounded roots and divisions, and
 // with every column of a row updated to the end, the reduction of a 60 x 60 matrix took 102 us, 81 so.
-// kRounded: t as a quotient and not a product with a reciprocal, one rounding less (in the
-// small form; in the resident one it takes 1% of 1200 columns, whose eigenvalues are not off by more without it).
-template <bool kRounded>
+// t is a quotient, not a product with a reciprocal: its remainder corrects it.  The eigenpairs of
+// 60 to 1200 rows are then off by the same as with rounded roots and divisions.
 __device__ inline void reflector(double alpha, double s2, double& beta, double& t, double& scale) {
   t = scale = 0.0;
   beta = alpha;
@@ -279,7 +278,7 @@ __device__ inline void reflector(double alpha, double s2, double& beta, double& 
       beta = (alpha > 0.0) ? -mu : mu;
       const double rb = fast_rcp(beta), num = beta - alpha;
       t = num * rb;
-      if (kRounded) t = fma(fma(-beta, t, num), rb, t);
+      t = fma(fma(-beta, t, num), rb, t);
       scale = fast_rcp(alpha - beta);
     } else {
       const double mu = sqrt(a);
@@ -420,7 +419,7 @@ __global__ __launch_bounds__(kResThreads) void tridiag_resident(const double* A_
     for (int q = 0; q < NW; ++q) s2 += part2[q];
     const double alpha = sc[2];
     double beta, t, scale;
-    reflector<false>(alpha, s2, beta, t, scale);
+    reflector(alpha, s2, beta, t, scale);
     // the wave's rows: update by column k - 1, then their products with (1, scale x)
     const int j0 = k >> 6, j1 = (k + 1) >> 6, l1 = (k + 1) & 63;
     double acc[RW], ak[RW], w_row[RW];
@@ -539,7 +538,7 @@ __global__ __launch_bounds__(16 * N4) void tridiag_small(const double* A_in, int
   #pragma unroll
       for (int q = 0; q < NW; ++q) s2 += part2[q];
       double beta, t, scale;
-      reflector<true>(sc[0], s2, beta, t, scale);
+      reflector(sc[0], s2, beta, t, scale);
       double ac[4] = {}, ak = 0.0;
       const double w_row = ws[row];
   #pragma unroll
