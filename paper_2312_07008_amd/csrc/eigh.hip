@@ -24,7 +24,7 @@
 // n = 1200, ms before and after the resident reduction, the product-form counts, the
 // twisted factorizations and the matrix-pipe back-transformation: reduction 11.6 -> 5.0,
 // eigenvalues 1.8 -> 0.46, vectors 5.9 -> 0.44, back-transformation 2.0 -> 0.48, the whole
-// call 22.5 -> 6.6.
+// call 22.5 -> 6.7.
 #include <algorithm>
 #include <cmath>
 #include <cfloat>
@@ -792,7 +792,7 @@ __device__ double multisect(const double* d, const double* e, int s, int t, int 
 // SIMDs idle, the chain of one count.  d and e^2 (or e) come from LDS up to n = kSturmLds.
 // n = 1200: 1.8 ms with full divisions and global reads, 1.3 ms with fast reciprocals (and two
 // points per lane, to fill their latency); in the product form 0.66 ms with two points and
-// 0.50 with one.  n = 60: 33 us with W = 1, 21 us
+// 0.46 with one.  n = 60: 33 us with W = 1, 21 us
 // with W = 4.  The last blocks form the factors of the back-transformation (wy16_t), which
 // takes no time of its own here.
 constexpr int kSturmLds = 4096;
