@@ -700,7 +700,7 @@ int run_pass(const PassPlan& pl, const dfpt2_opts& o, const double* eps_h, const
 
   // Few tile partials, of one batch, are reduced by the last kernel, whose single workgroup takes
   // a pair per thread, instead of a launch of a wave per pair over the whole chip.  Up to 8
-  // partials a pair (192 virtuals).  Whole FP64 passes, us, one kernel and two, on two boxes: 60
+  // partials a pair (192 virtuals).  Whole FP64 passes, us, one kernel and two, measured twice: 60
   // virtuals (1 partial a pair), 55 pairs 64.5 and 66.4, 63.5 and 66.8; 2080 pairs 323 and 324, 321 and 325;
   // 4095 pairs 574 and 575, 571 and 574; 128 virtuals (3), 300 pairs 149.4 and 150.6, 148.1 and 151.3; 1035 pairs
   // 356 and 357, 355 and 357; 4095 pairs 1203 and 1199, 1199 and 1197; 20100 pairs 5830 and 5790, 5797 and 5769;
