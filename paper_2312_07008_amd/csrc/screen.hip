@@ -168,7 +168,6 @@ __global__ __launch_bounds__(kThreads, 1) void mlp_kernel(const float* Wp, const
 #pragma unroll
   for (int r = 0; r < 4; ++r) g2[0][r] = g2[1][r] = gx[r] = 0.f;
   float gb2 = 0.f, gw3 = 0.f, gb3 = 0.f, loss = 0.f;
-  const float two_n = 2.f / (float)n;
   for (int tile = blockIdx.x; tile < ntile; tile += gridDim.x) {
     const int s0 = tile * TS, ns = min(TS, n - s0);
     __syncthreads();  // the previous tile's readers are done
@@ -242,7 +241,7 @@ __global__ __launch_bounds__(kThreads, 1) void mlp_kernel(const float* Wp, const
           if (MODE == kForward && r < ns) out[s0 + r] = o;
           if (MODE == kTrain) {
             const float e = r < ns ? o - yr : 0.f;
-            sdo[r] = e * two_n;
+            sdo[r] = 2.f * e / (float)n;  // (a product with a rounded 2 / n would scale all gradients by its error)
             loss = fmaf(e, e, loss);
           }
         }
@@ -331,10 +330,14 @@ __global__ __launch_bounds__(kThreads, 1) void mlp_kernel(const float* Wp, const
     const int which = tid < 2 * H ? tid >> 6 : tid & 1;
     const float* v = tid < 2 * H ? &red[which][0][lane] : lred[which];
     const int step = tid < 2 * H ? H : 1;
-    float acc = 0.f;
+    float s[kWaves];
 #pragma unroll
-    for (int k = 0; k < kWaves; ++k) acc += v[k * step];
-    part[tid >= 2 * H ? (which ? NP : OFF_B3) : (which ? OFF_W3 : OFF_B2) + lane] = acc;
+    for (int k = 0; k < kWaves; ++k) s[k] = v[k * step];
+#pragma unroll
+    for (int w = kWaves / 2; w > 0; w >>= 1)
+#pragma unroll
+      for (int k = 0; k < w; ++k) s[k] += s[k + w];
+    part[tid >= 2 * H ? (which ? NP : OFF_B3) : (which ? OFF_W3 : OFF_B2) + lane] = s[0];
   }
 }
 
@@ -342,7 +345,7 @@ __global__ __launch_bounds__(kThreads, 1) void mlp_kernel(const float* Wp, const
 // Adam on the parameter and the loss
 struct AdamArgs {
   float *W, *m, *v, *loss;
-  float lr, b1, b2, eps, c1, c2, inv_n;
+  float lr, b1, b2, eps, c1, c2, n;
 };
 
 __device__ inline void adam_update(float& W, float& m, float& v, float g, const AdamArgs& a) {
@@ -365,10 +368,17 @@ __global__ __launch_bounds__(512) void sum_partials_kernel(const float* partial,
   sh[q][c] = acc;
   __syncthreads();
   if (q != 0 || k > NP) return;
-  for (int b = 1; b < 16; ++b) acc += sh[b][c];
+  float s[16];  // in pairs
+#pragma unroll
+  for (int b = 0; b < 16; ++b) s[b] = sh[b][c];
+#pragma unroll
+  for (int w = 8; w > 0; w >>= 1)
+#pragma unroll
+    for (int b = 0; b < w; ++b) s[b] += s[b + w];
+  acc = s[0];
   if (kAdam) {
     if (k < NP) adam_update(a.W[k], a.m[k], a.v[k], acc, a);
-    else *a.loss = acc * a.inv_n;
+    else *a.loss = acc / a.n;
   } else if (k < NP) {
     dW[k] = acc;
   }
@@ -619,7 +629,7 @@ int pairscreen_train(float* W, float* m, float* v, const float* feats, const flo
     launch_mlp<kTrain>(p, s, W, feats, y, (int)n, nullptr, nullptr, nullptr, partial);
     AdamArgs a = adam_args(W, m, v, lr, 0.9f, 0.999f, 1e-8f, step0 + t);
     a.loss = losses + (t - 1);
-    a.inv_n = 1.f / (float)n;
+    a.n = (float)n;
     hipLaunchKernelGGL(sum_partials_kernel<true>, dim3((NP + 32) / 32), dim3(512), 0, s, partial, p.groups, nullptr, a);
     const hipError_t le = hipGetLastError();
     if (le != hipSuccess) return hip_fail(le, "train");
